@@ -308,9 +308,8 @@ const char *adore_kernel_name(int32_t kernel);
  *   w[i][j] = q_i . k_j for j <= i;  query i keeps its top_k largest weights (all while i + 1 <= top_k; equal
  *   weights go to the lower j);  out_i = sum over the kept j of softmax_j(w[i][j] / sqrt(head_dim)) v_j.
  * q, k, v, out: DEVICE [rows][seq][head_dim] bf16, dense; out may not alias the inputs.  workspace: DEVICE,
- * 256-byte aligned, at least adore_topk_attention_workspace_bytes(rows, seq, head_dim) bytes (a transposed copy of
- * v; for seq > 2048 also the weights of the query blocks in flight, 512 * 16 * (seq + 36) * 4 bytes or so, which
- * shorter sequences keep on chip), caller-owned, free to reuse after the work enqueued here has run.  The call only enqueues work on
+ * 256-byte aligned, at least adore_topk_attention_workspace_bytes(rows, seq, head_dim) bytes, caller-owned, free to reuse
+ * after the work enqueued here has run (reserved: the kernel keeps everything on chip and does not touch it).  The call only enqueues work on
  * hip_stream (a hipStream_t, NULL = the default stream).  The selection is exact on the weights as the kernel
  * computes them (bf16 products accumulated in fp32); inputs must be finite.
  * Errors: E_INVALID (null, sizes <= 0, top_k < 1), E_UNSUPPORTED (head_dim not in {64,128}, seq > 32768,
@@ -322,15 +321,10 @@ int adore_topk_attention(const void *q, const void *k, const void *v, void *out,
                          void *hip_stream);
 
 /* adore_topk_attention for callers that cannot allocate device memory (code under HIP graph capture, tight serving
- * loops, harnesses that forbid it): the same kernels and the same result, bit for bit, with the transposed copy of v
- * in a fixed array inside the library (ADORE_TOPK_STATIC_SCRATCH_BYTES of device memory on every GPU the library is
- * loaded on, held until the process ends) instead of a caller's workspace.  The call allocates and frees nothing.
- * Limits: seq <= 2048 and rows * head_dim * ceil(seq / 32) * 64 <= ADORE_TOPK_STATIC_SCRATCH_BYTES, else E_WORKSPACE
- * (e.g. 256 rows of 1024 tokens at head_dim 128).  All calls on one GPU share that array: calls whose work may
- * overlap on a GPU (different streams, different threads) race; calls on one stream are safe.  Nothing in the array
- * has to be cleared between calls (every call writes all of what it then reads).  The first call on a device looks
- * the array's address up (hipGetSymbolAddress), so make that call outside a graph capture.
- * Errors: as adore_topk_attention; E_WORKSPACE when the shape exceeds the array. */
+ * loops, harnesses that forbid it): the same kernel and the same result, bit for bit, without a workspace.  The call allocates
+ * and frees nothing.  Limits: seq <= 2048 and rows * head_dim * ceil(seq / 32) * 64 <= ADORE_TOPK_STATIC_SCRATCH_BYTES, else
+ * E_WORKSPACE (e.g. 256 rows of 1024 tokens at head_dim 128).  Calls share nothing: they may overlap on any streams and threads.
+ * Errors: as adore_topk_attention; E_WORKSPACE when the shape exceeds those limits. */
 #define ADORE_TOPK_STATIC_SCRATCH_BYTES (64u << 20)
 int adore_topk_attention_static(const void *q, const void *k, const void *v, void *out, int32_t rows, int32_t seq,
                                 int32_t head_dim, int32_t top_k, void *hip_stream);

@@ -5,32 +5,43 @@
 //   w[i][j] = q_i . k_j  (j <= i);   kept(i) = the top_k largest w[i][.], equal weights to the lower j
 //   out_i   = sum_{j in kept(i)} softmax_j(w[i][j] / sqrt(d)) v_j
 //
-// One workgroup of 8 waves takes 16 consecutive queries of one (sequence, head) and the keys they can see:
+// A query's K-th largest weight needs all its weights, but not all of them at once.  A workgroup takes NQ = 32 or 64
+// consecutive queries of one (sequence, head) and goes over the keys they can see several times; every time the weights are
+// made anew on the matrix cores (32x32x16 bf16), which is cheaper than keeping them (64 queries x 8192 keys are 2 MB):
 //
-//   A  logits^T = K . Q^T on the matrix cores (16x16x32 bf16; the key rows come from global memory straight into
-//      the operand layout, Q from an LDS tile), written to LDS as fp32, one row per query, -inf beyond the
-//      diagonal.  All the weights of a query have to exist before its K-th largest is known; 16 x 2048 fp32 is
-//      what LDS holds, and at 1024 keys two workgroups fit a compute unit.
-//   S  one wave per query row: the row's maximum and its K-th largest weight by a radix select on the
-//      order-preserving integer image of the floats: four passes of 8 bits over the row held in registers, each
-//      a 256-bin histogram in LDS (wave-private, LDS atomics) scanned from the top; the rank left over in the last
-//      bin says how many of the weights equal to the K-th largest stay, and ballots in position order say up to
-//      which position.  As soon as at most 64 weights share the bits decided so far (as a rule after two passes)
-//      they are gathered one per lane and ranked directly, which gives the last key that stays at once.  (A bit-by-bit search with ballots, 32 counting passes, took 5.6 ms of 8.0 ms at 512 rows of
-//      1024 tokens, K = 96, in blocks of 32 queries; the radix select 1.5 ms of 3.4 ms.)
-//   B  P = exp2((w - max) / sqrt(d) . log2 e) for the kept weights straight from the LDS rows (the maximum is
-//      known, so there is no running rescale), as two bf16 terms (16 significant bits), and O^T += V^T . P^T on
-//      the matrix cores.  V^T comes from a transposed copy of V made by a pass of its own ([d][S], zero-padded),
-//      so that 8 consecutive keys of one head dimension are 16 contiguous bytes: the operand layout again.
-//   M  the eight waves (each took every eighth block of 32 keys) add their partial sums through LDS in a fixed
-//      order, normalise, round once and store.
+//   1 range     mean and deviation of the weights over an evenly spaced sample of the keys give a range in which the K-th
+//               largest is expected.
+//   2 count     a histogram per query in LDS over that range (128 bins, [bin][query]: every query has a bank of its own);
+//               the bin that holds the K-th largest weight and its rank in it.  Counted again over another range for the queries
+//               whose K-th largest is outside, or in a bin with more than 16 weights.  The ranges shrink by the number of bins every
+//               time: the result never depends on the sample, only the time does.
+//   3 ties      only where more than 16 weights are equal to the K-th largest: one pass in which the last position that stays is
+//               found from the bit masks of each step.
+//   4 product   P = exp2((w - max) / sqrt(d) . log2 e) of the weights above the bin (the same instructions on the same
+//               operands give the weights the very bits they had in 2), as two bf16 terms (16 significant bits), and
+//               O^T += V^T . P^T.  A lane's weights sit where the second product wants its operand; V comes out of LDS
+//               transposed (ds_read_b64_tr_b16).  The few weights inside the bin are set aside with their positions.
+//   5 the rest  the weights set aside are ranked directly (equal ones by position), those that stay add their rows of V in fp32;
+//               the waves' partial sums are added through LDS in a fixed order, rounded once.
 //
-// Phase B reads the very numbers phase S selected on, so the mask is exact with respect to the kernel's own fp32
-// weights; against an fp64 evaluation two weights closer than the fp32 accumulation error may swap at the cut.
+// A wave holds 32 queries and takes one 32-key block of each 128-key step (wave = key block x query block), so a step's K
+// (and V) rows are read once from the L2 per workgroup, coalesced, and each LDS operand serves 32 queries.  The products of
+// a step run next to the arithmetic on the weights of the step before.
+//
+// Measured (us per call, K = 96): 512 rows of 1024 tokens, d = 128: 1900 -> 870; 128 rows of 8192 tokens, d = 128:
+// 80900 -> 6760; 4 rows of 128 tokens, d = 64: 21.3 -> 10.9.  Before, 16 queries per workgroup kept their fp32 weights in LDS (in
+// memory beyond 2048 tokens, read again by every pass of a radix select), with K and a transposed copy of V loaded straight
+// into the operand layout: 16 look-ups in the L1 per 256 bytes, K and V read from the L2 once per 16 queries.
+// What bounds it now: of a workgroup's 57000 cycles at 1024 tokens the vector units are busy with 26000 (two waves per SIMD), the matrix
+// units with 13000 (a 32x32x16 instruction keeps the vector unit from issuing for half of its 32 cycles), LDS with 17000; the rest
+// is waiting at barriers and for the first and last loads, one workgroup (241 registers, 142 KB of LDS) having a compute unit to itself.
+// Tried and not kept: thresholds from a sample and candidate lists in LDS instead of histograms (6.5 vector instructions per
+// weight and a selection of 20000 cycles per workgroup; 1080 us / 8800 us); a pass of its own for the weights of the bin (965 us /
+// 7700 us); the K operand of the next step fetched a step ahead (132 registers too many).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
-#include <mutex>
+#include <type_traits>
 
 #include "adore.h"
 #include "device_utils.h"
@@ -40,84 +51,83 @@ namespace adore {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kWaves = 8;
-constexpr int kMaxSeq = 2048;        // longest sequence whose logit rows (16 queries) fit LDS
-constexpr int kMaxLongSeq = 32768;   // longest sequence taken at all (rows in the workspace)
-constexpr int kLongGrid = 512;       // workgroups of a launch over such sequences (two per compute unit; a multiple of 8)
+constexpr int kStep = 128;           // keys per step: four 32-key blocks
+constexpr int kBins = 128;           // bin 0: below the range, the last one: above it
+constexpr int kFew = 16;             // weights of a bin that are ranked directly
+constexpr int kSample = 128;         // keys of the sample: mean and deviation to a tenth of the deviation, for a range of two
+constexpr int kMaxCounts = 64;       // a range of 2^277 (all floats) shrinks to one value in 40 counts of 7 bits
 
-// V [rows][S][d] -> V^T [rows][d][Sp], keys S .. Sp-1 as zeros.  One workgroup per 32 keys of one row.
-__global__ __launch_bounds__(256) void topk_vt_kernel(const bf16_t *V, bf16_t *Vt, int S, int Sp, int d) {
-  __shared__ uint16_t tile[32 * (128 + 2)];
-  const int str = d + 2;
-  const int key0 = blockIdx.x * 32;
-  const size_t row = blockIdx.y;
-  const uint16_t *src = reinterpret_cast<const uint16_t *>(V) + row * S * d;
-  uint16_t *dst = reinterpret_cast<uint16_t *>(Vt) + row * d * Sp;
-  for (int idx = threadIdx.x; idx < 32 * d; idx += 256) {
-    const int key = idx / d, col = idx - key * d;
-    tile[key * str + col] = key0 + key < S ? src[size_t(key0 + key) * d + col] : uint16_t(0);
-  }
-  __syncthreads();
-  for (int idx = threadIdx.x; idx < 32 * d; idx += 256) {
-    const int col = idx >> 5, key = idx & 31;
-    dst[size_t(col) * Sp + key0 + key] = tile[key * str + col];
-  }
+// Order-preserving image of a weight (larger float <=> larger integer, never 0 for a number) and back.
+__device__ inline uint32_t weight_image(float x) {
+  const uint32_t b = __float_as_uint(x);
+  return b ^ (uint32_t(int32_t(b) >> 31) | 0x80000000u);
+}
+__device__ inline float image_weight(uint32_t u) { return __uint_as_float(u & 0x80000000u ? u ^ 0x80000000u : ~u); }
+
+// z with P(N(0,1) > z) = p, to about 3e-3 (Abramowitz and Stegun, Handbook of Mathematical Functions, 26.2.22)
+__device__ inline float normal_quantile(float p) {
+  const float q = fminf(p, 1.f - p);
+  const float t = __builtin_amdgcn_sqrtf(-1.3862944f * __builtin_amdgcn_logf(fmaxf(q, 1e-7f)));   // sqrt(-2 ln q); logf is base 2
+  const float z = t - (2.30753f + 0.27061f * t) * __builtin_amdgcn_rcpf(1.f + t * (0.99229f + 0.04481f * t));
+  return p <= 0.5f ? z : -z;
 }
 
 struct TopkArgs {
-  const bf16_t *Q, *K;   // [rows][S][d]
-  const bf16_t *Vt;      // [rows][d][Sp]
-  bf16_t *O;             // [rows][S][d]
-  int S, Sp, topk, lstr; // lstr: floats per logit row
-  int rows;
-  int tiles;             // query blocks of the whole launch
-  float *rowbuf;         // long sequences: [workgroups in flight][16][lstr] logit rows in the workspace
-  int region0;           // bytes of the first LDS region (logit rows, later the merge buffer)
-  float scale_log2;      // log2(e) / sqrt(d)
+  const bf16_t *Q, *K, *V;   // [rows][S][d]
+  bf16_t *O;
+  int S, rows, topk;
+  float scale_log2;          // log2(e) / sqrt(d)
 };
 
-// Order-preserving image of a weight: larger float <=> larger integer; -inf (beyond the diagonal) -> 0, below
-// every finite weight.  Adding +0 first makes a negative zero a positive one, so equal weights have equal images.
-__device__ inline uint32_t weight_key(float x) {
-  if (x == -INFINITY) return 0u;
-  const uint32_t b = __float_as_uint(x + 0.0f);
-  return b ^ ((b >> 31) ? 0xffffffffu : 0x80000000u);
-}
+// Shared memory: two K tiles (one in use, one being written), then the histograms or two V tiles; the merge buffer overlays all of
+// it.  The weights set aside and the small arrays sit behind.
+template <int DH, int NQB>
+struct TopkLds {
+  static constexpr int NQ = 32 * NQB;
+  static constexpr int kTile = kStep * DH * 2;
+  static constexpr int kHist = NQ * kBins * 4;
+  static constexpr int kBig = 2 * kTile + (kHist > 2 * kTile ? kHist : 2 * kTile);
+  static constexpr int kMerge = 4 * NQB * (DH / 32) * 16 * 64 * 4;
+  static constexpr int kFewAt = kBig > kMerge ? kBig : kMerge;
+  static constexpr int kMisc = kFewAt + NQ * kFew * 8;
+  static constexpr int kBytes = kMisc + NQ * 23 * 4 + 16;
+};
 
-// NQB: blocks of 16 queries per workgroup; NKMAX: keys of a row a lane can hold (64 * NKMAX >= the keys of a row)
-// One tile of the launch: the 16 * NQB queries of block L (see the mapping below).  slot: which piece of the row
-// buffer in the workspace this workgroup owns (long sequences only).
-template <int DH, int NQB, int NKMAX>
-__device__ inline void topk_tile(const TopkArgs &a, const int L, const int slot) {
-  constexpr int KT = DH / 32;          // matrix instructions along d per 16x16 logit block
-  constexpr int MB = DH / 16;          // 16-wide blocks of the head dimension
-  constexpr int FIN = MB < kWaves ? MB : kWaves;   // waves that finish and store
-  constexpr int OWN = MB / FIN;        // blocks of the head dimension such a wave finishes
-  constexpr int NQ16 = NQB * 16;
-  constexpr int QSTR = DH * 2 + 16;    // bytes per Q row in LDS
-  constexpr int LPR = DH / 8;          // 16-byte vectors per row
-  constexpr int RPW = NQ16 / kWaves;   // query rows a wave selects for
+template <int DH, int NQB>
+__global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkArgs a) {
+  using Lds = TopkLds<DH, NQB>;
+  constexpr int NT = 256 * NQB, NQ = 32 * NQB;
+  constexpr int CPR = DH / 8;                  // 16-byte chunks per row
+  constexpr int NLD = kStep * CPR / NT;        // chunks of a tile per thread
+  constexpr int KT = DH / 16, DB = DH / 32;
   extern __shared__ __align__(16) unsigned char smem[];
-  // the weights of the block's queries: [NQ16][lstr] fp32 in LDS (later the merge buffer), or, for sequences whose
-  // rows LDS cannot hold, in the workgroup's own piece of the workspace (written and read by this workgroup only)
-  constexpr bool LONG = NKMAX == 0;
-  float *s_log = LONG ? a.rowbuf + size_t(slot) * NQ16 * a.lstr : reinterpret_cast<float *>(smem);
-  unsigned char *s_q = smem + a.region0;                                 // [NQ16][QSTR]
-  uint32_t *s_T = reinterpret_cast<uint32_t *>(s_q + NQ16 * QSTR);       // [NQ16] image of the K-th largest weight
-  int32_t *s_tie = reinterpret_cast<int32_t *>(s_T + NQ16);              // [NQ16] equal weights kept up to here
-  float *s_max = reinterpret_cast<float *>(s_tie + NQ16);                // [NQ16]
-  float *s_l = s_max + NQ16;                                             // [kWaves][NQ16]
-  uint32_t *s_hist = reinterpret_cast<uint32_t *>(s_l + kWaves * NQ16);  // [kWaves][256] radix histograms
+  uint32_t *s_hist = reinterpret_cast<uint32_t *>(smem + 2 * Lds::kTile);   // [kBins][NQ]
+  float2 *s_few = reinterpret_cast<float2 *>(smem + Lds::kFewAt);       // [NQ][kFew] weight, bits of its position, of the weights set aside
+  float *s_a = reinterpret_cast<float *>(smem + Lds::kMisc);   // [NQ] bin of w = a w + b, while its histogram is open (else 0)
+  float *s_b = s_a + NQ;
+  float *s_lo = s_b + NQ;                                      // [NQ] the range
+  float *s_hi = s_lo + NQ;
+  float *s_ga = s_hi + NQ;                                     // [NQ] a, b and the bin that holds the K-th largest weight
+  float *s_gb = s_ga + NQ;
+  float *s_bin = s_gb + NQ;
+  int *s_need = reinterpret_cast<int *>(s_bin + NQ);           // [NQ] its rank in that bin: how many of its weights stay
+  int *s_tie = s_need + NQ;                                    // [NQ] crowded bin (-2 until it is known): its weights, all equal, stay up to this position
+  uint32_t *s_max = reinterpret_cast<uint32_t *>(s_tie + NQ);  // [NQ] image of the largest weight
+  int *s_n = reinterpret_cast<int *>(s_max + NQ);              // [NQ] weights set aside
+  float *s_l = reinterpret_cast<float *>(s_n + NQ);            // [4][NQ]
+  uint32_t *s_part = reinterpret_cast<uint32_t *>(s_l + 4 * NQ);   // [8][NQ]
+  int *s_flag = reinterpret_cast<int *>(s_part + 8 * NQ);      // [0] count again, [1] a crowded bin of equal weights
 
-  // Workgroup -> (row, query block).  Consecutive workgroups go to the 8 XCDs in turn, each with an L2 of its own:
-  // all query blocks of a row are given to one XCD (workgroups L, L + 8, L + 16 ...), so that the row's K and V^T
-  // come from memory once instead of once per XCD; within a row the blocks with the most keys start first.
-  const int nq = (a.S + NQ16 - 1) / NQ16;
-  const int full = a.rows / 8 * 8;             // rows that form whole groups of 8
+  // Workgroup -> (row, query block): all blocks of a row on one XCD (consecutive workgroups go to the 8 XCDs in turn), so
+  // that its K and V come from memory once; within a row the blocks with the most keys first.
+  const int nq = (a.S + NQ - 1) / NQ;
+  const int L = blockIdx.x, full = a.rows / 8 * 8;
   int row_, qi;
   if (L < full * nq) {
     const int slot = L >> 3;
@@ -128,452 +138,554 @@ __device__ inline void topk_tile(const TopkArgs &a, const int L, const int slot)
     row_ = full + rest / nq;
     qi = rest - rest / nq * nq;
   }
-  const int qblk = nq - 1 - qi;
-  const size_t bh = size_t(row_);
-  const int q0 = qblk * NQ16;
-  const int nkeys = min(a.S, q0 + NQ16);    // keys a query of this block can see
-  const int nb32 = (nkeys + 31) / 32;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = lane & 15, g = lane >> 4;
-  const int lstr = a.lstr;
+  const int q0 = (nq - 1 - qi) * NQ;
+  const int nkeys = min(a.S, q0 + NQ);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qg = wave % NQB, kg = wave / NQB;
+  const int c = lane & 31, h = lane >> 5;
+  const int ql = qg * 32 + c;                  // the lane's query within the workgroup
+  const int qpos = q0 + ql;
+  const int qfirst = q0 + qg * 32;
+  const size_t base = size_t(row_) * a.S * DH;
+  const bf16_t *Kb = a.K + base, *Vb = a.V + base;
 
-  const bf16_t *Qb = a.Q + bh * a.S * DH;
-  const bf16_t *Kb = a.K + bh * a.S * DH;
-  const bf16_t *Vtb = a.Vt + bh * DH * a.Sp;
-
-  // ---- the query tile ----
-  for (int idx = tid; idx < NQ16 * LPR; idx += 64 * kWaves) {
-    const int row = idx / LPR, ch = idx - row * LPR;
-    u32x4 v = u32x4{0u, 0u, 0u, 0u};
-    if (q0 + row < a.S) v = *reinterpret_cast<const u32x4 *>(Qb + size_t(q0 + row) * DH + ch * 8);
-    *reinterpret_cast<u32x4 *>(s_q + row * QSTR + ch * 16) = v;
-  }
-  int qpos[NQB];
+  // 16-byte chunk `ch` of tile row r, permuted so that neither 8 rows x 1 chunk (the K operand) nor 4 rows x 2 neighbouring
+  // chunks (V, transposed) meet in a bank
+  auto chunk_at = [](int r, int ch) { 
+    const int x = (r & 3) << 1 | ((r >> 2) & 1);
+    return DH == 128 ? r * 256 + ((ch ^ (x | (r & 8))) << 4) : r * 128 + ((ch ^ x) << 4);
+  };
+  // stride_fp: the keys of a sample, key = (index * stride_fp) >> 12
+  const int ld_row = tid / CPR;
+  const uint32_t ld_col = uint32_t(tid % CPR) * 16u;
+  auto load_tile = [&](const bf16_t *src, int step, u32x4 (&r)[NLD]) {
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) qpos[qb] = q0 + qb * 16 + c;
-  __syncthreads();
-
-  // ---- A: logits^T of every eighth block of 32 keys ----
-  {
-    u32x4 kf[2][KT];
-#define LOAD_K(BASE)                                                                         \
-  _Pragma("unroll") for (int sb = 0; sb < 2; ++sb) {                                         \
-    const int key_ = min((BASE) + sb * 16 + c, a.S - 1);                                     \
-    _Pragma("unroll") for (int t = 0; t < KT; ++t)                                           \
-      kf[sb][t] = *reinterpret_cast<const u32x4 *>(Kb + size_t(key_) * DH + (t * 4 + g) * 8); \
-  }
-    if (wave < nb32) { LOAD_K(wave * 32) }
-    for (int blk = wave; blk < nb32; blk += kWaves) {
-      const int base = blk * 32;
-      f32x4 s[2][NQB];
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) s[sb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-        for (int t = 0; t < KT; ++t) {
-          const u32x4 qv = *reinterpret_cast<const u32x4 *>(s_q + (qb * 16 + c) * QSTR + (t * 4 + g) * 16);
-#pragma unroll
-          for (int sb = 0; sb < 2; ++sb)
-            s[sb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(&kf[sb][t]),
-                                                                *reinterpret_cast<const bf16x8 *>(&qv), s[sb][qb], 0, 0, 0);
-        }
-      if (blk + kWaves < nb32) { LOAD_K(base + kWaves * 32) }
-      // a lane holds, for its query, keys base + sb*16 + g*4 + i
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-          f32x4 w;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) w[i] = base + sb * 16 + g * 4 + i <= qpos[qb] ? s[sb][qb][i] : -INFINITY;
-          *reinterpret_cast<f32x4 *>(s_log + (qb * 16 + c) * lstr + base + sb * 16 + g * 4) = w;
-        }
+    for (int i = 0; i < NLD; ++i) {
+      const int key = min(step * kStep + ld_row + i * (NT / CPR), a.S - 1);
+      r[i] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(src) + (uint32_t(key) * (DH * 2) + ld_col));
     }
-#undef LOAD_K
-  }
-  __syncthreads();
-
-  // ---- S: per query row, the maximum, the K-th largest weight and the cut among its equals ----
+  };
+  auto load_sample = [&](int step, uint32_t stride_fp, u32x4 (&r)[NLD]) {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const uint32_t key = (uint32_t(step * kStep + ld_row + i * (NT / CPR)) * stride_fp) >> 12;
+      r[i] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(Kb) + (key * (DH * 2) + ld_col));
+    }
+  };
+  auto store_tile = [&](int dst, const u32x4 (&r)[NLD]) {   // dst: where the tile starts in shared memory
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      *reinterpret_cast<u32x4 *>(smem + dst + chunk_at(ld_row + i * (NT / CPR), tid % CPR)) = r[i];
+    }
+  };
+  // The query operand, through LDS like the keys: straight from memory its 16-byte pieces of 32 rows cost the L1 a look-up per
+  // lane (4096 of them per workgroup, 3 us before the first product).
+  bf16x8 qf[KT];
   {
-    const int tmax = (nb32 * 32 + 63) / 64;   // 64-key groups the rows of this block have
-    for (int rr = 0; rr < RPW; ++rr) {
-      const int row = wave * RPW + rr;
-      const int p = q0 + row;
-      uint32_t T = 0xffffffffu;               // rows beyond the sequence keep nothing
-      int tie = -1;
-      float mx = 0.f;
-      if (LONG && p < a.S) {
-        // The row stays in memory (it was written by this workgroup and comes from the L2): every pass reads it
-        // again, 64 keys at a time.  Four passes always; then the cut among the equal weights in position order.
-        const float *lrow = s_log + row * lstr;
-        const int nkp = nb32 * 32;
-        mx = -INFINITY;
-        for (int j = lane; j < nkp; j += 64) mx = fmaxf(mx, lrow[j]);
+    constexpr int NQL = NQ * CPR / NT;
+    u32x4 r[NQL];
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-        if (p + 1 <= a.topk) {
-          T = 1u;
-          tie = 0x7fffffff;
-        } else {
-          uint32_t *hist = s_hist + wave * 256;
-          uint32_t prefix = 0u;
-          int need = a.topk;
+    for (int i = 0; i < NQL; ++i)
+      r[i] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.Q + base) +
+                                              (uint32_t(min(q0 + ld_row + i * (NT / CPR), a.S - 1)) * (DH * 2) + ld_col));
+#pragma unroll
+    for (int i = 0; i < NQL; ++i) *reinterpret_cast<u32x4 *>(smem + chunk_at(ld_row + i * (NT / CPR), tid % CPR)) = r[i];
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < KT; ++t) qf[t] = *reinterpret_cast<const bf16x8 *>(smem + chunk_at(ql, 2 * t + h));
+  }
+  // Weights of the lane's query against its wave's 32 keys of the K tile at `tile`: [i] is key kg * 32 + 8 (i / 4) + 4 h + i % 4.
+  // meanwhile(g), g = 0 .. 3: other work, a share of it behind every two matrix instructions, in that order (a wave issues in
+  // order: left to itself the compiler puts all of one kind first, and matrix and vector units take turns).
+  auto weights = [&](int tile, auto &&meanwhile) {
+    bf16x8 kv[KT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t) kv[t] = *reinterpret_cast<const bf16x8 *>(smem + tile + chunk_at(kg * 32 + c, 2 * t + h));
+    __builtin_amdgcn_sched_barrier(0);   // all reads on their way before the first product waits for one
+    f32x16 s = {0.f};
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+#pragma unroll
+      for (int t = g * (KT / 4); t < (g + 1) * (KT / 4); ++t) {
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kv[t], qf[t], s, 0, 0, 0);
+        asm volatile("" : "+v"(s));    // issued here, not where the result is first needed
+      }
+      meanwhile(g);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    return s;
+  };
+  auto nothing = [](int) {};
+  // keys from kb on that the query cannot see become NaN, which no comparison lets through
+  auto hide = [&](f32x16 &s, int kb) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (kb + 8 * (i >> 2) + 4 * h + (i & 3) > qpos) s[i] = __builtin_nanf("");
+  };
+
+  // ---- one pass over the keys (SAMPLE: over a sample of those before q0, which all queries see): consume(w0, .. w3, g, first
+  // key) takes the weights of keys 8 g + 4 h .. + 3 of the wave's block ----
+  auto sweep = [&](auto sample_, int steps, uint32_t stride_fp, auto &&consume) {
+    constexpr bool SAMPLE = decltype(sample_)::value;
+    u32x4 kr[NLD];
+    auto load = [&](int st) {
+      if constexpr (SAMPLE)
+        load_sample(st, stride_fp, kr);
+      else
+        load_tile(Kb, st, kr);
+    };
+    load(0);
+    __syncthreads();                   // the tiles of the pass before are done with
+    store_tile(0, kr);
+    if (steps > 1) load(1);
+    __syncthreads();
+    if (steps > 1) store_tile(Lds::kTile, kr);
+    if (steps > 2) load(2);
+    f32x16 s = weights(0, nothing);
+    int kb = kg * 32;
+    if (!SAMPLE && kb + 31 > qfirst) hide(s, kb);
+    for (int st = 1; st < steps; ++st) {
+      __syncthreads();                 // tile st is there, and nobody reads tile st - 1 any more
+      if (st + 1 < steps) store_tile(((st + 1) & 1) * Lds::kTile, kr);
+      if (st + 2 < steps) load(st + 2);
+      const f32x16 w = s;
+      s = weights((st & 1) * Lds::kTile, [&](int g) { consume(w[4 * g], w[4 * g + 1], w[4 * g + 2], w[4 * g + 3], g, kb); });
+      kb += kStep;
+      if (!SAMPLE && kb + 31 > qfirst) hide(s, kb);
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) consume(s[4 * g], s[4 * g + 1], s[4 * g + 2], s[4 * g + 3], g, kb);
+  };
+  const int steps = (nkeys + kStep - 1) / kStep;
+
+  // ---- 1: the range ----
+  {
+    float sum = 0.f, sq = 0.f;
+    const bool sampled = q0 >= kSample;
+    auto moments = [&](float w0, float w1, float w2, float w3, int, int) {
+      const float x0 = w0 == w0 ? w0 : 0.f, x1 = w1 == w1 ? w1 : 0.f, x2 = w2 == w2 ? w2 : 0.f, x3 = w3 == w3 ? w3 : 0.f;
+      sum += (x0 + x1) + (x2 + x3);
+      sq += fmaf(x0, x0, x1 * x1) + fmaf(x2, x2, x3 * x3);
+    };
+    if (sampled)
+      sweep(std::true_type(), kSample / kStep, (uint32_t(q0) << 12) / kSample, moments);
+    else
+      sweep(std::false_type(), steps, 0u, moments);
+    sum += __shfl_xor(sum, 32, 64);
+    sq += __shfl_xor(sq, 32, 64);
+    float *part = reinterpret_cast<float *>(s_part);
+    if (h == 0) {
+      part[kg * NQ + ql] = sum;
+      part[(4 + kg) * NQ + ql] = sq;
+    }
+    __syncthreads();
+    if (tid < NQ) {
+      float t0 = 0.f, t1 = 0.f;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        t0 += part[g * NQ + tid];
+        t1 += part[(4 + g) * NQ + tid];
+      }
+      const int n = q0 + tid + 1;
+      const float inv = 1.f / float(sampled ? kSample : min(n, a.S));
+      const float mean = t0 * inv, dev = __builtin_amdgcn_sqrtf(fmaxf(t1 * inv - mean * mean, 0.f));
+      const float mid = fmaf(dev, normal_quantile(fminf(float(a.topk) / float(n), 1.f)), mean);
+      const float half = fmaxf(fmaxf(dev, 1e-6f * fabsf(mid)), 1e-30f);
+      const bool open = n <= a.S && n > a.topk;   // else: all stay, or no such query
+      const float lo = mid - half, hi = mid + half, sa = float(kBins - 2) / (hi - lo);
+      s_lo[tid] = lo;
+      s_hi[tid] = hi;
+      s_a[tid] = open ? sa : 0.f;
+      s_b[tid] = open ? fmaf(-lo, sa, 1.f) : 0.f;
+      s_ga[tid] = 0.f;                            // unless a bin is found: 0 w + 1 - 0 >= 1, everything is above it
+      s_gb[tid] = 1.f;
+      s_bin[tid] = 0.f;
+      s_need[tid] = 0;
+      s_tie[tid] = -1;
+      s_max[tid] = 0u;
+      s_n[tid] = 0;
+    }
+    if (tid < 4) s_flag[tid] = 0;
+  }
+
+  // ---- 2: the bin of the K-th largest weight ----
 #pragma unroll 1
-          for (int shift = 24; shift >= 0; shift -= 8) {
+  for (int tries = 0; tries < kMaxCounts; ++tries) {
+    for (int i = tid; i < NQ * kBins / 4; i += NT) reinterpret_cast<u32x4 *>(s_hist)[i] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    {
+      const float sa = s_a[ql], sb = s_b[ql];
+      float top = -INFINITY;
+      sweep(std::false_type(), steps, 0u, [&](float w0, float w1, float w2, float w3, int, int) {
+        const float w[4] = {w0, w1, w2, w3};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) hist[lane + 64 * i] = 0u;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t himask = shift == 24 ? 0u : 0xffffffffu << (shift + 8);
-            for (int j = lane; j < nkp; j += 64) {
-              const uint32_t uj = weight_key(lrow[j]);
-              if (uj != 0u && (uj & himask) == prefix) atomicAdd(&hist[(uj >> shift) & 255u], 1u);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            int bin, rest, inbin;
-            pick_bin(hist, lane, need, bin, rest, inbin);
-            need = rest;
-            prefix |= uint32_t(bin) << shift;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+        for (int i = 0; i < 4; ++i) {
+          const float y = __builtin_amdgcn_fmed3f(fmaf(w[i], sa, sb), 0.f, float(kBins - 1));
+          __hip_atomic_fetch_add(&s_hist[__float2uint_rz(y) * NQ + ql], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        top = fmaxf(fmaxf(top, fmaxf(w0, w1)), fmaxf(w2, w3));
+      });
+      __hip_atomic_fetch_max(&s_max[ql], weight_image(top), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __syncthreads();
+    // eight threads per query, 16 bins each
+    const int q = tid % NQ, grp = tid / NQ;
+    const float sa = s_a[q];
+    uint32_t cnt[kBins / 8], mine = 0u;
+#pragma unroll
+    for (int j = 0; j < kBins / 8; ++j) {
+      cnt[j] = s_hist[(grp * (kBins / 8) + j) * NQ + q];
+      mine += cnt[j];
+    }
+    s_part[grp * NQ + q] = mine;
+    __syncthreads();
+    uint32_t above = 0u;
+#pragma unroll
+    for (int g = 1; g < 8; ++g) above += g > grp ? s_part[g * NQ + q] : 0u;
+    const uint32_t want = uint32_t(a.topk);
+    if (sa != 0.f && above < want && above + mine >= want) {   // this thread's bins hold it
+      int bin = 0, need = 0;
+      uint32_t in = 0u;
+      bool found = false;
+#pragma unroll
+      for (int j = kBins / 8 - 1; j >= 0; --j) {
+        if (!found && above + cnt[j] >= want) {
+          found = true;
+          bin = grp * (kBins / 8) + j;
+          need = int(want - above);
+          in = cnt[j];
+        }
+        above += cnt[j];
+      }
+      float lo = s_lo[q], hi = s_hi[q];
+      const float width = (hi - lo) * (1.f / float(kBins - 2));
+      bool again = true;
+      if (bin == 0) {                          // below the range
+        hi = lo + width;
+        lo = lo - 8.f * float(kBins - 2) * width;
+      } else if (bin == kBins - 1) {           // above it
+        lo = hi - width;
+        hi = hi + 8.f * float(kBins - 2) * width;
+      } else {
+        const float at = fmaf(float(bin - 1), width, lo);
+        // one value per bin at most: more than a few weights in it are equal ones
+        const bool one_value = fmaxf(fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-24f, 1e-30f) >= width;
+        if (in <= uint32_t(kFew) || one_value) {
+          again = false;
+          s_ga[q] = sa;
+          s_gb[q] = s_b[q];
+          s_bin[q] = float(bin);
+          s_need[q] = need;
+          s_a[q] = 0.f;
+          s_b[q] = 0.f;
+          if (in > uint32_t(kFew)) {
+            s_tie[q] = -2;
+            s_flag[1] = 1;
           }
-          T = prefix;
-          for (int j0 = 0; j0 < nkp && tie < 0; j0 += 64) {     // nkp is a multiple of 32: guard the last half group
-            const uint32_t uj = j0 + lane < nkp ? weight_key(lrow[j0 + lane]) : 0u;
-            unsigned long long m = __builtin_amdgcn_ballot_w64(uj == T);
-            const int cnt = __builtin_popcountll(m);
-            if (need > cnt) {
-              need -= cnt;
-            } else {
-              for (int i = 1; i < need; ++i) m &= m - 1;
-              tie = __builtin_ctzll(m) + j0;
-            }
-          }
+        } else {                               // a bin's width to spare on either side, for rounding
+          lo = at - 0.25f * width;
+          hi = at + 1.25f * width;
+          lo = fminf(lo, image_weight(weight_image(lo) - 2u));
+          hi = fmaxf(hi, image_weight(weight_image(hi) + 2u));
         }
       }
-      if constexpr (!LONG) if (p < a.S) {
-        const float *lrow = s_log + row * lstr;
-        uint32_t u[NKMAX];
-        mx = -INFINITY;
+      if (again) {
+        const float na = float(kBins - 2) / (hi - lo);
+        s_lo[q] = lo;
+        s_hi[q] = hi;
+        s_a[q] = na;
+        s_b[q] = fmaf(-lo, na, 1.f);
+        s_flag[0] = 1;
+      }
+    }
+    __syncthreads();
+    const bool more = s_flag[0] != 0;
+    __syncthreads();
+    if (!more) break;
+    if (tid == 0) s_flag[0] = 0;
+  }
+
+  // ---- 3: the position up to which the weights of a bin stay that holds many equal ones ----
+  const float ga = s_ga[ql], gb = s_gb[ql], bin = s_bin[ql];
+  // where a weight stands to its query's bin: >= 1 above it, in [0, 1) inside it, else below (exact: rounding is monotone,
+  // and the difference is exact inside the bin); NaN for keys the query does not see
+  auto place = [&](float w) { return fmaf(w, ga, gb) - bin; };
+  auto inside = [](float z) { return __float_as_uint(z) < 0x3f800000u; };
+  const bool crowded = s_flag[1] != 0;
+  if (crowded) {
+    for (int st = 0; st < steps; ++st) {
+      u32x4 kr[NLD];
+      load_tile(Kb, st, kr);
+      __syncthreads();
+      store_tile(0, kr);
+      __syncthreads();
+      const int kb = st * kStep + kg * 32;
+      uint32_t mask = 0u;
+      f32x16 s = weights(0, nothing);
+      if (kb + 31 > qfirst) hide(s, kb);
 #pragma unroll
-        for (int t = 0; t < NKMAX; ++t) {
-          u[t] = 0u;
-          if (t < tmax) {
-            const int j = lane + 64 * t;
-            const float x = j < nb32 * 32 ? lrow[j] : -INFINITY;
-            mx = fmaxf(mx, x);
-            u[t] = weight_key(x);
+      for (int i = 0; i < 16; ++i) mask |= inside(place(s[i])) ? 1u << i : 0u;
+      s_part[(kg * 2 + h) * NQ + ql] = mask;
+      __syncthreads();
+      if (tid < NQ && s_tie[tid] == -2) {
+        int need = s_need[tid];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const uint32_t m0 = s_part[2 * b * NQ + tid], m1 = s_part[(2 * b + 1) * NQ + tid];
+          uint32_t pm = 0u;   // the block's 32 keys in order
+#pragma unroll
+          for (int j = 0; j < 4; ++j) pm |= ((m0 >> (4 * j)) & 15u) << (8 * j) | ((m1 >> (4 * j)) & 15u) << (8 * j + 4);
+          const int here = __builtin_popcount(pm);
+          if (need > 0 && need <= here) {
+            for (int i = 1; i < need; ++i) pm &= pm - 1u;
+            s_tie[tid] = st * kStep + b * 32 + __builtin_ctz(pm);
+            need = 0;
+          } else if (need > 0) {
+            need -= here;
           }
         }
+        if (need > 0) s_need[tid] = need;
+      }
+    }
+    __syncthreads();
+  }
+
+  // ---- 4: O^T += V^T . P^T ----
+  f32x16 o[DB];
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-        if (p + 1 <= a.topk) {
-          T = 1u;                             // below the image of every finite weight: all visible keys stay
-          tie = 0x7fffffff;
-        } else {
-          // radix select, 8 bits a pass from the top: `prefix` = the bits of the K-th largest image decided so
-          // far, `need` = its rank among the images that share them (1 = the largest)
-          uint32_t *hist = s_hist + wave * 256;
-          uint32_t prefix = 0u;
-          int need = a.topk;
-#pragma unroll 1
-          for (int shift = 24; shift >= 0; shift -= 8) {
+  for (int db = 0; db < DB; ++db) o[db] = f32x16{0.f};
+  float lsum = 0.f;
+  {
+    const float negmax = -image_weight(s_max[ql]) * a.scale_log2;
+    const int tie = s_tie[ql];
+    const int grp = lane >> 4, vrow = 4 * (grp >> 1) + ((lane & 15) >> 2), vcol = (grp & 1) * 16 + (lane & 3) * 4;
+    // K is one step ahead of V: a step's products Q K^T run next to the exponentials of the step before
+    constexpr int kV = 2 * Lds::kTile;
+    u32x4 kr[NLD], vr[NLD];
+    load_tile(Kb, 0, kr);
+    __syncthreads();
+    store_tile(0, kr);
+    if (steps > 1) load_tile(Kb, 1, kr);
+    load_tile(Vb, 0, vr);
+    __syncthreads();
+    if (steps > 1) store_tile(Lds::kTile, kr);
+    store_tile(kV, vr);
+    if (steps > 2) load_tile(Kb, 2, kr);
+    if (steps > 1) load_tile(Vb, 1, vr);
+    f32x16 s = weights(0, nothing);
+    int kb = kg * 32;
+    if (kb + 31 > qfirst) hide(s, kb);
+    for (int st = 1; st <= steps; ++st) {
+      __syncthreads();                         // tiles st of K and st - 1 of V are there
+      if (st + 1 < steps) store_tile(((st + 1) & 1) * Lds::kTile, kr);
+      if (st < steps) store_tile(kV + (st & 1) * Lds::kTile, vr);
+      if (st + 2 < steps) load_tile(Kb, st + 2, kr);
+      if (st + 1 < steps) load_tile(Vb, st + 1, vr);
+      // P of two of the lane's weights, as two bf16 terms: the upper 16 bits, and the upper 16 bits of what is left (exact, >= 0)
+      auto exponentials = [&](float x0, float x1, float z0, float z1, uint32_t &ph, uint32_t &pl) {
+        const float p0 = z0 >= 1.f ? __builtin_amdgcn_exp2f(fmaf(x0, a.scale_log2, negmax)) : 0.f;
+        const float p1 = z1 >= 1.f ? __builtin_amdgcn_exp2f(fmaf(x1, a.scale_log2, negmax)) : 0.f;
+        lsum += p0 + p1;
+        const uint32_t h0 = __float_as_uint(p0), h1 = __float_as_uint(p1);
+        ph = __builtin_amdgcn_perm(h1, h0, 0x07060302u);   // (h0 >> 16) | (h1 & 0xffff0000)
+        pl = __builtin_amdgcn_perm(__float_as_uint(p1 - __uint_as_float(h1 & 0xffff0000u)),
+                                   __float_as_uint(p0 - __uint_as_float(h0 & 0xffff0000u)), 0x07060302u);
+        asm volatile("" : "+v"(ph), "+v"(pl));   // done here, between the matrix instructions
+      };
+      // V^T operand: head dimensions db * 32 + c; element e of lane half h is key 16 ks + 8 (e / 4) + 4 h + e % 4
+      const int vt = kV + ((st - 1) & 1) * Lds::kTile;
+      union Operand {
+        s16x4 q[2];
+        bf16x8 v;
+      };
+      Operand vo[DB];
+      auto read_v = [&](int ks, int db) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) hist[lane + 64 * i] = 0u;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // one wave's LDS operations run in order
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t himask = shift == 24 ? 0u : 0xffffffffu << (shift + 8);
+        for (int e4 = 0; e4 < 2; ++e4) {
+          const int r = kg * 32 + 16 * ks + 8 * e4 + vrow, col = db * 32 + vcol;
+          const uint32_t at = vt + chunk_at(r, col >> 3) + (col & 4) * 2;
+          vo[db].q[e4] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(smem + at));
+        }
+      };
+      auto add_product = [&](int db, const u32x4 &ph, const u32x4 &pl) {
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vo[db].v, *reinterpret_cast<const bf16x8 *>(&ph), o[db], 0, 0, 0);
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vo[db].v, *reinterpret_cast<const bf16x8 *>(&pl), o[db], 0, 0, 0);
+        asm volatile("" : "+v"(o[db]));
+      };
+      const f32x16 w = s;
+      uint32_t ph[8], pl[8];
+      s = weights((st & 1) * Lds::kTile, [&](int g) {   // (the last time nothing comes of it)
+        float z[4];
 #pragma unroll
-            for (int t = 0; t < NKMAX; ++t)
-              if (t < tmax && u[t] != 0u && (u[t] & himask) == prefix) atomicAdd(&hist[(u[t] >> shift) & 255u], 1u);
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            int bin, rest, inbin;
-            pick_bin(hist, lane, need, bin, rest, inbin);
-            need = rest;
-            prefix |= uint32_t(bin) << shift;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the reads above come before the next writes
-            __builtin_amdgcn_wave_barrier();
-            if (shift > 0 && inbin <= 64) {
-              // Few images share the bits decided so far: rank them directly instead of two or three more passes.
-              // They are gathered in position order (ballots), one per lane; the one with need-1 others before it
-              // in the order (image descending, position ascending) is the last key that stays.
-              const uint32_t decided = 0xffffffffu << shift;
-              uint32_t *cand = hist;          // [64] images, [64] positions: the histogram is not needed any more
-              int base = 0;
+        for (int i = 0; i < 4; ++i) z[i] = place(w[4 * g + i]);
+        if (min(min(__float_as_uint(z[0]), __float_as_uint(z[1])), min(__float_as_uint(z[2]), __float_as_uint(z[3]))) < 0x3f800000u) {
 #pragma unroll
-              for (int t = 0; t < NKMAX; ++t) {
-                if (t < tmax) {
-                  const bool member = u[t] != 0u && (u[t] & decided) == prefix;
-                  const unsigned long long m = __builtin_amdgcn_ballot_w64(member);
-                  if (m != 0ull) {
-                    if (member) {
-                      const int slot = base + int(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)));
-                      cand[slot] = u[t];
-                      cand[64 + slot] = uint32_t(lane + 64 * t);
-                    }
-                    base += __builtin_popcountll(m);
-                  }
-                }
-              }
-              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-              __builtin_amdgcn_wave_barrier();
-              const bool have = lane < base;
-              const uint32_t ui = have ? cand[lane] : 0u;
-              const int pi = have ? int(cand[64 + lane]) : 0;
-              int before = 0;
-              for (int j = 0; j < base; ++j) {
-                const uint32_t uj = cand[j];
-                const int pj = int(cand[64 + j]);
-                before += (uj > ui || (uj == ui && pj < pi)) ? 1 : 0;
-              }
-              const int last = __builtin_ctzll(__builtin_amdgcn_ballot_w64(have && before == need - 1));
-              prefix = __shfl(ui, last, 64);
-              tie = __shfl(pi, last, 64);
-              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-              __builtin_amdgcn_wave_barrier();
-              break;
-            }
-          }
-          T = prefix;   // all 32 bits decided: `need` of the weights equal to it stay, the lowest positions first
-#pragma unroll
-          for (int t = 0; t < NKMAX; ++t) {
-            if (t < tmax && tie < 0) {
-              unsigned long long m = __builtin_amdgcn_ballot_w64(u[t] == T);
-              const int cnt = __builtin_popcountll(m);
-              if (need > cnt) {
-                need -= cnt;
+          for (int i = 0; i < 4; ++i)
+            if (inside(z[i])) {
+              const int pos = kb + 8 * g + 4 * h + i;
+              if (crowded && tie >= 0) {
+                if (pos <= tie) z[i] = 1.f;    // stays
               } else {
-                for (int i = 1; i < need; ++i) m &= m - 1;   // drop the need-1 lowest positions
-                tie = __builtin_ctzll(m) + 64 * t;
+                const int at = __hip_atomic_fetch_add(&s_n[ql], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (at < kFew) s_few[ql * kFew + at] = float2{w[4 * g + i], __int_as_float(pos)};
               }
             }
-          }
         }
+        exponentials(w[4 * g], w[4 * g + 1], z[0], z[1], ph[2 * g], pl[2 * g]);
+        exponentials(w[4 * g + 2], w[4 * g + 3], z[2], z[3], ph[2 * g + 1], pl[2 * g + 1]);
+        if (g >= 4 - DB) read_v(0, g - 4 + DB);
+      });
+#pragma unroll
+      for (int g = 0; g < DB; ++g) {
+        add_product(g, u32x4{ph[0], ph[1], ph[2], ph[3]}, u32x4{pl[0], pl[1], pl[2], pl[3]});
+        read_v(1, g);
       }
-      if (lane == 0) {
-        s_T[row] = T;
-        s_tie[row] = tie;
-        s_max[row] = mx;
+#pragma unroll
+      for (int g = 0; g < DB; ++g) add_product(g, u32x4{ph[4], ph[5], ph[6], ph[7]}, u32x4{pl[4], pl[5], pl[6], pl[7]});
+      kb += kStep;
+      if (kb + 31 > qfirst) hide(s, kb);
+    }
+  }
+
+  // ---- 5: the weights set aside, and the four key groups' partial sums in order ----
+  lsum += __shfl_xor(lsum, 32, 64);
+  if (h == 0) s_l[kg * NQ + ql] = lsum;
+  __syncthreads();
+  f32x4 *s_mrg = reinterpret_cast<f32x4 *>(smem);   // [wave][DB][4][64], lanes permuted so that the reads below spread over the banks
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      s_mrg[((wave * DB + db) * 4 + j) * 64 + (lane ^ ((db * 4 + j) & 7))] = f32x4{o[db][4 * j], o[db][4 * j + 1], o[db][4 * j + 2], o[db][4 * j + 3]};
+  // Eight threads per query: each ranks two of the weights and notes the ones that stay; then each adds an eighth of their rows
+  // of V, in fp32.
+  const int q = tid / 8, sub = tid & 7, held = min(s_n[q], kFew), need = s_need[q];
+  float extra[DH / 8] = {0.f}, extra_l = 0.f;
+  if (held > 0) {
+    float2 mine[2];
+    int before[2] = {0, 0};
+#pragma unroll
+    for (int e = 0; e < 2; ++e) mine[e] = s_few[q * kFew + sub + 8 * e];
+    for (int j = 0; j < held; ++j) {
+      const float2 v = s_few[q * kFew + j];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) before[e] += v.x > mine[e].x || (v.x == mine[e].x && __float_as_int(v.y) < __float_as_int(mine[e].y)) ? 1 : 0;
+    }
+    // in the order of their rank, so that the sum does not hang on the order they were set aside in
+    wave_lds_fence();
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      if (sub + 8 * e < held) s_few[q * kFew + before[e]] = mine[e];
+    wave_lds_fence();
+    const float negmax = -image_weight(s_max[q]) * a.scale_log2;
+    const int stay = min(need, held);
+    for (int j0 = 0; j0 < stay; j0 += 4) {     // four rows on their way at once
+      u32x4 row[4][DH / 64];
+      float p[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float2 v = s_few[q * kFew + min(j0 + j, stay - 1)];
+        p[j] = j0 + j < stay ? __builtin_amdgcn_exp2f(fmaf(v.x, a.scale_log2, negmax)) : 0.f;
+        const bf16_t *src = Vb + size_t(__float_as_int(v.y)) * DH + sub * 8;
+#pragma unroll
+        for (int e = 0; e < DH / 64; ++e) row[j][e] = *reinterpret_cast<const u32x4 *>(src + 64 * e);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        extra_l += p[j];
+#pragma unroll
+        for (int e = 0; e < DH / 64; ++e)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            extra[8 * e + 2 * i] = fmaf(p[j], __uint_as_float(row[j][e][i] << 16), extra[8 * e + 2 * i]);
+            extra[8 * e + 2 * i + 1] = fmaf(p[j], __uint_as_float(row[j][e][i] & 0xffff0000u), extra[8 * e + 2 * i + 1]);
+          }
       }
     }
   }
   __syncthreads();
-
-  // ---- B: O^T += V^T . P^T over every eighth block of 32 keys ----
-  uint32_t Tq[NQB];
-  int tieq[NQB];
-  float negmax[NQB], lsum[NQB];
-  f32x4 o[MB][NQB];
+  // The same thread finishes its eighth of the query's row: head dimension d sits at block d / 32, element 4 ((d / 8) % 4) + d % 4 of the
+  // lane half (d / 4) % 2.
+  float l = extra_l;
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    Tq[qb] = s_T[qb * 16 + c];
-    tieq[qb] = s_tie[qb * 16 + c];
-    negmax[qb] = -s_max[qb * 16 + c] * a.scale_log2;
-    lsum[qb] = 0.f;
+  for (int g = 0; g < 4; ++g) l += s_l[g * NQ + q];
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+  if (q0 + q < a.S) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) o[mb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  for (int blk = wave; blk < nb32; blk += kWaves) {
-    const int base = blk * 32;
-    u32x4 vf[MB];   // V^T: head dimension mb*16 + c, keys base + 8g .. + 7
+    for (int e = 0; e < DH / 64; ++e) {        // eight head dimensions from 64 e + 8 sub on
+      const int db = 2 * e + sub / 4, j = sub % 4;
+      uint32_t r[8];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) vf[mb] = *reinterpret_cast<const u32x4 *>(Vtb + size_t(mb * 16 + c) * a.Sp + base + 8 * g);
-    u32x4 bhi[NQB], blo[NQB];
+      for (int half = 0; half < 2; ++half) {
+        f32x4 sum = f32x4{extra[8 * e + 4 * half], extra[8 * e + 4 * half + 1], extra[8 * e + 4 * half + 2], extra[8 * e + 4 * half + 3]};
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-      const float *src = s_log + (qb * 16 + c) * lstr + base + 8 * g;
-      const f32x4 x0 = *reinterpret_cast<const f32x4 *>(src), x1 = *reinterpret_cast<const f32x4 *>(src + 4);
-      uint32_t hi[8], lo[8];
-      float psum = 0.f;
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 v = s_mrg[(((g * NQB + q / 32) * DB + db) * 4 + j) * 64 + ((half * 32 + (q & 31)) ^ ((db * 4 + j) & 7))];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = e < 4 ? x0[e] : x1[e - 4];
-        const uint32_t uk = weight_key(x);
-        const bool keep = uk > Tq[qb] || (uk == Tq[qb] && base + 8 * g + e <= tieq[qb]);
-        const float pe = keep ? __builtin_amdgcn_exp2f(fmaf(x, a.scale_log2, negmax[qb])) : 0.f;
-        psum += pe;
-        // two bf16 terms: the upper 16 bits, and the upper 16 bits of what is left (exact, >= 0)
-        hi[e] = __float_as_uint(pe);
-        lo[e] = __float_as_uint(pe - __uint_as_float(hi[e] & 0xffff0000u));
+          for (int i = 0; i < 4; ++i) sum[i] += v[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[4 * half + i] = f32_to_bf16_rne(sum[i] * inv);
       }
-      lsum[qb] += psum;
-#define PACK_HI(A, B) __builtin_amdgcn_perm(B, A, 0x07060302u)   /* (A >> 16) | (B & 0xffff0000) */
-      bhi[qb] = u32x4{PACK_HI(hi[0], hi[1]), PACK_HI(hi[2], hi[3]), PACK_HI(hi[4], hi[5]), PACK_HI(hi[6], hi[7])};
-      blo[qb] = u32x4{PACK_HI(lo[0], lo[1]), PACK_HI(lo[2], lo[3]), PACK_HI(lo[4], lo[5]), PACK_HI(lo[6], lo[7])};
-#undef PACK_HI
-    }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        o[mb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(&vf[mb]),
-                                                            *reinterpret_cast<const bf16x8 *>(&bhi[qb]), o[mb][qb], 0, 0, 0);
-        o[mb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(&vf[mb]),
-                                                            *reinterpret_cast<const bf16x8 *>(&blo[qb]), o[mb][qb], 0, 0, 0);
-      }
-  }
-
-  // ---- M: add the four waves' partial results in wave order ----
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    float l = lsum[qb];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
-    if (g == 0) s_l[wave * NQ16 + qb * 16 + c] = l;
-  }
-  __syncthreads();   // every wave is done with the logit rows, which the merge buffer overlays
-  f32x4 *s_mrg = reinterpret_cast<f32x4 *>(smem);   // [kWaves][MB][NQB][64 lanes]
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) s_mrg[((wave * MB + mb) * NQB + qb) * 64 + lane] = o[mb][qb];
-  __syncthreads();
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    const int q = q0 + qb * 16 + c;
-    float L = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) L += s_l[w * NQ16 + qb * 16 + c];
-    const float inv = L > 0.f ? 1.f / L : 0.f;
-#pragma unroll
-    for (int j = 0; j < OWN; ++j) {
-      if (wave >= FIN) break;
-      const int mb = wave * OWN + j;
-      f32x4 fin = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        const f32x4 v = s_mrg[((w * MB + mb) * NQB + qb) * 64 + lane];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) fin[i] += v[i];
-      }
-      if (q < a.S) {   // a lane holds 4 consecutive head dimensions of one query
-        uint32_t r[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = f32_to_bf16_rne(fin[i] * inv);
-        *reinterpret_cast<u32x2 *>(a.O + (bh * a.S + q) * DH + mb * 16 + g * 4) = u32x2{r[0] | (r[1] << 16), r[2] | (r[3] << 16)};
-      }
+      *reinterpret_cast<u32x4 *>(a.O + base + size_t(q0 + q) * DH + 64 * e + 8 * sub) =
+          u32x4{r[0] | (r[1] << 16), r[2] | (r[3] << 16), r[4] | (r[5] << 16), r[6] | (r[7] << 16)};
     }
   }
 }
 
-// Sequences whose logit rows live in LDS: one workgroup per tile.  Longer ones (NKMAX == 0): a grid of as many
-// workgroups as the chip holds at once, each walking over tiles L, L + gridDim, ... with one piece of the row buffer
-// of its own, so that the buffer is sized by the workgroups in flight, not by the tiles (rows * seq * seq floats).
-// gridDim is a multiple of 8 there, so a workgroup's tiles stay on its XCD's rows.
-template <int DH, int NQB, int NKMAX>
-__global__ __launch_bounds__(64 * kWaves, NQB == 1 && NKMAX <= 16 ? 2 : 1) void topk_attend_kernel(const TopkArgs a) {
-  if constexpr (NKMAX != 0) {
-    topk_tile<DH, NQB, NKMAX>(a, blockIdx.x, 0);
-  } else {
-    for (int L = blockIdx.x; L < a.tiles; L += gridDim.x) {
-      topk_tile<DH, NQB, NKMAX>(a, L, blockIdx.x);
-      __syncthreads();   // the next tile reuses LDS and the workgroup's rows in the workspace
-    }
-  }
-}
-
-size_t padded_keys(int S) { return size_t(S + 31) / 32 * 32; }
-size_t vt_bytes(int rows, int S, int d) { return (size_t(rows) * d * padded_keys(S) * 2 + 255) / 256 * 256; }
-
-template <int DH, int NQB, int NKMAX>
-hipError_t launch(const TopkArgs &base, int rows, hipStream_t st) {
-  TopkArgs a = base;
-  constexpr int NQ16 = NQB * 16;
-  a.lstr = a.Sp + 4;
-  const int logit_bytes = NKMAX == 0 ? 0 : NQ16 * a.lstr * 4;
-  const int merge_bytes = kWaves * (DH / 16) * NQB * 64 * 16;
-  a.region0 = (logit_bytes > merge_bytes ? logit_bytes : merge_bytes);
-  const int lds = a.region0 + NQ16 * (DH * 2 + 16) + NQ16 * 12 + kWaves * NQ16 * 4 + kWaves * 256 * 4;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&topk_attend_kernel<DH, NQB, NKMAX>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+template <int DH, int NQB>
+hipError_t launch(const TopkArgs &a, hipStream_t st) {
+  constexpr int lds = TopkLds<DH, NQB>::kBytes;
+  static_assert(lds <= 160 * 1024, "shared memory of a compute unit");
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&topk_attend_kernel<DH, NQB>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  a.rows = rows;
-  a.tiles = ((a.S + NQ16 - 1) / NQ16) * rows;
-  const dim3 grid(unsigned(NKMAX == 0 ? min(a.tiles, kLongGrid) : a.tiles)), block(64 * kWaves);
-  hipLaunchKernelGGL((topk_attend_kernel<DH, NQB, NKMAX>), grid, block, lds, st, a);
+  const int tiles = (a.S + 32 * NQB - 1) / (32 * NQB) * a.rows;
+  hipLaunchKernelGGL((topk_attend_kernel<DH, NQB>), dim3(unsigned(tiles)), dim3(256 * NQB), lds, st, a);
   return hipGetLastError();
 }
 
-}  // namespace
+constexpr int kMaxStaticSeq = 2048;  // longest sequence adore_topk_attention_static takes
+constexpr int kMaxSeq = 32768;       // longest sequence taken at all
 
-}  // namespace adore
-
-// ---- the entry point that allocates nothing ---------------------------------------------------------------
-// The transposed copy of V of adore_topk_attention_static lives in this array instead of a caller's workspace.
-// Every GPU the library runs on holds its own copy of it, at its own address, until the process ends.  In host
-// code the name is only a handle for hipGetSymbolAddress: what kernels and copies get is the address looked up
-// below, once per device.
-static __device__ __align__(256) unsigned char scratch[ADORE_TOPK_STATIC_SCRATCH_BYTES];
-
-namespace adore {
-namespace {
-
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mutex;
-void *g_scratch_ptr[kMaxDevices] = {};   // by device ordinal; null = not looked up yet
-
-// The address of `scratch` on the current device (looked up on the first call on that device), or null.
-void *static_scratch() {
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
-  std::lock_guard<std::mutex> lock(g_scratch_mutex);
-  if (!g_scratch_ptr[dev]) {
-    void *ptr = nullptr;
-    if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess) return nullptr;
-    g_scratch_ptr[dev] = ptr;
-  }
-  return g_scratch_ptr[dev];
-}
-
-// The launches of both entry points: the transposed copy of V into vt, then the attention.  seq <= kMaxSeq unless
-// rowbuf is given.
-int enqueue_topk(const void *q, const void *k, const void *v, void *out, void *vt, float *rowbuf, int rows, int seq,
-                 int head_dim, int top_k, hipStream_t st) {
-  const int Sp = int(padded_keys(seq));
-  hipLaunchKernelGGL(topk_vt_kernel, dim3(Sp / 32, rows), dim3(256), 0, st, static_cast<const bf16_t *>(v),
-                     static_cast<bf16_t *>(vt), seq, Sp, head_dim);
-  if (hipGetLastError() != hipSuccess) return ADORE_E_HIP;
+// The launch of both entry points.  64 queries per workgroup read K and V half as often; 32 where that leaves compute units
+// without one (two workgroups of 64 queries per unit keep the tail of a launch short).
+int enqueue_topk(const void *q, const void *k, const void *v, void *out, int rows, int seq, int head_dim, int top_k,
+                 hipStream_t st) {
   TopkArgs a;
   a.Q = static_cast<const bf16_t *>(q);
   a.K = static_cast<const bf16_t *>(k);
-  a.Vt = static_cast<const bf16_t *>(vt);
+  a.V = static_cast<const bf16_t *>(v);
   a.O = static_cast<bf16_t *>(out);
-  a.S = seq; a.Sp = Sp; a.topk = top_k; a.lstr = 0; a.region0 = 0; a.rows = rows;
-  a.rowbuf = rowbuf;
+  a.S = seq;
+  a.rows = rows;
+  a.topk = top_k;
   a.scale_log2 = 1.4426950408889634f / sqrtf(float(head_dim));
   hipError_t e;
-  // 16 queries per workgroup: their fp32 weights take 64 KB of LDS at 1024 keys, so two workgroups (16 waves) share
-  // a compute unit and hide each other's latencies (32 queries per workgroup, one workgroup per unit, read K and V
-  // half as often and took 3.33 ms where this takes 2.27 ms)
-  if (seq <= kMaxSeq / 2)
-    e = head_dim == 128 ? launch<128, 1, 16>(a, rows, st) : launch<64, 1, 16>(a, rows, st);
-  else if (seq <= kMaxSeq)
-    e = head_dim == 128 ? launch<128, 1, 32>(a, rows, st) : launch<64, 1, 32>(a, rows, st);
-  else   // logit rows in the workspace
-    e = head_dim == 128 ? launch<128, 1, 0>(a, rows, st) : launch<64, 1, 0>(a, rows, st);
+  if (rows * ((seq + 63) / 64) < 512)
+    e = head_dim == 128 ? launch<128, 1>(a, st) : launch<64, 1>(a, st);
+  else
+    e = head_dim == 128 ? launch<128, 2>(a, st) : launch<64, 2>(a, st);
   return e == hipSuccess ? ADORE_OK : ADORE_E_HIP;
 }
 
+// What the ABI promises to ask a caller for: room for a transposed copy of V and, for long sequences, for the weights of 512
+// workgroups of 16 queries.  Nothing uses it any more; the amounts stay, so that callers who keep track of them see no change.
+size_t padded_keys(int S) { return size_t(S + 31) / 32 * 32; }
+size_t vt_bytes(int rows, int S, int d) { return (size_t(rows) * d * padded_keys(S) * 2 + 255) / 256 * 256; }
+
 }  // namespace
+
 }  // namespace adore
 
 extern "C" {
 
 size_t adore_topk_attention_workspace_bytes(int32_t rows, int32_t seq, int32_t head_dim) {
   if (rows <= 0 || seq <= 0 || head_dim <= 0) return 0;
-  if (seq > adore::kMaxLongSeq || rows > 65535 || head_dim > 1024) return 0;   // nothing the entry point would take
-  const size_t vt = adore::vt_bytes(rows, seq, head_dim);
-  // sequences whose logit rows LDS cannot hold: 16 rows of fp32 weights per workgroup of 16 queries
-  const size_t tiles = size_t(rows) * ((seq + 15) / 16);
-  const size_t rowbuf = seq > adore::kMaxSeq ? (tiles < size_t(adore::kLongGrid) ? tiles : size_t(adore::kLongGrid)) * 16 *
-                                                   (adore::padded_keys(seq) + 4) * 4
-                                             : 0;
-  return vt + (rowbuf + 255) / 256 * 256;
+  if (seq > adore::kMaxSeq || rows > 65535 || head_dim > 1024) return 0;   // nothing the entry point would take
+  const size_t blocks = size_t(rows) * ((seq + 15) / 16);
+  const size_t weights = seq > adore::kMaxStaticSeq ? (blocks < 512 ? blocks : 512) * 16 * (adore::padded_keys(seq) + 4) * 4 : 0;
+  return adore::vt_bytes(rows, seq, head_dim) + (weights + 255) / 256 * 256;
 }
 
 int adore_topk_attention(const void *q, const void *k, const void *v, void *out, void *workspace,
@@ -581,12 +693,11 @@ int adore_topk_attention(const void *q, const void *k, const void *v, void *out,
                          void *hip_stream) {
   using namespace adore;
   if (!q || !k || !v || !out || !workspace || rows <= 0 || seq <= 0 || head_dim <= 0 || top_k < 1) return ADORE_E_INVALID;
-  if ((head_dim != 64 && head_dim != 128) || seq > kMaxLongSeq || rows > 65535) return ADORE_E_UNSUPPORTED;
+  if ((head_dim != 64 && head_dim != 128) || seq > kMaxSeq || rows > 65535) return ADORE_E_UNSUPPORTED;
   if (workspace_bytes < adore_topk_attention_workspace_bytes(rows, seq, head_dim) ||
       (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
     return ADORE_E_WORKSPACE;
-  float *rowbuf = reinterpret_cast<float *>(static_cast<char *>(workspace) + vt_bytes(rows, seq, head_dim));
-  return enqueue_topk(q, k, v, out, workspace, rowbuf, rows, seq, head_dim, top_k, static_cast<hipStream_t>(hip_stream));
+  return enqueue_topk(q, k, v, out, rows, seq, head_dim, top_k, static_cast<hipStream_t>(hip_stream));
 }
 
 int adore_topk_attention_static(const void *q, const void *k, const void *v, void *out, int32_t rows, int32_t seq,
@@ -594,11 +705,8 @@ int adore_topk_attention_static(const void *q, const void *k, const void *v, voi
   using namespace adore;
   if (!q || !k || !v || !out || rows <= 0 || seq <= 0 || head_dim <= 0 || top_k < 1) return ADORE_E_INVALID;
   if ((head_dim != 64 && head_dim != 128) || rows > 65535) return ADORE_E_UNSUPPORTED;
-  // beyond kMaxSeq tokens the weights of the query blocks need a buffer of 512 x 16 rows of seq floats: not in this variant
-  if (seq > kMaxSeq || vt_bytes(rows, seq, head_dim) > size_t(ADORE_TOPK_STATIC_SCRATCH_BYTES)) return ADORE_E_WORKSPACE;
-  void *vt = static_scratch();
-  if (!vt) return ADORE_E_HIP;
-  return enqueue_topk(q, k, v, out, vt, nullptr, rows, seq, head_dim, top_k, static_cast<hipStream_t>(hip_stream));
+  if (seq > kMaxStaticSeq || vt_bytes(rows, seq, head_dim) > size_t(ADORE_TOPK_STATIC_SCRATCH_BYTES)) return ADORE_E_WORKSPACE;
+  return enqueue_topk(q, k, v, out, rows, seq, head_dim, top_k, static_cast<hipStream_t>(hip_stream));
 }
 
 }  // extern "C"

@@ -201,3 +201,26 @@ def test_topk_attention_at_the_long_context_shape_sampled_rows():
     q64, k64, v64 = (t[sel].float().cpu().numpy().astype(np.float64) for t in (q, k, v))
     _check_rows_allowing_swaps_at_the_cut(O, q64, k64, v64, got[sel].float().cpu().numpy().astype(np.float64), top_k,
                                           "long-context shape")
+
+
+@pytest.mark.parametrize("rows,S,d,top_k,same", [
+    (1, 1, 64, 1, 0), (2, 31, 64, 8, 0), (1, 33, 128, 32, 0), (2, 129, 64, 17, 0),   # query blocks of 32, key steps of 128
+    (1, 161, 128, 40, 0),        # the last query block samples its keys, the ones before it see all of them
+    (1, 257, 64, 256, 0), (1, 320, 128, 400, 0),                                      # top_k at and beyond the sequence
+    (512, 40, 64, 12, 0), (260, 65, 128, 20, 0),                                      # query blocks of 64
+    (1, 300, 128, 50, 300), (2, 200, 64, 30, 60),   # (runs of) identical keys: more equal weights than are ranked directly
+])
+def test_topk_attention_at_the_edges_of_its_blocks(rows, S, d, top_k, same):
+    """Exactly representable weights, as above; up to four rows of a launch are checked, the first and the last among them."""
+    torch, O, topk_attention = _mods()
+    rng = np.random.default_rng(rows * 7919 + S * 31 + top_k)
+    q = rng.integers(-8, 9, size=(rows, S, d)) / 4.0
+    k = rng.integers(-8, 9, size=(rows, S, d)) / 4.0
+    if same:
+        k[:, :same] = k[:, :1]
+    v = _bf16_values(torch, rng.standard_normal((rows, S, d)))
+    got = topk_attention(_to_gpu(torch, q), _to_gpu(torch, k), _to_gpu(torch, v), top_k).float().cpu().numpy().astype(np.float64)
+    pick = sorted({0, rows // 3, rows // 2, rows - 1})
+    want, _ = O.topk_attention(q[pick], k[pick], v[pick], top_k)
+    e = _row_err(got[pick], want)
+    assert e.max() < TOL, f"rows={rows} S={S} d={d} K={top_k}: {e.max()}"
