@@ -527,6 +527,170 @@ __global__ __launch_bounds__(256) void ctrl_scan128_kernel(const CellArgs a, flo
   if (tid < DP) a.z[size_t(b) * DP + tid] = hcur;
 }
 
+// The same recurrence with bf16 weights, on the matrix cores: W_hh z with z as three bf16 terms (8 + 8 + 8 significant
+// bits: the split is exact, so is every product, and the sums are fp32).  One workgroup of 4 waves per sequence; wave w owns
+// the units 32w .. 32w+31 of all three gates: six 16-row tiles of W_hh in registers as 16x16x32 operands (96 registers).  The
+// columns of the other operand are the three terms (column c holds term c % 4, the fourth is zero), so a token costs a wave
+// 24 matrix instructions; four neighbouring lanes then hold the terms of one sum, two DPP additions put it together, and the
+// gates follow in the same wave: one barrier per token, for the exchange of z through LDS.
+// What bounds it is the serial chain of a token on one compute unit: 384 cycles of matrix instructions, then the sums, the
+// gates' three exponentials and reciprocals, and the trip of z through LDS.  0.365 us per token (187 us per chunk of 512; 386 us
+// with 192 fp32 multiply-adds per lane and token, two barriers: ctrl_scan128_kernel, which fp32 weights still take).  Error of z
+// against 64 bits over prompts of 8 to 2048 tokens: 1.0e-7 to 2.1e-7 relative, as before.
+template <int CTRL>
+__device__ inline float quad_add(float v) {   // v + the value of the lane that CTRL (a quad_perm) names
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+// SPLIT: the pre-activations come in several D-slices (a short prompt of few sequences); they are added up and staged
+// through LDS, 16 tokens at a time.  Otherwise a lane reads its own three values, kAhead tokens before their use: a wait for a
+// block of staged loads cost 2 to 3 us per 16 tokens, as much as the arithmetic.
+template <bool SPLIT>
+__global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArgs a, float *__restrict__ zseq) {
+  constexpr int DP = 128, kAhead = 8;
+  constexpr int TB = 16, GPT = TB * (3 * DP / 4) / 256;    // SPLIT: tokens per block; float4 per thread
+  constexpr int SPS = DP + 32;                             // distance between two terms: 16 lanes' reads hit 64 different banks
+  __shared__ __attribute__((aligned(16))) uint16_t sp[2][4 * SPS];   // z as bf16 terms, of two tokens in turn
+  __shared__ float4 gbuf[SPLIT ? 2 : 1][SPLIT ? TB * (3 * DP / 4) : 1];   // input pre-activations of two blocks of tokens
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = lane & 15, g = lane >> 4;
+  bf16x8 w[6][4];                                          // [gate * 2 + half of the wave's units][k-step]
+#pragma unroll
+  for (int t = 0; t < 6; ++t)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int row = (t >> 1) * DP + wave * 32 + (t & 1) * 16 + c;
+      w[t][s] = *reinterpret_cast<const bf16x8 *>(static_cast<const bf16_t *>(a.W_hh) + size_t(row) * DP + s * 32 + g * 8);
+    }
+  // this lane's unit: register c / 4 of the rows 4g .. 4g+3 of the half c % 2 (lanes with c & 2 repeat it)
+  const int unit = wave * 32 + (c & 1) * 16 + 4 * g + (c >> 2);
+  const bool odd = ((c >> 2) & 1) != 0, upper = (c >> 3) != 0, half1 = (c & 1) != 0, twin = (c & 2) != 0;
+  const float b_r = a.b_ih[unit] + a.b_hh[unit];
+  const float b_u = a.b_ih[DP + unit] + a.b_hh[DP + unit];
+  const float b_in = a.b_ih[2 * DP + unit], b_hn = a.b_hh[2 * DP + unit];
+  float hcur = a.z[size_t(b) * DP + unit];
+  auto put_state = [&](uint16_t *dst) {   // the first term rounded down to 8 bits, the second the next 8, the third the rest
+    const uint32_t hi = __float_as_uint(hcur) & 0xffff0000u;
+    const float rest = hcur - __uint_as_float(hi);
+    const uint32_t mid = __float_as_uint(rest) & 0xffff0000u;
+    const float lo = rest - __uint_as_float(mid);
+    dst[(twin ? SPS : 0) + unit] = uint16_t((twin ? mid : hi) >> 16);
+    if (!twin) dst[2 * SPS + unit] = uint16_t(__float_as_uint(lo) >> 16);
+  };
+  float *zout = zseq + size_t(b) * a.nsteps * DP + unit;
+  int cur = 0;
+  // one token, from the state in sp[cur] to the state in sp[cur ^ 1]; the caller's barrier follows
+  auto token = [&](float g_r, float g_u, float g_n) {
+    bf16x8 hv[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) hv[s] = *reinterpret_cast<const bf16x8 *>(&sp[cur][(c & 3) * SPS + s * 32 + g * 8]);
+    f32x4 acc[6];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // two gates' tiles side by side (no instruction waits for the one before it), the third's under the first gates' sums
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][s], hv[s], acc[t], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int t = 4; t < 6; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][s], hv[s], acc[t], 0, 0, 0);
+    float sum[3];
+#pragma unroll
+    for (int gate = 0; gate < 3; ++gate) {
+      float x[2];
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        const f32x4 v = acc[gate * 2 + hf];
+        const float lo2 = odd ? v[1] : v[0], hi2 = odd ? v[3] : v[2];
+        x[hf] = quad_add<0x4E>(quad_add<0xB1>(upper ? hi2 : lo2));   // lanes 0+1, 2+3 of a quad, then both
+      }
+      sum[gate] = half1 ? x[1] : x[0];
+    }
+    const float r = scan_sigmoid(g_r + b_r + sum[0]);
+    const float u = scan_sigmoid(g_u + b_u + sum[1]);
+    const float cand = scan_tanh(g_n + b_in + r * (sum[2] + b_hn));
+    hcur = (1.0f - u) * cand + u * hcur;
+    cur ^= 1;
+    put_state(sp[cur]);
+    if (!twin) *zout = hcur;
+    zout += DP;
+  };
+  for (int i = tid; i < SPS; i += 256) sp[0][3 * SPS + i] = sp[1][3 * SPS + i] = 0;
+  put_state(sp[0]);
+  if constexpr (SPLIT) {
+    const int nblk = (a.nsteps + TB - 1) / TB;
+    const float4 *gsrc = reinterpret_cast<const float4 *>(a.gi) + size_t(b) * a.nsteps * (3 * DP / 4);
+    const size_t slice4 = size_t(a.ntok) * (3 * DP / 4);   // distance between two D-slices
+    float4 stage[GPT];
+    auto fetch = [&](int blk) {
+      const int rows = a.nsteps - blk * TB < TB ? a.nsteps - blk * TB : TB;
+#pragma unroll
+      for (int q = 0; q < GPT; ++q) {
+        const int idx = tid + 256 * q;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (idx < rows * (3 * DP / 4)) {
+          const float4 *p = gsrc + size_t(blk) * TB * (3 * DP / 4) + idx;
+          v = p[0];
+          for (int k = 1; k < a.ksplit; ++k) {
+            const float4 t = p[size_t(k) * slice4];
+            v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+          }
+        }
+        stage[q] = v;
+      }
+    };
+    auto park = [&](int buf) {
+#pragma unroll
+      for (int q = 0; q < GPT; ++q) gbuf[buf][tid + 256 * q] = stage[q];
+    };
+    fetch(0);
+    park(0);
+    __syncthreads();
+    for (int blk = 0; blk < nblk; ++blk) {
+      if (blk + 1 < nblk) fetch(blk + 1);
+      const float *gt = reinterpret_cast<const float *>(gbuf[blk & 1]) + unit;
+      const int rows = a.nsteps - blk * TB < TB ? a.nsteps - blk * TB : TB;
+      for (int ii = 0; ii < rows; ++ii, gt += 3 * DP) {
+        token(gt[0], gt[DP], gt[2 * DP]);
+        // the next block's rows: their buffer was last read a block ago, and they are read behind the barrier
+        if (ii == rows - 1 && blk + 1 < nblk) park((blk + 1) & 1);
+        __syncthreads();
+      }
+    }
+  } else {
+    const float *gsrc = a.gi + size_t(b) * a.nsteps * (3 * DP) + unit;
+    float pre[kAhead][3];
+    auto ahead = [&](float (&v)[3], int i) {
+      const float *p = gsrc + size_t(min(i, a.nsteps - 1)) * (3 * DP);
+      v[0] = p[0]; v[1] = p[DP]; v[2] = p[2 * DP];
+    };
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) ahead(pre[j], j);
+    __syncthreads();
+    int i0 = 0;
+    for (; i0 + kAhead <= a.nsteps; i0 += kAhead) {
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) {
+        token(pre[j][0], pre[j][1], pre[j][2]);
+        ahead(pre[j], i0 + j + kAhead);
+        __syncthreads();
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      if (i0 + j < a.nsteps) {            // uniform over the workgroup
+        token(pre[j][0], pre[j][1], pre[j][2]);
+        __syncthreads();
+      }
+    }
+  }
+  if (!twin) a.z[size_t(b) * DP + unit] = hcur;
+}
+
 // sigma_i = sigmoid(out_w . tanh(W_1 (p_i + z_i) + b_1) + out_b) for the tokens of a chunk, from the z_i the scan
 // left.  grid (ceil(nsteps / 16), B), 4 waves, 4 tokens per wave one after the other; the arithmetic is the cell
 // kernel's (rows_times_vec, same order), so a token scored here and one scored by a step agree bit for bit
@@ -739,7 +903,10 @@ hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0
     {
       ScopedTimer t(ctx, ADORE_KERNEL_CTRL_CELL, st);
       if (c.dtype == ADORE_BF16) {
-        ADORE_LAUNCH(t, (ctrl_scan128_kernel<bf16_t>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq);
+        if (ksplit > 1)
+          ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<true>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq);
+        else
+          ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<false>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq);
       } else {
         ADORE_LAUNCH(t, (ctrl_scan128_kernel<float>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq);
       }

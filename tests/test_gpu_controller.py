@@ -1,0 +1,61 @@
+"""The controller over a prompt (d' = 128) against the same recurrence in 64 bits."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DP = 128
+
+
+def _reference(w, x, pos_scale):
+    f = {k: v.double().cpu() for k, v in w.items()}
+    x = x.double().cpu()
+    gi = x @ f["gru_w_ih"].t() + f["gru_b_ih"]
+    h = torch.zeros(x.shape[0], DP, dtype=torch.float64)
+    scores = []
+    for t in range(x.shape[1]):
+        g, gh = gi[:, t], h @ f["gru_w_hh"].t() + f["gru_b_hh"]
+        r = torch.sigmoid(g[:, :DP] + gh[:, :DP])
+        u = torch.sigmoid(g[:, DP:2 * DP] + gh[:, DP:2 * DP])
+        h = (1 - u) * torch.tanh(g[:, 2 * DP:] + r * gh[:, 2 * DP:]) + u * h
+        p = f["pos_w"] * (t * pos_scale) + f["pos_b"]
+        scores.append(torch.sigmoid(torch.tanh((p + h) @ f["mlp_w1"].t() + f["mlp_b1"]) @ f["out_w"] + f["out_b"]))
+    return torch.stack(scores, 1), h
+
+
+# one token (the step's kernels), around the read-ahead of 8 tokens and the staged blocks of 16 (few tokens: sliced
+# projection), more than 256 tokens (whole projection), across two chunks of 512; the last without a sliced projection's widths
+@pytest.mark.parametrize("batch,S,D", [(2, 1, 512), (1, 2, 512), (3, 7, 512), (2, 8, 512), (2, 9, 512), (1, 16, 512), (2, 17, 512),
+                                       (1, 33, 1024), (2, 129, 512), (3, 263, 384), (1, 515, 512), (2, 1100, 256), (2, 40, 200),
+                                       (1, 300, 200)])
+def test_scores_and_state_after_a_prompt(batch, S, D):
+    from paper_2407_02328_amd import Adore, make_config
+    g = torch.Generator().manual_seed(1000 * S + D)
+
+    def normal(shape, std, dtype):
+        return (torch.randn(shape, generator=g) * std).to(dtype).cuda()
+    H, d, K, R, n_max = 2, 64, 24, 3, S + 4
+    bf, f32 = torch.bfloat16, torch.float32
+    w = {"w_kv": normal((1, 2 * H * d, D), 0.02, bf), "gru_w_ih": normal((3 * DP, D), D ** -0.5, bf),
+         "gru_w_hh": normal((3 * DP, DP), DP ** -0.5, bf), "gru_b_ih": normal((3 * DP,), 0.1, f32),
+         "gru_b_hh": normal((3 * DP,), 0.1, f32), "pos_w": normal((DP,), 1.0, f32), "pos_b": normal((DP,), 0.1, f32),
+         "mlp_w1": normal((DP, DP), DP ** -0.5, f32), "mlp_b1": normal((DP,), 0.1, f32), "out_w": normal((DP,), 0.3, f32),
+         "out_b": normal((1,), 0.1, f32)}
+    pos_scale = 2.0 ** -12
+    job = Adore(make_config(layers=1, batch=batch, heads=H, head_dim=d, hidden=D, cache_slots=K, rebuild_budget=R,
+                            max_positions=n_max, ctrl_hidden=DP, dtype="bf16", pos_scale=pos_scale), w, "cuda")
+    x = normal((batch, S, D), 1.0, bf)
+    hidden = torch.zeros((1, batch, n_max, D), dtype=bf, device="cuda")
+    hidden[0, :, :S] = x
+    kv = normal((1, batch, H, S, d), 1.0, bf)
+    scores = torch.zeros((batch, n_max), device="cuda")
+    z = torch.zeros((batch, DP), device="cuda")
+    job.init_cache(kv, kv, hidden, x.contiguous(), None, S)
+    job.get_state(scores=scores, z=z)
+    torch.cuda.synchronize()
+    want_scores, want_z = _reference(w, x, pos_scale)
+    # |z| <= 1; a pre-activation is a sum of D + 128 fp32 products of order one (error about 2^-24 sqrt(D) < 2e-6), the gates
+    # damp what earlier tokens bring along, and the scores are as smooth: 4e-6 leaves a factor of two
+    assert (z.cpu().double() - want_z).abs().max() <= 4e-6
+    assert (scores[:, :S].cpu().double() - want_scores).abs().max() <= 4e-6
+    job.close()
