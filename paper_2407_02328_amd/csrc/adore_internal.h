@@ -71,8 +71,9 @@ struct adore_ctx {
   float *att_part;           // [B*H][kMaxSplits][d+2]
   float *att_logit;          // H2O mode: [B*H][K] the step's logits in base 2, as the attention kernel scaled them
   float *att_ml;             // H2O mode: [B*H][2] their maximum and the sum of exp2(logit - maximum) over the row
-  float *gi;                 // [ksplit][tokens][3d'] GRU input pre-activations, per D-slice
-  float *zseq;               // [B][kPromptChunk][d'] GRU states of a prompt chunk, between its scan and its scoring
+  // two copies, which the chunks of a prompt take in turn
+  float *gi[2];              // [ksplit][tokens][3d'] GRU input pre-activations, per D-slice (steps: copy 0)
+  float *zseq[2];            // [B][kPromptChunk][d'] GRU states of a prompt chunk, between its scan and its scoring
   float *cvec;               // rescore mode: [B][N_max][d']  W_1 (z_i + pos_b) + b_1 of every token
   float *avec;               // rescore mode: [d']  W_1 pos_w  (what one unit of distance adds)
   void *fwd_q, *fwd_o;       // rebuild forward: [B*(R+1)][H*d] query rows / attention outputs of the layer in flight
@@ -158,9 +159,14 @@ size_t riding_lds_bytes(int n, int K, int r);
 hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k_new,
                          const void *v_new, float *out, const RidingSelections *sel = nullptr);
 hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int ntok, int per_seq,
-                             int seq_rows, int *ksplit_out);
+                             int seq_rows, int buf, int *ksplit_out);
 hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0,
-                            const float *score_override, int override_stride, int ksplit);
+                            const float *score_override, int override_stride, int buf, int ksplit);
+// A prompt chunk of more than one token where ctrl_chunk_in_two(): the recurrence, then the layers above it.
+bool ctrl_chunk_in_two(const adore_config &c, int nsteps);
+hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf, int ksplit);
+hipError_t launch_ctrl_score(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0, const float *score_override,
+                             int override_stride, int buf);
 // The two selections also write the caller's copies of their results (slot map, released and rebuilt
 // positions) when given a pointer, so a step needs no device-to-device copies.
 hipError_t launch_release(adore_ctx *ctx, hipStream_t st, int src, int dst, int x, int32_t *map_out,

@@ -305,27 +305,9 @@ __device__ inline float dot2(uint32_t u, float x0, float x1) {
 }
 __device__ inline float dot2(float2 u, float x0, float x1) { return fmaf(u.x, x0, u.y * x1); }
 
-// out[row0 + r] = bias[row0 + r] + W[row0 + r][:] . x   for r < N, x held as (x0, x1) = x[2*lane], x[2*lane+1]
-template <typename T, int N>
-__device__ inline void rows_times_vec(const T *W, int row0, float x0, float x1, const float *bias, float *out,
-                                      int lane) {
-  decltype(load_raw2(W)) raw[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) raw[i] = load_raw2(W + size_t(row0 + i) * 128 + 2 * lane);
-  __builtin_amdgcn_sched_barrier(0);   // all N loads go out before the first is waited for
-  float v[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = dot2(raw[i], x0, x1);
-  const float s = reduce_rows<N>(v, lane);
-  constexpr int LPRW = 64 / N;   // lanes holding the same row
-  if ((lane & (LPRW - 1)) == 0) {
-    const int r = row0 + lane / LPRW;
-    out[r] = s + bias[r];
-  }
-}
-
-// The same product in two halves: the N row loads go out where the caller wants them (next to everything else a
-// step reads), the arithmetic follows once x is known.
+// out[row0 + r] = bias[row0 + r] + W[row0 + r][:] . x   for r < N, x held as (x0, x1) = x[2*lane], x[2*lane+1], in two
+// halves: the N row loads go out where the caller wants them (next to everything else a step reads), the arithmetic follows
+// once x is known.
 template <typename T, int N>
 __device__ inline void rows_request(const T *W, int row0, int lane, decltype(load_raw2(W)) (&raw)[N]) {
 #pragma unroll
@@ -407,8 +389,8 @@ __global__ __launch_bounds__(768) void ctrl_cell128_kernel(const CellArgs a) {
 
 // ---- a prompt chunk, d' = 128: the recurrence alone, then the layers above it for all tokens at once ----
 // Only z_i = GRU(x_i, z_{i-1}) ties a token to the one before it; the position, interaction and output layers
-// do not.  The scan therefore does nothing but the recurrence, one workgroup of 4 waves per sequence, with W_hh
-// in registers as fp32 for the whole chunk: wave w keeps columns 32w .. 32w+31 of all 384 rows (lane l: rows
+// do not.  The scan therefore does nothing but the recurrence, one workgroup of 4 waves per sequence.  With fp32
+// weights W_hh stays in registers as fp32 for the whole chunk: wave w keeps columns 32w .. 32w+31 of all 384 rows (lane l: rows
 // l, l+64, .., l+320), so a token costs a wave 8 16-byte reads of the state from LDS (same address in every
 // lane) and 192 multiply-adds per lane on each of the four SIMDs; the four partial sums of a row meet in LDS,
 // 128 threads apply the gates.  Two barriers and no memory round trip per token.  The gates use the hardware's exp2 and reciprocal
@@ -547,6 +529,7 @@ __device__ inline float quad_add(float v) {   // v + the value of the lane that 
 // block of staged loads cost 2 to 3 us per 16 tokens, as much as the arithmetic.
 template <bool SPLIT>
 __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArgs a, float *__restrict__ zseq) {
+  __builtin_amdgcn_s_setprio(3);   // a serial chain that may share its compute unit with the scoring of the chunk before
   constexpr int DP = 128, kAhead = 8;
   constexpr int TB = 16, GPT = TB * (3 * DP / 4) / 256;    // SPLIT: tokens per block; float4 per thread
   constexpr int SPS = DP + 32;                             // distance between two terms: 16 lanes' reads hit 64 different banks
@@ -692,38 +675,48 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
 }
 
 // sigma_i = sigmoid(out_w . tanh(W_1 (p_i + z_i) + b_1) + out_b) for the tokens of a chunk, from the z_i the scan
-// left.  grid (ceil(nsteps / 16), B), 4 waves, 4 tokens per wave one after the other; the arithmetic is the cell
-// kernel's (rows_times_vec, same order), so a token scored here and one scored by a step agree bit for bit
-// given the same z_i.
+// left.  grid (ceil(nsteps / 16), B), 4 waves, 4 tokens per wave; the arithmetic is the cell kernel's (rows_request,
+// rows_finish, same order), so a token scored here and one scored by a step agree bit for bit given the same z_i.
+// A wave multiplies each batch of 32 rows of W_1 by its four tokens: read once per token, the 64 KB of W_1 were what bound it
+// (8192 tokens: 48 -> 23 us).
 __global__ __launch_bounds__(256) void ctrl_mlp128_kernel(const CellArgs a, const float *__restrict__ zseq) {
-  constexpr int DP = 128;
-  __shared__ float u1[4][DP];
+  constexpr int DP = 128, TPW = 4;
+  __shared__ float u1[4][TPW][DP];
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int q = 0; q < 4; ++q) {
-    const int i = blockIdx.x * 16 + wave * 4 + q;
-    const bool on = i < a.nsteps;                      // uniform over the wave; the barriers are not skipped
-    const size_t tok = size_t(b) * a.nsteps + (on ? i : 0);
+  const int i0 = blockIdx.x * 16 + wave * TPW;
+  float x0[TPW], x1[TPW];
+#pragma unroll
+  for (int q = 0; q < TPW; ++q) {
+    const int i = i0 + q < a.nsteps ? i0 + q : 0;       // lanes past the end redo token 0 and store nothing
+    const size_t tok = size_t(b) * a.nsteps + i;
     const float delta = a.cvec ? 0.f : float(a.pos0 + i) * a.pos_scale;   // rescore mode: distance to itself
-    const float x0 = fmaf(a.pos_w[2 * lane], delta, a.pos_b[2 * lane]) + zseq[tok * DP + 2 * lane];
-    const float x1 = fmaf(a.pos_w[2 * lane + 1], delta, a.pos_b[2 * lane + 1]) + zseq[tok * DP + 2 * lane + 1];
+    x0[q] = fmaf(a.pos_w[2 * lane], delta, a.pos_b[2 * lane]) + zseq[tok * DP + 2 * lane];
+    x1[q] = fmaf(a.pos_w[2 * lane + 1], delta, a.pos_b[2 * lane + 1]) + zseq[tok * DP + 2 * lane + 1];
+  }
 #pragma unroll 1
-    for (int part = 0; part < 4; ++part) rows_times_vec<float, 32>(a.W1, part * 32, x0, x1, a.b1, u1[wave], lane);
-    __syncthreads();
-    if (on) {
-      if (a.cvec) {
-        float *c = a.cvec + (size_t(b) * a.N_max + a.pos0 + i) * DP;
-        c[lane] = u1[wave][lane];
-        c[lane + 64] = u1[wave][lane + 64];
-      }
-      float s = fmaf(a.out_w[lane], tanhf(u1[wave][lane]), a.out_w[lane + 64] * tanhf(u1[wave][lane + 64]));
-      s = wave_sum(s);
-      if (lane == 0) {
-        float sig = sigmoidf_(s + a.out_b[0]);
-        if (a.override_) sig = a.override_[size_t(b) * a.override_stride + i];
-        a.score[size_t(b) * a.N_max + a.pos0 + i] = sig;
-      }
+  for (int part = 0; part < 4; ++part) {
+    float2 raw[32];
+    rows_request<float, 32>(a.W1, part * 32, lane, raw);
+#pragma unroll
+    for (int q = 0; q < TPW; ++q) rows_finish<float2, 32>(raw, part * 32, x0[q], x1[q], a.b1, u1[wave][q], lane);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < TPW; ++q) {
+    const int i = i0 + q;
+    if (i >= a.nsteps) break;                           // uniform over the wave
+    if (a.cvec) {
+      float *c = a.cvec + (size_t(b) * a.N_max + a.pos0 + i) * DP;
+      c[lane] = u1[wave][q][lane];
+      c[lane + 64] = u1[wave][q][lane + 64];
     }
-    __syncthreads();
+    float s = fmaf(a.out_w[lane], tanhf(u1[wave][q][lane]), a.out_w[lane + 64] * tanhf(u1[wave][q][lane + 64]));
+    s = wave_sum(s);
+    if (lane == 0) {
+      float sig = sigmoidf_(s + a.out_b[0]);
+      if (a.override_) sig = a.override_[size_t(b) * a.override_stride + i];
+      a.score[size_t(b) * a.N_max + a.pos0 + i] = sig;
+    }
   }
 }
 
@@ -849,43 +842,46 @@ int ctrl_input_ksplit(const adore_config &c, int ntok) {
 
 }  // namespace
 
+// buf: which of the two copies of the pre-activations is written (a prompt's chunks take them in turn).
 hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int ntok, int per_seq,
-                             int seq_rows, int *ksplit_out) {
+                             int seq_rows, int buf, int *ksplit_out) {
   const adore_config &c = ctx->cfg;
   const int G3 = 3 * c.ctrl_hidden;
+  float *gi = ctx->gi[buf];
   ScopedTimer t(ctx, ADORE_KERNEL_CTRL_INPUT, st);
   *ksplit_out = 1;
   if (ntok > kCtrlSplitTokens &&
-      launch_plain_projection(ctx, t, st, x, ctx->w.gru_w_ih, ctx->gi, ntok, per_seq, seq_rows, G3, c.hidden)) {
+      launch_plain_projection(ctx, t, st, x, ctx->w.gru_w_ih, gi, ntok, per_seq, seq_rows, G3, c.hidden)) {
     // a prompt chunk on the rebuild's 128x128 tile (3d' a multiple of 128, D of 64)
   } else if (c.dtype == ADORE_BF16 && c.hidden % 128 == 0 && ntok > kCtrlSplitTokens) {
     dim3 grid((G3 + 63) / 64, (ntok + 63) / 64);
     ADORE_LAUNCH(t, ctrl_input_prompt_kernel, grid, dim3(256), 0, st,
-                       static_cast<const bf16_t *>(ctx->w.gru_w_ih), static_cast<const bf16_t *>(x), ctx->gi,
+                       static_cast<const bf16_t *>(ctx->w.gru_w_ih), static_cast<const bf16_t *>(x), gi,
                        c.hidden, G3, ntok, per_seq, seq_rows);
   } else if (c.dtype == ADORE_BF16 && c.hidden % 128 == 0) {
     const int ks = ctrl_input_ksplit(c, ntok);
     *ksplit_out = ks;
     dim3 grid((G3 + 15) / 16, (ntok + 15) / 16, ks);
     ADORE_LAUNCH(t, ctrl_input_mfma_kernel, grid, dim3(256), 0, st,
-                       static_cast<const bf16_t *>(ctx->w.gru_w_ih), static_cast<const bf16_t *>(x), ctx->gi,
+                       static_cast<const bf16_t *>(ctx->w.gru_w_ih), static_cast<const bf16_t *>(x), gi,
                        c.hidden, G3, ntok, per_seq, seq_rows, c.hidden / ks);
   } else if (c.dtype == ADORE_BF16) {
     dim3 grid((G3 + JT - 1) / JT, (ntok + NB - 1) / NB);
     ADORE_LAUNCH(t, (ctrl_input_kernel<bf16_t>), grid, dim3(256), 0, st,
-                       static_cast<const bf16_t *>(ctx->w.gru_w_ih), static_cast<const bf16_t *>(x), ctx->gi,
+                       static_cast<const bf16_t *>(ctx->w.gru_w_ih), static_cast<const bf16_t *>(x), gi,
                        c.hidden, G3, ntok, per_seq, seq_rows);
   } else {
     dim3 grid((G3 + JT - 1) / JT, (ntok + NB - 1) / NB);
     ADORE_LAUNCH(t, (ctrl_input_kernel<float>), grid, dim3(256), 0, st,
-                       static_cast<const float *>(ctx->w.gru_w_ih), static_cast<const float *>(x), ctx->gi,
+                       static_cast<const float *>(ctx->w.gru_w_ih), static_cast<const float *>(x), gi,
                        c.hidden, G3, ntok, per_seq, seq_rows);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0,
-                            const float *score_override, int override_stride, int ksplit) {
+namespace {
+
+CellArgs cell_args(adore_ctx *ctx, int nsteps, int pos0, const float *score_override, int override_stride, int buf, int ksplit) {
   const adore_config &c = ctx->cfg;
   CellArgs a;
   a.W_hh = ctx->w.gru_w_hh;
@@ -893,31 +889,51 @@ hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0
   a.pos_w = ctx->w.pos_w; a.pos_b = ctx->w.pos_b;
   a.W1 = ctx->w.mlp_w1; a.b1 = ctx->w.mlp_b1;
   a.out_w = ctx->w.out_w; a.out_b = ctx->w.out_b;
-  a.gi = ctx->gi; a.z = ctx->z; a.score = ctx->score;
+  a.gi = ctx->gi[buf]; a.z = ctx->z; a.score = ctx->score;
   a.cvec = c.score_mode == ADORE_SCORE_RESCORE ? ctx->cvec : nullptr;
   a.override_ = score_override; a.override_stride = override_stride;
   a.dp = c.ctrl_hidden; a.nsteps = nsteps; a.pos0 = pos0; a.N_max = c.max_positions;
   a.ksplit = ksplit; a.ntok = c.batch * nsteps;
   a.pos_scale = c.pos_scale;
-  if (c.ctrl_hidden == 128 && nsteps > 1) {   // a prompt chunk: the recurrence, then the layers above it
-    {
-      ScopedTimer t(ctx, ADORE_KERNEL_CTRL_CELL, st);
-      if (c.dtype == ADORE_BF16) {
-        if (ksplit > 1)
-          ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<true>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq);
-        else
-          ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<false>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq);
-      } else {
-        ADORE_LAUNCH(t, (ctrl_scan128_kernel<float>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq);
-      }
-    }
-    ScopedTimer t(ctx, ADORE_KERNEL_CTRL_CELL, st);
-    ADORE_LAUNCH(t, ctrl_mlp128_kernel, dim3((nsteps + 15) / 16, c.batch), dim3(256), 0, st, a,
-                 static_cast<const float *>(ctx->zseq));
-    return hipGetLastError();
-  }
+  return a;
+}
+
+}  // namespace
+
+// A chunk of several tokens at d' = 128 is two launches, of which only the first has to wait for the chunk before it.
+bool ctrl_chunk_in_two(const adore_config &c, int nsteps) { return c.ctrl_hidden == 128 && nsteps > 1; }
+
+hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf, int ksplit) {
+  const adore_config &c = ctx->cfg;
+  const CellArgs a = cell_args(ctx, nsteps, 0, nullptr, 0, buf, ksplit);
   ScopedTimer t(ctx, ADORE_KERNEL_CTRL_CELL, st);
-  if (c.ctrl_hidden == 128) {
+  if (c.dtype == ADORE_BF16) {
+    if (ksplit > 1)
+      ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<true>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq[buf]);
+    else
+      ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<false>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq[buf]);
+  } else {
+    ADORE_LAUNCH(t, (ctrl_scan128_kernel<float>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq[buf]);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_ctrl_score(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0, const float *score_override,
+                             int override_stride, int buf) {
+  const adore_config &c = ctx->cfg;
+  const CellArgs a = cell_args(ctx, nsteps, pos0, score_override, override_stride, buf, 1);
+  ScopedTimer t(ctx, ADORE_KERNEL_CTRL_CELL, st);
+  ADORE_LAUNCH(t, ctrl_mlp128_kernel, dim3((nsteps + 15) / 16, c.batch), dim3(256), 0, st, a,
+               static_cast<const float *>(ctx->zseq[buf]));
+  return hipGetLastError();
+}
+
+hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0,
+                            const float *score_override, int override_stride, int buf, int ksplit) {
+  const adore_config &c = ctx->cfg;
+  const CellArgs a = cell_args(ctx, nsteps, pos0, score_override, override_stride, buf, ksplit);
+  ScopedTimer t(ctx, ADORE_KERNEL_CTRL_CELL, st);
+  if (c.ctrl_hidden == 128 && nsteps == 1) {
     if (c.dtype == ADORE_BF16) {
       ADORE_LAUNCH(t, (ctrl_cell128_kernel<bf16_t>), dim3(c.batch), dim3(768), 0, st, a);
     } else {

@@ -1,13 +1,12 @@
-"""The controller over a prompt (d' = 128) against the same recurrence in 64 bits."""
+"""The controller over a prompt against the same recurrence in 64 bits."""
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
-DP = 128
-
 
 def _reference(w, x, pos_scale):
+    DP = w["gru_w_hh"].shape[1]
     f = {k: v.double().cpu() for k, v in w.items()}
     x = x.double().cpu()
     gi = x @ f["gru_w_ih"].t() + f["gru_b_ih"]
@@ -27,8 +26,18 @@ def _reference(w, x, pos_scale):
 # projection), more than 256 tokens (whole projection), across two chunks of 512; the last without a sliced projection's widths
 @pytest.mark.parametrize("batch,S,D", [(2, 1, 512), (1, 2, 512), (3, 7, 512), (2, 8, 512), (2, 9, 512), (1, 16, 512), (2, 17, 512),
                                        (1, 33, 1024), (2, 129, 512), (3, 263, 384), (1, 515, 512), (2, 1100, 256), (2, 40, 200),
-                                       (1, 300, 200)])
+                                       (1, 300, 200), (2, 1025, 256), (1, 2100, 128)])
 def test_scores_and_state_after_a_prompt(batch, S, D):
+    _check_prompt(batch, S, D, 128)
+
+
+# the general cell kernel, one chunk and several
+@pytest.mark.parametrize("batch,S,D,DP", [(2, 9, 256, 64), (1, 600, 128, 64), (2, 1030, 64, 20)])
+def test_scores_and_state_after_a_prompt_other_controller_widths(batch, S, D, DP):
+    _check_prompt(batch, S, D, DP)
+
+
+def _check_prompt(batch, S, D, DP):
     from paper_2407_02328_amd import Adore, make_config
     g = torch.Generator().manual_seed(1000 * S + D)
 
