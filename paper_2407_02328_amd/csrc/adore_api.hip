@@ -23,7 +23,8 @@
 // on the caller's stream at the top of the call, like any work on the caller's stream itself; the side
 // stream then never runs ahead and the periodic wait above is not needed.  A caller whose inputs are
 // complete in memory when the call is made switches this off and saves that event.
-// ADORE_NO_OVERLAP=1 puts everything on the caller's stream.
+// A step whose work is shorter than what the events cost goes to the caller's stream as a whole instead
+// (steps_on_one_stream below; decided per job by adore_init_cache).  ADORE_NO_OVERLAP=1 puts everything there, always.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -226,10 +227,36 @@ int ensure_side_stream(adore_ctx *ctx) {
   return ADORE_OK;
 }
 
+// Whether every launch of a job's steps goes to the caller's stream, in order.  What the side streams hide (the controller's
+// two launches, 10 to 20 us, and where they do not ride in the attention launch the two selections, 15 to 40 us) is bought
+// with two or three cross-stream events a step, which hold an overlapped step at about 50 us however little it does.
+// Measured per step, side streams against one: 1 sequence of 4 heads of 64 in fp32 43-49 -> 31 us, 3 of 12 heads with
+// rescoring 67-83 -> 43 us, 8 of 16 heads of 128 (attention 3 us + projection 13 us by the estimate) 44-50 -> 40 us, the same
+// with rescoring 61-74 -> 52 us; but 4 of 32 heads (7 + 25 us) 53.6 -> 53.7 us and with inputs known ahead 49 -> 54 us, 16 of
+// 32 heads (13 + 41 us) 72 -> 76 us.  So: one stream where those two come to less than kOneStreamMicros.
+// A stack of layers called one by one with ordered inputs starts its selections behind the last layer's attention, so
+// that the side streams could hide nothing but the controller, once per L layers: 4 layers of 8 sequences 151 -> 122 us,
+// of 32 sequences 561 -> 546 us, 3 layers of 64 sequences 418 -> 406 us.  (The forward's selections run beside all its layers: it keeps the side streams.)
+// ADORE_STEP_STREAMS=1 / 0 in the environment: side streams always / never, for comparison runs.
+constexpr float kOneStreamMicros = 20.f;
+bool steps_on_one_stream(const adore_ctx *ctx, bool forward) {
+  const adore_config &c = ctx->cfg;
+  if (const char *e = getenv("ADORE_STEP_STREAMS")) return atoi(e) == 0;
+  if (forward) return false;
+  if (c.layers > 1) return ctx->ordered;
+  const double bytes = 2.0 * c.batch * c.heads * double(c.cache_slots) * c.head_dim * elem_size(c);
+  return bytes / 5e6 + rebuild_gemm_micros(c) < kOneStreamMicros;   // the attention reads 5 TB/s
+}
+
+// Whether the steps of the present job use the side streams, and the streams of its selections and its controller.
+bool side_steps(const adore_ctx *ctx) { return ctx->overlap && !ctx->one_stream; }
+hipStream_t selection_stream(const adore_ctx *ctx) { return side_steps(ctx) ? ctx->side : ctx->stream; }
+hipStream_t controller_stream(const adore_ctx *ctx) { return side_steps(ctx) ? ctx->side2 : ctx->stream; }
+
 // Ordered inputs: the side stream starts a step's work behind everything the caller's stream holds now.
 // selections: the step has work on the selections' stream as well (not when they ride in the attention launch).
 hipError_t order_side_after_caller(adore_ctx *ctx, bool selections = true) {
-  if (!ctx->overlap || !ctx->ordered) return hipSuccess;
+  if (!side_steps(ctx) || !ctx->ordered) return hipSuccess;
   hipError_t e = hipEventRecord(ctx->ev_in, ctx->stream);
   if (e == hipSuccess && selections) e = hipStreamWaitEvent(ctx->side, ctx->ev_in, 0);
   if (e == hipSuccess && ctx->side2 != ctx->side) e = hipStreamWaitEvent(ctx->side2, ctx->ev_in, 0);
@@ -237,7 +264,7 @@ hipError_t order_side_after_caller(adore_ctx *ctx, bool selections = true) {
 }
 
 // Whether the side stream may run ahead of the caller's stream (and so needs the periodic wait of the ring).
-bool runs_ahead(const adore_ctx *ctx) { return ctx->overlap && !ctx->ordered; }
+bool runs_ahead(const adore_ctx *ctx) { return side_steps(ctx) && !ctx->ordered; }
 
 // The controller of the current step, on a stream of its own: the selections of the next step wait for it
 // (ev_ctrl), those of this step do not queue behind it.  They do not need its score: the current token is exempt
@@ -245,11 +272,11 @@ bool runs_ahead(const adore_ctx *ctx) { return ctx->overlap && !ctx->ordered; }
 // vector the later rescorings start from; the tokens before it are rescored on the selections' stream.)
 hipError_t launch_controller(adore_ctx *ctx, const void *x_n, int seq_rows, const float *score_override) {
   const adore_config &c = ctx->cfg;
-  hipStream_t st = ctx->side2;
+  hipStream_t st = controller_stream(ctx);
   int ksplit = 1;
   hipError_t e = launch_ctrl_input(ctx, st, x_n, c.batch, 1, seq_rows, 0, &ksplit);
   if (e == hipSuccess) e = launch_ctrl_cell(ctx, st, 1, ctx->n, score_override, 1, 0, ksplit);
-  if (e == hipSuccess && ctx->overlap) e = hipEventRecord(ctx->ev_ctrl, st);
+  if (e == hipSuccess && side_steps(ctx)) e = hipEventRecord(ctx->ev_ctrl, st);
   return e;
 }
 
@@ -403,6 +430,7 @@ int adore_create(const adore_config *cfg, const adore_weights *weights, void *wo
   ctx->ev_ctrl = nullptr;
   ctx->ev_att = ctx->ev_join = ctx->ev_in = nullptr;
   ctx->ordered = true;
+  ctx->one_stream = steps_on_one_stream(ctx, false);
   ctx->steps_done = 0;
   ctx->side_ready = false;
   ctx->attended.assign(cfg->layers, 0);
@@ -458,6 +486,7 @@ int adore_init_cache(adore_ctx *ctx, const void *prompt_k, const void *prompt_v,
     ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_ctrl, 0));
   }
   hipStream_t st = ctx->stream;
+  ctx->one_stream = steps_on_one_stream(ctx, forward);   // both side streams are behind us
   ctx->cur = 0;
   if (h2o_mode(ctx)) {
     // the prompt's scores are given (or zero); every head picks its own residents, then the per-sequence choice
@@ -493,9 +522,9 @@ int adore_init_cache(adore_ctx *ctx, const void *prompt_k, const void *prompt_v,
   for (int l = 0; l < c.layers && !forward; ++l) {
     ADORE_TRY(launch_rebuild_gemm(ctx, l, static_cast<const char *>(hidden_store) + l * hs_layer, ctx->cur + 1, r0));
   }
-  if (ctx->overlap) ADORE_TRY(hipEventRecord(ctx->ev_att, st));   // the first selections wait for everything above
+  if (side_steps(ctx)) ADORE_TRY(hipEventRecord(ctx->ev_att, st));   // the first selections wait for everything above
   ctx->steps_done = 0;
-  if (ctx->overlap) {   // what the first step waits for is all above
+  if (side_steps(ctx)) {   // what the first step waits for is all above
     ADORE_TRY(hipEventRecord(ctx->ev_join, st));
     ADORE_TRY(hipEventRecord(ctx->ev_ctrl, st));
     // The side streams start behind the init whatever the input order: the first step's controller reads the GRU
@@ -552,7 +581,7 @@ int do_schedule(adore_ctx *ctx, const void *x_n, const float *score_override, in
   const int pool = ctx->n + 1 - kept;
   const int r = pool < c.rebuild_budget ? pool : c.rebuild_budget;
   const int src = ctx->cur, dst = (ctx->cur + 1) % kRing;
-  hipStream_t st = ctx->side;
+  hipStream_t st = selection_stream(ctx);
   ADORE_TRY(order_side_after_caller(ctx));
   if (ctx->rode && runs_ahead(ctx)) {
     // the steps before this one ran their selections on the caller's stream: the side stream catches up once
@@ -564,14 +593,14 @@ int do_schedule(adore_ctx *ctx, const void *x_n, const float *score_override, in
 
   // the selections rank the tokens before the current one: they wait for the previous step's controller, not for
   // this step's (which touches only its own state and the score array and may run as early as its inputs allow)
-  if (ctx->overlap) ADORE_TRY(hipStreamWaitEvent(st, ctx->ev_ctrl, 0));
+  if (side_steps(ctx)) ADORE_TRY(hipStreamWaitEvent(st, ctx->ev_ctrl, 0));
   ADORE_TRY(launch_controller(ctx, x_n, 1, score_override));
   if (c.score_mode == ADORE_SCORE_RESCORE) ADORE_TRY(launch_rescore(ctx, st, ctx->n, ctx->n - 1));
   // copy `dst` was `cur` kRing - 1 steps ago: see the note on the ring at the top of this file
   if (runs_ahead(ctx) && ctx->steps_done % kSyncEvery == 0) ADORE_TRY(hipStreamWaitEvent(st, ctx->ev_att, 0));
   ADORE_TRY(launch_release(ctx, st, src, dst, x, slot_map, released_pos));
   ADORE_TRY(launch_rebuild_select(ctx, st, dst, r, slot_map, rebuilt_pos));
-  if (ctx->overlap) ADORE_TRY(hipEventRecord(ctx->ev_join, st));
+  if (side_steps(ctx)) ADORE_TRY(hipEventRecord(ctx->ev_join, st));
   ctx->scheduled = true;
   ctx->r_step = r;
   ctx->occ = kept + r;
@@ -579,7 +608,7 @@ int do_schedule(adore_ctx *ctx, const void *x_n, const float *score_override, in
 }
 
 int do_rebuild(adore_ctx *ctx, int32_t layer, const void *hidden_store_layer) {
-  if (ctx->n_rebuilt == 0 && ctx->overlap) {
+  if (ctx->n_rebuilt == 0 && side_steps(ctx)) {
     // from here on the caller's stream sees everything the selections wrote, outputs included
     ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0));
   }
@@ -612,7 +641,7 @@ int do_ridden_step(adore_ctx *ctx, const void *q, const void *k_new, const void 
   const int r = pool < c.rebuild_budget ? pool : c.rebuild_budget;
   const int dst = (ctx->cur + 1) % kRing;
   ADORE_TRY(order_side_after_caller(ctx, false));
-  ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_ctrl, 0));   // the controller of the step before
+  if (side_steps(ctx)) ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_ctrl, 0));   // the controller of the step before
   ADORE_TRY(launch_controller(ctx, x_n, 1, score_override));
   RidingSelections sel;
   sel.dst = dst; sel.x = x; sel.r = r;
@@ -698,7 +727,7 @@ int adore_forward_step(adore_ctx *ctx, const adore_forward_weights *fw, const vo
   // everything the layers read (slot map, slots of the rebuilt tokens and of the current one) was written
   // by the previous step's selections
   ADORE_TRY(order_side_after_caller(ctx));
-  if (ctx->overlap) ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0));
+  if (side_steps(ctx)) ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0));
   // this step's controller and selections: they read the same lists and write the other buffer, so they
   // run on the side stream next to the layers
   const char *x_n = static_cast<const char *>(embed) + size_t(ctx->n) * c.hidden * es;
@@ -710,14 +739,14 @@ int adore_forward_step(adore_ctx *ctx, const adore_forward_weights *fw, const vo
     const int pool = ctx->n + 1 - kept;
     const int r_next = pool < c.rebuild_budget ? pool : c.rebuild_budget;
     const int src = ctx->cur, dst = (ctx->cur + 1) % kRing;
-    hipStream_t st = ctx->side;
-    if (ctx->overlap) ADORE_TRY(hipStreamWaitEvent(st, ctx->ev_ctrl, 0));   // the previous step's controller
+    hipStream_t st = selection_stream(ctx);
+    if (side_steps(ctx)) ADORE_TRY(hipStreamWaitEvent(st, ctx->ev_ctrl, 0));   // the previous step's controller
     ADORE_TRY(launch_controller(ctx, x_n, c.max_positions, score_override));
     if (c.score_mode == ADORE_SCORE_RESCORE) ADORE_TRY(launch_rescore(ctx, st, ctx->n, ctx->n - 1));
     if (runs_ahead(ctx) && ctx->steps_done % kSyncEvery == 0) ADORE_TRY(hipStreamWaitEvent(st, ctx->ev_att, 0));   // see the note on the ring
     ADORE_TRY(launch_release(ctx, st, src, dst, x, slot_map, released_pos));
     ADORE_TRY(launch_rebuild_select(ctx, st, dst, r_next, slot_map, rebuilt_pos));
-    if (ctx->overlap) ADORE_TRY(hipEventRecord(ctx->ev_join, st));
+    if (side_steps(ctx)) ADORE_TRY(hipEventRecord(ctx->ev_join, st));
     ctx->r_step = r_next;
     ctx->occ = kept + r_next;
   }
@@ -762,7 +791,7 @@ int adore_get_state(adore_ctx *ctx, int32_t *slot_pos, float *scores, float *z, 
   const size_t BH = size_t(c.batch) * c.heads;
   const size_t cache_bytes = size_t(c.layers) * BH * c.cache_slots * c.head_dim * elem_size(c);
   if (step) *step = ctx->n;
-  if (ctx->overlap && ctx->side_ready) {   // the last selections and the controller's last score
+  if (side_steps(ctx) && ctx->side_ready) {   // the last selections and the controller's last score
     ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0));
     ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_ctrl, 0));
   }

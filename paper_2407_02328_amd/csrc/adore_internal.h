@@ -50,6 +50,7 @@ struct adore_ctx {
   hipEvent_t ev_in;          // ordered inputs: recorded on `stream` at the top of a step, the side stream starts behind it
   bool ordered;              // the side stream reads a step's inputs behind everything enqueued on `stream` before the call
   bool overlap;              // two-stream mode requested
+  bool one_stream;           // the steps of the present job use the caller's stream only (short ones)
   bool side_ready;           // side stream and events exist (made on first GPU use)
 
   // --- workspace sections (device) ---
@@ -175,6 +176,7 @@ hipError_t launch_rebuild_select(adore_ctx *ctx, hipStream_t st, int dst, int r,
                                  int32_t *rb_out);
 // map_dst / map_out: null, or the slot map (ring copy and the caller's) into which the kernel enters the rebuilt
 // tokens' positions itself (when the per-sequence choice did not do it)
+float rebuild_gemm_micros(const adore_config &c);
 hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_layer, int lists, int r,
                                int32_t *map_dst = nullptr, int32_t *map_out = nullptr);
 bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, const void *x, const void *W, float *out,

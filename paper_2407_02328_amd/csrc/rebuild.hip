@@ -869,6 +869,16 @@ void fill_common(adore_ctx *ctx, GemmArgs &a, int lists, int r) {
 
 }  // namespace
 
+// About how long a full rebuild (R tokens of every sequence, one layer) takes, in microseconds.
+float rebuild_gemm_micros(const adore_config &c) {
+  const int M = c.batch * c.rebuild_budget, Hd = c.heads * c.head_dim;
+  if (M == 0) return 0.f;
+  const int pick = c.dtype == ADORE_BF16 ? pick_tile(M, 2 * Hd, c.hidden, Hd, c.head_dim, false) : -1;
+  if (pick < 0) return float(4.0 * M * Hd * c.hidden / 6e6);   // one wave per output: 6 TFLOP/s
+  const long long tiles = (long long)((M + kTiles[pick].bm - 1) / kTiles[pick].bm) * (2 * Hd / kTiles[pick].bn);
+  return float((tiles + 255) / 256) * kTileMicros[pick] * c.hidden / 4096.f;
+}
+
 hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_layer, int lists, int r,
                                int32_t *map_dst, int32_t *map_out) {
   const adore_config &c = ctx->cfg;

@@ -1168,3 +1168,30 @@ def test_random_medium_configurations_with_rotary_embedding(name, kw, calls, ord
     whole = {"fine": None, "whole": lambda t: True, "mixed": lambda t: t % 3 != 1}[calls]
     worst, job, _ = h.lockstep(w, steps=w.T, check_cache_every=2, whole=whole, ordered=ordered)
     job.adore.close()
+
+
+@pytest.mark.parametrize("streams", ["0", "1"])
+@pytest.mark.parametrize("ordered", [True, False])
+def test_steps_on_one_stream_and_on_the_side_streams(streams, ordered, monkeypatch):
+    """Where a job's steps are launched follows from its size (short ones, like those of most tests, keep to the caller's
+    stream); here both ways are forced on the same small jobs: whole-step calls mixed with the fine-grained ones, two
+    layers, rescoring, the forward, and a prompt of two chunks followed at once by steps and by a second job."""
+    monkeypatch.setenv("ADORE_STEP_STREAMS", streams)
+    h = _harness()
+    for w, whole in ((Workload("st_mix", **ORDER_W), lambda t: (t // 3) % 2 == 0),
+                     (Workload("st_chunks", **dict(ORDER_W, S=600, T=6)), lambda t: True),
+                     (Workload("st_l2", L=2, B=2, H=4, d=64, D=128, K=72, R=6, S=90, T=12, dtype="bf16", dprime=32), None),
+                     (Workload("st_rescore", L=1, B=2, H=2, d=64, D=256, K=48, R=6, S=60, T=12, dtype="bf16", dprime=128,
+                               pos_scale=2.0 ** -6, rescore=True), lambda t: t % 3 != 2)):
+        worst, job, _ = h.lockstep(w, steps=w.T, check_cache_every=4, ordered=ordered, **({"whole": whole} if whole else {}))
+        job.adore.close()
+    h.forward_lockstep(Workload("st_fwd", L=2, B=2, H=2, d=128, D=256, K=64, R=7, S=80, T=8, dtype="bf16", dprime=32), 8,
+                       ordered=ordered)
+
+
+@pytest.mark.parametrize("calls", ["whole", "fine"])
+def test_order_of_inputs_and_init_on_the_side_streams(calls, monkeypatch):
+    monkeypatch.setenv("ADORE_STEP_STREAMS", "1")
+    test_inputs_produced_on_the_stream_are_waited_for()
+    test_first_steps_without_a_synchronise_after_the_init_when_inputs_are_not_ordered(calls)
+    test_input_order_switched_between_steps()
