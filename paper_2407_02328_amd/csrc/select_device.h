@@ -16,19 +16,51 @@ namespace adore {
 // if i is not a candidate.  Finds (*thr, *shift) such that exactly c candidates
 // have (key >> shift) >= thr.  Needs 1 <= c <= number of candidates.
 // s_hist: 256 uints; s_ctl: 4 uint64.  All threads of the block must call it.
+// The first digit starts at the highest bit in which two candidates differ: scores of one sequence share most of their
+// exponent, so that a digit from the top of the key would put nearly all of them into one or two bins (atomics on one
+// address, 64 in turn per wave) and tell nothing.  4 sequences of 8200 tokens: release 22.4 -> 19.0 us, choice 19.2 -> 17.1 us.
 template <class KeyFn>
 __device__ inline void radix_select(KeyFn key_of, int ncand, int c, uint32_t *s_hist, uint64_t *s_ctl,
                                     uint64_t *thr, int *shift_out) {
-  uint64_t prefix = 0;
+  uint32_t *s_or = reinterpret_cast<uint32_t *>(s_ctl + 3), *s_and = s_or + 1;   // upper words of all candidates
+  if (threadIdx.x == 0) {
+    *s_or = 0u;
+    *s_and = ~0u;
+  }
+  __syncthreads();
+  uint32_t or_hi = 0u, and_hi = ~0u;
+  for (int i = threadIdx.x; i < ncand; i += blockDim.x) {
+    const uint64_t key = key_of(i);
+    if (key != 0) {
+      or_hi |= uint32_t(key >> 32);
+      and_hi &= uint32_t(key >> 32);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    or_hi |= __shfl_xor(or_hi, off, 64);
+    and_hi &= __shfl_xor(and_hi, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicOr(s_or, or_hi);
+    atomicAnd(s_and, and_hi);
+  }
+  __syncthreads();
+  const uint32_t diff = *s_or & ~*s_and;
+  // bits from `prev` up are decided; equal scores: the positions decide (below 2^24, so the key's lower word starts 0xff)
+  int prev = diff ? 64 - __clz(int(diff)) : 24;
+  uint64_t prefix = prev == 64 ? 0 : ((uint64_t(*s_and) << 32) | 0xff000000u) >> prev;
   int remaining = c;
-  int shift = 56;
-  for (int pass = 0; pass < 8; ++pass, shift -= 8) {
+  int shift = 0;
+  for (;;) {
+    shift = max(prev - 8, 0);
+    const uint32_t digits = (1u << (prev - shift)) - 1u;
     for (int t = threadIdx.x; t < 256; t += blockDim.x) s_hist[t] = 0;
     __syncthreads();
     for (int i = threadIdx.x; i < ncand; i += blockDim.x) {
       const uint64_t key = key_of(i);
-      if (key != 0 && (pass == 0 || (key >> (shift + 8)) == prefix)) {
-        atomicAdd(&s_hist[(key >> shift) & 0xff], 1u);
+      if (key != 0 && (prev == 64 || (key >> prev) == prefix)) {
+        atomicAdd(&s_hist[uint32_t(key >> shift) & digits], 1u);
       }
     }
     __syncthreads();
@@ -59,13 +91,13 @@ __device__ inline void radix_select(KeyFn key_of, int ncand, int c, uint32_t *s_
       }
     }
     __syncthreads();
-    prefix = (prefix << 8) | s_ctl[0];
+    prefix = (prefix << (prev - shift)) | s_ctl[0];
     remaining = int(s_ctl[1]);
     const bool whole_bucket = s_ctl[2] == s_ctl[1];
     __syncthreads();
-    if (whole_bucket) break;
+    prev = shift;
+    if (whole_bucket || shift == 0) break;   // the last digit used: keys are distinct, the bucket held one key
   }
-  if (shift < 0) shift = 0;  // all eight digits used: keys are distinct, the bucket held one key
   *thr = prefix;
   *shift_out = shift;
 }
@@ -165,16 +197,17 @@ __device__ inline void release_row(int row, int s_ins, const int32_t *__restrict
   if (x < 0) need = max(0, nactive + 1 - m_keep);
   if (need > 0 && nactive > need) {
     // The `need` lowest keys are the `need` largest of the inverted keys: radix select on those, 8 bits a pass from
-    // the top, the wave's own 256-bin histogram in LDS.  A pass is skipped when no two candidates differ in its
-    // digit; the search ends as soon as the bin the rank falls into is taken whole (keys are distinct, so after
-    // the last digit at the latest).
+    // the top, the wave's own 256-bin histogram in LDS.  Every digit starts at a bit in which candidates differ (bytes from
+    // the top would put the candidates, which share most of their exponent, into a bin or two first); the search ends
+    // as soon as the bin the rank falls into is taken whole (keys are distinct, so after the last digit at the latest).
     bool done = false;
 #pragma unroll 1
     for (int word = 1; word >= 0 && !done; --word) {
-      const uint32_t diff = word ? diff_hi : diff_lo;
+      uint32_t diff = word ? diff_hi : diff_lo;
 #pragma unroll 1
-      for (int shift = 24; shift >= 0 && !done; shift -= 8) {
-        if (((diff >> shift) & 0xffu) == 0u) continue;
+      while (diff != 0u && !done) {
+        const int shift = max(24 - __clz(int(diff)), 0);   // a digit from the highest bit that tells two candidates apart
+        diff &= (1u << shift) - 1u;
         *reinterpret_cast<uint4 *>(hist + 4 * lane) = uint4{0u, 0u, 0u, 0u};
         wave_lds_fence();
 #pragma unroll
