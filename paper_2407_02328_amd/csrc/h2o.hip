@@ -163,25 +163,30 @@ __global__ __launch_bounds__(256) void h2o_place_kernel(const H2OChoiceArgs a, i
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // the wave's LDS stores before its LDS loads
   __builtin_amdgcn_wave_barrier();
-  int taken = 0, rho = 0;
-  for (; rho < a.R; ++rho) {
-    const int t = sel[rho];
-    if (t < 0) break;                            // the chosen positions come first, then -1 (uniform over the wave)
-    bool found = false;
+  // 64 ranks at a time, lane = rank: each rank's token is broadcast to the wave, whose ballot says whether the row holds it;
+  // the slots then follow from a count.  (Rank after rank with two LDS reads and lane 0's stores in turn: 10.1 us for
+  // 32 ranks of 512 rows; now 6.8.)
+  int taken = 0;
+  for (int rho0 = 0; rho0 < a.R; rho0 += 64) {
+    const int mine = rho0 + lane < a.R ? sel[rho0 + lane] : -1;
+    const int count = __popcll(__ballot(mine >= 0));   // the chosen positions come first, then -1
+    uint64_t missing = 0;
+    for (int q = 0; q < count; ++q) {
+      const int t = __builtin_amdgcn_readlane(mine, q);
+      bool found = false;
 #pragma unroll
-    for (int j = 0; j < KPL; ++j) found |= pos[j] == t;
-    const bool held = __ballot(found) != 0;
-    int slot = -1;
-    if (!held) slot = fr[taken++];
-    if (lane == 0) {
-      a.free_list[size_t(row) * a.R1 + rho] = slot;
-      if (slot >= 0) {
-        a.slot_pos[size_t(row) * a.K + slot] = t;
-        if (a.map_out) a.map_out[size_t(row) * a.K + slot] = t;
-      }
+      for (int j = 0; j < KPL; ++j) found |= pos[j] == t;
+      if (__ballot(found) == 0) missing |= uint64_t(1) << q;
     }
+    int slot = -1;
+    if ((missing >> lane) & 1u) {
+      slot = fr[taken + __popcll(missing & ((uint64_t(1) << lane) - 1))];
+      a.slot_pos[size_t(row) * a.K + slot] = mine;
+      if (a.map_out) a.map_out[size_t(row) * a.K + slot] = mine;
+    }
+    if (rho0 + lane < a.R) a.free_list[size_t(row) * a.R1 + rho0 + lane] = slot;
+    taken += __popcll(missing);
   }
-  for (int q = rho + lane; q < a.R; q += 64) a.free_list[size_t(row) * a.R1 + q] = -1;
   if (lane == 0) a.insert_slot[row] = fr[taken];   // taken <= R: the list holds R + 1 free slots
 }
 
