@@ -233,7 +233,8 @@ int ensure_side_stream(adore_ctx *ctx) {
 // Measured per step, side streams against one: 1 sequence of 4 heads of 64 in fp32 43-49 -> 31 us, 3 of 12 heads with
 // rescoring 67-83 -> 43 us, 8 of 16 heads of 128 (attention 3 us + projection 13 us by the estimate) 44-50 -> 40 us, the same
 // with rescoring 61-74 -> 52 us; but 4 of 32 heads (7 + 25 us) 53.6 -> 53.7 us and with inputs known ahead 49 -> 54 us, 16 of
-// 32 heads (13 + 41 us) 72 -> 76 us.  So: one stream where those two come to less than kOneStreamMicros.
+// 32 heads (13 + 41 us) 72 -> 76 us.  In fp32, whose controller reads twice the bytes: 2 of 8 heads (4 us) 42 -> 34 us, 4 of
+// 16 heads (20 us) 45 -> 54 us.  So: one stream where those two come to less than kOneStreamMicros, half of it in fp32.
 // A stack of layers called one by one with ordered inputs starts its selections behind the last layer's attention, so
 // that the side streams could hide nothing but the controller, once per L layers: 4 layers of 8 sequences 151 -> 122 us,
 // of 32 sequences 561 -> 546 us, 3 layers of 64 sequences 418 -> 406 us.  (The forward's selections run beside all its layers: it keeps the side streams.)
@@ -245,7 +246,8 @@ bool steps_on_one_stream(const adore_ctx *ctx, bool forward) {
   if (forward) return false;
   if (c.layers > 1) return ctx->ordered;
   const double bytes = 2.0 * c.batch * c.heads * double(c.cache_slots) * c.head_dim * elem_size(c);
-  return bytes / 5e6 + rebuild_gemm_micros(c) < kOneStreamMicros;   // the attention reads 5 TB/s
+  // (the attention reads 5 TB/s)
+  return bytes / 5e6 + rebuild_gemm_micros(c) < (c.dtype == ADORE_F32 ? 0.5f : 1.f) * kOneStreamMicros;
 }
 
 // Whether the steps of the present job use the side streams, and the streams of its selections and its controller.

@@ -157,6 +157,38 @@ __global__ __launch_bounds__(256) void ctrl_input_prompt_kernel(const bf16_t *__
   }
 }
 
+// Sums over a wave of a batch of rows at once: at every halving step a lane keeps one half of its partial sums and hands the
+// other half to its partner, so N rows cost N-1 shuffles instead of 6N.
+// v[i] is this lane's partial sum of row i.  Returns, in every lane, the complete sum of row
+// lane / (64 / N).
+template <int N, int OFF>
+struct ReduceRows {
+  __device__ static inline float run(float (&v)[N], int lane) {
+    const bool upper = (lane & OFF) != 0;
+    float w[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      const float keep = upper ? v[i + N / 2] : v[i];
+      const float send = upper ? v[i] : v[i + N / 2];
+      w[i] = keep + __shfl_xor(send, OFF, 64);
+    }
+    return ReduceRows<N / 2, OFF / 2>::run(w, lane);
+  }
+};
+template <int OFF>
+struct ReduceRows<1, OFF> {
+  __device__ static inline float run(float (&v)[1], int) {
+    float s = v[0];
+#pragma unroll
+    for (int off = OFF; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    return s;
+  }
+};
+template <int N>
+__device__ inline float reduce_rows(float (&v)[N], int lane) {
+  return ReduceRows<N, 32>::run(v, lane);
+}
+
 // ---- input projection, any storage type, plain ALUs ---------------------------------
 constexpr int JT = 4;  // gate rows per workgroup
 constexpr int NB = 8;  // tokens per workgroup
@@ -204,13 +236,9 @@ __global__ __launch_bounds__(256) void ctrl_input_kernel(const T *__restrict__ W
   }
   __shared__ float red[4][JT][NB];
   const int wave = tid >> 6, lane = tid & 63;
-#pragma unroll
-  for (int jj = 0; jj < JT; ++jj)
-#pragma unroll
-    for (int tt = 0; tt < NB; ++tt) {
-      const float s = wave_sum(acc[jj][tt]);
-      if (lane == 0) red[wave][jj][tt] = s;
-    }
+  // (one sum at a time, 192 shuffles, was a quarter of a decode step's launch)
+  const float s = reduce_rows<JT * NB>(reinterpret_cast<float (&)[JT * NB]>(acc), lane);
+  if ((lane & 1) == 0) red[wave][lane / 2 / NB][lane / 2 % NB] = s;
   __syncthreads();
   if (tid < JT * NB) {
     const int jj = tid / NB, tt = tid % NB;
@@ -266,36 +294,6 @@ __device__ inline float gi_sum(const CellArgs &a, size_t tok, int j) {
 // (two elements per lane); a wave multiplies a batch of rows by the state it holds in registers and
 // reduces the whole batch at once: at every halving step a lane keeps one half of its partial sums
 // and hands the other half to its partner, so N rows cost N-1 shuffles instead of 6N.
-
-// v[i] is this lane's partial sum of row i.  Returns, in every lane, the complete sum of row
-// lane / (64 / N).
-template <int N, int OFF>
-struct ReduceRows {
-  __device__ static inline float run(float (&v)[N], int lane) {
-    const bool upper = (lane & OFF) != 0;
-    float w[N / 2];
-#pragma unroll
-    for (int i = 0; i < N / 2; ++i) {
-      const float keep = upper ? v[i + N / 2] : v[i];
-      const float send = upper ? v[i] : v[i + N / 2];
-      w[i] = keep + __shfl_xor(send, OFF, 64);
-    }
-    return ReduceRows<N / 2, OFF / 2>::run(w, lane);
-  }
-};
-template <int OFF>
-struct ReduceRows<1, OFF> {
-  __device__ static inline float run(float (&v)[1], int) {
-    float s = v[0];
-#pragma unroll
-    for (int off = OFF; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    return s;
-  }
-};
-template <int N>
-__device__ inline float reduce_rows(float (&v)[N], int lane) {
-  return ReduceRows<N, 32>::run(v, lane);
-}
 
 // two consecutive elements of a weight row, raw, and their conversion
 __device__ inline uint32_t load_raw2(const bf16_t *p) { return *reinterpret_cast<const uint32_t *>(p); }
@@ -850,7 +848,8 @@ hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int 
   float *gi = ctx->gi[buf];
   ScopedTimer t(ctx, ADORE_KERNEL_CTRL_INPUT, st);
   *ksplit_out = 1;
-  if (ntok > kCtrlSplitTokens &&
+  // fp32: a row's sums are a wave's 16 at a time there, so from a tile's rows on
+  if (ntok > (c.dtype == ADORE_BF16 ? kCtrlSplitTokens : 15) &&
       launch_plain_projection(ctx, t, st, x, ctx->w.gru_w_ih, gi, ntok, per_seq, seq_rows, G3, c.hidden)) {
     // a prompt chunk on the rebuild's 128x128 tile (3d' a multiple of 128, D of 64)
   } else if (c.dtype == ADORE_BF16 && c.hidden % 128 == 0 && ntok > kCtrlSplitTokens) {

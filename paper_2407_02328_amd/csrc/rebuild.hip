@@ -21,7 +21,7 @@
 // are XOR-swizzled (conflict-free for 16-byte reads and writes).  The output tile
 // is rounded to bf16 into LDS and leaves as 16-byte vectors: a row of the tile is
 // a run of contiguous head slices of cache rows.
-// fp32 path (and shapes the tile kernel does not take): one wave per output.
+// fp32 path: tiles of 16x16x4 fp32 matrix instructions (f32_tile_kernel).  bf16 shapes that no tile takes: one wave per output.
 #include "device_utils.h"
 
 namespace adore {
@@ -627,6 +627,110 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   }
 }
 
+// The same product in fp32, on the fp32 matrix instructions; also the controller's input projection over a prompt (PLAIN).
+// A workgroup owns a tile of 16 MT rows x 16 NT columns; its four waves take every fourth step of 16 k.  Lane (c, g) reads the
+// 4 values at k = 16 s + 4 g of rows c of both operands (64-byte runs of every row; both sides use the same assignment, so
+// the order of k does not matter), U steps in flight, straight into the operands: with four waves on different k the tile's
+// rows pass the L1 once, and 4 MT NT instructions of 32 cycles per step hide the MT + NT reads.  Element e of the four goes to
+// accumulator e, and after two steps (chains of eight products) the four are added up in 64 bits, as are the waves' sums at the
+// end (chains through the whole row were further from 64 bits than the kernel before: 1.5e-7 against 1.0e-7 at k = 1024).
+// One wave per output element, which read both rows from the L1 for every output, reached 6 TFLOP/s: the step of 4 sequences
+// with 160 rows x 2048 columns x 1024 took 138 us, and 45 us on these tiles (measured with fp32 chains).
+template <int MODE, int MT, int NT, int U>
+__global__ __launch_bounds__(256) void f32_tile_kernel(const GemmArgs a) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = lane & 15, g = lane >> 4;
+  const int tm = blockIdx.x / a.tiles_n, tn = blockIdx.x - tm * a.tiles_n;
+  const int m0 = tm * (16 * MT), n0 = tn * (16 * NT);
+  const float *pa[MT], *pb[NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int mi = min(m0 + 16 * i + c, a.M - 1);         // padded rows read a valid one; dropped at the store
+    const int b = mi / a.r, j = mi - b * a.r;
+    const size_t row = MODE == MODE_REBUILD ? row_by_position(a, b, j) : size_t(b) * a.xrps + j;
+    pa[i] = static_cast<const float *>(a.X) + row * a.D;
+  }
+#pragma unroll
+  for (int i = 0; i < NT; ++i) pb[i] = static_cast<const float *>(a.W) + size_t(min(n0 + 16 * i + c, a.N - 1)) * a.D;
+  static_assert(U % 2 == 0, "sums are taken over two steps");
+  double sum[MT][NT][4];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sum[i][j][v] = 0.0;
+  for (int k0 = wave * 16 + g * 4; k0 - g * 4 < a.D; k0 += 64 * U) {   // uniform over the wave; D is a multiple of 4
+    f32x4 va[U][MT], vb[U][NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 64 * u;
+      const bool in = k < a.D;                            // behind the end of a row both operands are zero
+#pragma unroll
+      for (int i = 0; i < MT; ++i) va[u][i] = in ? *reinterpret_cast<const f32x4 *>(pa[i] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NT; ++i) vb[u][i] = in ? *reinterpret_cast<const f32x4 *>(pb[i] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int u = 0; u < U; u += 2)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          f32x4 acc[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u][i][e], vb[u][j][e], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[u + 1][i][e], vb[u + 1][j][e], acc[e], 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            sum[i][j][v] += (double(acc[0][v]) + double(acc[1][v])) + (double(acc[2][v]) + double(acc[3][v]));
+        }
+  }
+  // sum v of lane (c, g): row 4*g + v, column c of its tile
+  __shared__ double red[4][MT * NT][16][17];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[wave][i * NT + j][4 * g + v][c] = sum[i][j][v];
+    }
+  __syncthreads();
+  const int m = tid >> 4, nn = tid & 15;
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int mi = m0 + 16 * i + m;
+    if (mi >= a.M) continue;
+    const int b = mi / a.r, rho = mi - b * a.r;
+    const int pos = MODE == MODE_REBUILD ? a.rebuilt_pos[size_t(b) * a.Rdim + rho] : 0;
+    if (pos < 0) continue;                                // an empty rank
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int n = n0 + 16 * j + nn, t = i * NT + j;
+      if (n >= a.N) continue;
+      const float val = float((red[0][t][m][nn] + red[1][t][m][nn]) + (red[2][t][m][nn] + red[3][t][m][nn]));
+      if (MODE == MODE_PLAIN) {
+        static_cast<float *>(a.Out)[size_t(mi) * a.N + n] = val;
+        continue;
+      }
+      const int Hd = a.H * a.d;
+      const int half = n / Hd, rem = n - half * Hd;
+      const int h = rem / a.d, cc = rem - h * a.d;
+      const int slot = a.free_list[(size_t(b) * a.H + h) * a.R1 + rho];
+      if (slot < 0) continue;                             // the head still holds this token's row
+      static_cast<float *>(half ? a.Vc : a.Kc)[((size_t(b) * a.H + h) * a.K + slot) * a.d + cc] = val;
+      if (a.map_dst && half == 0 && cc == 0) {
+        a.map_dst[(size_t(b) * a.H + h) * a.K + slot] = pos;
+        if (a.map_out) a.map_out[(size_t(b) * a.H + h) * a.K + slot] = pos;
+      }
+    }
+  }
+}
+
 // One wave per output element: dot of a gathered hidden row with one W row.
 template <typename T>
 __global__ __launch_bounds__(256) void rebuild_dot_kernel(const GemmArgs a) {
@@ -835,6 +939,18 @@ int pick_tile(int M, int N, int kdim, int section, int head_dim, bool dense, int
   return pick;
 }
 
+// 32x32 tiles where there are enough of them for every compute unit, otherwise 16x16 ones.
+template <int MODE>
+void launch_f32_tile(ScopedTimer &t, hipStream_t stream, GemmArgs &a) {
+  const long long big = (long long)((a.M + 31) / 32) * ((a.N + 31) / 32);
+  const int side = big >= 256 ? 32 : 16;
+  a.tiles_m = (a.M + side - 1) / side;
+  a.tiles_n = (a.N + side - 1) / side;
+  const dim3 grid(unsigned(a.tiles_m) * unsigned(a.tiles_n)), block(256);
+  if (side == 32) ADORE_LAUNCH(t, (f32_tile_kernel<MODE, 2, 2, 2>), grid, block, 0, stream, a);
+  else ADORE_LAUNCH(t, (f32_tile_kernel<MODE, 1, 1, 4>), grid, block, 0, stream, a);
+}
+
 template <int MODE>
 void launch_tile(ScopedTimer &t, hipStream_t stream, int pick, GemmArgs &a) {
   a.tiles_m = (a.M + kTiles[pick].bm - 1) / kTiles[pick].bm;
@@ -874,7 +990,7 @@ float rebuild_gemm_micros(const adore_config &c) {
   const int M = c.batch * c.rebuild_budget, Hd = c.heads * c.head_dim;
   if (M == 0) return 0.f;
   const int pick = c.dtype == ADORE_BF16 ? pick_tile(M, 2 * Hd, c.hidden, Hd, c.head_dim, false) : -1;
-  if (pick < 0) return float(4.0 * M * Hd * c.hidden / 6e6);   // one wave per output: 6 TFLOP/s
+  if (pick < 0) return float(4.0 * M * Hd * c.hidden / (c.dtype == ADORE_F32 ? 40e6 : 6e6));   // 40 and 6 TFLOP/s
   const long long tiles = (long long)((M + kTiles[pick].bm - 1) / kTiles[pick].bm) * (2 * Hd / kTiles[pick].bn);
   return float((tiles + 255) / 256) * kTileMicros[pick] * c.hidden / 4096.f;
 }
@@ -901,14 +1017,12 @@ hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_lay
   if (turned) a.rope = ctx->rope_f;
   if (pick >= 0) {
     launch_tile<MODE_REBUILD>(t, ctx->stream, pick, a);
+  } else if (c.dtype == ADORE_F32) {
+    launch_f32_tile<MODE_REBUILD>(t, ctx->stream, a);
   } else {
     const size_t waves = size_t(a.M) * a.N;
     const unsigned blocks = unsigned((waves + 3) / 4);
-    if (c.dtype == ADORE_BF16) {
-      ADORE_LAUNCH(t, (rebuild_dot_kernel<bf16_t>), dim3(blocks), dim3(256), 0, ctx->stream, a);
-    } else {
-      ADORE_LAUNCH(t, (rebuild_dot_kernel<float>), dim3(blocks), dim3(256), 0, ctx->stream, a);
-    }
+    ADORE_LAUNCH(t, (rebuild_dot_kernel<bf16_t>), dim3(blocks), dim3(256), 0, ctx->stream, a);
   }
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && rope && !turned) e = launch_rope_rows(ctx, layer, lists, r, 0, r, false, 0);
@@ -1064,17 +1178,23 @@ hipError_t launch_fwd_oproj(adore_ctx *ctx, const void *w_o_layer, const void *x
   return hipGetLastError();
 }
 // gi[tok][j] = W_ih[j][:] . x_tok for the ntok tokens of a prompt chunk (token b * per_seq + i at row
-// b * seq_rows + i of x), fp32, on the 128x128 tile.  False if the shape does not fit that tile.
+// b * seq_rows + i of x), fp32 sums: fp32 storage on the fp32 tiles, bf16 on the 128x128 tile.  False if the shape does not
+// fit that tile.
 bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, const void *x, const void *W, float *out,
                              int ntok, int per_seq, int seq_rows, int N, int D) {
   constexpr int kTile = 2;   // 128 x 128 x 64
-  if (ctx->cfg.dtype != ADORE_BF16 || N % kTiles[kTile].bn != 0 || D % kTiles[kTile].bk != 0) return false;
+  const bool bf16 = ctx->cfg.dtype == ADORE_BF16;
+  if (bf16 && (N % kTiles[kTile].bn != 0 || D % kTiles[kTile].bk != 0)) return false;
   GemmArgs a;
   fill_common(ctx, a, 0, per_seq);
   a.X = x; a.W = W; a.Out = out;
   a.Kc = a.Vc = nullptr;
   a.D = D; a.M = ntok; a.N = N;
   a.xrps = seq_rows; a.a_gather = 0;
+  if (!bf16) {
+    launch_f32_tile<MODE_PLAIN>(t, st, a);
+    return true;
+  }
   a.tiles_m = (a.M + kTiles[kTile].bm - 1) / kTiles[kTile].bm;
   a.tiles_n = a.N / kTiles[kTile].bn;
   const dim3 grid((a.tiles_m * a.tiles_n + 7) / 8 * 8), block(512);
