@@ -12,9 +12,12 @@
 //   1 range     mean and deviation of the weights over an evenly spaced sample of the keys give a range in which the K-th
 //               largest is expected.
 //   2 count     a histogram per query in LDS over that range (128 bins, [bin][query]: every query has a bank of its own);
-//               the bin that holds the K-th largest weight and its rank in it.  Counted again over another range for the queries
-//               whose K-th largest is outside, or in a bin with more than 16 weights.  The ranges shrink by the number of bins every
-//               time: the result never depends on the sample, only the time does.
+//               the bin that holds the K-th largest weight and its rank in it.  Counted again for the queries whose K-th largest is
+//               outside the range, or in a bin with more than 16 weights: up to twice over another range, then over bins that
+//               are equal in the order-preserving integer images of the weights, between the two weights it is known to lie
+//               between (7 of at most 32 bits a count; at once where the bin stands alone, as one of equal weights does).  So a
+//               workgroup counts at most 3 + 5 times whatever the weights' sizes and distribution, and the result never
+//               depends on the sample, only the time does.
 //   3 ties      only where more than 16 weights are equal to the K-th largest: one pass in which the last position that stays is
 //               found from the bit masks of each step.
 //   4 product   P = exp2((w - max) / sqrt(d) . log2 e) of the weights above the bin (the same instructions on the same
@@ -32,6 +35,9 @@
 // 80900 -> 6760; 4 rows of 128 tokens, d = 64: 21.3 -> 10.9.  Before, 16 queries per workgroup kept their fp32 weights in LDS (in
 // memory beyond 2048 tokens, read again by every pass of a radix select), with K and a transposed copy of V loaded straight
 // into the operand layout: 16 look-ups in the L1 per 256 bytes, K and V read from the L2 once per 16 queries.
+// Those are Gaussian weights, which mostly need one count.  512 rows of 1024 tokens with 60 % of the keys zeroed take 1250 us, with
+// whole-numbered q and k 1565 us (2190 and 1770 with ranges alone, which took 17 counts to close in on a zero and dropped keys
+// where the weights were below 1e-29); keys of widely different lengths 1209 us (1162), weights of 2^-100 1490 us.
 // What bounds it now: of a workgroup's 57000 cycles at 1024 tokens the vector units are busy with 26000 (two waves per SIMD), the matrix
 // units with 13000 (a 32x32x16 instruction keeps the vector unit from issuing for half of its 32 cycles), LDS with 17000; the rest
 // is waiting at barriers and for the first and last loads, one workgroup (241 registers, 142 KB of LDS) having a compute unit to itself.
@@ -61,7 +67,7 @@ constexpr int kStep = 128;           // keys per step: four 32-key blocks
 constexpr int kBins = 128;           // bin 0: below the range, the last one: above it
 constexpr int kFew = 16;             // weights of a bin that are ranked directly
 constexpr int kSample = 128;         // keys of the sample: mean and deviation to a tenth of the deviation, for a range of two
-constexpr int kMaxCounts = 64;       // a range of 2^277 (all floats) shrinks to one value in 40 counts of 7 bits
+constexpr int kRangeCounts = 3;      // most counts over ranges of weights; then at most ceil(32 / 7) over images
 
 // Order-preserving image of a weight (larger float <=> larger integer, never 0 for a number) and back.
 __device__ inline uint32_t weight_image(float x) {
@@ -77,6 +83,10 @@ __device__ inline float normal_quantile(float p) {
   const float z = t - (2.30753f + 0.27061f * t) * __builtin_amdgcn_rcpf(1.f + t * (0.99229f + 0.04481f * t));
   return p <= 0.5f ? z : -z;
 }
+
+constexpr uint32_t kLowest = 0x007fffffu, kHighest = 0xff800000u;   // images of the infinities
+// Right shift after which the distances 0 .. span fit the bins.
+__device__ inline int image_shift(uint32_t span) { return max(0, 25 - __clz(int(span))); }
 
 struct TopkArgs {
   const bf16_t *Q, *K, *V;   // [rows][S][d]
@@ -96,7 +106,7 @@ struct TopkLds {
   static constexpr int kMerge = 4 * NQB * (DH / 32) * 16 * 64 * 4;
   static constexpr int kFewAt = kBig > kMerge ? kBig : kMerge;
   static constexpr int kMisc = kFewAt + NQ * kFew * 8;
-  static constexpr int kBytes = kMisc + NQ * 23 * 4 + 16;
+  static constexpr int kBytes = kMisc + NQ * 28 * 4 + 16;
 };
 
 template <int DH, int NQB>
@@ -109,20 +119,25 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   extern __shared__ __align__(16) unsigned char smem[];
   uint32_t *s_hist = reinterpret_cast<uint32_t *>(smem + 2 * Lds::kTile);   // [kBins][NQ]
   float2 *s_few = reinterpret_cast<float2 *>(smem + Lds::kFewAt);       // [NQ][kFew] weight, bits of its position, of the weights set aside
-  float *s_a = reinterpret_cast<float *>(smem + Lds::kMisc);   // [NQ] bin of w = a w + b, while its histogram is open (else 0)
+  float *s_a = reinterpret_cast<float *>(smem + Lds::kMisc);   // [NQ] bin of w = a w + b, while its range is counted (else 0)
   float *s_b = s_a + NQ;
   float *s_lo = s_b + NQ;                                      // [NQ] the range
   float *s_hi = s_lo + NQ;
-  float *s_ga = s_hi + NQ;                                     // [NQ] a, b and the bin that holds the K-th largest weight
-  float *s_gb = s_ga + NQ;
+  float *s_ga = s_hi + NQ;                                     // [NQ] a, b and the bin that holds the K-th largest weight; where images
+  float *s_gb = s_ga + NQ;                                     // were counted (s_flag[3]) its lower end and the weight above it
   float *s_bin = s_gb + NQ;
-  int *s_need = reinterpret_cast<int *>(s_bin + NQ);           // [NQ] its rank in that bin: how many of its weights stay
+  uint32_t *s_first = reinterpret_cast<uint32_t *>(s_bin + NQ);   // [NQ] images between which it is known to be; both 0 once it is found
+  uint32_t *s_last = s_first + NQ;
+  uint32_t *s_over = s_last + NQ;                              // [NQ] weights above s_last
+  uint32_t *s_min = s_over + NQ;                               // [NQ] smallest and largest image among the weights just counted
+  uint32_t *s_most = s_min + NQ;
+  int *s_need = reinterpret_cast<int *>(s_most + NQ);          // [NQ] its rank in that bin: how many of its weights stay
   int *s_tie = s_need + NQ;                                    // [NQ] crowded bin (-2 until it is known): its weights, all equal, stay up to this position
   uint32_t *s_max = reinterpret_cast<uint32_t *>(s_tie + NQ);  // [NQ] image of the largest weight
   int *s_n = reinterpret_cast<int *>(s_max + NQ);              // [NQ] weights set aside
   float *s_l = reinterpret_cast<float *>(s_n + NQ);            // [4][NQ]
   uint32_t *s_part = reinterpret_cast<uint32_t *>(s_l + 4 * NQ);   // [8][NQ]
-  int *s_flag = reinterpret_cast<int *>(s_part + 8 * NQ);      // [0] count again, [1] a crowded bin of equal weights
+  int *s_flag = reinterpret_cast<int *>(s_part + 8 * NQ);      // [0] count images again, [1] a crowded bin of equal weights, [2] count ranges again, [3] some queries need images counted
 
   // Workgroup -> (row, query block): all blocks of a row on one XCD (consecutive workgroups go to the 8 XCDs in turn), so
   // that its K and V come from memory once; within a row the blocks with the most keys first.
@@ -155,7 +170,6 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     const int x = (r & 3) << 1 | ((r >> 2) & 1);
     return DH == 128 ? r * 256 + ((ch ^ (x | (r & 8))) << 4) : r * 128 + ((ch ^ x) << 4);
   };
-  // stride_fp: the keys of a sample, key = (index * stride_fp) >> 12
   const int ld_row = tid / CPR;
   const uint32_t ld_col = uint32_t(tid % CPR) * 16u;
   auto load_tile = [&](const bf16_t *src, int step, u32x4 (&r)[NLD]) {
@@ -165,7 +179,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       r[i] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(src) + (uint32_t(key) * (DH * 2) + ld_col));
     }
   };
-  auto load_sample = [&](int step, uint32_t stride_fp, u32x4 (&r)[NLD]) {
+  auto load_sample = [&](int step, uint32_t stride_fp, u32x4 (&r)[NLD]) {   // key = (index * stride_fp) >> 12
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       const uint32_t key = (uint32_t(step * kStep + ld_row + i * (NT / CPR)) * stride_fp) >> 12;
@@ -180,6 +194,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   };
   // The query operand, through LDS like the keys: straight from memory its 16-byte pieces of 32 rows cost the L1 a look-up per
   // lane (4096 of them per workgroup, 3 us before the first product).
+  if (tid < 4) s_flag[tid] = 0;
   bf16x8 qf[KT];
   {
     constexpr int NQL = NQ * CPR / NT;
@@ -258,6 +273,18 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   };
   const int steps = (nkeys + kStep - 1) / kStep;
 
+  // Query q counts over lo .. hi next, or over images where that makes no grid: an empty, huge or tiny range, or bins below
+  // four units in the last place of its ends.
+  auto set_range = [&](int q, float lo, float hi) {
+    const float sa = float(kBins - 2) / (hi - lo);
+    const bool grid = hi > lo && sa < 1e30f && fmaxf(fabsf(lo), fabsf(hi)) * sa < 0x1p22f;
+    s_lo[q] = lo;
+    s_hi[q] = hi;
+    s_a[q] = grid ? sa : 0.f;
+    s_b[q] = grid ? fmaf(-lo, sa, 1.f) : 0.f;
+    s_flag[grid ? 2 : 3] = 1;
+  };
+
   // ---- 1: the range ----
   {
     float sum = 0.f, sq = 0.f;
@@ -290,13 +317,13 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       const float inv = 1.f / float(sampled ? kSample : min(n, a.S));
       const float mean = t0 * inv, dev = __builtin_amdgcn_sqrtf(fmaxf(t1 * inv - mean * mean, 0.f));
       const float mid = fmaf(dev, normal_quantile(fminf(float(a.topk) / float(n), 1.f)), mean);
-      const float half = fmaxf(fmaxf(dev, 1e-6f * fabsf(mid)), 1e-30f);
+      const float half = fmaxf(dev, 1e-6f * fabsf(mid));
       const bool open = n <= a.S && n > a.topk;   // else: all stay, or no such query
-      const float lo = mid - half, hi = mid + half, sa = float(kBins - 2) / (hi - lo);
-      s_lo[tid] = lo;
-      s_hi[tid] = hi;
-      s_a[tid] = open ? sa : 0.f;
-      s_b[tid] = open ? fmaf(-lo, sa, 1.f) : 0.f;
+      s_a[tid] = s_b[tid] = 0.f;
+      if (open) set_range(tid, mid - half, mid + half);
+      s_first[tid] = open ? kLowest : 0u;
+      s_last[tid] = open ? kHighest : 0u;
+      s_over[tid] = 0u;
       s_ga[tid] = 0.f;                            // unless a bin is found: 0 w + 1 - 0 >= 1, everything is above it
       s_gb[tid] = 1.f;
       s_bin[tid] = 0.f;
@@ -305,15 +332,43 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       s_max[tid] = 0u;
       s_n[tid] = 0;
     }
-    if (tid < 4) s_flag[tid] = 0;
   }
 
   // ---- 2: the bin of the K-th largest weight ----
+  // Images of the smallest weights whose a w + b reaches `bin` and `bin` + 1 (rounding is monotone): searched for next to the
+  // points the line gives, both at once.
+  auto ends_of = [&](float sa, float sb, float bin, uint32_t (&from)[2]) {
+    const float inv = __builtin_amdgcn_rcpf(sa);
+    uint32_t below[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float y = bin + float(i), at = (y - sb) * inv, slack = 0x1p-20f * fmaxf(fabsf(at), fabsf(sb * inv)) + 0x1p-17f * inv;
+      below[i] = weight_image(at - slack);
+      from[i] = weight_image(at + slack);
+      if (!(fmaf(image_weight(below[i]), sa, sb) < y)) below[i] = kLowest;
+      if (!(fmaf(image_weight(from[i]), sa, sb) >= y)) from[i] = kHighest;
+    }
+    while (max(from[0] - below[0], from[1] - below[1]) > 1u) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const uint32_t mid = below[i] + ((from[i] - below[i]) >> 1);   // (`below` itself once the search is over)
+        const bool reached = fmaf(image_weight(mid), sa, sb) >= bin + float(i);
+        from[i] = reached ? mid : from[i];
+        below[i] = reached ? below[i] : mid;
+      }
+    }
+  };
 #pragma unroll 1
-  for (int tries = 0; tries < kMaxCounts; ++tries) {
+  for (int tries = 0, ranges = 1; tries < kRangeCounts + 5; ++tries) {
+    if (tid == 0) s_flag[0] = 0;
+    if (tid == 1) s_flag[2] = 0;
     for (int i = tid; i < NQ * kBins / 4; i += NT) reinterpret_cast<u32x4 *>(s_hist)[i] = u32x4{0u, 0u, 0u, 0u};
+    if (tid < NQ) {
+      s_min[tid] = ~0u;
+      s_most[tid] = 0u;
+    }
     __syncthreads();
-    {
+    if (ranges) {
       const float sa = s_a[ql], sb = s_b[ql];
       float top = -INFINITY;
       sweep(std::false_type(), steps, 0u, [&](float w0, float w1, float w2, float w3, int, int) {
@@ -326,6 +381,24 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
         top = fmaxf(fmaxf(top, fmaxf(w0, w1)), fmaxf(w2, w3));
       });
       __hip_atomic_fetch_max(&s_max[ql], weight_image(top), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+      const uint32_t last = s_last[ql], span = last - s_first[ql];
+      const int shift = image_shift(span);
+      uint32_t least = ~0u, most = 0u;
+      sweep(std::false_type(), steps, 0u, [&](float w0, float w1, float w2, float w3, int, int) {
+        const float w[4] = {w0, w1, w2, w3};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t u = weight_image(w[i] + 0.f), down = last - u;   // (-0 counts as 0)
+          if (down <= span) {                    // not for the NaN of a hidden key, whose image is beyond both infinities'
+            __hip_atomic_fetch_add(&s_hist[(kBins - 1 - (down >> shift)) * NQ + ql], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            least = min(least, u);
+            most = max(most, u);
+          }
+        }
+      });
+      __hip_atomic_fetch_min(&s_min[ql], least, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_max(&s_most[ql], most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __syncthreads();
     // eight threads per query, 16 bins each
@@ -338,78 +411,111 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       mine += cnt[j];
     }
     s_part[grp * NQ + q] = mine;
+    const bool open = ranges ? sa != 0.f : s_last[q] != 0u;
+    uint32_t above = ranges ? 0u : s_over[q];
     __syncthreads();
-    uint32_t above = 0u;
 #pragma unroll
     for (int g = 1; g < 8; ++g) above += g > grp ? s_part[g * NQ + q] : 0u;
     const uint32_t want = uint32_t(a.topk);
-    if (sa != 0.f && above < want && above + mine >= want) {   // this thread's bins hold it
-      int bin = 0, need = 0;
-      uint32_t in = 0u;
+    if (open && above < want && above + mine >= want) {   // this thread's bins hold it
+      int bin = 0;
+      uint32_t in = 0u, need = 0u, beside = 0u;
       bool found = false;
 #pragma unroll
       for (int j = kBins / 8 - 1; j >= 0; --j) {
         if (!found && above + cnt[j] >= want) {
           found = true;
           bin = grp * (kBins / 8) + j;
-          need = int(want - above);
+          need = want - above;
           in = cnt[j];
+          beside = (j > 0 ? cnt[j - 1] : 0u) + (j + 1 < kBins / 8 ? cnt[j + 1] : 0u);
         }
         above += cnt[j];
       }
-      float lo = s_lo[q], hi = s_hi[q];
-      const float width = (hi - lo) * (1.f / float(kBins - 2));
-      bool again = true;
-      if (bin == 0) {                          // below the range
-        hi = lo + width;
-        lo = lo - 8.f * float(kBins - 2) * width;
-      } else if (bin == kBins - 1) {           // above it
-        lo = hi - width;
-        hi = hi + 8.f * float(kBins - 2) * width;
-      } else {
-        const float at = fmaf(float(bin - 1), width, lo);
-        // one value per bin at most: more than a few weights in it are equal ones
-        const bool one_value = fmaxf(fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-24f, 1e-30f) >= width;
-        if (in <= uint32_t(kFew) || one_value) {
-          again = false;
+      const bool few = in <= uint32_t(kFew);
+      if (ranges) {
+        const float sb = s_b[q];
+        s_a[q] = 0.f;
+        s_b[q] = 0.f;
+        if (few && bin > 0 && bin < kBins - 1) {
           s_ga[q] = sa;
-          s_gb[q] = s_b[q];
+          s_gb[q] = sb;
           s_bin[q] = float(bin);
-          s_need[q] = need;
-          s_a[q] = 0.f;
-          s_b[q] = 0.f;
-          if (in > uint32_t(kFew)) {
+          s_need[q] = int(need);
+          s_first[q] = s_last[q] = 0u;
+        } else {
+          uint32_t end[2];
+          ends_of(sa, sb, float(bin), end);
+          if (bin > 0) s_first[q] = max(s_first[q], end[0]);
+          if (bin < kBins - 1 && end[1] <= s_last[q]) {
+            s_last[q] = end[1] - 1u;
+            s_over[q] = want - need;
+          }
+          const float lo = s_lo[q], hi = s_hi[q], width = (hi - lo) * (1.f / float(kBins - 2));
+          const float at = fmaf(float(bin - 1), width, lo);
+          const bool lonely = bin > 0 && bin < kBins - 1 && 8u * beside < in;
+          if (lonely || tries + 1 == kRangeCounts)
+            s_flag[3] = 1;
+          else if (bin == 0)                     // below the range
+            set_range(q, lo - 8.f * float(kBins - 2) * width, lo + width);
+          else if (bin == kBins - 1)             // above it
+            set_range(q, hi - width, hi + 8.f * float(kBins - 2) * width);
+          else                                   // a quarter of a bin to spare on either side, for rounding
+            set_range(q, at - 0.25f * width, at + 1.25f * width);
+        }
+      } else {
+        uint32_t first = s_first[q], last = s_last[q];
+        const int shift = image_shift(last - first);
+        const uint32_t size = (1u << shift) - 1u;
+        last -= uint32_t(kBins - 1 - bin) << shift;
+        if (last - first > size) first = last - size;
+        if (few || shift == 0 || s_min[q] == s_most[q]) {   // few weights, or all of them equal
+          s_ga[q] = image_weight(first);
+          s_gb[q] = image_weight(last + 1u);     // (NaN behind infinity: nothing is above)
+          s_bin[q] = -1.f;
+          s_need[q] = int(need);
+          first = last = 0u;
+          if (!few) {
             s_tie[q] = -2;
             s_flag[1] = 1;
           }
-        } else {                               // a bin's width to spare on either side, for rounding
-          lo = at - 0.25f * width;
-          hi = at + 1.25f * width;
-          lo = fminf(lo, image_weight(weight_image(lo) - 2u));
-          hi = fmaxf(hi, image_weight(weight_image(hi) + 2u));
+        } else {
+          s_flag[0] = 1;
         }
-      }
-      if (again) {
-        const float na = float(kBins - 2) / (hi - lo);
-        s_lo[q] = lo;
-        s_hi[q] = hi;
-        s_a[q] = na;
-        s_b[q] = fmaf(-lo, na, 1.f);
-        s_flag[0] = 1;
+        s_first[q] = first;
+        s_last[q] = last;
+        s_over[q] = want - need;
       }
     }
     __syncthreads();
-    const bool more = s_flag[0] != 0;
+    const bool more = ranges ? (s_flag[2] | s_flag[3]) != 0 : s_flag[0] != 0;
+    ranges = ranges ? s_flag[2] : 0;
     __syncthreads();
     if (!more) break;
-    if (tid == 0) s_flag[0] = 0;
+  }
+  // Bins of images are told by their ends; in a workgroup with such queries the others' are as well.
+  const bool by_ends = __builtin_amdgcn_readfirstlane(s_flag[3]) != 0;
+  if (by_ends) {
+    if (tid < NQ && s_bin[tid] >= 0.f) {
+      const float sa = s_ga[tid], sb = s_gb[tid], bin = s_bin[tid];
+      uint32_t end[2] = {kHighest, kLowest};
+      if (bin > 0.f) ends_of(sa, sb, bin, end);
+      s_ga[tid] = image_weight(end[0]);
+      s_gb[tid] = image_weight(end[1]);
+    }
+    __syncthreads();
   }
 
   // ---- 3: the position up to which the weights of a bin stay that holds many equal ones ----
   const float ga = s_ga[ql], gb = s_gb[ql], bin = s_bin[ql];
   // where a weight stands to its query's bin: >= 1 above it, in [0, 1) inside it, else below (exact: rounding is monotone,
-  // and the difference is exact inside the bin); NaN for keys the query does not see
-  auto place = [&](float w) { return fmaf(w, ga, gb) - bin; };
+  // and the difference is exact inside the bin), and so for the NaN of keys the query does not see
+  auto place = [&](auto by_ends_, float w) {
+    if constexpr (decltype(by_ends_)::value)
+      return w >= gb ? 1.f : w >= ga ? 0.f : -1.f;
+    else
+      return fmaf(w, ga, gb) - bin;
+  };
   auto inside = [](float z) { return __float_as_uint(z) < 0x3f800000u; };
   const bool crowded = s_flag[1] != 0;
   if (crowded) {
@@ -424,7 +530,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       f32x16 s = weights(0, nothing);
       if (kb + 31 > qfirst) hide(s, kb);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) mask |= inside(place(s[i])) ? 1u << i : 0u;
+      for (int i = 0; i < 16; ++i) mask |= inside(place(std::true_type(), s[i])) ? 1u << i : 0u;
       s_part[(kg * 2 + h) * NQ + ql] = mask;
       __syncthreads();
       if (tid < NQ && s_tie[tid] == -2) {
@@ -455,7 +561,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
 #pragma unroll
   for (int db = 0; db < DB; ++db) o[db] = f32x16{0.f};
   float lsum = 0.f;
-  {
+  auto product = [&](auto by_ends_) {
     const float negmax = -image_weight(s_max[ql]) * a.scale_log2;
     const int tie = s_tie[ql];
     const int grp = lane >> 4, vrow = 4 * (grp >> 1) + ((lane & 15) >> 2), vcol = (grp & 1) * 16 + (lane & 3) * 4;
@@ -517,13 +623,13 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       s = weights((st & 1) * Lds::kTile, [&](int g) {   // (the last time nothing comes of it)
         float z[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) z[i] = place(w[4 * g + i]);
+        for (int i = 0; i < 4; ++i) z[i] = place(by_ends_, w[4 * g + i]);
         if (min(min(__float_as_uint(z[0]), __float_as_uint(z[1])), min(__float_as_uint(z[2]), __float_as_uint(z[3]))) < 0x3f800000u) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             if (inside(z[i])) {
               const int pos = kb + 8 * g + 4 * h + i;
-              if (crowded && tie >= 0) {
+              if (decltype(by_ends_)::value && crowded && tie >= 0) {
                 if (pos <= tie) z[i] = 1.f;    // stays
               } else {
                 const int at = __hip_atomic_fetch_add(&s_n[ql], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -545,7 +651,11 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       kb += kStep;
       if (kb + 31 > qfirst) hide(s, kb);
     }
-  }
+  };
+  if (by_ends)
+    product(std::true_type());
+  else
+    product(std::false_type());
 
   // ---- 5: the weights set aside, and the four key groups' partial sums in order ----
   lsum += __shfl_xor(lsum, 32, 64);

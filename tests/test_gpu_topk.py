@@ -224,3 +224,48 @@ def test_topk_attention_at_the_edges_of_its_blocks(rows, S, d, top_k, same):
     want, _ = O.topk_attention(q[pick], k[pick], v[pick], top_k)
     e = _row_err(got[pick], want)
     assert e.max() < TOL, f"rows={rows} S={S} d={d} K={top_k}: {e.max()}"
+
+
+def _checked_rows(O, torch, topk_attention, q, k, top_k, rng, what):
+    """Exactly representable weights: the kept sets are the oracle's.  The first, the last and two other rows are checked."""
+    rows = q.shape[0]
+    v = _bf16_values(torch, rng.standard_normal(q.shape))
+    got = topk_attention(_to_gpu(torch, q), _to_gpu(torch, k), _to_gpu(torch, v), top_k).float().cpu().numpy().astype(np.float64)
+    pick = sorted({0, rows // 3, rows // 2, rows - 1})
+    want, _ = O.topk_attention(q[pick], k[pick], v[pick], top_k)
+    e = _row_err(got[pick], want)
+    print(f"{what}: worst row error {e.max():.2e}", flush=True)
+    assert e.max() < TOL, f"{what}: {e.max()}"
+
+
+# 32 and 64 queries per workgroup.  The weights are multiples of 2^(2 exponent - 4): down to the smallest normal numbers, where
+# their squares vanish, and up to where they stay well inside the range in which the softmax's own products are exact enough
+@pytest.mark.parametrize("rows,S,d,top_k", [(2, 300, 64, 40), (260, 200, 128, 33)])
+@pytest.mark.parametrize("exponent", [-60, -52, -46, -25, 8])
+def test_topk_attention_far_from_unit_scale(rows, S, d, top_k, exponent):
+    torch, O, topk_attention = _mods()
+    rng = np.random.default_rng(100 * S - exponent)
+    q, k = (rng.integers(-8, 9, size=(rows, S, d)) / 4.0 * 2.0 ** exponent for _ in range(2))
+    _checked_rows(O, torch, topk_attention, q, k, top_k, rng, f"rows={rows} exponent={exponent}")
+
+
+# Keys whose weights crowd one value (and so go by position) or lead the sampled range astray, for both workgroup sizes.
+# From position 512 on a query block samples every fourth key (multiples of four) or fewer.
+KEYS = {
+    "zeroed": lambda k, rng: np.where(rng.random(k.shape[:2])[..., None] < 0.6, 0.0, k),           # the K-th weight is often 0
+    "zeroed tail": lambda k, rng: np.where((np.arange(k.shape[1]) >= k.shape[1] // 2)[None, :, None], 0.0, k),
+    "runs": lambda k, rng: np.where((np.arange(k.shape[1]) % 5 < 3)[None, :, None], k[:, :1], k),
+    "whole numbers": lambda k, rng: np.rint(k),
+    "samples zero": lambda k, rng: np.where((np.arange(k.shape[1]) % 4 == 0)[None, :, None], 0.0, k),
+    "samples large": lambda k, rng: np.where((np.arange(k.shape[1]) % 4 == 0)[None, :, None], 64.0 * k, k),
+    "samples equal": lambda k, rng: np.where((np.arange(k.shape[1]) % 4 == 0)[None, :, None], k[:, :1], k),
+}
+
+
+@pytest.mark.parametrize("rows,S,d,top_k", [(2, 620, 64, 200), (56, 620, 64, 50), (2, 580, 128, 290), (56, 580, 128, 20)])
+@pytest.mark.parametrize("keys", list(KEYS))
+def test_topk_attention_with_crowded_or_misleading_keys(rows, S, d, top_k, keys):
+    torch, O, topk_attention = _mods()
+    rng = np.random.default_rng(rows * 31 + S + len(keys))
+    q, k = (rng.integers(-8, 9, size=(rows, S, d)) / 4.0 for _ in range(2))
+    _checked_rows(O, torch, topk_attention, q, KEYS[keys](k, rng), top_k, rng, f"rows={rows} {keys}")
