@@ -744,14 +744,25 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
 }
 
 template <int DH, int NQB>
-hipError_t launch(const TopkArgs &a, hipStream_t st) {
+hipError_t launch(TopkArgs a, hipStream_t st) {
   constexpr int lds = TopkLds<DH, NQB>::kBytes;
   static_assert(lds <= 160 * 1024, "shared memory of a compute unit");
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&topk_attend_kernel<DH, NQB>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  const int tiles = (a.S + 32 * NQB - 1) / (32 * NQB) * a.rows;
-  hipLaunchKernelGGL((topk_attend_kernel<DH, NQB>), dim3(unsigned(tiles)), dim3(256 * NQB), lds, st, a);
+  // A launch holds fewer than 2^32 threads: whole groups of eight rows (one per XCD) at a time where there are more
+  // (from 8193 tokens on, at 65535 rows).
+  const int blocks = (a.S + 32 * NQB - 1) / (32 * NQB), rows = a.rows;
+  const int most = int(0xffffffffu / (256u * NQB * unsigned(blocks)) / 8u * 8u);
+  for (int r0 = 0; r0 < rows; r0 += most) {
+    a.rows = rows - r0 < most ? rows - r0 : most;
+    hipLaunchKernelGGL((topk_attend_kernel<DH, NQB>), dim3(unsigned(a.rows) * unsigned(blocks)), dim3(256 * NQB), lds, st, a);
+    const size_t done = size_t(a.rows) * a.S * DH;
+    a.Q += done;
+    a.K += done;
+    a.V += done;
+    a.O += done;
+  }
   return hipGetLastError();
 }
 

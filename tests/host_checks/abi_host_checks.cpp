@@ -1,7 +1,7 @@
 // Host-side paths of the C-ABI under AddressSanitizer and UndefinedBehaviorSanitizer: argument validation, the
-// workspace layout, context creation and destruction, calls out of order, the table look-ups.  Nothing here reaches
-// a kernel launch: every call either fails its checks on the host or only builds host state, so the program runs
-// with or without a GPU.  Built and run by tests/test_host_sanitizers.py; exit status 0 = every call answered as
+// workspace layout, context creation and destruction, calls out of order, the table look-ups.  Nothing here launches
+// a kernel: every call either fails its checks on the host, only builds host state or ends in the stand-ins for the
+// runtime's launch below, which note the launch's size, so the program runs with or without a GPU.  Built and run by tests/test_host_sanitizers.py; exit status 0 = every call answered as
 // expected and no sanitizer report.
 #include <cstdint>
 #include <cstdio>
@@ -10,7 +10,21 @@
 #include <string>
 #include <vector>
 
+#include <hip/hip_runtime_api.h>
+
 #include "adore.h"
+
+// In place of the runtime's, which want a device: what the top-K attention would launch.
+static std::vector<dim3> launched_grid, launched_block;
+extern "C" hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t) {
+  launched_grid.push_back(grid);
+  launched_block.push_back(block);
+  return hipSuccess;
+}
+extern "C" hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { return hipSuccess; }
+extern "C" hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { return hipSuccess; }
+extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
 
 static int failures = 0;
 #define EXPECT(cond)                                                          \
@@ -130,6 +144,24 @@ int main() {
   EXPECT(adore_topk_attention_static(fake, fake, fake, nullptr, 2, 64, 64, 4, nullptr) == ADORE_E_INVALID);
   EXPECT(adore_topk_attention_static(fake, fake, fake, fake, 2, 4096, 64, 4, nullptr) == ADORE_E_WORKSPACE);
   EXPECT(adore_topk_attention_static(fake, fake, fake, fake, 60000, 2048, 128, 4, nullptr) == ADORE_E_WORKSPACE);
+  // ... and the sizes of its launches: HIP takes fewer than 2^32 threads, and every block of queries has its workgroup
+  for (int32_t rows : {1, 15, 512, 16385, 65535})
+    for (int32_t seq : {1, 64, 65, 8192, 8193, 16500, 32768})
+      for (int32_t d : {64, 128}) {
+        launched_grid.clear();
+        launched_block.clear();
+        const size_t bytes = adore_topk_attention_workspace_bytes(rows, seq, d);
+        EXPECT(adore_topk_attention(fake, fake, fake, fake, fake, bytes, rows, seq, d, 96, nullptr) == ADORE_OK);
+        uint64_t groups = 0;
+        for (size_t i = 0; i < launched_grid.size(); ++i) {
+          EXPECT(uint64_t(launched_grid[i].x) * launched_block[i].x < (uint64_t(1) << 32));
+          EXPECT(launched_block[i].x == launched_block[0].x && launched_grid[i].y == 1 && launched_grid[i].z == 1);
+          groups += launched_grid[i].x;
+        }
+        EXPECT(!launched_grid.empty());
+        const int32_t queries = launched_grid.empty() ? 1 : int32_t(launched_block[0].x) / 8;
+        EXPECT(groups == uint64_t(rows) * ((seq + queries - 1) / queries));
+      }
   if (failures) {
     std::fprintf(stderr, "%d unexpected answers\n", failures);
     return 1;
