@@ -60,8 +60,10 @@ size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
 struct Layout {
   size_t cache_k, cache_v, slot_pos, score, z, insert_slot, free_list, released_pos, rebuilt_pos, init_res,
-      att_part, att_logit, att_ml, gi[2], zseq[2], cvec, avec, fwd_q, fwd_o, fwd_x, rope, total;
+      att_part, att_logit, att_ml, gi[2], zseq[2], gi_rows[2], cvec, avec, fwd_q, fwd_o, fwd_x, rope;
+  size_t least, total;          // bytes without and with a second copy of what the prompt's chunks pass on (below)
   std::vector<size_t> guards;   // offsets of the guard words (debug layout), one run behind every region
+  size_t least_guards;          // ... of which within `least`
 };
 
 // Debug layout (ADORE_GUARD_WORDS=1 in the environment of the process): every region of the workspace is followed
@@ -115,7 +117,7 @@ Layout make_layout(const adore_config &c) {
   const size_t es = elem_size(c);
   const size_t BH = size_t(c.batch) * c.heads;
   const size_t R1 = size_t(c.rebuild_budget) + 1;
-  Layout l;
+  Layout l = {};
   size_t off = 0;
   const bool guarded = guard_words_on();
   auto take = [&](size_t bytes) {
@@ -143,10 +145,8 @@ Layout make_layout(const adore_config &c) {
   l.att_ml = take(h2o ? BH * 2 * 4 : 0);
   size_t gi_rows = size_t(c.batch) * kPromptChunk;
   if (gi_rows < size_t(kMaxCtrlSplit) * kCtrlSplitTokens) gi_rows = size_t(kMaxCtrlSplit) * kCtrlSplitTokens;
-  for (int i = 0; i < 2; ++i) {
-    l.gi[i] = take(gi_rows * 3 * c.ctrl_hidden * 4);
-    l.zseq[i] = take(size_t(c.batch) * kPromptChunk * c.ctrl_hidden * 4);
-  }
+  l.gi[0] = take(gi_rows * 3 * c.ctrl_hidden * 4);
+  l.zseq[0] = take(size_t(c.batch) * kPromptChunk * c.ctrl_hidden * 4);
   const bool rescore = c.score_mode == ADORE_SCORE_RESCORE;
   l.cvec = take(rescore ? size_t(c.batch) * c.max_positions * c.ctrl_hidden * 4 : 0);
   l.avec = take(rescore ? size_t(c.ctrl_hidden) * 4 : 0);
@@ -155,6 +155,23 @@ Layout make_layout(const adore_config &c) {
   l.fwd_o = take(fwd_rows * c.heads * c.head_dim * es);
   l.fwd_x = take(fwd_rows * c.hidden * es);
   l.rope = take(c.rope_base > 0.f ? size_t(c.max_positions) * (c.head_dim / 2) * 24 : 0);   // fp64 table, fp32 copy
+  l.least = off;
+  l.least_guards = l.guards.size();
+  // A second copy of pre-activations and states lets neighbouring chunks of a prompt be worked on side by side.  The cache, which
+  // is filled behind the controller, has room for it unless the model is small and its prompts long (then 5 to 12 % of
+  // an init hang on it: 1620 us for 1700 at one sequence of 4096 tokens, 1090 for 1220 at 64 of 2048); a workspace of `least` bytes does without.
+  const size_t row_bytes = size_t(3) * c.ctrl_hidden * 4, cache_bytes = size_t(c.layers) * BH * c.cache_slots * c.head_dim * es;
+  l.gi_rows[0] = l.gi_rows[1] = gi_rows;
+  if (h2o || c.max_positions <= kPromptChunk + 1) {
+    l.gi_rows[1] = 0;                      // never a second chunk
+  } else if (cache_bytes >= size_t(c.batch) * kPromptChunk * row_bytes) {
+    l.gi[1] = l.cache_k;
+    l.zseq[1] = l.cache_v;
+    l.gi_rows[1] = cache_bytes / row_bytes;
+  } else {
+    l.gi[1] = take(gi_rows * row_bytes);
+    l.zseq[1] = take(size_t(c.batch) * kPromptChunk * c.ctrl_hidden * 4);
+  }
   l.total = off;
   return l;
 }
@@ -286,7 +303,7 @@ hipError_t launch_controller(adore_ctx *ctx, const void *x_n, int seq_rows, cons
 // the chunk before it, and it takes one workgroup per sequence; so with several chunks the input projection of the next one
 // (first side stream) and the scoring of the one before (second) run next to it.  The projection's tiles take whole
 // compute units: they become ready with the recurrence that runs beside them, which is ahead of them by a queue's latency.
-// Two copies of what passes between the three: a chunk's projection waits for the recurrence, a chunk's recurrence for the
+// Two copies of what passes between the three (one, and one stream, where the workspace has no room): a chunk's projection waits for the recurrence, a chunk's recurrence for the
 // scoring, of the chunk two before it.  Everything is complete on the caller's stream when this returns its last wait.
 // 16 prompts of 1024 tokens (two chunks) to the first token 770 -> 684 us; 32 prompts of 2048 tokens: 4 x 370 us of controller
 // -> 1.14 ms in all.
@@ -294,14 +311,15 @@ hipError_t prompt_controller(adore_ctx *ctx, const void *ctrl_input, const float
   const adore_config &c = ctx->cfg;
   const size_t token_bytes = size_t(c.hidden) * elem_size(c);
   const int nchunks = (S + kPromptChunk - 1) / kPromptChunk;
-  const bool apart = ctx->overlap && nchunks > 1;
+  const bool two_copies = ctx->gi_rows[1] > 0, apart = ctx->overlap && nchunks > 1 && two_copies;
   hipStream_t st = ctx->stream, st_proj = apart ? ctx->side : st, st_score = apart ? ctx->side2 : st;
   hipEvent_t ev_proj = ctx->ev_in, ev_scan = ctx->ev_att, ev_score = ctx->ev_join;
   int ksplit[2] = {1, 1};
   auto length = [&](int i) { return std::min(kPromptChunk, S - i * kPromptChunk); };
+  auto copy_of = [&](int i) { return two_copies ? i & 1 : 0; };
   auto project = [&](int i, hipStream_t on) {
     const char *x = static_cast<const char *>(ctrl_input) + size_t(i) * kPromptChunk * token_bytes;
-    return launch_ctrl_input(ctx, on, x, c.batch * length(i), length(i), S, i & 1, &ksplit[i & 1]);
+    return launch_ctrl_input(ctx, on, x, c.batch * length(i), length(i), S, copy_of(i), &ksplit[copy_of(i)]);
   };
 #define CHUNK_TRY(EXPR)                          \
   do {                                           \
@@ -316,7 +334,7 @@ hipError_t prompt_controller(adore_ctx *ctx, const void *ctrl_input, const float
   }
   CHUNK_TRY(project(0, st));
   for (int i = 0; i < nchunks; ++i) {
-    const int len = length(i), buf = i & 1, pos0 = i * kPromptChunk;
+    const int len = length(i), buf = copy_of(i), pos0 = i * kPromptChunk;
     const float *given = score_override ? score_override + pos0 : nullptr;
     const bool two = ctrl_chunk_in_two(c, len);
     if (apart && i > 0) CHUNK_TRY(hipStreamWaitEvent(st, ev_proj, 0));
@@ -366,7 +384,7 @@ int adore_create(const adore_config *cfg, const adore_weights *weights, void *wo
     return ADORE_E_INVALID;
   if (!config_supported(cfg)) return ADORE_E_UNSUPPORTED;
   const Layout l = make_layout(*cfg);
-  if (workspace_bytes < l.total || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return ADORE_E_WORKSPACE;
+  if (workspace_bytes < l.least || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return ADORE_E_WORKSPACE;
   adore_ctx *ctx = new (std::nothrow) adore_ctx();
   if (!ctx) return ADORE_E_INVALID;
   ctx->cfg = *cfg;
@@ -391,9 +409,11 @@ int adore_create(const adore_config *cfg, const adore_weights *weights, void *wo
   ctx->att_part = reinterpret_cast<float *>(base + l.att_part);
   ctx->att_logit = reinterpret_cast<float *>(base + l.att_logit);
   ctx->att_ml = reinterpret_cast<float *>(base + l.att_ml);
+  const bool whole = workspace_bytes >= l.total;
   for (int i = 0; i < 2; ++i) {
-    ctx->gi[i] = reinterpret_cast<float *>(base + l.gi[i]);
-    ctx->zseq[i] = reinterpret_cast<float *>(base + l.zseq[i]);
+    ctx->gi_rows[i] = i == 0 || l.gi[1] < l.least || whole ? l.gi_rows[i] : 0;
+    ctx->gi[i] = ctx->gi_rows[i] ? reinterpret_cast<float *>(base + l.gi[i]) : nullptr;
+    ctx->zseq[i] = ctx->gi_rows[i] ? reinterpret_cast<float *>(base + l.zseq[i]) : nullptr;
   }
   ctx->cvec = reinterpret_cast<float *>(base + l.cvec);
   ctx->avec = reinterpret_cast<float *>(base + l.avec);
@@ -404,6 +424,7 @@ int adore_create(const adore_config *cfg, const adore_weights *weights, void *wo
   ctx->rope_f = reinterpret_cast<float2 *>(base + l.rope + size_t(cfg->max_positions) * (cfg->head_dim / 2) * 16);
   ctx->ws_base = base;
   ctx->guard_off = l.guards;
+  if (!whole) ctx->guard_off.resize(l.least_guards);
   ctx->guards_ready = false;
   ctx->forward = false;
   ctx->r_pending = 0;

@@ -72,9 +72,10 @@ struct adore_ctx {
   float *att_part;           // [B*H][kMaxSplits][d+2]
   float *att_logit;          // H2O mode: [B*H][K] the step's logits in base 2, as the attention kernel scaled them
   float *att_ml;             // H2O mode: [B*H][2] their maximum and the sum of exp2(logit - maximum) over the row
-  // two copies, which the chunks of a prompt take in turn
+  // two copies, which the chunks of a prompt take in turn (the second may lie in the cache, or be missing)
   float *gi[2];              // [ksplit][tokens][3d'] GRU input pre-activations, per D-slice (steps: copy 0)
   float *zseq[2];            // [B][kPromptChunk][d'] GRU states of a prompt chunk, between its scan and its scoring
+  size_t gi_rows[2];         // rows of 3d' floats in each; 0: no such copy
   float *cvec;               // rescore mode: [B][N_max][d']  W_1 (z_i + pos_b) + b_1 of every token
   float *avec;               // rescore mode: [d']  W_1 pos_w  (what one unit of distance adds)
   void *fwd_q, *fwd_o;       // rebuild forward: [B*(R+1)][H*d] query rows / attention outputs of the layer in flight

@@ -830,11 +830,14 @@ __global__ __launch_bounds__(256) void rescore_kernel(const float *__restrict__ 
 // there are few tokens, and slices short enough that a wave walks at most four 32-wide steps of its quarter (the
 // operand loads of a step touch 64 cache lines and wait for each other: at 128 tokens, two slices of 2048 took
 // 225 us); one slice when there are many tokens.  A slice is a multiple of 128 (4 waves x 32).
-int ctrl_input_ksplit(const adore_config &c, int ntok) {
+// rows: what the copy of the pre-activations holds (ntok per slice).
+int ctrl_input_ksplit(const adore_config &c, int ntok, size_t rows) {
   const int tiles = ((3 * c.ctrl_hidden + 15) / 16) * ((ntok + 15) / 16);
   int ks = 1;
   if (ntok > kCtrlSplitTokens) return 1;
-  while (ks < kMaxCtrlSplit && (tiles * ks < 256 || c.hidden / ks > 512) && c.hidden % (ks * 2 * 128) == 0) ks *= 2;
+  while (ks < kMaxCtrlSplit && (tiles * ks < 256 || c.hidden / ks > 512) && c.hidden % (ks * 2 * 128) == 0 &&
+         size_t(ks) * 2 * ntok <= rows)
+    ks *= 2;
   return ks;
 }
 
@@ -858,7 +861,7 @@ hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int 
                        static_cast<const bf16_t *>(ctx->w.gru_w_ih), static_cast<const bf16_t *>(x), gi,
                        c.hidden, G3, ntok, per_seq, seq_rows);
   } else if (c.dtype == ADORE_BF16 && c.hidden % 128 == 0) {
-    const int ks = ctrl_input_ksplit(c, ntok);
+    const int ks = ctrl_input_ksplit(c, ntok, ctx->gi_rows[buf]);
     *ksplit_out = ks;
     dim3 grid((G3 + 15) / 16, (ntok + 15) / 16, ks);
     ADORE_LAUNCH(t, ctrl_input_mfma_kernel, grid, dim3(256), 0, st,

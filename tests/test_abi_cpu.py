@@ -60,6 +60,36 @@ def test_workspace_bytes(lib):
     assert lib.adore_workspace_bytes(None) == 0
 
 
+LONG = dict(head_dim=64, hidden=512, rebuild_budget=8, ctrl_hidden=128, dtype="bf16", layers=1)
+
+
+# What callers of earlier versions may have allocated: bytes that were enough before the chunks of a prompt ran side by side.
+@pytest.mark.parametrize("kw,enough,same", [
+    (dict(layers=1, batch=16, heads=32, head_dim=128, hidden=4096, cache_slots=512, rebuild_budget=32, max_positions=1536,
+          ctrl_hidden=128, dtype="bf16"), 177399808, True),
+    (dict(layers=1, batch=128, heads=32, head_dim=128, hidden=4096, cache_slots=256, rebuild_budget=16, max_positions=576,
+          ctrl_hidden=128, dtype="bf16"), 795394048, True),
+    (dict(layers=4, batch=32, heads=32, head_dim=128, hidden=4096, cache_slots=512, rebuild_budget=32, max_positions=2064,
+          ctrl_hidden=128, dtype="bf16"), 1160173568, True),
+    (dict(layers=1, batch=1, heads=4, head_dim=64, hidden=256, cache_slots=64, rebuild_budget=8, max_positions=384,
+          ctrl_hidden=128, dtype="f32"), 6746112, True),                                    # one chunk at most
+    (dict(layers=1, batch=3, heads=4, head_dim=64, hidden=256, cache_slots=64, rebuild_budget=8, max_positions=4096,
+          ctrl_hidden=64, dtype="bf16"), 3911680, False),                                   # a small cache
+    (dict(layers=1, batch=1, heads=32, head_dim=128, hidden=4096, cache_slots=512, rebuild_budget=32, max_positions=9000,
+          ctrl_hidden=1024, dtype="bf16"), 62504448, False),
+    (dict(LONG, batch=2, heads=8, cache_slots=96, max_positions=2000, score_mode=1), 9458432, False),
+    (dict(LONG, batch=2, heads=8, cache_slots=96, max_positions=2000, score_mode=2), 7533568, True),   # no controller
+])
+def test_workspaces_of_earlier_versions_are_still_taken(lib, kw, enough, same):
+    c, wt = make_config(**dict(dict(pos_scale=2.0 ** -12), **kw)), fake_weights()
+    h = ctypes.c_void_p()
+    n = lib.adore_workspace_bytes(ctypes.byref(c))
+    assert n == enough if same else n > enough
+    assert lib.adore_create(ctypes.byref(c), ctypes.byref(wt), FAKE, enough, None, ctypes.byref(h)) == 0
+    assert lib.adore_destroy(h) == 0
+    assert lib.adore_create(ctypes.byref(c), ctypes.byref(wt), FAKE, enough - 1, None, ctypes.byref(h)) == -4
+
+
 def test_create_rejects_bad_arguments(lib):
     w = workload("tiny")
     c, wt = cfg_for(w), fake_weights()

@@ -37,13 +37,13 @@ def test_scores_and_state_after_a_prompt_other_controller_widths(batch, S, D, DP
     _check_prompt(batch, S, D, DP)
 
 
-def _check_prompt(batch, S, D, DP):
+def _check_prompt(batch, S, D, DP, H=2, K=24):
     from paper_2407_02328_amd import Adore, make_config
     g = torch.Generator().manual_seed(1000 * S + D)
 
     def normal(shape, std, dtype):
         return (torch.randn(shape, generator=g) * std).to(dtype).cuda()
-    H, d, K, R, n_max = 2, 64, 24, 3, S + 4
+    d, R, n_max = 64, 3, S + 4
     bf, f32 = torch.bfloat16, torch.float32
     w = {"w_kv": normal((1, 2 * H * d, D), 0.02, bf), "gru_w_ih": normal((3 * DP, D), D ** -0.5, bf),
          "gru_w_hh": normal((3 * DP, DP), DP ** -0.5, bf), "gru_b_ih": normal((3 * DP,), 0.1, f32),
@@ -68,3 +68,27 @@ def _check_prompt(batch, S, D, DP):
     assert (z.cpu().double() - want_z).abs().max() <= 4e-6
     assert (scores[:, :S].cpu().double() - want_scores).abs().max() <= 4e-6
     job.close()
+
+
+# The chunks' second copy in the cache (with sliced tails, and at the smallest cache that holds it), behind everything else, and
+# missing; with the guard words of the debug layout, which tests/conftest.py counts when the job closes.
+@pytest.mark.parametrize("guards", [False, True])
+@pytest.mark.parametrize("batch,S,D,H,K,without", [(1, 1100, 512, 16, 512, False), (1, 770, 1024, 12, 512, False),
+                                                   (3, 1537, 256, 12, 512, False), (2, 1100, 256, 2, 24, False),
+                                                   (2, 1100, 256, 2, 24, True), (1, 700, 512, 2, 24, True)])
+def test_places_of_the_chunks_second_copy(batch, S, D, H, K, without, guards, monkeypatch):
+    from paper_2407_02328_amd import binding
+    if guards:
+        monkeypatch.setenv("ADORE_GUARD_WORDS", "1")
+    if without:
+        lib = binding.load_library()
+        second = max(512 * batch, 4096) * 3 * 128 * 4 + 512 * batch * 128 * 4 + (512 if guards else 0)
+
+        class Smaller:
+            def __getattr__(self, name):
+                return getattr(lib, name)
+
+            def adore_workspace_bytes(self, cfg):
+                return lib.adore_workspace_bytes(cfg) - second
+        monkeypatch.setattr(binding, "load_library", lambda: Smaller())
+    _check_prompt(batch, S, D, 128, H, K)
