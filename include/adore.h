@@ -257,7 +257,8 @@ int adore_set_state(adore_ctx *ctx, const int32_t *slot_pos, const float *scores
                     const float *z, const void *cache_k, const void *cache_v, int32_t step);
 
 /* Input order.  The controller and the selections of a step run on a stream of the
- * context's own, next to the attention and the rebuild; they read x_n / embed and
+ * context's own, next to the attention and the rebuild (where a step is too short for
+ * that to pay, on the context's stream like everything else); they read x_n / embed and
  * score_override.  ordered != 0 (the default): they start behind everything that was
  * enqueued on the context's stream before the call, so those inputs may come from
  * kernels enqueued there, at the price of one more cross-stream event per step.

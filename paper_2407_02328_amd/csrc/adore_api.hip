@@ -24,7 +24,7 @@
 // stream then never runs ahead and the periodic wait above is not needed.  A caller whose inputs are
 // complete in memory when the call is made switches this off and saves that event.
 // A step whose work is shorter than what the events cost goes to the caller's stream as a whole instead
-// (steps_on_one_stream below; decided per job by adore_init_cache).  ADORE_NO_OVERLAP=1 puts everything there, always.
+// (steps_on_one_stream below; decided by adore_create, adore_init_cache and adore_set_input_order).  ADORE_NO_OVERLAP=1 puts everything there, always.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -271,6 +271,29 @@ bool steps_on_one_stream(const adore_ctx *ctx, bool forward) {
 bool side_steps(const adore_ctx *ctx) { return ctx->overlap && !ctx->one_stream; }
 hipStream_t selection_stream(const adore_ctx *ctx) { return side_steps(ctx) ? ctx->side : ctx->stream; }
 hipStream_t controller_stream(const adore_ctx *ctx) { return side_steps(ctx) ? ctx->side2 : ctx->stream; }
+
+// Moves the steps to come between the caller's stream and the side streams, behind everything these hold now.  Between steps.
+hipError_t place_steps(adore_ctx *ctx, bool one) {
+  if (one == ctx->one_stream) return hipSuccess;
+  hipError_t e = hipSuccess;
+  auto then = [&](hipError_t r) { if (e == hipSuccess) e = r; };
+  if (ctx->overlap && ctx->side_ready) {
+    if (one) {
+      then(hipEventRecord(ctx->ev_join, ctx->side));
+      then(hipEventRecord(ctx->ev_ctrl, ctx->side2));
+      then(hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0));
+      then(hipStreamWaitEvent(ctx->stream, ctx->ev_ctrl, 0));
+    } else {   // as behind an init
+      for (hipEvent_t ev : {ctx->ev_att, ctx->ev_join, ctx->ev_ctrl}) then(hipEventRecord(ev, ctx->stream));
+      then(hipStreamWaitEvent(ctx->side, ctx->ev_ctrl, 0));
+      then(hipStreamWaitEvent(ctx->side2, ctx->ev_ctrl, 0));
+      ctx->steps_done = 0;
+      ctx->rode = false;
+    }
+  }
+  if (e == hipSuccess) ctx->one_stream = one;
+  return e;
+}
 
 // Ordered inputs: the side stream starts a step's work behind everything the caller's stream holds now.
 // selections: the step has work on the selections' stream as well (not when they ride in the attention launch).
@@ -921,6 +944,7 @@ int adore_set_input_order(adore_ctx *ctx, int32_t ordered) {
     ctx->rode = false;
   }
   ctx->ordered = on;
+  ADORE_TRY(place_steps(ctx, steps_on_one_stream(ctx, ctx->forward)));
   return ADORE_OK;
 }
 

@@ -50,7 +50,7 @@ struct adore_ctx {
   hipEvent_t ev_in;          // ordered inputs: recorded on `stream` at the top of a step, the side stream starts behind it
   bool ordered;              // the side stream reads a step's inputs behind everything enqueued on `stream` before the call
   bool overlap;              // two-stream mode requested
-  bool one_stream;           // the steps of the present job use the caller's stream only (short ones)
+  bool one_stream;           // the steps use the caller's stream only (short ones)
   bool side_ready;           // side stream and events exist (made on first GPU use)
 
   // --- workspace sections (device) ---

@@ -12,7 +12,7 @@
 
 #include <hip/hip_runtime_api.h>
 
-#include "adore.h"
+#include "adore_internal.h"
 
 // In place of the runtime's, which want a device: what the top-K attention would launch.
 static std::vector<dim3> launched_grid, launched_block;
@@ -119,6 +119,17 @@ int main() {
   EXPECT(adore_get_state(h, nullptr, nullptr, nullptr, nullptr, nullptr, &step) == ADORE_E_STATE);
   EXPECT(adore_destroy(h) == ADORE_OK);
   EXPECT(adore_destroy(nullptr) == ADORE_E_INVALID);
+  // a stack called layer by layer keeps to the caller's stream while its inputs are ordered, whenever that is said
+  {
+    adore_config x = tiny();
+    x.layers = 3;
+    adore_ctx *hx = nullptr;
+    EXPECT(adore_create(&x, &wt, fake, adore_workspace_bytes(&x), nullptr, &hx) == ADORE_OK);
+    EXPECT(hx->one_stream);
+    EXPECT(adore_set_input_order(hx, 0) == ADORE_OK && !hx->one_stream);
+    EXPECT(adore_set_input_order(hx, 1) == ADORE_OK && hx->one_stream);
+    EXPECT(adore_destroy(hx) == ADORE_OK);
+  }
   // the debug layout
   setenv("ADORE_GUARD_WORDS", "1", 1);
   const size_t guarded = adore_workspace_bytes(&c);

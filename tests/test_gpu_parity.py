@@ -1195,3 +1195,64 @@ def test_order_of_inputs_and_init_on_the_side_streams(calls, monkeypatch):
     test_inputs_produced_on_the_stream_are_waited_for()
     test_first_steps_without_a_synchronise_after_the_init_when_inputs_are_not_ordered(calls)
     test_input_order_switched_between_steps()
+
+
+def _enqueue(h, job, steps, outs, maps, start):
+    """Steps start .. start + len(steps) - 1 of a job, every call enqueued without waiting for the one before."""
+    w = job.w
+    for t, (qkv, x, ordered, whole) in enumerate(steps):
+        if ordered is not None:
+            job.adore.set_input_order(ordered)
+        q, k, v = qkv
+        if whole:
+            job.adore.decode_step(q[0], k[0], v[0], job.hidden[0], x, None, outs[t][0], maps[t])
+            continue
+        for l in range(w.L):
+            job.adore.attend(l, q[l], k[l], v[l], outs[t][l])
+        job.adore.schedule(x, None, maps[t], None, None)
+        for l in range(w.L):
+            job.adore.rebuild(l, job.hidden[l])
+
+
+def _free_running(h, w, inp, steps, runs, sync):
+    """The init and the steps of one context, `runs` times over without a synchronisation (sync: one before every call).
+    steps(t) gives the input order to set before step t (or None) and whether it is one call.  Every run's outputs."""
+    st = h.storage_dtype(w)
+    job = h.GpuJob(w, inp)
+    pk, pv = (h.to_dev(a, st) for a in job.prompt_np)
+    ctrl = job.hidden[0][:, :w.S].contiguous()
+    plan = [([h.to_dev(a, st) for a in inp.step_qkv(w.S + t)], job.hidden[0][:, w.S + t].contiguous(), *steps(t))
+            for t in range(w.T)]
+    outs = [[torch.empty((w.L, w.B, w.H, w.d), dtype=torch.float32, device=h.DEV) for _ in plan] for _ in range(runs)]
+    maps = [[torch.empty((w.B, w.H, w.K), dtype=torch.int32, device=h.DEV) for _ in plan] for _ in range(runs)]
+    torch.cuda.synchronize()
+    for r in range(runs):
+        job.adore.init_cache(pk, pv, job.hidden, ctrl, None, w.S)
+        for t in range(w.T):
+            if sync:
+                torch.cuda.synchronize()
+            _enqueue(h, job, plan[t:t + 1], outs[r][t:t + 1], maps[r][t:t + 1], w.S + t)
+    torch.cuda.synchronize()
+    state = job.snapshot()
+    job.adore.close()
+    return [([o.cpu().numpy() for o in outs[r]], [m.cpu().numpy() for m in maps[r]]) for r in range(runs)], state
+
+
+def _same_runs(w, got, want):
+    for r, (a, b) in enumerate(zip(got[0], want[0])):
+        for t in range(w.T):
+            assert np.array_equal(a[1][t], b[1][t]), f"slot map at step {t} of run {r}"
+            assert np.array_equal(a[0][t], b[0][t]), f"output at step {t} of run {r}"
+    for key, n in (("scores", w.S + w.T), ("z", None)):
+        assert np.array_equal(got[1][key][..., :n], want[1][key][..., :n]), key
+
+
+@pytest.mark.parametrize("L,whole", [(1, True), (1, False), (2, False)])
+def test_input_order_switched_between_free_running_steps(L, whole):
+    """The order of the inputs is part of what decides where steps are launched; switched every few steps, with nothing
+    but the library's own ordering between them, the bits are those of the run that waits before every call."""
+    h = _harness()
+    w = Workload("switch", **dict(ORDER_W, L=L, T=40))
+    inp = SyntheticInputs(w)
+    steps = lambda t: ((t // 3) % 2 == 1 if t % 3 == 0 else None, whole)
+    _same_runs(w, _free_running(h, w, inp, steps, 1, False), _free_running(h, w, inp, steps, 1, True))

@@ -34,7 +34,7 @@ def test_host_paths_are_clean_under_asan_and_ubsan(tmp_path):
     main_obj = str(tmp_path / "abi_host_checks.o")
     cc = subprocess.run(
         [HIPCC, "--offload-arch=gfx950", "--cuda-host-only", "-O1", "-g", "-std=c++17", *SAN,
-         "-I", os.path.join(ROOT, "include"), "-c", os.path.join(ROOT, "tests", "host_checks", "abi_host_checks.cpp"),
+         "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", os.path.join(ROOT, "tests", "host_checks", "abi_host_checks.cpp"),
          "-o", main_obj], capture_output=True, text=True, timeout=600)
     assert cc.returncode == 0, cc.stdout[-4000:] + cc.stderr[-4000:]
     exe = str(tmp_path / "abi_host_checks")
