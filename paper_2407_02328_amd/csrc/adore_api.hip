@@ -246,25 +246,42 @@ int ensure_side_stream(adore_ctx *ctx) {
 
 // Whether every launch of a job's steps goes to the caller's stream, in order.  What the side streams hide (the controller's
 // two launches, 10 to 20 us, and where they do not ride in the attention launch the two selections, 15 to 40 us) is bought
-// with two or three cross-stream events a step, which hold an overlapped step at about 50 us however little it does.
-// Measured per step, side streams against one: 1 sequence of 4 heads of 64 in fp32 43-49 -> 31 us, 3 of 12 heads with
-// rescoring 67-83 -> 43 us, 8 of 16 heads of 128 (attention 3 us + projection 13 us by the estimate) 44-50 -> 40 us, the same
-// with rescoring 61-74 -> 52 us; but 4 of 32 heads (7 + 25 us) 53.6 -> 53.7 us and with inputs known ahead 49 -> 54 us, 16 of
-// 32 heads (13 + 41 us) 72 -> 76 us.  In fp32, whose controller reads twice the bytes: 2 of 8 heads (4 us) 42 -> 34 us, 4 of
-// 16 heads (20 us) 45 -> 54 us.  So: one stream where those two come to less than kOneStreamMicros, half of it in fp32.
+// with cross-stream events: two or three a step, which hold an overlapped step with ordered inputs at 40 to 55 us however little
+// it does, and one a step that waits for nothing recent where the selections ride and the inputs are known ahead.
+// Measured per step, one stream against the side streams (attention + projection by the estimate):
+//   ordered inputs, selections riding: 1 sequence of 4 heads of 64 (1.6 us) 24 / 42 us, 8 of 16 heads of 128 (16 us) 39 / 45, 16 of
+//     16 (19 us) 37 / 42, 32 of 8 (23 us) 38 / 40, 4 of 32 (28 us) 48 / 47, 1 of 24 behind 2000 tokens (21 us) 58 / 54, 8 of 32 (53 us) 55 / 51;
+//   selections as launches of their own, ordered inputs or not: 8 of 16 heads (16 us) 48 / 78 and 48 / 66, 4 of 32 (28 us) 56 / 78 and
+//     56 / 63, with rescoring 51 / 78 and 51 / 66; 1 of 4 heads behind 5000, 16000 and 40000 tokens 31 / 76, 42 / 76, 67 / 80 and 31 / 59, 42 / 58, 66 / 57;
+//   riding, inputs known ahead: 1 of 4 heads (1.6 us) 24 / 25 to 25 / 28, 3 of 12 (5.1 us) 29 / 27 to 29.5 / 30.5, but 8 of 12 (5.9 us) 32 / 27, 16 of 8
+//     (7.9 us) 32 / 27 to 32 / 30, 8 of 16 (16 us) 39 / 30.
+// In fp32, whose controller reads twice the bytes: ordered 2 of 16 heads (7.5 us) 39 / 43, 3 of 16 (11 us) 44 / 42; known ahead 1 of 4
+// (0.1 us) 24.8 / 25.0, 2 of 8 (1.0 us) 31 / 27.
+// So: one stream where the two come to less than kOneStreamMicros, half of it in fp32; kOneStreamReadyMicros, an eighth of it in fp32,
+// for riding selections with inputs known ahead.
 // A stack of layers called one by one with ordered inputs starts its selections behind the last layer's attention, so
 // that the side streams could hide nothing but the controller, once per L layers: 4 layers of 8 sequences 151 -> 122 us,
 // of 32 sequences 561 -> 546 us, 3 layers of 64 sequences 418 -> 406 us.  (The forward's selections run beside all its layers: it keeps the side streams.)
 // ADORE_STEP_STREAMS=1 / 0 in the environment: side streams always / never, for comparison runs.
-constexpr float kOneStreamMicros = 20.f;
-bool steps_on_one_stream(const adore_ctx *ctx, bool forward) {
+constexpr float kOneStreamMicros = 20.f, kOneStreamReadyMicros = 5.5f;
+bool steps_on_one_stream(const adore_ctx *ctx, bool forward, bool riding) {
   const adore_config &c = ctx->cfg;
   if (const char *e = getenv("ADORE_STEP_STREAMS")) return atoi(e) == 0;
   if (forward) return false;
   if (c.layers > 1) return ctx->ordered;
   const double bytes = 2.0 * c.batch * c.heads * double(c.cache_slots) * c.head_dim * elem_size(c);
+  const bool f32 = c.dtype == ADORE_F32;
+  const float limit = riding && !ctx->ordered ? kOneStreamReadyMicros * (f32 ? 0.125f : 1.f) : kOneStreamMicros * (f32 ? 0.5f : 1.f);
   // (the attention reads 5 TB/s)
-  return bytes / 5e6 + rebuild_gemm_micros(c) < (c.dtype == ADORE_F32 ? 0.5f : 1.f) * kOneStreamMicros;
+  return bytes / 5e6 + rebuild_gemm_micros(c) < limit;
+}
+
+// The decision for steps that adore_decode_step makes in one launch and a projection and for all others; the first is taken to come
+// next where it can (the first step of the other kind moves).
+bool riding_expected(const adore_ctx *ctx) { return ctx->cfg.layers == 1 && ctx->ride && ctx->ride_fits; }
+bool decide_streams(adore_ctx *ctx, bool forward) {
+  for (int riding = 0; riding < 2; ++riding) ctx->one_when[riding] = steps_on_one_stream(ctx, forward, riding != 0);
+  return ctx->one_when[riding_expected(ctx)];
 }
 
 // Whether the steps of the present job use the side streams, and the streams of its selections and its controller.
@@ -476,7 +493,7 @@ int adore_create(const adore_config *cfg, const adore_weights *weights, void *wo
   ctx->ev_ctrl = nullptr;
   ctx->ev_att = ctx->ev_join = ctx->ev_in = nullptr;
   ctx->ordered = true;
-  ctx->one_stream = steps_on_one_stream(ctx, false);
+  ctx->one_stream = decide_streams(ctx, false);
   ctx->steps_done = 0;
   ctx->side_ready = false;
   ctx->attended.assign(cfg->layers, 0);
@@ -532,7 +549,7 @@ int adore_init_cache(adore_ctx *ctx, const void *prompt_k, const void *prompt_v,
     ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_ctrl, 0));
   }
   hipStream_t st = ctx->stream;
-  ctx->one_stream = steps_on_one_stream(ctx, forward);   // both side streams are behind us
+  ctx->one_stream = decide_streams(ctx, forward);   // both side streams are behind us
   ctx->cur = 0;
   if (h2o_mode(ctx)) {
     // the prompt's scores are given (or zero); every head picks its own residents, then the per-sequence choice
@@ -714,6 +731,7 @@ int adore_attend(adore_ctx *ctx, int32_t layer, const void *q, const void *k_new
   if (layer < 0 || layer >= ctx->cfg.layers) return ADORE_E_INVALID;
   if (!ctx->inited || ctx->forward || ctx->scheduled || ctx->attended[layer] || ctx->n >= ctx->cfg.max_positions)
     return ADORE_E_STATE;
+  if (ctx->n_attended == 0) ADORE_TRY(place_steps(ctx, ctx->one_when[0]));
   return do_attend(ctx, layer, q, k_new, v_new, out);
 }
 
@@ -742,6 +760,7 @@ int adore_decode_step(adore_ctx *ctx, const void *q, const void *k_new, const vo
     return ADORE_E_STATE;
   if (ctx->ride && ctx->ride_fits) {
     if (ensure_side_stream(ctx) != ADORE_OK) return ADORE_E_HIP;
+    ADORE_TRY(place_steps(ctx, ctx->one_when[1]));
     return do_ridden_step(ctx, q, k_new, v_new, hidden_store, x_n, score_override, out, slot_map);
   }
   if (h2o_mode(ctx)) {   // the selections need this step's attention
@@ -944,7 +963,7 @@ int adore_set_input_order(adore_ctx *ctx, int32_t ordered) {
     ctx->rode = false;
   }
   ctx->ordered = on;
-  ADORE_TRY(place_steps(ctx, steps_on_one_stream(ctx, ctx->forward)));
+  ADORE_TRY(place_steps(ctx, decide_streams(ctx, ctx->forward)));
   return ADORE_OK;
 }
 

@@ -51,6 +51,7 @@ struct adore_ctx {
   bool ordered;              // the side stream reads a step's inputs behind everything enqueued on `stream` before the call
   bool overlap;              // two-stream mode requested
   bool one_stream;           // the steps use the caller's stream only (short ones)
+  bool one_when[2];          // ... decided for steps whose selections are launches of their own [0] or ride in the attention launch [1]
   bool side_ready;           // side stream and events exist (made on first GPU use)
 
   // --- workspace sections (device) ---

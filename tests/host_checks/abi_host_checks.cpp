@@ -129,6 +129,14 @@ int main() {
     EXPECT(adore_set_input_order(hx, 0) == ADORE_OK && !hx->one_stream);
     EXPECT(adore_set_input_order(hx, 1) == ADORE_OK && hx->one_stream);
     EXPECT(adore_destroy(hx) == ADORE_OK);
+    // one layer whose selections ride in the attention launch has little to wait for once its inputs are known ahead; as
+    // launches of their own they stay where they are
+    x = tiny();
+    x.dtype = ADORE_BF16; x.batch = 8; x.heads = 16; x.head_dim = 128; x.hidden = 2048; x.cache_slots = 256; x.rebuild_budget = 16;
+    EXPECT(adore_create(&x, &wt, fake, adore_workspace_bytes(&x), nullptr, &hx) == ADORE_OK);
+    EXPECT(hx->one_stream && hx->one_when[0] && hx->one_when[1]);
+    EXPECT(adore_set_input_order(hx, 0) == ADORE_OK && !hx->one_stream && hx->one_when[0]);
+    EXPECT(adore_destroy(hx) == ADORE_OK);
   }
   // the debug layout
   setenv("ADORE_GUARD_WORDS", "1", 1);
