@@ -851,8 +851,13 @@ hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int 
   float *gi = ctx->gi[buf];
   ScopedTimer t(ctx, ADORE_KERNEL_CTRL_INPUT, st);
   *ksplit_out = 1;
-  // fp32: a row's sums are a wave's 16 at a time there, so from a tile's rows on
-  if (ntok > (c.dtype == ADORE_BF16 ? kCtrlSplitTokens : 15) &&
+  // fp32: a tile of 16 tokens x 16 rows walks all of D in one workgroup, whose time is the row's (4.3, 5.7, 7.9, 11.7, 18.5 us
+  // at D = 256, 512, 1024, 2048, 4096) until there are more tiles than compute units; the plain kernel's grows with the outputs.
+  // Plain / tiles at d' = 128: D = 256, 16 tokens 5.7 / 5.7 us; 512, 32: 6.7 / 5.6; 1024, 32: 6.5 / 7.8, 96: 8.5 / 8.5, 256: 14.4 / 11.2;
+  // 2048, 64: 9.2 / 11.6, 128: 12.2 / 12.5, 256: 19.4 / 18.6; 4096, 16: 10.3 / 18.3, 128: 20.1 / 20.3, 256: 33.7 / 33.6.  d' = 64 and 512 turn
+  // at the same number of outputs.
+  const bool tiled = c.dtype == ADORE_BF16 ? ntok > kCtrlSplitTokens : ntok >= 16 && (long long)ntok * G3 >= 24LL * c.hidden;
+  if (tiled &&
       launch_plain_projection(ctx, t, st, x, ctx->w.gru_w_ih, gi, ntok, per_seq, seq_rows, G3, c.hidden)) {
     // a prompt chunk on the rebuild's 128x128 tile (3d' a multiple of 128, D of 64)
   } else if (c.dtype == ADORE_BF16 && c.hidden % 128 == 0 && ntok > kCtrlSplitTokens) {

@@ -46,7 +46,7 @@ def test_rebuilt_rows(batch, heads, d, D, R):
     job.close()
 
 
-# just below and above the number of tokens from which the tiles take the projection, one chunk and two
+# just below and above the least number of tokens for the tiles, one chunk and two
 @pytest.mark.parametrize("batch,S,D", [(1, 15, 200), (1, 16, 200), (3, 33, 264), (2, 520, 1024)])
 def test_controller_over_an_fp32_prompt(batch, S, D):
     from paper_2407_02328_amd import Adore, make_config
@@ -75,4 +75,37 @@ def test_controller_over_an_fp32_prompt(batch, S, D):
     # as for bf16 weights: a pre-activation is a sum of D + 128 fp32 products of order one, and |z| <= 1
     assert (z.cpu().double() - want_z).abs().max() <= 4e-6
     assert (scores[:, :S].cpu().double() - want_scores).abs().max() <= 4e-6
+    job.close()
+
+
+# decode steps of many sequences: the plain projection and the tiles on either side of the line between them (16 tokens, and
+# 24 * D outputs), a ragged last tile
+@pytest.mark.parametrize("batch,D", [(15, 256), (16, 256), (16, 264), (63, 1024), (64, 1024), (17, 2048), (131, 2080)])
+def test_controller_over_fp32_steps(batch, D):
+    from paper_2407_02328_amd import Adore, make_config
+    from tests.test_gpu_controller import _reference
+    g = torch.Generator().manual_seed(batch + D)
+    DP, H, d, K, S, T = 128, 1, 64, 8, 5, 4
+
+    def normal(shape, std):
+        return (torch.randn(shape, generator=g) * std).cuda()
+    w = {"w_kv": normal((1, 2 * H * d, D), 0.02), "gru_w_ih": normal((3 * DP, D), D ** -0.5),
+         "gru_w_hh": normal((3 * DP, DP), DP ** -0.5), "gru_b_ih": normal((3 * DP,), 0.1), "gru_b_hh": normal((3 * DP,), 0.1),
+         "pos_w": normal((DP,), 1.0), "pos_b": normal((DP,), 0.1), "mlp_w1": normal((DP, DP), DP ** -0.5),
+         "mlp_b1": normal((DP,), 0.1), "out_w": normal((DP,), 0.3), "out_b": normal((1,), 0.1)}
+    pos_scale = 2.0 ** -12
+    job = Adore(make_config(layers=1, batch=batch, heads=H, head_dim=d, hidden=D, cache_slots=K, rebuild_budget=2,
+                            max_positions=S + T, ctrl_hidden=DP, dtype="f32", pos_scale=pos_scale), w, "cuda")
+    hidden, kv, out = normal((1, batch, S + T, D), 1.0), normal((1, batch, H, S, d), 1.0), normal((batch, H, d), 1.0)
+    qkv = [normal((T, batch, H, d), 1.0) for _ in range(3)]
+    scores, z = torch.zeros((batch, S + T), device="cuda"), torch.zeros((batch, DP), device="cuda")
+    job.init_cache(kv, kv, hidden, hidden[0, :, :S].contiguous(), None, S)
+    for t in range(T):
+        job.decode_step(*(a[t] for a in qkv), hidden[0], hidden[0, :, S + t].contiguous(), None, out, None)
+    job.get_state(scores=scores, z=z)
+    torch.cuda.synchronize()
+    want_scores, want_z = _reference(w, hidden[0], pos_scale)
+    # as over a prompt
+    assert (z.cpu().double() - want_z).abs().max() <= 4e-6
+    assert (scores.cpu().double() - want_scores).abs().max() <= 4e-6
     job.close()
