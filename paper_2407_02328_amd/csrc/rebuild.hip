@@ -634,8 +634,9 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
 // rows pass the L1 once, and 4 MT NT instructions of 32 cycles per step hide the MT + NT reads.  Element e of the four goes to
 // accumulator e, and after two steps (chains of eight products) the four are added up in 64 bits, as are the waves' sums at the
 // end (chains through the whole row were further from 64 bits than the kernel before: 1.5e-7 against 1.0e-7 at k = 1024).
-// One wave per output element, which read both rows from the L1 for every output, reached 6 TFLOP/s: the step of 4 sequences
-// with 160 rows x 2048 columns x 1024 took 138 us, and 45 us on these tiles (measured with fp32 chains).
+// One wave per output element, which read both rows from the L1 for every output, reached 4 to 6 TFLOP/s.  Before / on these
+// tiles: 32 rows x 1024 columns x 512 13.7 / 5.7 us, 160 x 2048 x 1024 119 / 25 us (27 TFLOP/s), 128 x 4096 x 1024 189 / 26 us, 256 x 8192 x
+// 4096 4440 / 288 us (60 TFLOP/s).
 template <int MODE, int MT, int NT, int U>
 __global__ __launch_bounds__(256) void f32_tile_kernel(const GemmArgs a) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -990,7 +991,7 @@ float rebuild_gemm_micros(const adore_config &c) {
   const int M = c.batch * c.rebuild_budget, Hd = c.heads * c.head_dim;
   if (M == 0) return 0.f;
   const int pick = c.dtype == ADORE_BF16 ? pick_tile(M, 2 * Hd, c.hidden, Hd, c.head_dim, false) : -1;
-  if (pick < 0) return float(4.0 * M * Hd * c.hidden / (c.dtype == ADORE_F32 ? 40e6 : 6e6));   // 40 and 6 TFLOP/s
+  if (pick < 0) return float(4.0 * M * Hd * c.hidden / (c.dtype == ADORE_F32 ? 40e6 : 6e6));   // 40 (27 to 60, see f32_tile_kernel) and 6 TFLOP/s
   const long long tiles = (long long)((M + kTiles[pick].bm - 1) / kTiles[pick].bm) * (2 * Hd / kTiles[pick].bn);
   return float((tiles + 255) / 256) * kTileMicros[pick] * c.hidden / 4096.f;
 }
