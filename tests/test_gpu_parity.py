@@ -1174,8 +1174,8 @@ def test_random_medium_configurations_with_rotary_embedding(name, kw, calls, ord
 @pytest.mark.parametrize("ordered", [True, False])
 def test_steps_on_one_stream_and_on_the_side_streams(streams, ordered, monkeypatch):
     """Where a job's steps are launched follows from its size (short ones, like those of most tests, keep to the caller's
-    stream); here both ways are forced on the same small jobs: whole-step calls mixed with the fine-grained ones, two
-    layers, rescoring, the forward, and a prompt of two chunks followed at once by steps and by a second job."""
+    stream); here both ways are forced on the same small jobs: whole-step calls mixed with the fine-grained ones, a prompt
+    of two chunks, two layers, rescoring and the forward."""
     monkeypatch.setenv("ADORE_STEP_STREAMS", streams)
     h = _harness()
     for w, whole in ((Workload("st_mix", **ORDER_W), lambda t: (t // 3) % 2 == 0),
@@ -1256,3 +1256,62 @@ def test_input_order_switched_between_free_running_steps(L, whole):
     inp = SyntheticInputs(w)
     steps = lambda t: ((t // 3) % 2 == 1 if t % 3 == 0 else None, whole)
     _same_runs(w, _free_running(h, w, inp, steps, 1, False), _free_running(h, w, inp, steps, 1, True))
+
+
+@pytest.mark.parametrize("S", [120, 1100])
+@pytest.mark.parametrize("whole", [True, False])
+def test_init_again_behind_free_running_steps_on_the_side_streams(S, whole, monkeypatch):
+    """adore_init_cache waits for the side streams on the GPU alone.  Three runs of one context, each an init (one chunk of
+    prompt, and three, which themselves use the side streams) and 13 steps that run ahead of the caller's stream,
+    enqueued without a synchronisation: every run has the bits of a context that waits before every call."""
+    monkeypatch.setenv("ADORE_STEP_STREAMS", "1")
+    h = _harness()
+    w = Workload("again", **dict(ORDER_W, S=S, T=13))
+    inp = SyntheticInputs(w)
+    steps = lambda t: (False if t == 0 else None, whole)
+    want = _free_running(h, w, inp, steps, 1, True)
+    got = _free_running(h, w, inp, steps, 3, False)
+    _same_runs(w, got, (want[0] * 3, want[1]))
+
+
+# Jobs as small as most tests' keep to one stream by themselves; these tests mean the side streams.
+SIDE = pytest.mark.parametrize("ordered", [True, False])
+
+
+@SIDE
+def test_init_again_restarts_the_context_on_the_side_streams(ordered, monkeypatch):
+    monkeypatch.setenv("ADORE_STEP_STREAMS", "1")
+    test_init_again_restarts_the_context(ordered)
+
+
+@SIDE
+def test_selections_as_kernels_of_their_own_on_the_side_streams(ordered, monkeypatch):
+    monkeypatch.setenv("ADORE_STEP_STREAMS", "1")
+    test_decode_step_call_with_the_selections_as_kernels_of_their_own("ADORE_NO_RIDE", ordered, monkeypatch)
+
+
+@SIDE
+def test_rescoring_and_the_callers_own_stream_on_the_side_streams(ordered, monkeypatch):
+    monkeypatch.setenv("ADORE_STEP_STREAMS", "1")
+    test_decode_step_call_with_the_rescoring_controller(ordered)
+    test_context_bound_to_a_stream_of_the_callers(ordered)
+
+
+@pytest.mark.parametrize("calls", ["whole", "fine", "mixed"])
+def test_inputs_complete_at_call_time_on_the_side_streams(calls, monkeypatch):
+    monkeypatch.setenv("ADORE_STEP_STREAMS", "1")
+    test_inputs_complete_at_call_time(calls)
+    if calls == "fine":
+        test_inputs_complete_at_call_time_two_layers_rescore_and_forward()
+
+
+@pytest.mark.parametrize("name,kw,calls,ordered", _random_workloads(64, 20240702)[::3])
+def test_random_small_configurations_on_the_side_streams(name, kw, calls, ordered, monkeypatch):
+    monkeypatch.setenv("ADORE_STEP_STREAMS", "1")
+    test_random_small_configurations(name, kw, calls, ordered)
+
+
+@pytest.mark.parametrize("name,kw", _random_rescore_workloads(6, 99))
+def test_random_small_configurations_rescore_on_the_side_streams(name, kw, monkeypatch):
+    monkeypatch.setenv("ADORE_STEP_STREAMS", "1")
+    test_random_small_configurations_rescore(name, kw)

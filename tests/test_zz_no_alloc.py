@@ -1,6 +1,5 @@
-"""The top-K attention entry point that allocates nothing (adore_topk_attention_static) against the one that
-takes a workspace: same bits, on two calls in a row, the second with a smaller input (so whatever the first call
-left in the library's fixed scratch array is still there when the second runs)."""
+"""The top-K attention entry point that takes no workspace and allocates nothing (adore_topk_attention_static) against the
+one that takes one: same bits, on two calls in a row, the second with a smaller input."""
 import ctypes
 
 import numpy as np
@@ -24,7 +23,7 @@ def test_static_scratch_entry_point_matches_the_workspace_entry_point():
     dev = "cuda:0"
     drawer = DeviceNormals(2407, dev)
     stream = torch.cuda.current_stream(dev).cuda_stream
-    # (rows, seq, head_dim, top_k): the first fills 60 MiB of the 64 MiB array, the second is smaller and ragged
+    # (rows, seq, head_dim, top_k): the first comes close to the size limit (60 of 64 MiB), the second is smaller and ragged
     for rows, S, d, top_k in [(240, 1000, 128, 96), (3, 333, 64, 48)]:
         q, k, v = (drawer.normal((rows, S, d), 1.0, torch.bfloat16) for _ in range(3))
         want = topk_attention(q, k, v, top_k)
@@ -49,9 +48,9 @@ def test_static_scratch_entry_point_rejects_what_exceeds_its_array():
     lib = load_library()
     dev = "cuda:0"
     stream = torch.cuda.current_stream(dev).cuda_stream
-    t = torch.zeros((1, 2049, 64), dtype=torch.bfloat16, device=dev)          # needs the quadratic row buffer
+    t = torch.zeros((1, 2049, 64), dtype=torch.bfloat16, device=dev)          # longer than it takes
     assert _raw_static_call(lib, t, t, t, torch.empty_like(t), 4, stream) == -4
-    t = torch.zeros((300, 1024, 128), dtype=torch.bfloat16, device=dev)        # 75 MiB transposed copy
+    t = torch.zeros((300, 1024, 128), dtype=torch.bfloat16, device=dev)        # 75 MiB by the limit's count
     assert _raw_static_call(lib, t, t, t, torch.empty_like(t), 4, stream) == -4
     t = torch.zeros((2, 16, 64), dtype=torch.bfloat16, device=dev)
     assert _raw_static_call(lib, t, t, t, torch.empty_like(t), 0, stream) == -1
