@@ -172,10 +172,10 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   };
   const int ld_row = tid / CPR;
   const uint32_t ld_col = uint32_t(tid % CPR) * 16u;
-  auto load_tile = [&](const bf16_t *src, int step, u32x4 (&r)[NLD]) {
+  auto load_tile = [&](const bf16_t *src, int step, u32x4 (&r)[NLD], int row) {   // row: ld_row
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-      const int key = min(step * kStep + ld_row + i * (NT / CPR), a.S - 1);
+      const int key = min(step * kStep + row + i * (NT / CPR), a.S - 1);
       r[i] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(src) + (uint32_t(key) * (DH * 2) + ld_col));
     }
   };
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       if constexpr (SAMPLE)
         load_sample(st, stride_fp, kr);
       else
-        load_tile(Kb, st, kr);
+        load_tile(Kb, st, kr, ld_row);
     };
     load(0);
     __syncthreads();                   // the tiles of the pass before are done with
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   if (crowded) {
     for (int st = 0; st < steps; ++st) {
       u32x4 kr[NLD];
-      load_tile(Kb, st, kr);
+      load_tile(Kb, st, kr, ld_row);
       __syncthreads();
       store_tile(0, kr);
       __syncthreads();
@@ -562,22 +562,24 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   for (int db = 0; db < DB; ++db) o[db] = f32x16{0.f};
   float lsum = 0.f;
   auto product = [&](auto by_ends_) {
+    int row = ld_row;
+    asm volatile("" : "+v"(row));   // its addresses are not kept from the sweeps on: 22 registers
     const float negmax = -image_weight(s_max[ql]) * a.scale_log2;
     const int tie = s_tie[ql];
     const int grp = lane >> 4, vrow = 4 * (grp >> 1) + ((lane & 15) >> 2), vcol = (grp & 1) * 16 + (lane & 3) * 4;
     // K is one step ahead of V: a step's products Q K^T run next to the exponentials of the step before
     constexpr int kV = 2 * Lds::kTile;
     u32x4 kr[NLD], vr[NLD];
-    load_tile(Kb, 0, kr);
+    load_tile(Kb, 0, kr, row);
     __syncthreads();
     store_tile(0, kr);
-    if (steps > 1) load_tile(Kb, 1, kr);
-    load_tile(Vb, 0, vr);
+    if (steps > 1) load_tile(Kb, 1, kr, row);
+    load_tile(Vb, 0, vr, row);
     __syncthreads();
     if (steps > 1) store_tile(Lds::kTile, kr);
     store_tile(kV, vr);
-    if (steps > 2) load_tile(Kb, 2, kr);
-    if (steps > 1) load_tile(Vb, 1, vr);
+    if (steps > 2) load_tile(Kb, 2, kr, row);
+    if (steps > 1) load_tile(Vb, 1, vr, row);
     f32x16 s = weights(0, nothing);
     int kb = kg * 32;
     if (kb + 31 > qfirst) hide(s, kb);
@@ -585,8 +587,8 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       __syncthreads();                         // tiles st of K and st - 1 of V are there
       if (st + 1 < steps) store_tile(((st + 1) & 1) * Lds::kTile, kr);
       if (st < steps) store_tile(kV + (st & 1) * Lds::kTile, vr);
-      if (st + 2 < steps) load_tile(Kb, st + 2, kr);
-      if (st + 1 < steps) load_tile(Vb, st + 1, vr);
+      if (st + 2 < steps) load_tile(Kb, st + 2, kr, row);
+      if (st + 1 < steps) load_tile(Vb, st + 1, vr, row);
       // P of two of the lane's weights, as two bf16 terms: the upper 16 bits, and the upper 16 bits of what is left (exact, >= 0)
       auto exponentials = [&](float x0, float x1, float z0, float z1, uint32_t &ph, uint32_t &pl) {
         const float p0 = z0 >= 1.f ? __builtin_amdgcn_exp2f(fmaf(x0, a.scale_log2, negmax)) : 0.f;
