@@ -38,9 +38,9 @@
 // Those are Gaussian weights, which mostly need one count.  512 rows of 1024 tokens with 60 % of the keys zeroed take 1250 us, with
 // whole-numbered q and k 1565 us (2190 and 1770 with ranges alone, which took 17 counts to close in on a zero and dropped keys
 // where the weights were below 1e-29); keys of widely different lengths 1209 us (1162), weights of 2^-100 1490 us.
-// What bounds it now: of a workgroup's 57000 cycles at 1024 tokens the vector units are busy with 26000 (two waves per SIMD), the matrix
-// units with 13000 (a 32x32x16 instruction keeps the vector unit from issuing for half of its 32 cycles), LDS with 17000; the rest
-// is waiting at barriers and for the first and last loads, one workgroup (241 registers, 142 KB of LDS) having a compute unit to itself.
+// What bounds it now: of a workgroup's 57000 cycles at 1024 tokens each SIMD issues vector instructions in 26800 and has matrix
+// work for 10200 (counters); a wave waits for 12400; one workgroup (252 registers, 143 KB of LDS) has a compute unit to itself, and
+// a second one would have to fit the registers as well as LDS.
 // Tried and not kept: thresholds from a sample and candidate lists in LDS instead of histograms (6.5 vector instructions per
 // weight and a selection of 20000 cycles per workgroup; 1080 us / 8800 us); a pass of its own for the weights of the bin (965 us /
 // 7700 us); the K operand of the next step fetched a step ahead (132 registers too many).
@@ -106,7 +106,7 @@ struct TopkLds {
   static constexpr int kMerge = 4 * NQB * (DH / 32) * 16 * 64 * 4;
   static constexpr int kFewAt = kBig > kMerge ? kBig : kMerge;
   static constexpr int kMisc = kFewAt + NQ * kFew * 8;
-  static constexpr int kBytes = kMisc + NQ * 28 * 4 + 16;
+  static constexpr int kBytes = kMisc + NQ * 28 * 4 + 32;
 };
 
 template <int DH, int NQB>
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   int *s_n = reinterpret_cast<int *>(s_max + NQ);              // [NQ] weights set aside
   float *s_l = reinterpret_cast<float *>(s_n + NQ);            // [4][NQ]
   uint32_t *s_part = reinterpret_cast<uint32_t *>(s_l + 4 * NQ);   // [8][NQ]
-  int *s_flag = reinterpret_cast<int *>(s_part + 8 * NQ);      // [0] count images again, [1] a crowded bin of equal weights, [2] count ranges again, [3] some queries need images counted
+  int *s_flag = reinterpret_cast<int *>(s_part + 8 * NQ);      // [0] count images again, [1] a crowded bin of equal weights, [2] count ranges again, [3] some queries need images counted, [4] huge weights
 
   // Workgroup -> (row, query block): all blocks of a row on one XCD (consecutive workgroups go to the 8 XCDs in turn), so
   // that its K and V come from memory once; within a row the blocks with the most keys first.
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   };
   // The query operand, through LDS like the keys: straight from memory its 16-byte pieces of 32 rows cost the L1 a look-up per
   // lane (4096 of them per workgroup, 3 us before the first product).
-  if (tid < 4) s_flag[tid] = 0;
+  if (tid < 5) s_flag[tid] = 0;
   bf16x8 qf[KT];
   {
     constexpr int NQL = NQ * CPR / NT;
@@ -381,6 +381,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
         top = fmaxf(fmaxf(top, fmaxf(w0, w1)), fmaxf(w2, w3));
       });
       __hip_atomic_fetch_max(&s_max[ql], weight_image(top), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (fabsf(top) * a.scale_log2 > 0x1p27f && top != -INFINITY) s_flag[4] = 1;   // (-infinity: no key of these was visible)
     } else {
       const uint32_t last = s_last[ql], span = last - s_first[ql];
       const int shift = image_shift(span);
@@ -493,8 +494,10 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     __syncthreads();
     if (!more) break;
   }
-  // Bins of images are told by their ends; in a workgroup with such queries the others' are as well.
-  const bool by_ends = __builtin_amdgcn_readfirstlane(s_flag[3]) != 0;
+  // Bins of images are told by their ends; in a workgroup with such queries the others' are as well.  The same variant takes
+  // workgroups with weights so large that w / sqrt(d) . log2 e, rounded for the largest one, is off by several units: elsewhere
+  // that is a common factor of a query's weights, there they would overflow or vanish.
+  const bool by_ends = __builtin_amdgcn_readfirstlane(s_flag[3] | s_flag[4]) != 0;
   if (by_ends) {
     if (tid < NQ && s_bin[tid] >= 0.f) {
       const float sa = s_ga[tid], sb = s_gb[tid], bin = s_bin[tid];
@@ -564,7 +567,8 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   auto product = [&](auto by_ends_) {
     int row = ld_row;
     asm volatile("" : "+v"(row));   // its addresses are not kept from the sweeps on: 22 registers
-    const float negmax = -image_weight(s_max[ql]) * a.scale_log2;
+    const float top = image_weight(s_max[ql]), negmax = -top * a.scale_log2;
+    auto exponent = [&](float x) { return decltype(by_ends_)::value ? (x - top) * a.scale_log2 : fmaf(x, a.scale_log2, negmax); };
     const int tie = s_tie[ql];
     const int grp = lane >> 4, vrow = 4 * (grp >> 1) + ((lane & 15) >> 2), vcol = (grp & 1) * 16 + (lane & 3) * 4;
     // K is one step ahead of V: a step's products Q K^T run next to the exponentials of the step before
@@ -591,8 +595,8 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       if (st + 1 < steps) load_tile(Vb, st + 1, vr, row);
       // P of two of the lane's weights, as two bf16 terms: the upper 16 bits, and the upper 16 bits of what is left (exact, >= 0)
       auto exponentials = [&](float x0, float x1, float z0, float z1, uint32_t &ph, uint32_t &pl) {
-        const float p0 = z0 >= 1.f ? __builtin_amdgcn_exp2f(fmaf(x0, a.scale_log2, negmax)) : 0.f;
-        const float p1 = z1 >= 1.f ? __builtin_amdgcn_exp2f(fmaf(x1, a.scale_log2, negmax)) : 0.f;
+        const float p0 = z0 >= 1.f ? __builtin_amdgcn_exp2f(exponent(x0)) : 0.f;
+        const float p1 = z1 >= 1.f ? __builtin_amdgcn_exp2f(exponent(x1)) : 0.f;
         lsum += p0 + p1;
         const uint32_t h0 = __float_as_uint(p0), h1 = __float_as_uint(p1);
         ph = __builtin_amdgcn_perm(h1, h0, 0x07060302u);   // (h0 >> 16) | (h1 & 0xffff0000)
@@ -689,7 +693,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     for (int e = 0; e < 2; ++e)
       if (sub + 8 * e < held) s_few[q * kFew + before[e]] = mine[e];
     wave_lds_fence();
-    const float negmax = -image_weight(s_max[q]) * a.scale_log2;
+    const float top = image_weight(s_max[q]), less = by_ends ? top : 0.f, negmax = by_ends ? 0.f : -top * a.scale_log2;
     const int stay = min(need, held);
     for (int j0 = 0; j0 < stay; j0 += 4) {     // four rows on their way at once
       u32x4 row[4][DH / 64];
@@ -697,7 +701,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const float2 v = s_few[q * kFew + min(j0 + j, stay - 1)];
-        p[j] = j0 + j < stay ? __builtin_amdgcn_exp2f(fmaf(v.x, a.scale_log2, negmax)) : 0.f;
+        p[j] = j0 + j < stay ? __builtin_amdgcn_exp2f(fmaf(v.x - less, a.scale_log2, negmax)) : 0.f;   // (as in the product)
         const bf16_t *src = Vb + size_t(__float_as_int(v.y)) * DH + sub * 8;
 #pragma unroll
         for (int e = 0; e < DH / 64; ++e) row[j][e] = *reinterpret_cast<const u32x4 *>(src + 64 * e);
