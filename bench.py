@@ -424,7 +424,8 @@ def prefill_line(w, args):
                      peak=MFMA_PEAK_TFLOPS["f32"], unit="TFLOP/s",
                      frac=round(cell_flops / (us["ctrl_cell"] * 1e-6) / 1e12 / MFMA_PEAK_TFLOPS["f32"], 5),
                      traffic=None, us_per_launch=round(us["ctrl_cell"], 1),
-                     note="a recurrence: one workgroup per sequence, so at most B of the 256 compute units work on it")
+                     note="a recurrence: one workgroup per sequence, so at most B of the 256 compute units work on it (with bf16 weights "
+                          "on the matrix cores, the state as three bf16 terms; priced as the fp32 product that is)")
     roof_in = dict(kernel="ctrl_input", bound="mfma", achieved=round(in_flops / (us["ctrl_input"] * 1e-6) / 1e12, 1),
                    peak=MFMA_PEAK_TFLOPS.get(w.dtype, 157.3), unit="TFLOP/s",
                    frac=round(in_flops / (us["ctrl_input"] * 1e-6) / 1e12 / MFMA_PEAK_TFLOPS.get(w.dtype, 157.3), 4),
@@ -473,12 +474,12 @@ def topk_line(w, args):
     # what the method has to compute: every weight of the causal triangle, and the kept probabilities times V
     kept = sum(min(i + 1, K) for i in range(S))
     flops = 2.0 * rows * d * (S * (S + 1) / 2 + kept)
-    roof = dict(kernel="topk_attention (transpose of V + attention)", bound="mfma",
+    roof = dict(kernel="topk_attention", bound="mfma",
                 achieved=round(flops / (us * 1e-6) / 1e12, 1), peak=MFMA_PEAK_TFLOPS["bf16"], unit="TFLOP/s",
                 frac=round(flops / (us * 1e-6) / 1e12 / MFMA_PEAK_TFLOPS["bf16"], 4),
                 traffic=(recorded_traffic(w, "topk_attention").get("topk_attention") if K == 96 else None),
                 us_per_launch=round(us, 1), algorithmic_flops=flops,
-                note="the selection (a four-pass radix select per query: LDS histograms, wave scans) runs beside the matrix work")
+                note="one kernel; the selection (every weight into a histogram per query in LDS, once or a few times) runs beside the matrix work")
     line = {
         "metric": "prompt tokens/sec through top-K attention (one layer)", "value": round(w.B * S / elapsed, 1),
         "unit": "tokens/s", "n_gpus": 1, "steps": reps, "warmup": warm, "ms_per_step": round(1e3 * elapsed, 4),

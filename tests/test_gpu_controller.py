@@ -77,9 +77,11 @@ def _check_prompt(batch, S, D, DP, H=2, K=24):
                                                    (3, 1537, 256, 12, 512, False), (2, 1100, 256, 2, 24, False),
                                                    (2, 1100, 256, 2, 24, True), (1, 700, 512, 2, 24, True)])
 def test_places_of_the_chunks_second_copy(batch, S, D, H, K, without, guards, monkeypatch):
+    import os
     from paper_2407_02328_amd import binding
     if guards:
         monkeypatch.setenv("ADORE_GUARD_WORDS", "1")
+    guards = os.environ.get("ADORE_GUARD_WORDS", "0") != "0"
     if without:
         lib = binding.load_library()
         second = max(512 * batch, 4096) * 3 * 128 * 4 + 512 * batch * 128 * 4 + (512 if guards else 0)
