@@ -27,23 +27,28 @@
 //   5 the rest  the weights set aside are ranked directly (equal ones by position), those that stay add their rows of V in fp32;
 //               the waves' partial sums are added through LDS in a fixed order, rounded once.
 //
-// A wave holds 32 queries and takes one 32-key block of each 128-key step (wave = key block x query block), so a step's K
+// A wave holds 32 queries and takes one 32-key block of each step of KB blocks (wave = key block x query block), so a step's K
 // (and V) rows are read once from the L2 per workgroup, coalesced, and each LDS operand serves 32 queries.  The products of
-// a step run next to the arithmetic on the weights of the step before.
+// a step run next to the arithmetic on the weights of the step before.  64 queries go with KB = 2, four waves and 79 KB of LDS, so
+// that two workgroups share a compute unit: one works where the other waits at a barrier, for its first tiles, or for the bins and the
+// rows of V of the weights set aside (a third of the time at 1024 tokens).  One workgroup of eight waves and KB = 4 per unit took 850
+// us for 512 rows of 1024 tokens and 6670 us for 128 rows of 8192.
 //
-// Measured (us per call, K = 96): 512 rows of 1024 tokens, d = 128: 1900 -> 870; 128 rows of 8192 tokens, d = 128:
-// 80900 -> 6760; 4 rows of 128 tokens, d = 64: 21.3 -> 10.9.  Before, 16 queries per workgroup kept their fp32 weights in LDS (in
+// Measured (us per call, K = 96): 512 rows of 1024 tokens, d = 128: 1900 -> 662; 128 rows of 8192 tokens, d = 128:
+// 80900 -> 5640; 4 rows of 128 tokens, d = 64: 21.3 -> 10.6.  At first, 16 queries per workgroup kept their fp32 weights in LDS (in
 // memory beyond 2048 tokens, read again by every pass of a radix select), with K and a transposed copy of V loaded straight
 // into the operand layout: 16 look-ups in the L1 per 256 bytes, K and V read from the L2 once per 16 queries.
-// Those are Gaussian weights, which mostly need one count.  512 rows of 1024 tokens with 60 % of the keys zeroed take 1250 us, with
-// whole-numbered q and k 1565 us (2190 and 1770 with ranges alone, which took 17 counts to close in on a zero and dropped keys
-// where the weights were below 1e-29); keys of widely different lengths 1209 us (1162), weights of 2^-100 1490 us.
-// What bounds it now: of a workgroup's 57000 cycles at 1024 tokens each SIMD issues vector instructions in 26800 and has matrix
-// work for 10200 (counters); a wave waits for 12400; one workgroup (252 registers, 143 KB of LDS) has a compute unit to itself, and
-// a second one would have to fit the registers as well as LDS.
+// Those are Gaussian weights, which mostly need one count.  512 rows of 1024 tokens with 60 % of the keys zeroed take 866 us, with
+// whole-numbered q and k 674 us (ranges alone would take 17 counts to close in on a zero).
+// What bounds it now, at 8192 tokens: a wave issues an instruction in 42 % of its cycles, waits for LDS or a barrier in 26 %, and for
+// the matrix unit or the other wave of its SIMD in 32 % (counters); a SIMD issues vector instructions in 50 % of the cycles and has
+// matrix work in 31 %; two waves a SIMD are what 253 registers leave room for.  The counts take 1.6 ms of the 5.6 (0.5 of them the K
+// tiles' way through LDS, 0.3 the histograms' additions), the products 3.3, the weights set aside 0.5.
 // Tried and not kept: thresholds from a sample and candidate lists in LDS instead of histograms (6.5 vector instructions per
 // weight and a selection of 20000 cycles per workgroup; 1080 us / 8800 us); a pass of its own for the weights of the bin (965 us /
-// 7700 us); the K operand of the next step fetched a step ahead (132 registers too many).
+// 7700 us); the K operand of the next step fetched a step ahead (132 registers too many); the bins' ends searched for in every
+// workgroup, so that the product compares instead of multiplying (the same, 10.6 -> 11.0 us for the smallest); the product's loop
+// unrolled by two like the counts' (78 registers spilled).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -63,10 +68,12 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kStep = 128;           // keys per step: four 32-key blocks
 constexpr int kBins = 128;           // bin 0: below the range, the last one: above it
 constexpr int kFew = 16;             // weights of a bin that are ranked directly
 constexpr int kSample = 128;         // keys of the sample: mean and deviation to a tenth of the deviation, for a range of two
+// A weight's bin is read off the bits of y = a w + b: with bin 0 at kBin0 = 2^23, where floats are the integers, and kBinWidth =
+// 2^8 units a bin, bits 8 .. 14 of y hold it (one multiply-add and a clamp, no conversion).
+constexpr float kBin0 = 8388608.f, kBinWidth = 256.f;
 constexpr int kRangeCounts = 3;      // most counts over ranges of weights; then at most ceil(32 / 7) over images
 
 // Order-preserving image of a weight (larger float <=> larger integer, never 0 for a number) and back.
@@ -97,22 +104,24 @@ struct TopkArgs {
 
 // Shared memory: two K tiles (one in use, one being written), then the histograms or two V tiles; the merge buffer overlays all of
 // it.  The weights set aside and the small arrays sit behind.
-template <int DH, int NQB>
+template <int DH, int NQB, int KB>
 struct TopkLds {
   static constexpr int NQ = 32 * NQB;
-  static constexpr int kTile = kStep * DH * 2;
+  static constexpr int kTile = 32 * KB * DH * 2;
   static constexpr int kHist = NQ * kBins * 4;
   static constexpr int kBig = 2 * kTile + (kHist > 2 * kTile ? kHist : 2 * kTile);
-  static constexpr int kMerge = 4 * NQB * (DH / 32) * 16 * 64 * 4;
+  static constexpr int kMerge = KB * NQB * (DH / 32) * 16 * 64 * 4;
   static constexpr int kFewAt = kBig > kMerge ? kBig : kMerge;
   static constexpr int kMisc = kFewAt + NQ * kFew * 8;
-  static constexpr int kBytes = kMisc + NQ * 28 * 4 + 32;
+  static constexpr int kBytes = kMisc + NQ * (16 + 3 * KB) * 4 + 32;
 };
 
-template <int DH, int NQB>
-__global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkArgs a) {
-  using Lds = TopkLds<DH, NQB>;
-  constexpr int NT = 256 * NQB, NQ = 32 * NQB;
+template <int DH, int NQB, int KB>
+__global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const TopkArgs a) {
+  using Lds = TopkLds<DH, NQB, KB>;
+  constexpr int NT = 64 * NQB * KB, NQ = 32 * NQB;
+  constexpr int kStep = 32 * KB;               // keys per step
+  constexpr int TPQ = NT / NQ, BPT = kBins / TPQ;   // threads per query and bins per thread where the histograms are read
   constexpr int CPR = DH / 8;                  // 16-byte chunks per row
   constexpr int NLD = kStep * CPR / NT;        // chunks of a tile per thread
   constexpr int KT = DH / 16, DB = DH / 32;
@@ -135,9 +144,9 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   int *s_tie = s_need + NQ;                                    // [NQ] crowded bin (-2 until it is known): its weights, all equal, stay up to this position
   uint32_t *s_max = reinterpret_cast<uint32_t *>(s_tie + NQ);  // [NQ] image of the largest weight
   int *s_n = reinterpret_cast<int *>(s_max + NQ);              // [NQ] weights set aside
-  float *s_l = reinterpret_cast<float *>(s_n + NQ);            // [4][NQ]
-  uint32_t *s_part = reinterpret_cast<uint32_t *>(s_l + 4 * NQ);   // [8][NQ]
-  int *s_flag = reinterpret_cast<int *>(s_part + 8 * NQ);      // [0] count images again, [1] a crowded bin of equal weights, [2] count ranges again, [3] some queries need images counted, [4] huge weights
+  float *s_l = reinterpret_cast<float *>(s_n + NQ);            // [KB][NQ]
+  uint32_t *s_part = reinterpret_cast<uint32_t *>(s_l + KB * NQ);   // [2 KB][NQ]
+  int *s_flag = reinterpret_cast<int *>(s_part + 2 * KB * NQ);      // [0] count images again, [1] a crowded bin of equal weights, [2] count ranges again, [3] some queries need images counted, [4] huge weights
 
   // Workgroup -> (row, query block): all blocks of a row on one XCD (consecutive workgroups go to the 8 XCDs in turn), so
   // that its K and V come from memory once; within a row the blocks with the most keys first.
@@ -259,14 +268,27 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     f32x16 s = weights(0, nothing);
     int kb = kg * 32;
     if (!SAMPLE && kb + 31 > qfirst) hide(s, kb);
-    for (int st = 1; st < steps; ++st) {
+    // tile 0 or 1: the one of step st, known when compiled, so that the tiles' places in LDS are too and the weights change hands
+    // without moves
+    auto one = [&](auto tile_, int st, const f32x16 &w, f32x16 &next) {
+      constexpr int kThis = decltype(tile_)::value * Lds::kTile, kOther = Lds::kTile - kThis;
       __syncthreads();                 // tile st is there, and nobody reads tile st - 1 any more
-      if (st + 1 < steps) store_tile(((st + 1) & 1) * Lds::kTile, kr);
+      if (st + 1 < steps) store_tile(kOther, kr);
       if (st + 2 < steps) load(st + 2);
-      const f32x16 w = s;
-      s = weights((st & 1) * Lds::kTile, [&](int g) { consume(w[4 * g], w[4 * g + 1], w[4 * g + 2], w[4 * g + 3], g, kb); });
+      next = weights(kThis, [&](int g) { consume(w[4 * g], w[4 * g + 1], w[4 * g + 2], w[4 * g + 3], g, kb); });
       kb += kStep;
-      if (!SAMPLE && kb + 31 > qfirst) hide(s, kb);
+      if (!SAMPLE && kb + 31 > qfirst) hide(next, kb);
+    };
+    int st = 1;
+    for (; st + 1 < steps; st += 2) {
+      f32x16 t;
+      one(std::integral_constant<int, 1>(), st, s, t);
+      one(std::integral_constant<int, 0>(), st + 1, t, s);
+    }
+    if (st < steps) {
+      f32x16 t;
+      one(std::integral_constant<int, 1>(), st, s, t);
+      s = t;
     }
 #pragma unroll
     for (int g = 0; g < 4; ++g) consume(s[4 * g], s[4 * g + 1], s[4 * g + 2], s[4 * g + 3], g, kb);
@@ -280,8 +302,8 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     const bool grid = hi > lo && sa < 1e30f && fmaxf(fabsf(lo), fabsf(hi)) * sa < 0x1p22f;
     s_lo[q] = lo;
     s_hi[q] = hi;
-    s_a[q] = grid ? sa : 0.f;
-    s_b[q] = grid ? fmaf(-lo, sa, 1.f) : 0.f;
+    s_a[q] = grid ? kBinWidth * sa : 0.f;
+    s_b[q] = grid ? fmaf(-lo, kBinWidth * sa, kBin0 + kBinWidth) : 0.f;
     s_flag[grid ? 2 : 3] = 1;
   };
 
@@ -303,15 +325,15 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     float *part = reinterpret_cast<float *>(s_part);
     if (h == 0) {
       part[kg * NQ + ql] = sum;
-      part[(4 + kg) * NQ + ql] = sq;
+      part[(KB + kg) * NQ + ql] = sq;
     }
     __syncthreads();
     if (tid < NQ) {
       float t0 = 0.f, t1 = 0.f;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < KB; ++g) {
         t0 += part[g * NQ + tid];
-        t1 += part[(4 + g) * NQ + tid];
+        t1 += part[(KB + g) * NQ + tid];
       }
       const int n = q0 + tid + 1;
       const float inv = 1.f / float(sampled ? kSample : min(n, a.S));
@@ -324,8 +346,8 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       s_first[tid] = open ? kLowest : 0u;
       s_last[tid] = open ? kHighest : 0u;
       s_over[tid] = 0u;
-      s_ga[tid] = 0.f;                            // unless a bin is found: 0 w + 1 - 0 >= 1, everything is above it
-      s_gb[tid] = 1.f;
+      s_ga[tid] = 0.f;                            // unless a bin is found: 0 w + 1 bin - 0 >= 1 bin, everything is above it
+      s_gb[tid] = kBinWidth;
       s_bin[tid] = 0.f;
       s_need[tid] = 0;
       s_tie[tid] = -1;
@@ -335,16 +357,17 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   }
 
   // ---- 2: the bin of the K-th largest weight ----
-  // Images of the smallest weights whose a w + b reaches `bin` and `bin` + 1 (rounding is monotone): searched for next to the
-  // points the line gives, both at once.
+  // Images of the smallest weights whose a w + b reaches `bin` and the next one (rounding is monotone): searched for within four
+  // units in the last place of the points the line gives, both at once.
   auto ends_of = [&](float sa, float sb, float bin, uint32_t (&from)[2]) {
     const float inv = __builtin_amdgcn_rcpf(sa);
     uint32_t below[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const float y = bin + float(i), at = (y - sb) * inv, slack = 0x1p-20f * fmaxf(fabsf(at), fabsf(sb * inv)) + 0x1p-17f * inv;
-      below[i] = weight_image(at - slack);
-      from[i] = weight_image(at + slack);
+      const float y = bin + float(i) * kBinWidth, d = y - sb - 0.5f, q = d * inv;   // (a w + b is rounded to a unit)
+      const uint32_t at = weight_image(fmaf(fmaf(-q, sa, d), inv, q));
+      below[i] = at - 4u;
+      from[i] = at + 4u;
       if (!(fmaf(image_weight(below[i]), sa, sb) < y)) below[i] = kLowest;
       if (!(fmaf(image_weight(from[i]), sa, sb) >= y)) from[i] = kHighest;
     }
@@ -352,7 +375,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const uint32_t mid = below[i] + ((from[i] - below[i]) >> 1);   // (`below` itself once the search is over)
-        const bool reached = fmaf(image_weight(mid), sa, sb) >= bin + float(i);
+        const bool reached = fmaf(image_weight(mid), sa, sb) >= bin + float(i) * kBinWidth;
         from[i] = reached ? mid : from[i];
         below[i] = reached ? below[i] : mid;
       }
@@ -375,10 +398,11 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
         const float w[4] = {w0, w1, w2, w3};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float y = __builtin_amdgcn_fmed3f(fmaf(w[i], sa, sb), 0.f, float(kBins - 1));
-          __hip_atomic_fetch_add(&s_hist[__float2uint_rz(y) * NQ + ql], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          const float y = __builtin_amdgcn_fmed3f(fmaf(w[i], sa, sb), kBin0, kBin0 + float(kBins - 1) * kBinWidth);
+          const uint32_t at = (__float_as_uint(y) & uint32_t(kBins - 1) << 8) / (256 / NQ) | uint32_t(ql);   // row y's bin of [kBins][NQ]
+          __hip_atomic_fetch_add(&s_hist[at], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          top = __builtin_amdgcn_fmed3f(top, w[i], INFINITY);   // the larger one, or the one that is a number
         }
-        top = fmaxf(fmaxf(top, fmaxf(w0, w1)), fmaxf(w2, w3));
       });
       __hip_atomic_fetch_max(&s_max[ql], weight_image(top), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       if (fabsf(top) * a.scale_log2 > 0x1p27f && top != -INFINITY) s_flag[4] = 1;   // (-infinity: no key of these was visible)
@@ -402,13 +426,13 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       __hip_atomic_fetch_max(&s_most[ql], most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __syncthreads();
-    // eight threads per query, 16 bins each
+    // TPQ threads per query, BPT bins each
     const int q = tid % NQ, grp = tid / NQ;
     const float sa = s_a[q];
-    uint32_t cnt[kBins / 8], mine = 0u;
+    uint32_t cnt[BPT], mine = 0u;
 #pragma unroll
-    for (int j = 0; j < kBins / 8; ++j) {
-      cnt[j] = s_hist[(grp * (kBins / 8) + j) * NQ + q];
+    for (int j = 0; j < BPT; ++j) {
+      cnt[j] = s_hist[(grp * BPT + j) * NQ + q];
       mine += cnt[j];
     }
     s_part[grp * NQ + q] = mine;
@@ -416,20 +440,20 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     uint32_t above = ranges ? 0u : s_over[q];
     __syncthreads();
 #pragma unroll
-    for (int g = 1; g < 8; ++g) above += g > grp ? s_part[g * NQ + q] : 0u;
+    for (int g = 1; g < TPQ; ++g) above += g > grp ? s_part[g * NQ + q] : 0u;
     const uint32_t want = uint32_t(a.topk);
     if (open && above < want && above + mine >= want) {   // this thread's bins hold it
       int bin = 0;
       uint32_t in = 0u, need = 0u, beside = 0u;
       bool found = false;
 #pragma unroll
-      for (int j = kBins / 8 - 1; j >= 0; --j) {
+      for (int j = BPT - 1; j >= 0; --j) {
         if (!found && above + cnt[j] >= want) {
           found = true;
-          bin = grp * (kBins / 8) + j;
+          bin = grp * BPT + j;
           need = want - above;
           in = cnt[j];
-          beside = (j > 0 ? cnt[j - 1] : 0u) + (j + 1 < kBins / 8 ? cnt[j + 1] : 0u);
+          beside = (j > 0 ? cnt[j - 1] : 0u) + (j + 1 < BPT ? cnt[j + 1] : 0u);
         }
         above += cnt[j];
       }
@@ -441,12 +465,12 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
         if (few && bin > 0 && bin < kBins - 1) {
           s_ga[q] = sa;
           s_gb[q] = sb;
-          s_bin[q] = float(bin);
+          s_bin[q] = kBin0 + kBinWidth * float(bin);
           s_need[q] = int(need);
           s_first[q] = s_last[q] = 0u;
         } else {
           uint32_t end[2];
-          ends_of(sa, sb, float(bin), end);
+          ends_of(sa, sb, kBin0 + kBinWidth * float(bin), end);
           if (bin > 0) s_first[q] = max(s_first[q], end[0]);
           if (bin < kBins - 1 && end[1] <= s_last[q]) {
             s_last[q] = end[1] - 1u;
@@ -494,15 +518,16 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     __syncthreads();
     if (!more) break;
   }
-  // Bins of images are told by their ends; in a workgroup with such queries the others' are as well.  The same variant takes
-  // workgroups with weights so large that w / sqrt(d) . log2 e, rounded for the largest one, is off by several units: elsewhere
-  // that is a common factor of a query's weights, there they would overflow or vanish.
-  const bool by_ends = __builtin_amdgcn_readfirstlane(s_flag[3] | s_flag[4]) != 0;
-  if (by_ends) {
+  // Bins of images are told by their ends (weights >= s_gb are above, those >= s_ga and not above inside); in a workgroup with such
+  // queries the others' are as well.  The same variant takes workgroups with weights so large that w / sqrt(d) . log2 e, rounded for
+  // the largest one, is off by several units: elsewhere that is a common factor of a query's weights, there they would overflow or
+  // vanish.
+  const bool by_images = __builtin_amdgcn_readfirstlane(s_flag[3] | s_flag[4]) != 0;
+  if (by_images) {
     if (tid < NQ && s_bin[tid] >= 0.f) {
-      const float sa = s_ga[tid], sb = s_gb[tid], bin = s_bin[tid];
-      uint32_t end[2] = {kHighest, kLowest};
-      if (bin > 0.f) ends_of(sa, sb, bin, end);
+      const float bin = s_bin[tid];
+      uint32_t end[2] = {kHighest, kLowest};     // no bin was looked for: all weights are above it
+      if (bin > 0.f) ends_of(s_ga[tid], s_gb[tid], bin, end);
       s_ga[tid] = image_weight(end[0]);
       s_gb[tid] = image_weight(end[1]);
     }
@@ -510,16 +535,8 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
   }
 
   // ---- 3: the position up to which the weights of a bin stay that holds many equal ones ----
-  const float ga = s_ga[ql], gb = s_gb[ql], bin = s_bin[ql];
-  // where a weight stands to its query's bin: >= 1 above it, in [0, 1) inside it, else below (exact: rounding is monotone,
-  // and the difference is exact inside the bin), and so for the NaN of keys the query does not see
-  auto place = [&](auto by_ends_, float w) {
-    if constexpr (decltype(by_ends_)::value)
-      return w >= gb ? 1.f : w >= ga ? 0.f : -1.f;
-    else
-      return fmaf(w, ga, gb) - bin;
-  };
-  auto inside = [](float z) { return __float_as_uint(z) < 0x3f800000u; };
+  const float from = s_ga[ql], above = s_gb[ql], bin = s_bin[ql];   // the ends of the bin, or a, b and the bin
+  auto inside = [&](float w) { return bool((w >= from) & !(w >= above)); };   // (false for the NaN of a hidden key)
   const bool crowded = s_flag[1] != 0;
   if (crowded) {
     for (int st = 0; st < steps; ++st) {
@@ -533,13 +550,13 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       f32x16 s = weights(0, nothing);
       if (kb + 31 > qfirst) hide(s, kb);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) mask |= inside(place(std::true_type(), s[i])) ? 1u << i : 0u;
+      for (int i = 0; i < 16; ++i) mask |= inside(s[i]) ? 1u << i : 0u;
       s_part[(kg * 2 + h) * NQ + ql] = mask;
       __syncthreads();
       if (tid < NQ && s_tie[tid] == -2) {
         int need = s_need[tid];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
+        for (int b = 0; b < KB; ++b) {
           const uint32_t m0 = s_part[2 * b * NQ + tid], m1 = s_part[(2 * b + 1) * NQ + tid];
           uint32_t pm = 0u;   // the block's 32 keys in order
 #pragma unroll
@@ -564,13 +581,20 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
 #pragma unroll
   for (int db = 0; db < DB; ++db) o[db] = f32x16{0.f};
   float lsum = 0.f;
-  auto product = [&](auto by_ends_) {
+  auto product = [&](auto by_images_) {
+    constexpr bool IMAGES = decltype(by_images_)::value;
     int row = ld_row;
     asm volatile("" : "+v"(row));   // its addresses are not kept from the sweeps on: 22 registers
     const float top = image_weight(s_max[ql]), negmax = -top * a.scale_log2;
-    auto exponent = [&](float x) { return decltype(by_ends_)::value ? (x - top) * a.scale_log2 : fmaf(x, a.scale_log2, negmax); };
+    auto exponent = [&](float x) { return IMAGES ? (x - top) * a.scale_log2 : fmaf(x, a.scale_log2, negmax); };
     const int tie = s_tie[ql];
     const int grp = lane >> 4, vrow = 4 * (grp >> 1) + ((lane & 15) >> 2), vcol = (grp & 1) * 16 + (lane & 3) * 4;
+    int vat[DB][2];                            // where the lane reads V^T in a tile: block of 32 head dimensions, half of 16 keys
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int e4 = 0; e4 < 2; ++e4)
+        vat[db][e4] = chunk_at(kg * 32 + 8 * e4 + vrow, (db * 32 + vcol) >> 3) + (vcol & 4) * 2;
     // K is one step ahead of V: a step's products Q K^T run next to the exponentials of the step before
     constexpr int kV = 2 * Lds::kTile;
     u32x4 kr[NLD], vr[NLD];
@@ -587,16 +611,21 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     f32x16 s = weights(0, nothing);
     int kb = kg * 32;
     if (kb + 31 > qfirst) hide(s, kb);
-    for (int st = 1; st <= steps; ++st) {
+    // The weights w of step st - 1 into the result, and those of step st into next (unless LAST: no such step).
+    auto one = [&](auto last_, int st, const f32x16 &w, f32x16 &next) {
+      constexpr bool LAST = decltype(last_)::value;
+      const int tile = (st & 1) * Lds::kTile, other = Lds::kTile - tile;
       __syncthreads();                         // tiles st of K and st - 1 of V are there
-      if (st + 1 < steps) store_tile(((st + 1) & 1) * Lds::kTile, kr);
-      if (st < steps) store_tile(kV + (st & 1) * Lds::kTile, vr);
-      if (st + 2 < steps) load_tile(Kb, st + 2, kr, row);
-      if (st + 1 < steps) load_tile(Vb, st + 1, vr, row);
+      if constexpr (!LAST) {
+        if (st + 1 < steps) store_tile(other, kr);
+        store_tile(kV + tile, vr);
+        if (st + 2 < steps) load_tile(Kb, st + 2, kr, row);
+        if (st + 1 < steps) load_tile(Vb, st + 1, vr, row);
+      }
       // P of two of the lane's weights, as two bf16 terms: the upper 16 bits, and the upper 16 bits of what is left (exact, >= 0)
-      auto exponentials = [&](float x0, float x1, float z0, float z1, uint32_t &ph, uint32_t &pl) {
-        const float p0 = z0 >= 1.f ? __builtin_amdgcn_exp2f(exponent(x0)) : 0.f;
-        const float p1 = z1 >= 1.f ? __builtin_amdgcn_exp2f(exponent(x1)) : 0.f;
+      auto exponentials = [&](float x0, float x1, bool stays0, bool stays1, uint32_t &ph, uint32_t &pl) {
+        const float p0 = stays0 ? __builtin_amdgcn_exp2f(exponent(x0)) : 0.f;
+        const float p1 = stays1 ? __builtin_amdgcn_exp2f(exponent(x1)) : 0.f;
         lsum += p0 + p1;
         const uint32_t h0 = __float_as_uint(p0), h1 = __float_as_uint(p1);
         ph = __builtin_amdgcn_perm(h1, h0, 0x07060302u);   // (h0 >> 16) | (h1 & 0xffff0000)
@@ -605,7 +634,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
         asm volatile("" : "+v"(ph), "+v"(pl));   // done here, between the matrix instructions
       };
       // V^T operand: head dimensions db * 32 + c; element e of lane half h is key 16 ks + 8 (e / 4) + 4 h + e % 4
-      const int vt = kV + ((st - 1) & 1) * Lds::kTile;
+      const int vt = kV + other;
       union Operand {
         s16x4 q[2];
         bf16x8 v;
@@ -614,8 +643,7 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
       auto read_v = [&](int ks, int db) {
 #pragma unroll
         for (int e4 = 0; e4 < 2; ++e4) {
-          const int r = kg * 32 + 16 * ks + 8 * e4 + vrow, col = db * 32 + vcol;
-          const uint32_t at = vt + chunk_at(r, col >> 3) + (col & 4) * 2;
+          const int at = vat[db][e4] + vt + ks * (16 * DH * 2);
           vo[db].q[e4] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(smem + at));
         }
       };
@@ -624,41 +652,71 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vo[db].v, *reinterpret_cast<const bf16x8 *>(&pl), o[db], 0, 0, 0);
         asm volatile("" : "+v"(o[db]));
       };
-      const f32x16 w = s;
       uint32_t ph[8], pl[8];
-      s = weights((st & 1) * Lds::kTile, [&](int g) {   // (the last time nothing comes of it)
-        float z[4];
+      auto share = [&](int g) {
+        bool stays[4], in[4], any;
+        if constexpr (IMAGES) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) z[i] = place(by_ends_, w[4 * g + i]);
-        if (min(min(__float_as_uint(z[0]), __float_as_uint(z[1])), min(__float_as_uint(z[2]), __float_as_uint(z[3]))) < 0x3f800000u) {
+          for (int i = 0; i < 4; ++i) {
+            stays[i] = w[4 * g + i] >= above;
+            in[i] = inside(w[4 * g + i]);
+          }
+          any = in[0] | in[1] | in[2] | in[3];
+        } else {
+          // >= kBinWidth above the bin, in [0, kBinWidth) inside it, else below (exact: rounding is monotone, and the difference is
+          // exact inside the bin), and so for the NaN of a hidden key
+          constexpr uint32_t kOutside = 0x43800000u;   // bits of kBinWidth
+          uint32_t z[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (inside(z[i])) {
-              const int pos = kb + 8 * g + 4 * h + i;
-              if (decltype(by_ends_)::value && crowded && tie >= 0) {
-                if (pos <= tie) z[i] = 1.f;    // stays
-              } else {
-                const int at = __hip_atomic_fetch_add(&s_n[ql], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (at < kFew) s_few[ql * kFew + at] = float2{w[4 * g + i], __int_as_float(pos)};
-              }
-            }
+          for (int i = 0; i < 4; ++i) {
+            const float d = fmaf(w[4 * g + i], from, above) - bin;
+            stays[i] = d >= kBinWidth;
+            z[i] = __float_as_uint(d);
+            in[i] = z[i] < kOutside;
+          }
+          any = min(min(z[0], z[1]), min(z[2], z[3])) < kOutside;
         }
-        exponentials(w[4 * g], w[4 * g + 1], z[0], z[1], ph[2 * g], pl[2 * g]);
-        exponentials(w[4 * g + 2], w[4 * g + 3], z[2], z[3], ph[2 * g + 1], pl[2 * g + 1]);
+        if (any) {
+          if (IMAGES && crowded && tie >= 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) stays[i] |= in[i] & (kb + 8 * g + 4 * h + i <= tie);
+          } else {
+            int at = __hip_atomic_fetch_add(&s_n[ql], int(in[0]) + int(in[1]) + int(in[2]) + int(in[3]), __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (in[i] && at < kFew) s_few[ql * kFew + at++] = float2{w[4 * g + i], __int_as_float(kb + 8 * g + 4 * h + i)};
+          }
+        }
+        exponentials(w[4 * g], w[4 * g + 1], stays[0], stays[1], ph[2 * g], pl[2 * g]);
+        exponentials(w[4 * g + 2], w[4 * g + 3], stays[2], stays[3], ph[2 * g + 1], pl[2 * g + 1]);
         if (g >= 4 - DB) read_v(0, g - 4 + DB);
-      });
+      };
+      if constexpr (LAST) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) share(g);
+      } else {
+        next = weights(tile, share);
+      }
 #pragma unroll
       for (int g = 0; g < DB; ++g) {
         add_product(g, u32x4{ph[0], ph[1], ph[2], ph[3]}, u32x4{pl[0], pl[1], pl[2], pl[3]});
         read_v(1, g);
+        __builtin_amdgcn_sched_barrier(0);     // each read of the second half under the products of the first
       }
 #pragma unroll
       for (int g = 0; g < DB; ++g) add_product(g, u32x4{ph[4], ph[5], ph[6], ph[7]}, u32x4{pl[4], pl[5], pl[6], pl[7]});
       kb += kStep;
-      if (kb + 31 > qfirst) hide(s, kb);
+      if (!LAST && kb + 31 > qfirst) hide(next, kb);
+    };
+    int st = 1;
+    for (; st < steps; ++st) {
+      const f32x16 w = s;
+      one(std::false_type(), st, w, s);
     }
+    one(std::true_type(), st, s, s);
   };
-  if (by_ends)
+  if (by_images)
     product(std::true_type());
   else
     product(std::false_type());
@@ -673,30 +731,31 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       s_mrg[((wave * DB + db) * 4 + j) * 64 + (lane ^ ((db * 4 + j) & 7))] = f32x4{o[db][4 * j], o[db][4 * j + 1], o[db][4 * j + 2], o[db][4 * j + 3]};
-  // Eight threads per query: each ranks two of the weights and notes the ones that stay; then each adds an eighth of their rows
-  // of V, in fp32.
-  const int q = tid / 8, sub = tid & 7, held = min(s_n[q], kFew), need = s_need[q];
-  float extra[DH / 8] = {0.f}, extra_l = 0.f;
+  // TPQ threads per query: each ranks its share of the weights and notes the ones that stay; then each adds its share of their rows
+  // of V, 16-byte chunks sub, sub + TPQ, .., in fp32.
+  constexpr int RPT = kFew / TPQ, CPT = CPR / TPQ;   // weights and chunks per thread
+  const int q = tid / TPQ, sub = tid % TPQ, held = min(s_n[q], kFew), need = s_need[q];
+  float extra[8 * CPT] = {0.f}, extra_l = 0.f;
   if (held > 0) {
-    float2 mine[2];
-    int before[2] = {0, 0};
+    float2 mine[RPT];
+    int before[RPT] = {0};
 #pragma unroll
-    for (int e = 0; e < 2; ++e) mine[e] = s_few[q * kFew + sub + 8 * e];
+    for (int e = 0; e < RPT; ++e) mine[e] = s_few[q * kFew + sub + TPQ * e];
     for (int j = 0; j < held; ++j) {
       const float2 v = s_few[q * kFew + j];
 #pragma unroll
-      for (int e = 0; e < 2; ++e) before[e] += v.x > mine[e].x || (v.x == mine[e].x && __float_as_int(v.y) < __float_as_int(mine[e].y)) ? 1 : 0;
+      for (int e = 0; e < RPT; ++e) before[e] += v.x > mine[e].x || (v.x == mine[e].x && __float_as_int(v.y) < __float_as_int(mine[e].y)) ? 1 : 0;
     }
     // in the order of their rank, so that the sum does not hang on the order they were set aside in
     wave_lds_fence();
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
-      if (sub + 8 * e < held) s_few[q * kFew + before[e]] = mine[e];
+    for (int e = 0; e < RPT; ++e)
+      if (sub + TPQ * e < held) s_few[q * kFew + before[e]] = mine[e];
     wave_lds_fence();
-    const float top = image_weight(s_max[q]), less = by_ends ? top : 0.f, negmax = by_ends ? 0.f : -top * a.scale_log2;
+    const float top = image_weight(s_max[q]), less = by_images ? top : 0.f, negmax = by_images ? 0.f : -top * a.scale_log2;
     const int stay = min(need, held);
     for (int j0 = 0; j0 < stay; j0 += 4) {     // four rows on their way at once
-      u32x4 row[4][DH / 64];
+      u32x4 row[4][CPT];
       float p[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -704,13 +763,13 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
         p[j] = j0 + j < stay ? __builtin_amdgcn_exp2f(fmaf(v.x - less, a.scale_log2, negmax)) : 0.f;   // (as in the product)
         const bf16_t *src = Vb + size_t(__float_as_int(v.y)) * DH + sub * 8;
 #pragma unroll
-        for (int e = 0; e < DH / 64; ++e) row[j][e] = *reinterpret_cast<const u32x4 *>(src + 64 * e);
+        for (int e = 0; e < CPT; ++e) row[j][e] = *reinterpret_cast<const u32x4 *>(src + 8 * TPQ * e);
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         extra_l += p[j];
 #pragma unroll
-        for (int e = 0; e < DH / 64; ++e)
+        for (int e = 0; e < CPT; ++e)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             extra[8 * e + 2 * i] = fmaf(p[j], __uint_as_float(row[j][e][i] << 16), extra[8 * e + 2 * i]);
@@ -720,22 +779,22 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
     }
   }
   __syncthreads();
-  // The same thread finishes its eighth of the query's row: head dimension d sits at block d / 32, element 4 ((d / 8) % 4) + d % 4 of the
-  // lane half (d / 4) % 2.
+  // The same thread finishes its chunks of the query's row: chunk ch, head dimensions 8 ch + d, sits at block ch / 4, element
+  // 4 (ch % 4) + d % 4 of the lane half d / 4.
   float l = extra_l;
 #pragma unroll
-  for (int g = 0; g < 4; ++g) l += s_l[g * NQ + q];
+  for (int g = 0; g < KB; ++g) l += s_l[g * NQ + q];
   const float inv = l > 0.f ? 1.f / l : 0.f;
   if (q0 + q < a.S) {
 #pragma unroll
-    for (int e = 0; e < DH / 64; ++e) {        // eight head dimensions from 64 e + 8 sub on
-      const int db = 2 * e + sub / 4, j = sub % 4;
+    for (int e = 0; e < CPT; ++e) {
+      const int ch = TPQ * e + sub, db = ch / 4, j = ch % 4;
       uint32_t r[8];
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         f32x4 sum = f32x4{extra[8 * e + 4 * half], extra[8 * e + 4 * half + 1], extra[8 * e + 4 * half + 2], extra[8 * e + 4 * half + 3]};
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < KB; ++g) {
           const f32x4 v = s_mrg[(((g * NQB + q / 32) * DB + db) * 4 + j) * 64 + ((half * 32 + (q & 31)) ^ ((db * 4 + j) & 7))];
 #pragma unroll
           for (int i = 0; i < 4; ++i) sum[i] += v[i];
@@ -743,26 +802,26 @@ __global__ __launch_bounds__(256 * NQB, NQB) void topk_attend_kernel(const TopkA
 #pragma unroll
         for (int i = 0; i < 4; ++i) r[4 * half + i] = f32_to_bf16_rne(sum[i] * inv);
       }
-      *reinterpret_cast<u32x4 *>(a.O + base + size_t(q0 + q) * DH + 64 * e + 8 * sub) =
+      *reinterpret_cast<u32x4 *>(a.O + base + size_t(q0 + q) * DH + 8 * ch) =
           u32x4{r[0] | (r[1] << 16), r[2] | (r[3] << 16), r[4] | (r[5] << 16), r[6] | (r[7] << 16)};
     }
   }
 }
 
-template <int DH, int NQB>
+template <int DH, int NQB, int KB>
 hipError_t launch(TopkArgs a, hipStream_t st) {
-  constexpr int lds = TopkLds<DH, NQB>::kBytes;
+  constexpr int lds = TopkLds<DH, NQB, KB>::kBytes, threads = 64 * NQB * KB;
   static_assert(lds <= 160 * 1024, "shared memory of a compute unit");
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&topk_attend_kernel<DH, NQB>),
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&topk_attend_kernel<DH, NQB, KB>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
   // A launch holds fewer than 2^32 threads: whole groups of eight rows (one per XCD) at a time where there are more
   // (from 8193 tokens on, at 65535 rows).
   const int blocks = (a.S + 32 * NQB - 1) / (32 * NQB), rows = a.rows;
-  const int most = int(0xffffffffu / (256u * NQB * unsigned(blocks)) / 8u * 8u);
+  const int most = int(0xffffffffu / (unsigned(threads) * unsigned(blocks)) / 8u * 8u);
   for (int r0 = 0; r0 < rows; r0 += most) {
     a.rows = rows - r0 < most ? rows - r0 : most;
-    hipLaunchKernelGGL((topk_attend_kernel<DH, NQB>), dim3(unsigned(a.rows) * unsigned(blocks)), dim3(256 * NQB), lds, st, a);
+    hipLaunchKernelGGL((topk_attend_kernel<DH, NQB, KB>), dim3(unsigned(a.rows) * unsigned(blocks)), dim3(threads), lds, st, a);
     const size_t done = size_t(a.rows) * a.S * DH;
     a.Q += done;
     a.K += done;
@@ -775,8 +834,11 @@ hipError_t launch(TopkArgs a, hipStream_t st) {
 constexpr int kMaxStaticSeq = 2048;  // longest sequence adore_topk_attention_static takes
 constexpr int kMaxSeq = 32768;       // longest sequence taken at all
 
-// The launch of both entry points.  64 queries per workgroup read K and V half as often; 32 where that leaves compute units
-// without one (two workgroups of 64 queries per unit keep the tail of a launch short).
+// The launch of both entry points.  64 queries per workgroup read K and V half as often, and two such workgroups share a compute unit;
+// 32 where that leaves units without one.  At d = 128 a workgroup of 32 has a unit to itself, so that more than 256 of them take a
+// second round (us, 32 / 64 queries: 8 rows of 1024 tokens, 128 workgroups of 64, 47 / 48; 8 of 2048, 256 of them, 107 / 111; 4 of 4096, 256,
+// 258 / 139; 20 of 1024, 320, 104 / 60; 33 of 777, 429, 104 / 45); at d = 64 two of them fit (16 of 512, 128, 19.8 / 24.7; 24 of 1024, 384, 44.3 /
+// 46.2; 40 of 500, 320, 30.1 / 28.3).
 int enqueue_topk(const void *q, const void *k, const void *v, void *out, int rows, int seq, int head_dim, int top_k,
                  hipStream_t st) {
   TopkArgs a;
@@ -789,10 +851,10 @@ int enqueue_topk(const void *q, const void *k, const void *v, void *out, int row
   a.topk = top_k;
   a.scale_log2 = 1.4426950408889634f / sqrtf(float(head_dim));
   hipError_t e;
-  if (rows * ((seq + 63) / 64) < 512)
-    e = head_dim == 128 ? launch<128, 1>(a, st) : launch<64, 1>(a, st);
+  if (rows * ((seq + 63) / 64) < (head_dim == 128 ? 256 : 512))
+    e = head_dim == 128 ? launch<128, 1, 4>(a, st) : launch<64, 1, 4>(a, st);
   else
-    e = head_dim == 128 ? launch<128, 2>(a, st) : launch<64, 2>(a, st);
+    e = head_dim == 128 ? launch<128, 2, 2>(a, st) : launch<64, 2, 2>(a, st);
   return e == hipSuccess ? ADORE_OK : ADORE_E_HIP;
 }
 

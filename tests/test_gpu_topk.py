@@ -206,7 +206,8 @@ def test_topk_attention_at_the_long_context_shape_sampled_rows():
     (1, 1, 64, 1, 0), (2, 31, 64, 8, 0), (1, 33, 128, 32, 0), (2, 129, 64, 17, 0),   # query blocks of 32, key steps of 128
     (1, 161, 128, 40, 0),        # the last query block samples its keys, the ones before it see all of them
     (1, 257, 64, 256, 0), (1, 320, 128, 400, 0),                                      # top_k at and beyond the sequence
-    (512, 40, 64, 12, 0), (260, 65, 128, 20, 0),                                      # query blocks of 64
+    (512, 40, 64, 12, 0), (260, 65, 128, 20, 0),                                      # query blocks of 64, key steps of 64
+    (512, 64, 128, 63, 0), (176, 129, 128, 40, 0), (128, 193, 64, 50, 0), (56, 577, 128, 96, 0), (104, 300, 64, 30, 250),
     (1, 300, 128, 50, 300), (2, 200, 64, 30, 60),   # (runs of) identical keys: more equal weights than are ranked directly
 ])
 def test_topk_attention_at_the_edges_of_its_blocks(rows, S, d, top_k, same):
