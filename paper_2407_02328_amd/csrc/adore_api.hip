@@ -32,6 +32,7 @@
 #include <new>
 
 #include "adore_internal.h"
+#include "ctrl_device.h"
 
 using namespace adore;
 
@@ -246,39 +247,52 @@ int ensure_side_stream(adore_ctx *ctx) {
 
 // Whether every launch of a job's steps goes to the caller's stream, in order.  What the side streams hide (the controller's
 // two launches, 10 to 20 us, and where they do not ride in the attention launch the two selections, 15 to 40 us) is bought
-// with cross-stream events: two or three a step, which hold an overlapped step with ordered inputs at 40 to 55 us however little
-// it does, and one a step that waits for nothing recent where the selections ride and the inputs are known ahead.
+// with cross-stream events: two or three a step, which hold an overlapped step with ordered inputs at 36 to 55 us however little
+// it does, and one a step that waits for nothing recent where the selections ride and the inputs are known ahead.  On one stream the
+// riding step carries its controller inside its other launches (StepCtrl): two launches in all, three with rescoring.
 // Measured per step, one stream against the side streams (attention + projection by the estimate):
-//   ordered inputs, selections riding: 1 sequence of 4 heads of 64 (1.6 us) 24 / 42 us, 8 of 16 heads of 128 (16 us) 39 / 45, 16 of
-//     16 (19 us) 37 / 42, 32 of 8 (23 us) 38 / 40, 4 of 32 (28 us) 48 / 47, 1 of 24 behind 2000 tokens (21 us) 58 / 54, 8 of 32 (53 us) 55 / 51;
+//   riding, ordered inputs: 1 sequence of 4 heads of 64 (1.6 us) 18 / 37 us, 8 of 12 (5.9 us) 21 / 37, 16 of 8 heads of 128 (13 us) 26 / 37,
+//     8 of 16 (27 us) 30 / 42, 32 of 8 (24 us) 33 / 39, 4 of 32 (28 us) 39 / 51, 16 of 16 (34 us) 40 / 44, 12 of 24 (46 us) 47 / 55,
+//     8 of 32 (53 us) 53 / 55, but 32 of 16 (47 us) 60 / 57, 24 of 24 (85 us) 89 / 86, 16 of 32 (68 us) 76 / 73;
+//   riding, inputs known ahead: 18 / 29, 21 / 29, 26 / 30, 29 / 36, 33 / 33, 40 / 46, 39 / 38, 47 / 50, 53 / 49, 60 / 55, 89 / 81, 76 / 71;
+//   riding with rescoring, against selections as launches of their own on the side streams: 21 / 67, 25 / 63, 30 / 58, 33 / 59, 38 / 56, 42 / 72,
+//     43 / 64, 50 / 74, 56 / 76, 65 / 75, 93 / 98, 80 / 91 (about 12 us less on the side streams where the inputs are known ahead);
+//   in fp32, either order: 1 of 4 heads 20 / 39 and 34, 4 of 8 heads of 128 (17 us) 30 / 46 and 41, 4 of 16 (33 us) 39 / 55 and 47;
 //   selections as launches of their own, ordered inputs or not: 8 of 16 heads (16 us) 48 / 78 and 48 / 66, 4 of 32 (28 us) 56 / 78 and
-//     56 / 63, with rescoring 51 / 78 and 51 / 66; 1 of 4 heads behind 5000, 16000 and 40000 tokens 31 / 76, 42 / 76, 67 / 80 and 31 / 59, 42 / 58, 66 / 57;
-//   riding, inputs known ahead: 1 of 4 heads (1.6 us) 24 / 25 to 25 / 28, 3 of 12 (5.1 us) 29 / 27 to 29.5 / 30.5, but 8 of 12 (5.9 us) 32 / 27, 16 of 8
-//     (7.9 us) 32 / 27 to 32 / 30, 8 of 16 (16 us) 39 / 30.
-// In fp32, whose controller reads twice the bytes: ordered 2 of 16 heads (7.5 us) 39 / 43, 3 of 16 (11 us) 44 / 42; known ahead 1 of 4
-// (0.1 us) 24.8 / 25.0, 2 of 8 (1.0 us) 31 / 27.
-// So: one stream where the two come to less than kOneStreamMicros, half of it in fp32; kOneStreamReadyMicros, an eighth of it in fp32,
-// for riding selections with inputs known ahead.
+//     56 / 63; 1 of 4 heads behind 5000, 16000 and 40000 tokens 31 / 76, 42 / 76, 67 / 80 and 31 / 59, 42 / 58, 66 / 57.
+//   A riding step whose controller is in launches of its own (no hidden size of 128, no room next to the projection): ordered 8 of 16 39 /
+//     45, 4 of 32 48 / 47, known ahead 1 of 4 heads 24 / 25 to 25 / 28, 8 of 12 32 / 27; fp32 a half of that, known ahead an eighth.
 // A stack of layers called one by one with ordered inputs starts its selections behind the last layer's attention, so
 // that the side streams could hide nothing but the controller, once per L layers: 4 layers of 8 sequences 151 -> 122 us,
 // of 32 sequences 561 -> 546 us, 3 layers of 64 sequences 418 -> 406 us.  (The forward's selections run beside all its layers: it keeps the side streams.)
 // ADORE_STEP_STREAMS=1 / 0 in the environment: side streams always / never, for comparison runs.
-constexpr float kOneStreamMicros = 20.f, kOneStreamReadyMicros = 5.5f;
+constexpr float kOneStreamMicros = 20.f, kOneStreamReadyMicros = 5.5f;                                 // with launches of the controller's own
+// Carried in the other launches: the first pair beside attentions of less than kShortAttention, which hide less of the side streams' work.
+constexpr float kCarriedMicros[2] = {55.f, 40.f}, kCarriedReadyMicros[2] = {47.f, 28.f}, kCarriedRescoreMicros = 60.f, kShortAttention = 20.f;
 bool steps_on_one_stream(const adore_ctx *ctx, bool forward, bool riding) {
   const adore_config &c = ctx->cfg;
   if (const char *e = getenv("ADORE_STEP_STREAMS")) return atoi(e) == 0;
   if (forward) return false;
   if (c.layers > 1) return ctx->ordered;
-  const double bytes = 2.0 * c.batch * c.heads * double(c.cache_slots) * c.head_dim * elem_size(c);
-  const bool f32 = c.dtype == ADORE_F32;
-  const float limit = riding && !ctx->ordered ? kOneStreamReadyMicros * (f32 ? 0.125f : 1.f) : kOneStreamMicros * (f32 ? 0.5f : 1.f);
-  // (the attention reads 5 TB/s)
-  return bytes / 5e6 + rebuild_gemm_micros(c) < limit;
+  // the attention reads 5 TB/s
+  const double attention = 2.0 * c.batch * c.heads * double(c.cache_slots) * c.head_dim * elem_size(c) / 5e6;
+  const bool f32 = c.dtype == ADORE_F32, rescore = c.score_mode == ADORE_SCORE_RESCORE;
+  float limit;
+  if (riding && step_ctrl_supported(c) && rebuild_gemm_takes_tail(ctx, c.rebuild_budget))
+    limit = rescore ? kCarriedRescoreMicros : (ctx->ordered || f32 ? kCarriedMicros : kCarriedReadyMicros)[attention >= kShortAttention];
+  else if (riding && !ctx->ordered && !rescore)
+    limit = kOneStreamReadyMicros * (f32 ? 0.125f : 1.f);
+  else
+    limit = kOneStreamMicros * (f32 ? 0.5f : 1.f);
+  return attention + rebuild_gemm_micros(c) < limit;
 }
 
 // The decision for steps that adore_decode_step makes in one launch and a projection and for all others; the first is taken to come
 // next where it can (the first step of the other kind moves).
-bool riding_expected(const adore_ctx *ctx) { return ctx->cfg.layers == 1 && ctx->ride && ctx->ride_fits; }
+// (In RESCORE mode the scores are made anew ahead of the selections: these ride where everything is on one stream anyway.)
+bool riding_expected(const adore_ctx *ctx) {
+  return ctx->cfg.layers == 1 && ctx->ride && ctx->ride_fits && (ctx->cfg.score_mode == ADORE_SCORE_STATIC || ctx->one_when[1]);
+}
 bool decide_streams(adore_ctx *ctx, bool forward) {
   for (int riding = 0; riding < 2; ++riding) ctx->one_when[riding] = steps_on_one_stream(ctx, forward, riding != 0);
   return ctx->one_when[riding_expected(ctx)];
@@ -482,17 +496,18 @@ int adore_create(const adore_config *cfg, const adore_weights *weights, void *wo
   ctx->overlap = !(no && atoi(no) != 0) && cfg->score_mode != ADORE_SCORE_H2O;
   const char *nr = getenv("ADORE_NO_RIDE");
   ctx->ride = ctx->overlap && !(nr && atoi(nr) != 0);
-  // Whether the selections may ride in the attention launch: static scores, a cache that releases, and the role's
+  // Whether the selections may ride in the attention launch: scores that are there before the step, a cache that releases, and the role's
   // LDS at the last step of the longest sequence (its need grows with n) within what a workgroup gets without
   // asking for more, 64 KB, next to the attention kernel's own static LDS.  Decided once, here, so that no step
   // in the middle of a sequence finds its launch refused.
-  ctx->ride_fits = cfg->score_mode == ADORE_SCORE_STATIC && cfg->cache_slots <= kMaxSlots &&
+  ctx->ride_fits = cfg->score_mode != ADORE_SCORE_H2O && cfg->cache_slots <= kMaxSlots &&
                    riding_lds_bytes(cfg->max_positions - 1, cfg->cache_slots, cfg->rebuild_budget) + kAttendStaticLds <=
                        64 * 1024;
   ctx->side = ctx->side2 = ctx->stream;
   ctx->ev_ctrl = nullptr;
   ctx->ev_att = ctx->ev_join = ctx->ev_in = nullptr;
   ctx->ordered = true;
+  choose_split(ctx);
   ctx->one_stream = decide_streams(ctx, false);
   ctx->steps_done = 0;
   ctx->side_ready = false;
@@ -500,7 +515,6 @@ int adore_create(const adore_config *cfg, const adore_weights *weights, void *wo
   ctx->rebuilt.assign(cfg->layers, 0);
   ctx->timing = false;
   reset_step(ctx);
-  choose_split(ctx);
   *out = ctx;
   return ADORE_OK;
 }
@@ -703,14 +717,24 @@ int do_ridden_step(adore_ctx *ctx, const void *q, const void *k_new, const void 
   const int pool = ctx->n + 1 - kept;
   const int r = pool < c.rebuild_budget ? pool : c.rebuild_budget;
   const int dst = (ctx->cur + 1) % kRing;
-  ADORE_TRY(order_side_after_caller(ctx, false));
-  if (side_steps(ctx)) ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_ctrl, 0));   // the controller of the step before
-  ADORE_TRY(launch_controller(ctx, x_n, 1, score_override));
   RidingSelections sel;
   sel.dst = dst; sel.x = x; sel.r = r;
   sel.map_out = slot_map; sel.rel_out = nullptr; sel.rb_out = nullptr;
-  ADORE_TRY(launch_attend(ctx, 0, q, k_new, v_new, out, &sel));
-  ADORE_TRY(launch_rebuild_gemm(ctx, 0, hidden_store, dst, r, ctx->slot_pos[dst], slot_map));
+  if (c.score_mode == ADORE_SCORE_RESCORE) ADORE_TRY(launch_rescore(ctx, ctx->stream, ctx->n, ctx->n - 1));   // (one stream)
+  if (!side_steps(ctx) && step_ctrl_supported(c) && rebuild_gemm_takes_tail(ctx, r)) {
+    // the controller inside the two launches as well: a step of a job this small is as long as its launches are many
+    StepCtrl ctrl;
+    StepTail tail;
+    fill_step_ctrl(ctx, x_n, ctx->n, score_override, ctrl, tail);
+    ADORE_TRY(launch_attend(ctx, 0, q, k_new, v_new, out, &sel, &ctrl, &tail));
+    ADORE_TRY(launch_rebuild_gemm(ctx, 0, hidden_store, dst, r, ctx->slot_pos[dst], slot_map, &tail));
+  } else {
+    ADORE_TRY(order_side_after_caller(ctx, false));
+    if (side_steps(ctx)) ADORE_TRY(hipStreamWaitEvent(ctx->stream, ctx->ev_ctrl, 0));   // the controller of the step before
+    ADORE_TRY(launch_controller(ctx, x_n, 1, score_override));
+    ADORE_TRY(launch_attend(ctx, 0, q, k_new, v_new, out, &sel));
+    ADORE_TRY(launch_rebuild_gemm(ctx, 0, hidden_store, dst, r, ctx->slot_pos[dst], slot_map));
+  }
   ctx->occ = kept + r;
   ctx->n++;
   ctx->steps_done++;
@@ -758,7 +782,7 @@ int adore_decode_step(adore_ctx *ctx, const void *q, const void *k_new, const vo
   if (score_override && ctx->cfg.score_mode != ADORE_SCORE_STATIC) return ADORE_E_INVALID;
   if (!ctx->inited || ctx->forward || ctx->scheduled || ctx->n_attended != 0 || ctx->n >= ctx->cfg.max_positions)
     return ADORE_E_STATE;
-  if (ctx->ride && ctx->ride_fits) {
+  if (riding_expected(ctx)) {
     if (ensure_side_stream(ctx) != ADORE_OK) return ADORE_E_HIP;
     ADORE_TRY(place_steps(ctx, ctx->one_when[1]));
     return do_ridden_step(ctx, q, k_new, v_new, hidden_store, x_n, score_override, out, slot_map);

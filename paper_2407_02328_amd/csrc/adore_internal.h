@@ -159,8 +159,13 @@ struct RidingSelections {
 };
 // dynamic LDS of a workgroup that carries a sequence's selections in the attention launch at step n
 size_t riding_lds_bytes(int n, int K, int r);
+struct StepCtrl;   // the controller of a short step inside the step's other launches (ctrl_device.h)
+struct StepTail;
 hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k_new,
-                         const void *v_new, float *out, const RidingSelections *sel = nullptr);
+                         const void *v_new, float *out, const RidingSelections *sel = nullptr,
+                         const StepCtrl *ctrl = nullptr, StepTail *tail = nullptr);
+bool step_ctrl_supported(const adore_config &c);
+void fill_step_ctrl(adore_ctx *ctx, const void *x, int pos, const float *score_override, StepCtrl &s, StepTail &t);
 hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int ntok, int per_seq,
                              int seq_rows, int buf, int *ksplit_out);
 hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0,
@@ -180,7 +185,8 @@ hipError_t launch_rebuild_select(adore_ctx *ctx, hipStream_t st, int dst, int r,
 // tokens' positions itself (when the per-sequence choice did not do it)
 float rebuild_gemm_micros(const adore_config &c);
 hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_layer, int lists, int r,
-                               int32_t *map_dst = nullptr, int32_t *map_out = nullptr);
+                               int32_t *map_dst = nullptr, int32_t *map_out = nullptr, const StepTail *tail = nullptr);
+bool rebuild_gemm_takes_tail(const adore_ctx *ctx, int r);   // whether a launch of r tokens per sequence can carry a StepTail
 bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, const void *x, const void *W, float *out,
                              int ntok, int per_seq, int seq_rows, int N, int D);
 hipError_t launch_init_select(adore_ctx *ctx, int dst, int lists, int S, int keep, int r0);

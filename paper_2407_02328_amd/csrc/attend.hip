@@ -14,6 +14,7 @@
 // runs.  Softmax runs online in fp32, base 2.
 #include <cstdlib>
 
+#include "ctrl_device.h"
 #include "select_device.h"
 
 namespace adore {
@@ -47,6 +48,7 @@ struct AttendArgs {
   int n_sel;                       // the first n_sel workgroups carry the selections (they start first: their chain
                                    // of dependent steps is the longest), the attention's come behind them
   SchedArgs s;
+  StepCtrl c;                      // the c.n workgroups behind those carry the controller's first part (c.n = 0: none)
   float *part;                     // [B*H][nsplit][d+2]
   float *out;                      // [B*H][d]
   float *logit_out;                // null, or [B*H][K]: every slot's logit as scaled here (base 2; -inf for a free slot)
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
   // radix histograms there
   __shared__ float s_m[G], s_l[G];
   __shared__ float s_acc[G][DH];
-  static_assert(G * DH >= WAVES * 256, "room for one 256-bin histogram per wave");
+  static_assert(G * DH >= WAVES * 256 && G * DH >= (sizeof(T) == 2 ? kInputTileLds : 4 * JT * NB), "room for one 256-bin histogram per wave, for an input tile's sums");
 
   if (int(blockIdx.x) < a.n_sel) {   // uniform over the workgroup
     extern __shared__ uint64_t dyn_smem[];
@@ -145,7 +147,11 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
     }
     return;
   }
-  const int wg = blockIdx.x - a.n_sel;
+  if (int(blockIdx.x) < a.n_sel + a.c.n) {
+    step_ctrl_role<T>(a.c, blockIdx.x - a.n_sel, &s_acc[0][0]);
+    return;
+  }
+  const int wg = blockIdx.x - a.n_sel - a.c.n;
   const int bh = wg / a.nsplit;
   const int sp = wg - bh * a.nsplit;
   const int tid = threadIdx.x;
@@ -278,27 +284,11 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
 
 template <int DH>
 __global__ __launch_bounds__(DH) void attend_combine_kernel(const float *part, float *out, int nsplit, float *ml_out) {
-  const int bh = blockIdx.x;
-  const int tid = threadIdx.x;
-  const float *p = part + size_t(bh) * nsplit * (DH + 2);
-  float M = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) M = fmaxf(M, p[s * (DH + 2) + DH]);
-  float sum = 0.f, L = 0.f;
-  for (int s = 0; s < nsplit; ++s) {
-    const float ms = p[s * (DH + 2) + DH];
-    const float f = (ms == -INFINITY) ? 0.f : exp2f(ms - M);
-    sum = fmaf(p[s * (DH + 2) + tid], f, sum);
-    L = fmaf(p[s * (DH + 2) + DH + 1], f, L);
-  }
-  out[size_t(bh) * DH + tid] = sum / L;
-  if (ml_out && tid == 0) {
-    ml_out[size_t(bh) * 2] = M;
-    ml_out[size_t(bh) * 2 + 1] = L;
-  }
+  merge_splits(part, out, ml_out, blockIdx.x, threadIdx.x, nsplit, DH);
 }
 
 template <typename T, int DH>
-hipError_t launch_typed(adore_ctx *ctx, const AttendArgs &a, int rows, int waves, int extra_wgs, size_t dyn_lds) {
+hipError_t launch_typed(adore_ctx *ctx, const AttendArgs &a, int rows, int waves, int extra_wgs, size_t dyn_lds, bool merge) {
   {
     ScopedTimer t(ctx, ADORE_KERNEL_ATTEND, ctx->stream);
     const dim3 grid(rows * a.nsplit + extra_wgs);
@@ -311,7 +301,7 @@ hipError_t launch_typed(adore_ctx *ctx, const AttendArgs &a, int rows, int waves
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (a.nsplit > 1) {
+  if (a.nsplit > 1 && merge) {
     ScopedTimer t(ctx, ADORE_KERNEL_ATTEND_COMBINE, ctx->stream);
     ADORE_LAUNCH(t, (attend_combine_kernel<DH>), dim3(rows), dim3(DH), 0, ctx->stream, a.part, a.out,
                        a.nsplit, a.ml_out);
@@ -326,9 +316,10 @@ size_t riding_lds_bytes(int n, int K, int r) {
   return size_t((n + 2) / 2) * 8 + size_t((K + 1) / 2) * 8 + ridden_choice_lds_bytes(r, n);
 }
 
-// sel: null, or the selections of this step to carry in the same launch (see SchedArgs).
+// sel: null, or the selections of this step to carry in the same launch (see SchedArgs); ctrl: null, or (with sel) the first part of its
+// controller, in which case tail receives the merge of this launch's splits for the launch that carries the second.
 hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k_new, const void *v_new,
-                         float *out, const RidingSelections *sel) {
+                         float *out, const RidingSelections *sel, const StepCtrl *ctrl, StepTail *tail) {
   const adore_config &c = ctx->cfg;
   const size_t layer_bytes = size_t(c.batch) * c.heads * c.cache_slots * c.head_dim * elem_size(c);
   AttendArgs a;
@@ -347,13 +338,14 @@ hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k
   const int rows = c.batch * c.heads;
   a.n_sel = 0;
   a.s.rel_wgs = 0;
+  a.c.n = 0;
   int waves = ctx->attend_waves, extra = 0;
   size_t dyn = 0;
   if (sel) {
     // 4 waves per workgroup: half of a compute unit's wave slots and registers then stay free, so the extra
     // workgroups start at once next to the attention's instead of waiting for a round of them to end
     waves = 4;
-    if (const char *e = getenv("ADORE_RIDE_WAVES")) {   // tuning runs
+    if (const char *e = ctrl ? nullptr : getenv("ADORE_RIDE_WAVES")) {   // tuning runs (the controller's part has 4)
       const int v = atoi(e);
       if (v == 4 || v == 8) waves = v;
     }
@@ -383,13 +375,22 @@ hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k
     extra = c.batch * (s.rel_wgs + 1);
     a.n_sel = extra;
     dyn = riding_lds_bytes(ctx->n, c.cache_slots, sel->r);
+    if (ctrl) {
+      a.c = *ctrl;
+      extra += ctrl->n;
+      tail->part = ctx->att_part;
+      tail->out = out;
+      tail->rows = ctx->nsplit > 1 ? rows : 0;
+      tail->nsplit = ctx->nsplit;
+      tail->d = c.head_dim;
+    }
   }
   if (c.dtype == ADORE_BF16) {
-    return c.head_dim == 128 ? launch_typed<bf16_t, 128>(ctx, a, rows, waves, extra, dyn)
-                             : launch_typed<bf16_t, 64>(ctx, a, rows, waves, extra, dyn);
+    return c.head_dim == 128 ? launch_typed<bf16_t, 128>(ctx, a, rows, waves, extra, dyn, !ctrl)
+                             : launch_typed<bf16_t, 64>(ctx, a, rows, waves, extra, dyn, !ctrl);
   }
-  return c.head_dim == 128 ? launch_typed<float, 128>(ctx, a, rows, waves, extra, dyn)
-                           : launch_typed<float, 64>(ctx, a, rows, waves, extra, dyn);
+  return c.head_dim == 128 ? launch_typed<float, 128>(ctx, a, rows, waves, extra, dyn, !ctrl)
+                           : launch_typed<float, 64>(ctx, a, rows, waves, extra, dyn, !ctrl);
 }
 
 }  // namespace adore

@@ -14,57 +14,28 @@
 // slices are added up in a fixed order by the cell kernel.  ctrl_cell does the
 // recurrent part token by token: W_hh z, the gates, the MLP and the score.
 // All sums are fp32 in a fixed order, so results are reproducible run to run.
-#include "device_utils.h"
+#include "ctrl_device.h"
 
 namespace adore {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// ---- input projection, bf16, matrix cores -----------------------------------------
-// grid (3d'/16, ceil(ntok/16), ksplit), 256 threads.  The workgroup owns a 16-token x 16-row
-// tile and the D-slice z; its 4 waves cut the slice again and are summed through LDS.
-// Inside a wave, lane group g = lane/16 walks the g-th quarter of the wave's k-range in
-// 16-byte steps (both operands use the same assignment, so the order of k does not matter).
-// part[z][tok][j] = sum over the slice of W_ih[j][k] * x_tok[k].
+// grid (3d'/16, ceil(ntok/16), ksplit), 256 threads
 __global__ __launch_bounds__(256) void ctrl_input_mfma_kernel(const bf16_t *__restrict__ W_ih,
                                                               const bf16_t *__restrict__ x,
                                                               float *__restrict__ part, int D, int G3, int ntok,
                                                               int per_seq, int seq_rows, int kslice) {
   __builtin_amdgcn_s_setprio(3);   // short, latency-bound work that shares compute units with the GEMM: its waves go first
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int j0 = blockIdx.x * 16, t0 = blockIdx.y * 16;
-  const int kw = kslice / 4;                       // k-range of one wave, a multiple of 32
-  const int kbeg = blockIdx.z * kslice + wave * kw + (lane >> 4) * (kw / 4);
-  int tok = t0 + (lane & 15);
-  if (tok >= ntok) tok = ntok - 1;                 // padded rows read a valid token; dropped at the store
-  const size_t xrow = size_t(tok / per_seq) * seq_rows + tok % per_seq;
-  int j = j0 + (lane & 15);
-  if (j >= G3) j = G3 - 1;
-  const u32x4 *pa = reinterpret_cast<const u32x4 *>(x + xrow * D + kbeg);
-  const u32x4 *pb = reinterpret_cast<const u32x4 *>(W_ih + size_t(j) * D + kbeg);
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  const int steps = kw / 32;                       // each MFMA consumes 32 k: 8 per lane group
-  for (int s = 0; s < steps; ++s) {
-    const u32x4 va = pa[s], vb = pb[s];
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(&va),
-                                                  *reinterpret_cast<const bf16x8 *>(&vb), acc, 0, 0, 0);
-  }
-  // accumulator element v of lane L: token 4*(L/16) + v, gate row L%16
-  __shared__ float red[4][16][17];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) red[wave][4 * (lane >> 4) + v][lane & 15] = acc[v];
-  __syncthreads();
-  {
-    const int m = tid >> 4, nn = tid & 15;
-    if (t0 + m < ntok && j0 + nn < G3) {
-      const float s = (red[0][m][nn] + red[1][m][nn]) + (red[2][m][nn] + red[3][m][nn]);
-      part[(size_t(blockIdx.z) * ntok + t0 + m) * G3 + j0 + nn] = s;
-    }
-  }
+  __shared__ float red[kInputTileLds];
+  ctrl_input_mfma_tile(W_ih, x, part, D, G3, ntok, per_seq, seq_rows, kslice, blockIdx.x, blockIdx.y, blockIdx.z, red);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void ctrl_input_kernel(const T *__restrict__ W_ih, const T *__restrict__ x,
+                                                         float *__restrict__ gi, int D, int G3, int ntok,
+                                                         int per_seq, int seq_rows) {
+  __shared__ float red[4 * JT * NB];
+  ctrl_input_plain_tile<T>(W_ih, x, gi, D, G3, ntok, per_seq, seq_rows, blockIdx.x, blockIdx.y, red);
 }
 
 // ---- input projection of a prompt chunk, bf16, matrix cores ---------------------------
@@ -154,173 +125,6 @@ __global__ __launch_bounds__(256) void ctrl_input_prompt_kernel(const bf16_t *__
           const int tok = t0 + 16 * i + 4 * (lane >> 4) + v, j = j0 + 16 * jj + (lane & 15);
           if (tok < ntok && j < G3) gi[size_t(tok) * G3 + j] = acc[i][jj][v];
         }
-  }
-}
-
-// Sums over a wave of a batch of rows at once: at every halving step a lane keeps one half of its partial sums and hands the
-// other half to its partner, so N rows cost N-1 shuffles instead of 6N.
-// v[i] is this lane's partial sum of row i.  Returns, in every lane, the complete sum of row
-// lane / (64 / N).
-template <int N, int OFF>
-struct ReduceRows {
-  __device__ static inline float run(float (&v)[N], int lane) {
-    const bool upper = (lane & OFF) != 0;
-    float w[N / 2];
-#pragma unroll
-    for (int i = 0; i < N / 2; ++i) {
-      const float keep = upper ? v[i + N / 2] : v[i];
-      const float send = upper ? v[i] : v[i + N / 2];
-      w[i] = keep + __shfl_xor(send, OFF, 64);
-    }
-    return ReduceRows<N / 2, OFF / 2>::run(w, lane);
-  }
-};
-template <int OFF>
-struct ReduceRows<1, OFF> {
-  __device__ static inline float run(float (&v)[1], int) {
-    float s = v[0];
-#pragma unroll
-    for (int off = OFF; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    return s;
-  }
-};
-template <int N>
-__device__ inline float reduce_rows(float (&v)[N], int lane) {
-  return ReduceRows<N, 32>::run(v, lane);
-}
-
-// ---- input projection, any storage type, plain ALUs ---------------------------------
-constexpr int JT = 4;  // gate rows per workgroup
-constexpr int NB = 8;  // tokens per workgroup
-
-// gi[tok][j] = sum_t W_ih[j][t] * x_tok[t]       (bias added in the cell kernel)
-// Token tok = b * per_seq + i reads the row x[(b * seq_rows + i) * D].
-template <typename T>
-__global__ __launch_bounds__(256) void ctrl_input_kernel(const T *__restrict__ W_ih, const T *__restrict__ x,
-                                                         float *__restrict__ gi, int D, int G3, int ntok,
-                                                         int per_seq, int seq_rows) {
-  constexpr int EPL = Vec16<T>::EPL;
-  const int j0 = blockIdx.x * JT;
-  const int t0 = blockIdx.y * NB;
-  const int tid = threadIdx.x;
-  float acc[JT][NB];
-#pragma unroll
-  for (int jj = 0; jj < JT; ++jj)
-#pragma unroll
-    for (int tt = 0; tt < NB; ++tt) acc[jj][tt] = 0.f;
-
-  for (int c = tid * EPL; c < D; c += 256 * EPL) {
-    float wf[JT][EPL];
-#pragma unroll
-    for (int jj = 0; jj < JT; ++jj) {
-      if (j0 + jj < G3) {
-        Vec16<T>::load(W_ih + size_t(j0 + jj) * D + c, wf[jj]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) wf[jj][e] = 0.f;
-      }
-    }
-#pragma unroll
-    for (int tt = 0; tt < NB; ++tt) {
-      if (t0 + tt < ntok) {
-        float xf[EPL];
-        const int tok = t0 + tt;
-        const size_t row = size_t(tok / per_seq) * seq_rows + tok % per_seq;
-        Vec16<T>::load(x + row * D + c, xf);
-#pragma unroll
-        for (int jj = 0; jj < JT; ++jj)
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) acc[jj][tt] = fmaf(wf[jj][e], xf[e], acc[jj][tt]);
-      }
-    }
-  }
-  __shared__ float red[4][JT][NB];
-  const int wave = tid >> 6, lane = tid & 63;
-  // (one sum at a time, 192 shuffles, was a quarter of a decode step's launch)
-  const float s = reduce_rows<JT * NB>(reinterpret_cast<float (&)[JT * NB]>(acc), lane);
-  if ((lane & 1) == 0) red[wave][lane / 2 / NB][lane / 2 % NB] = s;
-  __syncthreads();
-  if (tid < JT * NB) {
-    const int jj = tid / NB, tt = tid % NB;
-    if (j0 + jj < G3 && t0 + tt < ntok) {
-      gi[size_t(t0 + tt) * G3 + j0 + jj] = (red[0][jj][tt] + red[1][jj][tt]) + (red[2][jj][tt] + red[3][jj][tt]);
-    }
-  }
-}
-
-__device__ inline float sigmoidf_(float a) { return 1.0f / (1.0f + expf(-a)); }
-
-struct CellArgs {
-  const void *W_hh;            // [3d'][d'] storage type
-  const float *b_ih, *b_hh;    // [3d']
-  const float *pos_w, *pos_b, *W1, *b1, *out_w, *out_b;
-  const float *gi;             // [ksplit][B*nsteps][3d'], token (b, i) at row b*nsteps + i
-  float *z;                    // [B][d']
-  float *score;                // [B][N_max]
-  float *cvec;                 // rescore mode: [B][N_max][d'] interaction-layer pre-activation at distance 0; else null
-  const float *override_;      // [B][override_stride] or null
-  int override_stride;
-  int dp, nsteps, pos0, N_max, ksplit, ntok;
-  float pos_scale;
-};
-
-// sum of the D-slices of one input pre-activation, in slice order; loads go out eight at a time
-__device__ inline float gi_sum(const CellArgs &a, size_t tok, int j) {
-  const size_t stride = size_t(a.ntok) * 3 * a.dp;
-  const float *p = a.gi + tok * 3 * a.dp + j;
-  float s = 0.f;
-  int k = 0;
-  for (; k + 16 <= a.ksplit; k += 16) {   // (sixteen at a time where there are that many: one trip to memory, same order)
-    float v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = p[size_t(k + u) * stride];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) s += v[u];
-  }
-  for (; k + 8 <= a.ksplit; k += 8) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = p[size_t(k + u) * stride];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += v[u];
-  }
-  for (; k < a.ksplit; ++k) s += p[size_t(k) * stride];
-  return s;
-}
-
-// ---- cell, d' = 128 --------------------------------------------------------------------
-// One workgroup of 4 waves per sequence, small enough in registers to share a compute unit with
-// the rebuild GEMM of the previous step.  A weight row of 128 elements is one coalesced wave load
-// (two elements per lane); a wave multiplies a batch of rows by the state it holds in registers and
-// reduces the whole batch at once: at every halving step a lane keeps one half of its partial sums
-// and hands the other half to its partner, so N rows cost N-1 shuffles instead of 6N.
-
-// two consecutive elements of a weight row, raw, and their conversion
-__device__ inline uint32_t load_raw2(const bf16_t *p) { return *reinterpret_cast<const uint32_t *>(p); }
-__device__ inline float2 load_raw2(const float *p) { return *reinterpret_cast<const float2 *>(p); }
-__device__ inline float dot2(uint32_t u, float x0, float x1) {
-  return fmaf(__uint_as_float(u << 16), x0, __uint_as_float(u & 0xffff0000u) * x1);
-}
-__device__ inline float dot2(float2 u, float x0, float x1) { return fmaf(u.x, x0, u.y * x1); }
-
-// out[row0 + r] = bias[row0 + r] + W[row0 + r][:] . x   for r < N, x held as (x0, x1) = x[2*lane], x[2*lane+1], in two
-// halves: the N row loads go out where the caller wants them (next to everything else a step reads), the arithmetic follows
-// once x is known.
-template <typename T, int N>
-__device__ inline void rows_request(const T *W, int row0, int lane, decltype(load_raw2(W)) (&raw)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) raw[i] = load_raw2(W + size_t(row0 + i) * 128 + 2 * lane);
-}
-template <typename R, int N>
-__device__ inline void rows_finish(const R (&raw)[N], int row0, float x0, float x1, const float *bias, float *out, int lane) {
-  float v[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = dot2(raw[i], x0, x1);
-  const float s = reduce_rows<N>(v, lane);
-  constexpr int LPRW = 64 / N;   // lanes holding the same row
-  if ((lane & (LPRW - 1)) == 0) {
-    const int r = row0 + lane / LPRW;
-    out[r] = s + bias[r];
   }
 }
 
@@ -841,6 +645,13 @@ int ctrl_input_ksplit(const adore_config &c, int ntok, size_t rows) {
   return ks;
 }
 
+// fp32: a tile of 16 tokens x 16 rows walks all of D in one workgroup, whose time is the row's (4.3, 5.7, 7.9, 11.7, 18.5 us
+// at D = 256, 512, 1024, 2048, 4096) until there are more tiles than compute units; the plain kernel's grows with the outputs.
+// Plain / tiles at d' = 128: D = 256, 16 tokens 5.7 / 5.7 us; 512, 32: 6.7 / 5.6; 1024, 32: 6.5 / 7.8, 96: 8.5 / 8.5, 256: 14.4 / 11.2;
+// 2048, 64: 9.2 / 11.6, 128: 12.2 / 12.5, 256: 19.4 / 18.6; 4096, 16: 10.3 / 18.3, 128: 20.1 / 20.3, 256: 33.7 / 33.6.  d' = 64 and 512 turn
+// at the same number of outputs.
+bool input_on_tiles(const adore_config &c, int ntok) { return ntok >= 16 && (long long)ntok * 3 * c.ctrl_hidden >= 24LL * c.hidden; }
+
 }  // namespace
 
 // buf: which of the two copies of the pre-activations is written (a prompt's chunks take them in turn).
@@ -851,12 +662,7 @@ hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int 
   float *gi = ctx->gi[buf];
   ScopedTimer t(ctx, ADORE_KERNEL_CTRL_INPUT, st);
   *ksplit_out = 1;
-  // fp32: a tile of 16 tokens x 16 rows walks all of D in one workgroup, whose time is the row's (4.3, 5.7, 7.9, 11.7, 18.5 us
-  // at D = 256, 512, 1024, 2048, 4096) until there are more tiles than compute units; the plain kernel's grows with the outputs.
-  // Plain / tiles at d' = 128: D = 256, 16 tokens 5.7 / 5.7 us; 512, 32: 6.7 / 5.6; 1024, 32: 6.5 / 7.8, 96: 8.5 / 8.5, 256: 14.4 / 11.2;
-  // 2048, 64: 9.2 / 11.6, 128: 12.2 / 12.5, 256: 19.4 / 18.6; 4096, 16: 10.3 / 18.3, 128: 20.1 / 20.3, 256: 33.7 / 33.6.  d' = 64 and 512 turn
-  // at the same number of outputs.
-  const bool tiled = c.dtype == ADORE_BF16 ? ntok > kCtrlSplitTokens : ntok >= 16 && (long long)ntok * G3 >= 24LL * c.hidden;
+  const bool tiled = c.dtype == ADORE_BF16 ? ntok > kCtrlSplitTokens : input_on_tiles(c, ntok);
   if (tiled &&
       launch_plain_projection(ctx, t, st, x, ctx->w.gru_w_ih, gi, ntok, per_seq, seq_rows, G3, c.hidden)) {
     // a prompt chunk on the rebuild's 128x128 tile (3d' a multiple of 128, D of 64)
@@ -955,6 +761,32 @@ hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0
     }
   }
   return hipGetLastError();
+}
+
+// Whether the controller of a step can ride in the step's other launches, and its two parts.
+bool step_ctrl_supported(const adore_config &c) {
+  return c.ctrl_hidden == 128 && (c.dtype == ADORE_F32 ? !input_on_tiles(c, c.batch) : c.batch <= kCtrlSplitTokens);
+}
+
+void fill_step_ctrl(adore_ctx *ctx, const void *x, int pos, const float *score_override, StepCtrl &s, StepTail &t) {
+  const adore_config &c = ctx->cfg;
+  const int G3 = 3 * c.ctrl_hidden;
+  const bool mfma = c.dtype == ADORE_BF16 && c.hidden % 128 == 0;
+  // behind the slices of the pre-activations there is room for B more rows
+  const int ks = mfma ? ctrl_input_ksplit(c, c.batch, ctx->gi_rows[0] - c.batch) : 1;
+  s.kslice = mfma ? c.hidden / ks : 0;
+  s.tiles_j = mfma ? (G3 + 15) / 16 : (G3 + JT - 1) / JT;
+  s.tiles_t = mfma ? (c.batch + 15) / 16 : (c.batch + NB - 1) / NB;
+  s.n_in = s.tiles_j * s.tiles_t * ks;
+  s.n = s.n_in + 6 * c.batch;
+  s.W_ih = ctx->w.gru_w_ih; s.x = x; s.W_hh = ctx->w.gru_w_hh;
+  s.z = ctx->z; s.b_hh = ctx->w.gru_b_hh;
+  s.gi = ctx->gi[0]; s.gh = ctx->gi[0] + size_t(ks) * c.batch * G3;
+  s.D = c.hidden; s.B = c.batch; s.seq_rows = 1;
+  t.cell = cell_args(ctx, 1, pos, score_override, 1, 0, ks);
+  t.gh = s.gh;
+  t.n_cell = c.batch;
+  t.rows = 0;
 }
 
 hipError_t launch_ctrl_avec(adore_ctx *ctx, hipStream_t st) {

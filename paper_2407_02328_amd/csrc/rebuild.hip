@@ -22,15 +22,13 @@
 // is rounded to bf16 into LDS and leaves as 16-byte vectors: a row of the tile is
 // a run of contiguous head slices of cache rows.
 // fp32 path: tiles of 16x16x4 fp32 matrix instructions (f32_tile_kernel).  bf16 shapes that no tile takes: one wave per output.
-#include "device_utils.h"
+#include "ctrl_device.h"
 
 namespace adore {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // plain vector: stays in registers
 
 // The same tile kernel serves the three projections of the path:
 //   REBUILD  C = X[b][rebuilt_pos] . W_kv^T         -> head slices scattered into the freed cache slots
@@ -39,7 +37,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // plain vector: s
 //   OPROJ    C = O_rows . W_o^T + X_rows (residual) -> dense rows, the next layer's input
 // and one more product of the same shape family, the controller's input projection over a prompt chunk:
 //   PLAIN    C = X_rows . W^T                        -> dense fp32 rows, no rounding
-enum { MODE_REBUILD = 0, MODE_QKV = 1, MODE_OPROJ = 2, MODE_PLAIN = 3 };
+// TAIL is REBUILD with the workgroups of a StepTail in front (an instance of its own: the others stay as they are).
+enum { MODE_REBUILD = 0, MODE_QKV = 1, MODE_OPROJ = 2, MODE_PLAIN = 3, MODE_TAIL = 4 };
 
 struct GemmArgs {
   const void *X;               // A operand: [B][N_max][D] gathered by position, or dense rows [M][D]
@@ -61,12 +60,14 @@ struct GemmArgs {
   int cur_pos;                 // position of the current token
   int a_gather, res_gather;    // 1: the row of a token is [b][its position]; 0: its row in a dense buffer
   int out_rps, out_cur;        // OPROJ: rank j is written to row b * out_rps + j, the current token to b * out_rps + out_cur
-  int n_cur;                   // QKV / OPROJ: the first n_cur workgroups of the tile launch take the current tokens' rows
+  int n_cur;                   // QKV / OPROJ: the first n_cur workgroups of the tile launch take the current tokens' rows; TAIL: the tail
   int cur_ks;                  // ... with the contraction cut over cur_ks (1, 2, 4, 8) of a workgroup's waves
   const float2 *rope_cur;      // QKV: the workgroups of the current tokens' rows turn their query and key rows (same
                                // table; null: they do not)
   const float2 *rope;          // tile kernel: [N_max][d/2] (cos, sin), the key (and query) tiles turn their rows by
                                // position as they leave; null: no rotary embedding, or a pass of its own does it
+  int tail_at;                 // TAIL: its first workgroup
+  StepTail tail;               // TAIL, and where the fp32 kernel carries one (tail.n > 0)
 };
 
 // A rank that stays empty (position -1: fewer tokens were chosen than the launch has rows for) reads row 0 of its
@@ -91,7 +92,6 @@ constexpr int kCurCols = 256;   // output columns per workgroup in this role whe
 
 template <int MODE>
 __device__ inline void cur_rows_role(const GemmArgs &a, int e, u32x4 *smem) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
   constexpr int U = 6;                                  // chunks of 64 k in flight
   const int ks = a.cur_ks;
   const int wg_cols = kCurCols / ks;
@@ -273,8 +273,9 @@ __device__ inline void cur_rows_role(const GemmArgs &a, int e, u32x4 *smem) {
 //                        fragments of the next step are fetched before the barrier.
 //   LDS -> fragments:    one 16-wide k-slice ahead of the MFMAs that use them
 // sched_barrier keeps the compiler from sinking the fragment loads below the MFMAs they overlap with.
-template <int MODE, int BM, int BN, int BK, int KG, int WM, int WN, int LS, int NS>
+template <int MODE_, int BM, int BN, int BK, int KG, int WM, int WN, int LS, int NS>
 __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
+  constexpr int MODE = MODE_ == MODE_TAIL ? MODE_REBUILD : MODE_;
   constexpr int CH = BK / 8;             // 16-byte chunks per tile row
   constexpr int RPP = 512 / CH;          // tile rows the workgroup loads per pass
   constexpr int TM = BM / (WM * 32), TN = BN / (WN * 32);   // 32x32 blocks per wave
@@ -304,6 +305,15 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   if constexpr (MODE == MODE_QKV || MODE == MODE_OPROJ) {
     if (bx < a.n_cur) {   // uniform over the workgroup; n_cur is a multiple of 8, so the tiles keep their XCDs
       cur_rows_role<MODE>(a, bx, smem);
+      return;
+    }
+    bx -= a.n_cur;
+  }
+  if constexpr (MODE_ == MODE_TAIL) {
+    // in front of the tiles (n_cur, a multiple of 8) or behind them (n_cur = 0; tail_at); uniform over the workgroup
+    const int e = bx - a.tail_at;
+    if (e >= 0 && e < max(a.n_cur, a.tail.n)) {
+      if (e < a.tail.n) step_tail_role<512>(a.tail, e, reinterpret_cast<float *>(smem));
       return;
     }
     bx -= a.n_cur;
@@ -639,10 +649,16 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
 // 4096 4440 / 288 us (60 TFLOP/s).
 template <int MODE, int MT, int NT, int U>
 __global__ __launch_bounds__(256) void f32_tile_kernel(const GemmArgs a) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
-  const int tm = blockIdx.x / a.tiles_n, tn = blockIdx.x - tm * a.tiles_n;
+  __shared__ double red[4][MT * NT][16][17];
+  if (MODE == MODE_REBUILD && int(blockIdx.x) < a.n_cur) {
+    static_assert(sizeof(red) >= kStepTailLds * sizeof(float), "room for the tail");
+    step_tail_role<256>(a.tail, blockIdx.x, reinterpret_cast<float *>(red));
+    return;
+  }
+  const int bx = blockIdx.x - a.n_cur;
+  const int tm = bx / a.tiles_n, tn = bx - tm * a.tiles_n;
   const int m0 = tm * (16 * MT), n0 = tn * (16 * NT);
   const float *pa[MT], *pb[NT];
 #pragma unroll
@@ -692,7 +708,6 @@ __global__ __launch_bounds__(256) void f32_tile_kernel(const GemmArgs a) {
         }
   }
   // sum v of lane (c, g): row 4*g + v, column c of its tile
-  __shared__ double red[4][MT * NT][16][17];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -823,7 +838,6 @@ __global__ __launch_bounds__(256) void proj_dot_kernel(const GemmArgs a) {
 // use the same assignment, so the order of k does not matter).  Epilogue as in the tile kernel.
 template <int MODE, int NC>
 __global__ __launch_bounds__(256) void cur_rows_kernel(const GemmArgs a) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
   const int j0 = blockIdx.x * (16 * NC), t0 = blockIdx.y * 16;
@@ -907,6 +921,7 @@ struct TileShape {
 };
 constexpr TileShape kTiles[] = {{256, 256, 32}, {256, 128, 64}, {128, 128, 64}, {128, 64, 64}, {128, 32, 64}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+constexpr int kFirstTailTile = 2;   // short steps take none of the 256-wide ones
 
 // kdim = length of the contraction; scatter modes write head slices (section = H*d columns of one kind)
 bool tile_fits(const TileShape &t, int kdim, int section, int head_dim, bool dense) {
@@ -947,7 +962,7 @@ void launch_f32_tile(ScopedTimer &t, hipStream_t stream, GemmArgs &a) {
   const int side = big >= 256 ? 32 : 16;
   a.tiles_m = (a.M + side - 1) / side;
   a.tiles_n = (a.N + side - 1) / side;
-  const dim3 grid(unsigned(a.tiles_m) * unsigned(a.tiles_n)), block(256);
+  const dim3 grid(unsigned(a.tiles_m) * unsigned(a.tiles_n) + unsigned(a.n_cur)), block(256);
   if (side == 32) ADORE_LAUNCH(t, (f32_tile_kernel<MODE, 2, 2, 2>), grid, block, 0, stream, a);
   else ADORE_LAUNCH(t, (f32_tile_kernel<MODE, 1, 1, 4>), grid, block, 0, stream, a);
 }
@@ -957,9 +972,16 @@ void launch_tile(ScopedTimer &t, hipStream_t stream, int pick, GemmArgs &a) {
   a.tiles_m = (a.M + kTiles[pick].bm - 1) / kTiles[pick].bm;
   a.tiles_n = a.N / kTiles[pick].bn;
   const int total = a.tiles_m * a.tiles_n;
-  const dim3 grid((total + 7) / 8 * 8 + a.n_cur), block(512);
+  a.tail_at = 0;
+  const bool behind = MODE == MODE_TAIL && a.n_cur == 0;
+  if (behind) a.tail_at = (total + 7) / 8 * 8;
+  const dim3 grid((total + 7) / 8 * 8 + (behind ? a.tail.n : a.n_cur)), block(512);
   //                                              BM   BN  BK KG WM WN LS NS
-  switch (pick) {
+  if constexpr (MODE == MODE_TAIL) {
+    if (pick == 2) ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 128, 64, 2, 2, 2, 3, 4>), grid, block, 0, stream, a);
+    else if (pick == 3) ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 64, 64, 2, 2, 2, 3, 4>), grid, block, 0, stream, a);
+    else ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 32, 64, 2, 4, 1, 3, 4>), grid, block, 0, stream, a);
+  } else switch (pick) {
     case 0: ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 256, 256, 32, 1, 2, 4, 4, 2>), grid, block, 0, stream, a); break;
     case 1: ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 256, 128, 64, 1, 4, 2, 3, 2>), grid, block, 0, stream, a); break;
     case 2: ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 128, 64, 2, 2, 2, 3, 4>), grid, block, 0, stream, a); break;
@@ -982,8 +1004,19 @@ void fill_common(adore_ctx *ctx, GemmArgs &a, int lists, int r) {
   a.cur_ks = 1;
   a.rope = nullptr;
   a.rope_cur = nullptr;
+  a.tail.n = 0;
+  a.tail_at = 0;
 }
 
+}  // namespace
+
+namespace {
+// Workgroups of `threads` threads that a step's tail takes: a cell per sequence, and the rows whose splits are merged.
+int step_tail_wgs(const adore_ctx *ctx, int threads) {
+  const adore_config &c = ctx->cfg;
+  const int per_wg = threads / c.head_dim;
+  return c.batch + (ctx->nsplit > 1 ? (c.batch * c.heads + per_wg - 1) / per_wg : 0);
+}
 }  // namespace
 
 // About how long a full rebuild (R tokens of every sequence, one layer) takes, in microseconds.
@@ -996,8 +1029,33 @@ float rebuild_gemm_micros(const adore_config &c) {
   return float((tiles + 255) / 256) * kTileMicros[pick] * c.hidden / 4096.f;
 }
 
+namespace {
+// Tile of a launch that carries a tail of `wgs` workgroups, which take compute units of their own next to the tiles (whose LDS leaves
+// room for nothing else): the tile that is best with them in front, unless that costs more than they take behind the tiles of the
+// one that is best without (about 4 us), where they start as the first tiles end.
+int pick_tile_with_tail(const adore_config &c, int M, int wgs, bool *front) {
+  const int Hd = c.heads * c.head_dim;
+  const int alone = pick_tile(M, 2 * Hd, c.hidden, Hd, c.head_dim, false), with = pick_tile(M, 2 * Hd, c.hidden, Hd, c.head_dim, false, wgs + 14);
+  *front = false;
+  if (alone < 0) return alone;
+  auto micros = [&](int pick, int extra) {
+    const long long tiles = (long long)((M + kTiles[pick].bm - 1) / kTiles[pick].bm) * (2 * Hd / kTiles[pick].bn);
+    return float((tiles + extra + 255) / 256) * kTileMicros[pick] * c.hidden / 4096.f;
+  };
+  *front = micros(with, wgs + 14) <= micros(alone, 0) + 4.f;   // (14: both parts of the grid are padded to multiples of 8)
+  return *front ? with : alone;
+}
+}  // namespace
+
+bool rebuild_gemm_takes_tail(const adore_ctx *ctx, int r) {
+  const adore_config &c = ctx->cfg;
+  if (r <= 0) return false;
+  bool front;
+  return c.dtype == ADORE_F32 || pick_tile_with_tail(c, c.batch * r, step_tail_wgs(ctx, 512), &front) >= kFirstTailTile;
+}
+
 hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_layer, int lists, int r,
-                               int32_t *map_dst, int32_t *map_out) {
+                               int32_t *map_dst, int32_t *map_out, const StepTail *tail) {
   const adore_config &c = ctx->cfg;
   if (r <= 0) return hipSuccess;
   const size_t es = elem_size(c);
@@ -1011,12 +1069,22 @@ hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_lay
   a.M = c.batch * r; a.N = 2 * c.heads * c.head_dim;
   a.map_dst = map_dst; a.map_out = map_out;
   ScopedTimer t(ctx, ADORE_KERNEL_REBUILD_GEMM, ctx->stream);
-  const int pick = c.dtype == ADORE_BF16 ? pick_tile(a.M, a.N, c.hidden, c.heads * c.head_dim, c.head_dim, false) : -1;
+  bool front = false;
+  const int pick = c.dtype != ADORE_BF16 ? -1
+                   : tail ? pick_tile_with_tail(c, a.M, step_tail_wgs(ctx, 512), &front)
+                          : pick_tile(a.M, a.N, c.hidden, c.heads * c.head_dim, c.head_dim, false);
   // the key tiles turn their rows themselves when a tile holds whole heads; otherwise a pass of its own follows
   const bool rope = c.rope_base > 0.f;
   const bool turned = rope && pick >= 0 && kTiles[pick].bn >= c.head_dim;
   if (turned) a.rope = ctx->rope_f;
-  if (pick >= 0) {
+  if (tail) {
+    a.tail = *tail;
+    a.tail.n = step_tail_wgs(ctx, pick >= 0 ? 512 : 256);
+    a.n_cur = pick < 0 ? a.tail.n : front ? (a.tail.n + 7) / 8 * 8 : 0;
+  }
+  if (pick >= 0 && tail) {
+    launch_tile<MODE_TAIL>(t, ctx->stream, pick, a);
+  } else if (pick >= 0) {
     launch_tile<MODE_REBUILD>(t, ctx->stream, pick, a);
   } else if (c.dtype == ADORE_F32) {
     launch_f32_tile<MODE_REBUILD>(t, ctx->stream, a);
