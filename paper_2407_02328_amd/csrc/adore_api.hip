@@ -392,7 +392,7 @@ hipError_t prompt_controller(adore_ctx *ctx, const void *ctrl_input, const float
     const float *given = score_override ? score_override + pos0 : nullptr;
     const bool two = ctrl_chunk_in_two(c, len);
     if (apart && i > 0) CHUNK_TRY(hipStreamWaitEvent(st, ev_proj, 0));
-    if (two) CHUNK_TRY(launch_ctrl_scan(ctx, st, len, buf, ksplit[buf]));
+    if (two) CHUNK_TRY(launch_ctrl_scan(ctx, st, len, buf, ksplit[buf], i == 0));
     else CHUNK_TRY(launch_ctrl_cell(ctx, st, len, pos0, given, S, buf, ksplit[buf]));
     if (i + 1 < nchunks) {
       if (apart && i > 0) CHUNK_TRY(hipStreamWaitEvent(st_proj, ev_scan, 0));   // of chunk i - 1

@@ -14,6 +14,8 @@
 // slices are added up in a fixed order by the cell kernel.  ctrl_cell does the
 // recurrent part token by token: W_hh z, the gates, the MLP and the score.
 // All sums are fp32 in a fixed order, so results are reproducible run to run.
+#include <algorithm>
+
 #include "ctrl_device.h"
 
 namespace adore {
@@ -329,16 +331,78 @@ __device__ inline float quad_add(float v) {   // v + the value of the lane that 
 // SPLIT: the pre-activations come in several D-slices (a short prompt of few sequences); they are added up and staged
 // through LDS, 16 tokens at a time.  Otherwise a lane reads its own three values, kAhead tokens before their use: a wait for a
 // block of staged loads cost 2 to 3 us per 16 tokens, as much as the arithmetic.
-template <bool SPLIT>
-__global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArgs a, float *__restrict__ zseq) {
+//
+// PIECES, MEET: the recurrence forgets where it started, so a chunk need not be one chain.  PIECES takes it in m.pieces pieces, one
+// workgroup each: the first starts from the state before the chunk, every other one from zero kWarmUp tokens before its own (grid
+// [sequences][pieces]).  MEET, one workgroup per sequence, then compares the state with which each piece began with the one in which
+// the piece before it ended.  Where they agree to kMeet in every unit, the piece stands: from there on the two are one chain, but for
+// rounding (two runs that differ in the last place of one state stay 2e-7 apart, they do not become equal).  Where they do not, the
+// tokens are worked through again from the true state until it meets the one that is there, which costs what the chain costs.  So
+// the result never hangs on how fast the recurrence forgets, only the time does; a sequence that had to do half a chunk again takes
+// its later chunks (m.first = 0) as one chain at once.  Error of z against 64 bits as above, 1.0e-7 to 2.1e-7.
+// 16 sequences, a chunk of 512 tokens: 187 -> 55 us (50 the pieces, next to the projection of the chunk after, 4 the meeting); where no
+// piece stands 215 for the first chunk and 205 for the ones after it.
+enum { WHOLE = 0, PIECES = 1, MEET = 2 };
+constexpr int kWarmUp = 64, kMinPiece = 32, kMaxPieces = 14;
+constexpr float kMeet = 0x1p-21f;
+struct ScanPieces {
+  int pieces, len;             // tokens of every piece but the first, which has what is left
+  int first;                   // the prompt's first chunk
+  float *guess;                // [B][pieces][128] the state a piece began with
+  int *alone;                  // [B] this sequence does not forget
+};
+
+template <bool SPLIT, int PART>
+__global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArgs a, float *__restrict__ zseq, const ScanPieces m) {
   __builtin_amdgcn_s_setprio(3);   // a serial chain that may share its compute unit with the scoring of the chunk before
   constexpr int DP = 128, kAhead = 8;
   constexpr int TB = 16, GPT = TB * (3 * DP / 4) / 256;    // SPLIT: tokens per block; float4 per thread
   constexpr int SPS = DP + 32;                             // distance between two terms: 16 lanes' reads hit 64 different banks
   __shared__ __attribute__((aligned(16))) uint16_t sp[2][4 * SPS];   // z as bf16 terms, of two tokens in turn
   __shared__ float4 gbuf[SPLIT ? 2 : 1][SPLIT ? TB * (3 * DP / 4) : 1];   // input pre-activations of two blocks of tokens
+  __shared__ int s_meet[4];                             // MEET: what the waves found
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
+  // this lane's unit: register c / 4 of the rows 4g .. 4g+3 of the half c % 2 (lanes with c & 2 repeat it)
+  const int unit = wave * 32 + (c & 1) * 16 + 4 * g + (c >> 2);
+  const int len0 = PART == WHOLE ? a.nsteps : a.nsteps - (m.pieces - 1) * m.len;   // tokens of the first piece
+  float *zrow = zseq + size_t(b) * a.nsteps * 128 + unit;
+  int begin = 0, end = a.nsteps, keep = 0;                 // tokens to go through; those from `keep` on are its own
+  uint32_t apart = 0;                                      // MEET: pieces (bits) that did not begin where the one before ended
+  if constexpr (PART == PIECES) {
+    const int j = blockIdx.y;
+    const bool alone = !m.first && m.alone[b];
+    if (j > 0 && alone) return;
+    keep = j == 0 ? 0 : len0 + (j - 1) * m.len;
+    begin = j == 0 ? 0 : max(keep - kWarmUp, 0);
+    end = alone ? a.nsteps : len0 + j * m.len;
+  }
+  if constexpr (PART == MEET) {
+    const bool alone = !m.first && m.alone[b];   // its first piece was the whole chunk
+    if (!alone) {
+      float was[kMaxPieces], is[kMaxPieces];
+#pragma unroll
+      for (int j = 1; j < kMaxPieces; ++j) {
+        const int jj = min(j, m.pieces - 1);
+        was[j] = m.guess[(size_t(b) * m.pieces + jj) * 128 + unit];
+        is[j] = zrow[size_t(len0 + (jj - 1) * m.len - 1) * 128];
+      }
+#pragma unroll
+      for (int j = 1; j < kMaxPieces; ++j) apart |= j < m.pieces && !(fabsf(was[j] - is[j]) <= kMeet) ? 1u << j : 0u;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) apart |= __shfl_xor(apart, off, 64);
+      if (lane == 0) s_meet[wave] = int(apart);
+      __syncthreads();
+      apart = uint32_t(s_meet[0] | s_meet[1] | s_meet[2] | s_meet[3]);
+      __syncthreads();
+    }
+    apart = __builtin_amdgcn_readfirstlane(apart);
+    if (apart == 0) {            // as a rule: all of them stand
+      if ((c & 2) == 0) a.z[size_t(b) * 128 + unit] = zrow[size_t(a.nsteps - 1) * 128];
+      if (tid == 0 && !alone) m.alone[b] = 0;
+      return;
+    }
+  }
   bf16x8 w[6][4];                                          // [gate * 2 + half of the wave's units][k-step]
 #pragma unroll
   for (int t = 0; t < 6; ++t)
@@ -347,13 +411,11 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
       const int row = (t >> 1) * DP + wave * 32 + (t & 1) * 16 + c;
       w[t][s] = *reinterpret_cast<const bf16x8 *>(static_cast<const bf16_t *>(a.W_hh) + size_t(row) * DP + s * 32 + g * 8);
     }
-  // this lane's unit: register c / 4 of the rows 4g .. 4g+3 of the half c % 2 (lanes with c & 2 repeat it)
-  const int unit = wave * 32 + (c & 1) * 16 + 4 * g + (c >> 2);
   const bool odd = ((c >> 2) & 1) != 0, upper = (c >> 3) != 0, half1 = (c & 1) != 0, twin = (c & 2) != 0;
   const float b_r = a.b_ih[unit] + a.b_hh[unit];
   const float b_u = a.b_ih[DP + unit] + a.b_hh[DP + unit];
   const float b_in = a.b_ih[2 * DP + unit], b_hn = a.b_hh[2 * DP + unit];
-  float hcur = a.z[size_t(b) * DP + unit];
+  float hcur = PART == PIECES && blockIdx.y > 0 ? 0.f : a.z[size_t(b) * DP + unit];
   auto put_state = [&](uint16_t *dst) {   // the first term rounded down to 8 bits, the second the next 8, the third the rest
     const uint32_t hi = __float_as_uint(hcur) & 0xffff0000u;
     const float rest = hcur - __uint_as_float(hi);
@@ -362,10 +424,9 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     dst[(twin ? SPS : 0) + unit] = uint16_t((twin ? mid : hi) >> 16);
     if (!twin) dst[2 * SPS + unit] = uint16_t(__float_as_uint(lo) >> 16);
   };
-  float *zout = zseq + size_t(b) * a.nsteps * DP + unit;
   int cur = 0;
   // one token, from the state in sp[cur] to the state in sp[cur ^ 1]; the caller's barrier follows
-  auto token = [&](float g_r, float g_u, float g_n) {
+  auto token = [&](int i, float g_r, float g_u, float g_n) {
     bf16x8 hv[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) hv[s] = *reinterpret_cast<const bf16x8 *>(&sp[cur][(c & 3) * SPS + s * 32 + g * 8]);
@@ -401,24 +462,84 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     hcur = (1.0f - u) * cand + u * hcur;
     cur ^= 1;
     put_state(sp[cur]);
-    if (!twin) *zout = hcur;
-    zout += DP;
+    if (!twin && (PART != PIECES || i >= keep)) zrow[size_t(i) * DP] = hcur;
+    if (PART == PIECES && i == keep - 1 && !twin) m.guess[(size_t(b) * m.pieces + blockIdx.y) * DP + unit] = hcur;
   };
   for (int i = tid; i < SPS; i += 256) sp[0][3 * SPS + i] = sp[1][3 * SPS + i] = 0;
+  const float *gsrc = a.gi + size_t(b) * a.nsteps * (3 * DP) + unit;
+  if constexpr (PART == MEET) {
+    // from the first piece apart on, the tokens again, eight at a time, until the state met the one that is there; then the next
+    // piece apart
+    int again = 0;
+    bool on = false;             // hcur is the true state behind token i - 1 (otherwise the one that is there stands)
+    float pre[kAhead][3], there = 0.f;
+    auto ahead = [&](float (&v)[3], int i) {
+      const float *p = gsrc + size_t(min(i, a.nsteps - 1)) * (3 * DP);
+      v[0] = p[0]; v[1] = p[DP]; v[2] = p[2 * DP];
+      if constexpr (SPLIT) {
+        for (int k = 1; k < a.ksplit; ++k) {
+          const float *q = p + size_t(k) * a.ntok * (3 * DP);
+          v[0] += q[0]; v[1] += q[DP]; v[2] += q[2 * DP];
+        }
+      }
+    };
+    for (int i = 0; i < a.nsteps;) {             // uniform over the workgroup
+      if (!on) {
+        const int next = i < len0 ? 1 : (i - len0 + m.len - 1) / m.len + 1;   // the first piece that begins at i or later
+        const uint32_t rest = next < m.pieces ? apart >> next << next : 0u;
+        if (rest == 0) break;
+        i = len0 + (__builtin_ctz(rest) - 1) * m.len;
+        hcur = zrow[size_t(i - 1) * DP];
+        put_state(sp[cur]);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) ahead(pre[u], i + u);
+        __syncthreads();
+        on = true;
+      }
+      const int count = min(kAhead, a.nsteps - i);
+      there = zrow[size_t(i + count - 1) * DP];
+      if (count == kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          token(i + u, pre[u][0], pre[u][1], pre[u][2]);
+          ahead(pre[u], i + u + kAhead);
+          __syncthreads();
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          if (u < count) {
+            token(i + u, pre[u][0], pre[u][1], pre[u][2]);
+            __syncthreads();
+          }
+        }
+      }
+      // (looked for at every token, with its own exchange: 0.55 us a token instead of 0.37)
+      const uint64_t off = __ballot(!(fabsf(hcur - there) <= kMeet));
+      if (lane == 0) s_meet[wave] = off != 0;
+      __syncthreads();
+      if ((s_meet[0] | s_meet[1] | s_meet[2] | s_meet[3]) == 0) on = false;
+      __syncthreads();
+      again += count;
+      i += count;
+    }
+    if (!on) hcur = zrow[size_t(a.nsteps - 1) * DP];
+    if (tid == 0) m.alone[b] = again * 2 > a.nsteps;
+  } else {
   put_state(sp[0]);
   if constexpr (SPLIT) {
-    const int nblk = (a.nsteps + TB - 1) / TB;
-    const float4 *gsrc = reinterpret_cast<const float4 *>(a.gi) + size_t(b) * a.nsteps * (3 * DP / 4);
+    const int ntok = end - begin, nblk = (ntok + TB - 1) / TB;
+    const float4 *gsrc4 = reinterpret_cast<const float4 *>(a.gi) + (size_t(b) * a.nsteps + begin) * (3 * DP / 4);
     const size_t slice4 = size_t(a.ntok) * (3 * DP / 4);   // distance between two D-slices
     float4 stage[GPT];
     auto fetch = [&](int blk) {
-      const int rows = a.nsteps - blk * TB < TB ? a.nsteps - blk * TB : TB;
+      const int rows = min(ntok - blk * TB, TB);
 #pragma unroll
       for (int q = 0; q < GPT; ++q) {
         const int idx = tid + 256 * q;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (idx < rows * (3 * DP / 4)) {
-          const float4 *p = gsrc + size_t(blk) * TB * (3 * DP / 4) + idx;
+          const float4 *p = gsrc4 + size_t(blk) * TB * (3 * DP / 4) + idx;
           v = p[0];
           for (int k = 1; k < a.ksplit; ++k) {
             const float4 t = p[size_t(k) * slice4];
@@ -438,41 +559,42 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     for (int blk = 0; blk < nblk; ++blk) {
       if (blk + 1 < nblk) fetch(blk + 1);
       const float *gt = reinterpret_cast<const float *>(gbuf[blk & 1]) + unit;
-      const int rows = a.nsteps - blk * TB < TB ? a.nsteps - blk * TB : TB;
+      const int rows = min(ntok - blk * TB, TB);
       for (int ii = 0; ii < rows; ++ii, gt += 3 * DP) {
-        token(gt[0], gt[DP], gt[2 * DP]);
+        token(begin + blk * TB + ii, gt[0], gt[DP], gt[2 * DP]);
         // the next block's rows: their buffer was last read a block ago, and they are read behind the barrier
         if (ii == rows - 1 && blk + 1 < nblk) park((blk + 1) & 1);
         __syncthreads();
       }
     }
   } else {
-    const float *gsrc = a.gi + size_t(b) * a.nsteps * (3 * DP) + unit;
     float pre[kAhead][3];
     auto ahead = [&](float (&v)[3], int i) {
-      const float *p = gsrc + size_t(min(i, a.nsteps - 1)) * (3 * DP);
+      const float *p = gsrc + size_t(min(i, end - 1)) * (3 * DP);
       v[0] = p[0]; v[1] = p[DP]; v[2] = p[2 * DP];
     };
 #pragma unroll
-    for (int j = 0; j < kAhead; ++j) ahead(pre[j], j);
+    for (int j = 0; j < kAhead; ++j) ahead(pre[j], begin + j);
     __syncthreads();
-    int i0 = 0;
-    for (; i0 + kAhead <= a.nsteps; i0 += kAhead) {
+    int i0 = begin;
+    for (; i0 + kAhead <= end; i0 += kAhead) {
 #pragma unroll
       for (int j = 0; j < kAhead; ++j) {
-        token(pre[j][0], pre[j][1], pre[j][2]);
+        token(i0 + j, pre[j][0], pre[j][1], pre[j][2]);
         ahead(pre[j], i0 + j + kAhead);
         __syncthreads();
       }
     }
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) {
-      if (i0 + j < a.nsteps) {            // uniform over the workgroup
-        token(pre[j][0], pre[j][1], pre[j][2]);
+      if (i0 + j < end) {                 // uniform over the workgroup
+        token(i0 + j, pre[j][0], pre[j][1], pre[j][2]);
         __syncthreads();
       }
     }
   }
+  }
+  if (PART == PIECES) return;
   if (!twin) a.z[size_t(b) * DP + unit] = hcur;
 }
 
@@ -716,18 +838,48 @@ CellArgs cell_args(adore_ctx *ctx, int nsteps, int pos0, const float *score_over
 // A chunk of several tokens at d' = 128 is two launches, of which only the first has to wait for the chunk before it.
 bool ctrl_chunk_in_two(const adore_config &c, int nsteps) { return c.ctrl_hidden == 128 && nsteps > 1; }
 
-hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf, int ksplit) {
+// In how many pieces a chunk's recurrence is worked through (bf16): as many as keep two workgroups a compute unit, of at least
+// kMinPiece tokens; 1: as one chain (two launches cost 5 us more than one, 14 tokens).
+int scan_pieces(const adore_config &c, int nsteps) {
+  const int most = std::min(kMaxPieces, (c.heads * kMaxSplits * (c.head_dim + 2) - 1) / 128);   // (what the attention's partials have room for)
+  const int n = std::min({most, 512 / c.batch, (nsteps - kWarmUp) / kMinPiece});
+  return n >= 2 && nsteps - kWarmUp - (nsteps - kWarmUp) / n > 32 ? n : 1;
+}
+
+hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf, int ksplit, bool first) {
   const adore_config &c = ctx->cfg;
   const CellArgs a = cell_args(ctx, nsteps, 0, nullptr, 0, buf, ksplit);
   ScopedTimer t(ctx, ADORE_KERNEL_CTRL_CELL, st);
-  if (c.dtype == ADORE_BF16) {
-    if (ksplit > 1)
-      ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<true>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq[buf]);
-    else
-      ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<false>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq[buf]);
-  } else {
-    ADORE_LAUNCH(t, (ctrl_scan128_kernel<float>), dim3(c.batch), dim3(256), 0, st, a, ctx->zseq[buf]);
+  float *zseq = ctx->zseq[buf];
+  ScanPieces m = {};
+  if (c.dtype != ADORE_BF16) {
+    ADORE_LAUNCH(t, (ctrl_scan128_kernel<float>), dim3(c.batch), dim3(256), 0, st, a, zseq);
+    return hipGetLastError();
   }
+  m.pieces = scan_pieces(c, nsteps);
+  if (m.pieces == 1) {
+    if (ksplit > 1)
+      ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<true, WHOLE>), dim3(c.batch), dim3(256), 0, st, a, zseq, m);
+    else
+      ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<false, WHOLE>), dim3(c.batch), dim3(256), 0, st, a, zseq, m);
+    return hipGetLastError();
+  }
+  m.len = (nsteps - kWarmUp) / m.pieces;
+  m.first = first;
+  m.guess = ctx->att_part;     // no attention runs before the init is through
+  m.alone = reinterpret_cast<int *>(ctx->att_part + size_t(c.batch) * m.pieces * 128);
+  if (!first) m.alone = reinterpret_cast<int *>(ctx->att_part + size_t(c.batch) * scan_pieces(c, kPromptChunk) * 128);   // where the chunk before left it
+  if (ksplit > 1)
+    ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<true, PIECES>), dim3(c.batch, m.pieces), dim3(256), 0, st, a, zseq, m);
+  else
+    ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<false, PIECES>), dim3(c.batch, m.pieces), dim3(256), 0, st, a, zseq, m);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  ScopedTimer tm(ctx, ADORE_KERNEL_CTRL_CELL, st);
+  if (ksplit > 1)
+    ADORE_LAUNCH(tm, (ctrl_scan128_mfma_kernel<true, MEET>), dim3(c.batch), dim3(256), 0, st, a, zseq, m);
+  else
+    ADORE_LAUNCH(tm, (ctrl_scan128_mfma_kernel<false, MEET>), dim3(c.batch), dim3(256), 0, st, a, zseq, m);
   return hipGetLastError();
 }
 

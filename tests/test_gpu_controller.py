@@ -37,7 +37,7 @@ def test_scores_and_state_after_a_prompt_other_controller_widths(batch, S, D, DP
     _check_prompt(batch, S, D, DP)
 
 
-def _check_prompt(batch, S, D, DP, H=2, K=24):
+def _check_prompt(batch, S, D, DP, H=2, K=24, slow=0.0):
     from paper_2407_02328_amd import Adore, make_config
     g = torch.Generator().manual_seed(1000 * S + D)
 
@@ -50,6 +50,7 @@ def _check_prompt(batch, S, D, DP, H=2, K=24):
          "gru_b_hh": normal((3 * DP,), 0.1, f32), "pos_w": normal((DP,), 1.0, f32), "pos_b": normal((DP,), 0.1, f32),
          "mlp_w1": normal((DP, DP), DP ** -0.5, f32), "mlp_b1": normal((DP,), 0.1, f32), "out_w": normal((DP,), 0.3, f32),
          "out_b": normal((1,), 0.1, f32)}
+    w["gru_b_ih"][DP:2 * DP] += slow
     pos_scale = 2.0 ** -12
     job = Adore(make_config(layers=1, batch=batch, heads=H, head_dim=d, hidden=D, cache_slots=K, rebuild_budget=R,
                             max_positions=n_max, ctrl_hidden=DP, dtype="bf16", pos_scale=pos_scale), w, "cuda")
@@ -68,6 +69,15 @@ def _check_prompt(batch, S, D, DP, H=2, K=24):
     assert (z.cpu().double() - want_z).abs().max() <= 4e-6
     assert (scores[:, :S].cpu().double() - want_scores).abs().max() <= 4e-6
     job.close()
+
+
+# The recurrence in pieces: chunks just long enough for two of them and just too short, the most there are, sliced projections, a last chunk
+# as one chain; update gates so far open (6: a state keeps 0.997 of itself) that no piece begins where the one before it ended, or some do (2).
+@pytest.mark.parametrize("batch,S,D,H", [(2, 130, 512, 4), (1, 161, 1024, 4), (2, 163, 512, 4), (3, 300, 384, 1), (2, 512, 256, 4), (1, 1200, 256, 4),
+                                         (40, 600, 128, 4), (2, 200, 200, 4)])
+@pytest.mark.parametrize("slow", [0.0, 2.0, 6.0])
+def test_prompts_in_pieces(batch, S, D, H, slow):
+    _check_prompt(batch, S, D, 128, H=H, slow=slow)
 
 
 # The chunks' second copy in the cache (with sliced tails, and at the smallest cache that holds it), behind everything else, and
