@@ -322,7 +322,8 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   const int per_xcd = (total + 7) / 8;
   const int lin = (bx & 7) * per_xcd + (bx >> 3);
   if (lin >= total) return;
-  const int tn = lin / a.tiles_m, tm = lin - tn * a.tiles_m;
+  // the tiles of a W panel on one XCD; PLAIN, whose X is the larger operand and N a few tiles: those of a panel of X
+  const int tn = MODE == MODE_PLAIN ? lin % a.tiles_n : lin / a.tiles_m, tm = MODE == MODE_PLAIN ? lin / a.tiles_n : lin - tn * a.tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1247,11 +1248,14 @@ hipError_t launch_fwd_oproj(adore_ctx *ctx, const void *w_o_layer, const void *x
   return hipGetLastError();
 }
 // gi[tok][j] = W_ih[j][:] . x_tok for the ntok tokens of a prompt chunk (token b * per_seq + i at row
-// b * seq_rows + i of x), fp32 sums: fp32 storage on the fp32 tiles, bf16 on the 128x128 tile.  False if the shape does not
-// fit that tile.
+// b * seq_rows + i of x), fp32 sums: fp32 storage on the fp32 tiles, bf16 on the 128-wide tiles.  False if the shape does not
+// fit them.
 bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, const void *x, const void *W, float *out,
                              int ntok, int per_seq, int seq_rows, int N, int D) {
-  constexpr int kTile = 2;   // 128 x 128 x 64
+  // 256 x 128 x 64 where its rounds over the compute units come out shorter than those of 128 x 128 x 64 (65536 tokens x 384 rows of 4096: 401 ->
+  // 242 us, with the order of the tiles below; 8192 tokens, one round of either: 54 us for 66)
+  const long long wide = ((ntok + 255) / 256) * (N / 128), narrow = ((ntok + 127) / 128) * (N / 128);
+  const int kTile = float((wide + 255) / 256) * kTileMicros[1] < float((narrow + 255) / 256) * kTileMicros[2] ? 1 : 2;
   const bool bf16 = ctx->cfg.dtype == ADORE_BF16;
   if (bf16 && (N % kTiles[kTile].bn != 0 || D % kTiles[kTile].bk != 0)) return false;
   GemmArgs a;
@@ -1267,7 +1271,10 @@ bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, con
   a.tiles_m = (a.M + kTiles[kTile].bm - 1) / kTiles[kTile].bm;
   a.tiles_n = a.N / kTiles[kTile].bn;
   const dim3 grid((a.tiles_m * a.tiles_n + 7) / 8 * 8), block(512);
-  ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE_PLAIN, 128, 128, 64, 2, 2, 2, 3, 4>), grid, block, 0, st, a);
+  if (kTile == 1)
+    ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE_PLAIN, 256, 128, 64, 1, 4, 2, 3, 2>), grid, block, 0, st, a);
+  else
+    ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE_PLAIN, 128, 128, 64, 2, 2, 2, 3, 4>), grid, block, 0, st, a);
   return true;
 }
 
