@@ -503,6 +503,14 @@ int adore_create(const adore_config *cfg, const adore_weights *weights, void *wo
   ctx->ride_fits = cfg->score_mode != ADORE_SCORE_H2O && cfg->cache_slots <= kMaxSlots &&
                    riding_lds_bytes(cfg->max_positions - 1, cfg->cache_slots, cfg->rebuild_budget) + kAttendStaticLds <=
                        64 * 1024;
+  // ... or with the choice in parts, whose scratch lies where a prompt's chunk keeps its states.  (kPartsFrom: see ride_in_parts.)
+  ctx->ride_whole = ctx->ride_fits;
+  ctx->ride_parts = cfg->score_mode != ADORE_SCORE_H2O && cfg->rebuild_budget > 0 && parts_fit(*cfg) &&
+                    parts_bytes(*cfg) <= size_t(cfg->batch) * kPromptChunk * cfg->ctrl_hidden * 4 &&
+                    (!ctx->ride_whole || (cfg->max_positions > kPartsFrom && cfg->batch * cfg->heads <= 2048));
+  ctx->ride_fits = ctx->ride_whole || ctx->ride_parts;
+  ctx->part_keys = reinterpret_cast<uint64_t *>(ctx->zseq[0]);
+  ctx->part_arrived = ctx->ride_parts ? reinterpret_cast<int32_t *>(base + l.zseq[0] + parts_bytes(*cfg) - size_t(cfg->batch) * 4) : nullptr;
   ctx->side = ctx->side2 = ctx->stream;
   ctx->ev_ctrl = nullptr;
   ctx->ev_att = ctx->ev_join = ctx->ev_in = nullptr;
@@ -599,6 +607,7 @@ int adore_init_cache(adore_ctx *ctx, const void *prompt_k, const void *prompt_v,
   for (int l = 0; l < c.layers && !forward; ++l) {
     ADORE_TRY(launch_rebuild_gemm(ctx, l, static_cast<const char *>(hidden_store) + l * hs_layer, ctx->cur + 1, r0));
   }
+  if (ctx->ride_parts) ADORE_TRY(launch_fill_i32(ctx, ctx->part_arrived, 0, c.batch));
   if (side_steps(ctx)) ADORE_TRY(hipEventRecord(ctx->ev_att, st));   // the first selections wait for everything above
   ctx->steps_done = 0;
   if (side_steps(ctx)) {   // what the first step waits for is all above
@@ -959,6 +968,7 @@ int adore_set_state(adore_ctx *ctx, const int32_t *slot_pos, const float *scores
   if (cache_k) ADORE_TRY(hipMemcpyAsync(ctx->cache_k, cache_k, cache_bytes, hipMemcpyDeviceToDevice, ctx->stream));
   if (cache_v) ADORE_TRY(hipMemcpyAsync(ctx->cache_v, cache_v, cache_bytes, hipMemcpyDeviceToDevice, ctx->stream));
   ADORE_TRY(launch_rope_table(ctx));              // a context restored without an init has none yet
+  if (ctx->ride_parts) ADORE_TRY(launch_fill_i32(ctx, ctx->part_arrived, 0, c.batch));
   ADORE_TRY(hipStreamSynchronize(ctx->stream));   // `ins` lives on this stack frame
   if (ctx->overlap) ADORE_TRY(hipEventRecord(ctx->ev_att, ctx->stream));   // the next selections may start at once
   ctx->steps_done = 0;

@@ -24,6 +24,7 @@ constexpr int kPromptChunk = 512;     // tokens per GRU input-projection launch 
 constexpr int kMaxCtrlSplit = 16;     // D-slices of the GRU input projection
 constexpr int kCtrlSplitTokens = 256; // the projection is only sliced for launches of at most this many tokens
 constexpr int kRing = 8;              // copies of the per-step lists (slot map, reserved slot, free slots, rebuilt tokens)
+constexpr int kPartsFrom = 2000;      // positions from which the riding choice is made in parts (where it can be made in one workgroup)
 constexpr int kSyncEvery = 4;         // the side stream waits for the caller's stream once in this many steps
 static_assert(kSyncEvery + 3 <= kRing, "a list is rewritten kRing - 1 steps after its last reader; see adore_api.hip");
 
@@ -76,6 +77,8 @@ struct adore_ctx {
   // two copies, which the chunks of a prompt take in turn (the second may lie in the cache, or be missing)
   float *gi[2];              // [ksplit][tokens][3d'] GRU input pre-activations, per D-slice (steps: copy 0)
   float *zseq[2];            // [B][kPromptChunk][d'] GRU states of a prompt chunk, between its scan and its scoring
+  uint64_t *part_keys;       // the choice in parts: in zseq[0], which is free between inits ([B][keys], then part_arrived [B])
+  int32_t *part_arrived;
   size_t gi_rows[2];         // rows of 3d' floats in each; 0: no such copy
   float *cvec;               // rescore mode: [B][N_max][d']  W_1 (z_i + pos_b) + b_1 of every token
   float *avec;               // rescore mode: [d']  W_1 pos_w  (what one unit of distance adds)
@@ -96,6 +99,7 @@ struct adore_ctx {
   bool ins_from_list;
   bool ride;                 // decode_step lets the selections ride in the attention launch when it can
   bool ride_fits;            // ... and this configuration allows it (score mode, slots, LDS at the last step)
+  bool ride_whole, ride_parts;   // ... with the choice in one workgroup, in parts (long sequences)
   bool rode;                 // the last step did
   int32_t cur;               // ring index valid for the next attention
   int32_t steps_done;        // steps since the last init / set_state
@@ -159,6 +163,9 @@ struct RidingSelections {
 };
 // dynamic LDS of a workgroup that carries a sequence's selections in the attention launch at step n
 size_t riding_lds_bytes(int n, int K, int r);
+// ... or with the choice in parts: whether a configuration can, and the bytes of scratch it takes
+bool parts_fit(const adore_config &c);
+size_t parts_bytes(const adore_config &c);
 struct StepCtrl;   // the controller of a short step inside the step's other launches (ctrl_device.h)
 struct StepTail;
 hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k_new,

@@ -37,6 +37,7 @@ struct SchedArgs {
   int32_t *released_pos, *map_out, *rel_out;
   int H, K, N_max, n, x, R1;
   RebuildSelectArgs sel;
+  ChoiceParts parts;                // long sequences: the choice in workgroups of its own, behind the release ones of each sequence
 };
 
 struct AttendArgs {
@@ -64,7 +65,7 @@ struct AttendArgs {
 // hist: 256 words of LDS per wave for the release's radix select (the attention's own merge buffer, which these
 // workgroups do not use otherwise).
 template <int WAVES, int KPL>
-__device__ inline void selections_role(const AttendArgs &a, int e, uint64_t *dyn, uint32_t *hist) {
+__device__ __forceinline__ void selections_role(const AttendArgs &a, int e, uint64_t *dyn, uint32_t *hist) {
   // Rows short enough to fit four of them into a wave's registers can be released four to a wave: with hundreds of
   // sequences the role's workgroups would otherwise take half of the chip's wave slots from the attention for the
   // time their trips to memory take.
@@ -122,6 +123,35 @@ __device__ inline void selections_role(const AttendArgs &a, int e, uint64_t *dyn
   choice_from_keys(s.sel, b, row_copy, choice);
 }
 
+// The same for sequences whose scores do not fit a workgroup's LDS (one launch, parts.n_parts > 0): per sequence rel_wgs workgroups
+// release heads 1 .. H-1, one head 0, and n_parts more share the choice (choice_part).  The scores of the rows held are gathered from memory.
+template <int WAVES, int KPL>
+__device__ __forceinline__ void selections_in_parts_role(const AttendArgs &a, int e, uint64_t *dyn, uint32_t *hist) {
+  static_assert(WAVES == 4, "256 threads");
+  const SchedArgs &s = a.s;
+  const int per_seq = s.rel_wgs + 1 + s.parts.n_parts;
+  const int b = e / per_seq, part = e - b * per_seq;
+  const int wave = threadIdx.x >> 6;
+  __builtin_amdgcn_s_setprio(3);
+  if (part > s.rel_wgs) {
+    choice_part(s.sel, s.parts, b, part - s.rel_wgs - 1, s.slot_src + size_t(b) * s.H * s.K, dyn);
+    choice_arrive(s.sel, s.parts, b, dyn);
+    return;
+  }
+  // heads 1 .. H-1, a wave each; the last of these workgroups head 0
+  const int h = part < s.rel_wgs ? 1 + part * WAVES + wave : wave == 0 ? 0 : s.H;
+  if (h < s.H) {                 // whole waves
+    const int row = b * s.H + h;
+    release_row<KPL>(row, a.insert_slot[size_t(row) * a.ins_stride + a.ins_off], s.slot_src, s.slot_dst, s.score + size_t(b) * s.N_max,
+                     s.free_list, s.released_pos, s.map_out, s.rel_out, s.K, s.n, s.x, s.R1, nullptr, hist + wave * 256);
+  }
+  if (part == s.rel_wgs) {
+    __syncthreads();             // head 0's released positions, written by this workgroup
+    choice_released(s.sel, s.parts, b, s.released_pos + size_t(b) * s.H * s.R1);
+    choice_arrive(s.sel, s.parts, b, dyn);
+  }
+}
+
 template <typename T, int DH, int U, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs a) {
   constexpr int EPL = Vec16<T>::EPL;    // elements per lane
@@ -139,6 +169,17 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
     extern __shared__ uint64_t dyn_smem[];
     const int e = blockIdx.x;
     uint32_t *hist = reinterpret_cast<uint32_t *>(&s_acc[0][0]);
+    if constexpr (WAVES == 4) {
+      if (a.s.parts.n_parts > 0) {
+        switch (a.s.kpl) {
+          case 2: selections_in_parts_role<WAVES, 2>(a, e, dyn_smem, hist); break;
+          case 4: selections_in_parts_role<WAVES, 4>(a, e, dyn_smem, hist); break;
+          case 8: selections_in_parts_role<WAVES, 8>(a, e, dyn_smem, hist); break;
+          default: selections_in_parts_role<WAVES, 16>(a, e, dyn_smem, hist); break;
+        }
+        return;
+      }
+    }
     switch (a.s.kpl) {
       case 2: selections_role<WAVES, 2>(a, e, dyn_smem, hist); break;
       case 4: selections_role<WAVES, 4>(a, e, dyn_smem, hist); break;
@@ -312,6 +353,23 @@ hipError_t launch_typed(adore_ctx *ctx, const AttendArgs &a, int rows, int waves
 
 }  // namespace
 
+// The choice in parts (see ChoiceParts): where a workgroup's LDS does not hold a sequence's scores and keys.
+int choice_parts(int n) { return (n + kPartTokens - 1) / kPartTokens; }
+bool parts_fit(const adore_config &c) {
+  const int Rdim = max(c.rebuild_budget, 1), parts = choice_parts(c.max_positions - 1);
+  return c.cache_slots <= kMaxSlots && parts <= kMostParts && choice_part_keys(parts, Rdim) <= kMostPartKeys;
+}
+size_t parts_bytes(const adore_config &c) {
+  return size_t(c.batch) * choice_part_keys(choice_parts(c.max_positions - 1), max(c.rebuild_budget, 1)) * 8 + size_t(c.batch) * 4;
+}
+// Where either is possible the parts win from about 2000 positions on (per step, one workgroup / parts): 1 sequence of 4 heads behind 900
+// tokens 14.6 / 17.4 us, 16 of 32 behind 1024 73.8 / 78.3, 3 of 12 behind 2000 21.7 / 20.2, 8 of 32 behind 2000 55.3 / 53.5, 2 of 8 behind 3500
+// 21.8 / 19.4, 16 of 16 behind 3500 39.7 / 33.8; with more than 2048 heads in all one workgroup per sequence and four heads a wave
+// (hpw) take less from the attention (128 of 32: 258 / 263).  Behind 8192 tokens (4 of 32, K = 1024), where one workgroup's LDS does not
+// hold a sequence: 84 us a step with the selections in launches of their own on side streams, whose events hold the host for 77 us,
+// 50 in parts (attention and all of it 25 us, projection 26).
+bool ride_in_parts(const adore_ctx *ctx, int r) { return ctx->ride_parts && r > 0 && (!ctx->ride_whole || ctx->n >= kPartsFrom); }
+
 size_t riding_lds_bytes(int n, int K, int r) {
   return size_t((n + 2) / 2) * 8 + size_t((K + 1) / 2) * 8 + ridden_choice_lds_bytes(r, n);
 }
@@ -372,9 +430,19 @@ hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k
     r.K = c.cache_slots; r.H = c.heads; r.N_max = c.max_positions; r.n = ctx->n; r.r = sel->r;
     r.R1 = c.rebuild_budget + 1; r.Rdim = max(c.rebuild_budget, 1);
     r.words = (c.max_positions + 31) / 32;
-    extra = c.batch * (s.rel_wgs + 1);
-    a.n_sel = extra;
+    s.parts.n_parts = 0;
     dyn = riding_lds_bytes(ctx->n, c.cache_slots, sel->r);
+    if (ride_in_parts(ctx, sel->r)) {
+      waves = 4;
+      s.hpw = 1;
+      s.rel_wgs = (c.heads - 1 + waves - 1) / waves;
+      s.parts.n_parts = choice_parts(ctx->n);
+      s.parts.keys = ctx->part_keys;
+      s.parts.arrived = ctx->part_arrived;
+      dyn = choice_parts_lds_bytes(s.parts.n_parts, r.Rdim);
+    }
+    extra = c.batch * (s.rel_wgs + 1 + s.parts.n_parts);
+    a.n_sel = extra;
     if (ctrl) {
       a.c = *ctrl;
       extra += ctrl->n;

@@ -18,7 +18,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // 16-byte steps (both operands use the same assignment, so the order of k does not matter).
 // part[z][tok][j] = sum over the slice of W_ih[j][k] * x_tok[k].
 constexpr int kInputTileLds = 4 * 16 * 17;
-__device__ inline void ctrl_input_mfma_tile(const bf16_t *__restrict__ W_ih, const bf16_t *__restrict__ x,
+__device__ __forceinline__ void ctrl_input_mfma_tile(const bf16_t *__restrict__ W_ih, const bf16_t *__restrict__ x,
                                             float *__restrict__ part, int D, int G3, int ntok, int per_seq, int seq_rows,
                                             int kslice, int jt, int tt, int z, float *lds) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -59,7 +59,7 @@ __device__ inline void ctrl_input_mfma_tile(const bf16_t *__restrict__ W_ih, con
 // lane / (64 / N).
 template <int N, int OFF>
 struct ReduceRows {
-  __device__ static inline float run(float (&v)[N], int lane) {
+  __device__ static __forceinline__ float run(float (&v)[N], int lane) {
     const bool upper = (lane & OFF) != 0;
     float w[N / 2];
 #pragma unroll
@@ -73,7 +73,7 @@ struct ReduceRows {
 };
 template <int OFF>
 struct ReduceRows<1, OFF> {
-  __device__ static inline float run(float (&v)[1], int) {
+  __device__ static __forceinline__ float run(float (&v)[1], int) {
     float s = v[0];
 #pragma unroll
     for (int off = OFF; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
@@ -81,7 +81,7 @@ struct ReduceRows<1, OFF> {
   }
 };
 template <int N>
-__device__ inline float reduce_rows(float (&v)[N], int lane) {
+__device__ __forceinline__ float reduce_rows(float (&v)[N], int lane) {
   return ReduceRows<N, 32>::run(v, lane);
 }
 
@@ -92,7 +92,7 @@ constexpr int NB = 8;  // tokens per 256 threads
 // gi[tok][j] = sum_t W_ih[j][t] * x_tok[t]       (bias added in the cell kernel)
 // Token tok = b * per_seq + i reads the row x[(b * seq_rows + i) * D].
 template <typename T>
-__device__ inline void ctrl_input_plain_tile(const T *__restrict__ W_ih, const T *__restrict__ x, float *__restrict__ gi, int D,
+__device__ __forceinline__ void ctrl_input_plain_tile(const T *__restrict__ W_ih, const T *__restrict__ x, float *__restrict__ gi, int D,
                                              int G3, int ntok, int per_seq, int seq_rows, int jt, int tt, float *lds) {
   constexpr int EPL = Vec16<T>::EPL;
   const int j0 = jt * JT;
@@ -143,7 +143,7 @@ __device__ inline void ctrl_input_plain_tile(const T *__restrict__ W_ih, const T
   }
 }
 
-__device__ inline float sigmoidf_(float a) { return 1.0f / (1.0f + expf(-a)); }
+__device__ __forceinline__ float sigmoidf_(float a) { return 1.0f / (1.0f + expf(-a)); }
 
 struct CellArgs {
   const void *W_hh;            // [3d'][d'] storage type
@@ -160,7 +160,7 @@ struct CellArgs {
 };
 
 // sum of the D-slices of one input pre-activation, in slice order; loads go out eight at a time
-__device__ inline float gi_sum(const CellArgs &a, size_t tok, int j) {
+__device__ __forceinline__ float gi_sum(const CellArgs &a, size_t tok, int j) {
   const size_t stride = size_t(a.ntok) * 3 * a.dp;
   const float *p = a.gi + tok * 3 * a.dp + j;
   float s = 0.f;
@@ -190,23 +190,23 @@ __device__ inline float gi_sum(const CellArgs &a, size_t tok, int j) {
 // and hands the other half to its partner, so N rows cost N-1 shuffles instead of 6N.
 
 // two consecutive elements of a weight row, raw, and their conversion
-__device__ inline uint32_t load_raw2(const bf16_t *p) { return *reinterpret_cast<const uint32_t *>(p); }
-__device__ inline float2 load_raw2(const float *p) { return *reinterpret_cast<const float2 *>(p); }
-__device__ inline float dot2(uint32_t u, float x0, float x1) {
+__device__ __forceinline__ uint32_t load_raw2(const bf16_t *p) { return *reinterpret_cast<const uint32_t *>(p); }
+__device__ __forceinline__ float2 load_raw2(const float *p) { return *reinterpret_cast<const float2 *>(p); }
+__device__ __forceinline__ float dot2(uint32_t u, float x0, float x1) {
   return fmaf(__uint_as_float(u << 16), x0, __uint_as_float(u & 0xffff0000u) * x1);
 }
-__device__ inline float dot2(float2 u, float x0, float x1) { return fmaf(u.x, x0, u.y * x1); }
+__device__ __forceinline__ float dot2(float2 u, float x0, float x1) { return fmaf(u.x, x0, u.y * x1); }
 
 // out[row0 + r] = bias[row0 + r] + W[row0 + r][:] . x   for r < N, x held as (x0, x1) = x[2*lane], x[2*lane+1], in two
 // halves: the N row loads go out where the caller wants them (next to everything else a step reads), the arithmetic follows
 // once x is known.
 template <typename T, int N>
-__device__ inline void rows_request(const T *W, int row0, int lane, decltype(load_raw2(W)) (&raw)[N]) {
+__device__ __forceinline__ void rows_request(const T *W, int row0, int lane, decltype(load_raw2(W)) (&raw)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) raw[i] = load_raw2(W + size_t(row0 + i) * 128 + 2 * lane);
 }
 template <typename R, int N>
-__device__ inline void rows_finish(const R (&raw)[N], int row0, float x0, float x1, const float *bias, float *out, int lane) {
+__device__ __forceinline__ void rows_finish(const R (&raw)[N], int row0, float x0, float x1, const float *bias, float *out, int lane) {
   float v[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] = dot2(raw[i], x0, x1);
@@ -221,7 +221,7 @@ __device__ inline void rows_finish(const R (&raw)[N], int row0, float x0, float 
 
 // ---- merge of the attention's splits: element e of row bh ---------------------------------------
 // part: [rows][nsplit][d + 2] (sums, maximum, sum of weights); ml_out: null, or where the row's maximum and sum go
-__device__ inline void merge_splits(const float *part, float *out, float *ml_out, int bh, int e, int nsplit, int d) {
+__device__ __forceinline__ void merge_splits(const float *part, float *out, float *ml_out, int bh, int e, int nsplit, int d) {
   const float *p = part + size_t(bh) * nsplit * (d + 2);
   float M = -INFINITY;
   for (int s = 0; s < nsplit; ++s) M = fmaxf(M, p[s * (d + 2) + d]);
@@ -258,7 +258,7 @@ struct StepCtrl {
 };
 
 template <typename T>
-__device__ inline void step_ctrl_role(const StepCtrl &s, int e, float *lds) {
+__device__ __forceinline__ void step_ctrl_role(const StepCtrl &s, int e, float *lds) {
   constexpr int DP = 128;
   if (e < s.n_in) {
     const int jt = e % s.tiles_j, rest = e / s.tiles_j, tt = rest % s.tiles_t, zz = rest / s.tiles_t;
@@ -295,7 +295,7 @@ struct StepTail {
 constexpr int kStepTailLds = 8 * 128;   // floats
 // NT threads (256 or 512); lds: kStepTailLds floats.
 template <int NT>
-__device__ inline void step_tail_role(const StepTail &s, int e, float *lds) {
+__device__ __forceinline__ void step_tail_role(const StepTail &s, int e, float *lds) {
   constexpr int DP = 128, RPW = DP / (NT / 64);        // rows of W_1 per wave
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (e >= s.n_cell) {

@@ -20,7 +20,7 @@ namespace adore {
 // exponent, so that a digit from the top of the key would put nearly all of them into one or two bins (atomics on one
 // address, 64 in turn per wave) and tell nothing.  4 sequences of 8200 tokens: release 22.4 -> 19.0 us, choice 19.2 -> 17.1 us.
 template <class KeyFn>
-__device__ inline void radix_select(KeyFn key_of, int ncand, int c, uint32_t *s_hist, uint64_t *s_ctl,
+__device__ __forceinline__ void radix_select(KeyFn key_of, int ncand, int c, uint32_t *s_hist, uint64_t *s_ctl,
                                     uint64_t *thr, int *shift_out) {
   uint32_t *s_or = reinterpret_cast<uint32_t *>(s_ctl + 3), *s_and = s_or + 1;   // upper words of all candidates
   if (threadIdx.x == 0) {
@@ -105,7 +105,7 @@ __device__ inline void radix_select(KeyFn key_of, int ncand, int c, uint32_t *s_
 // Gathers the c selected keys (those with (key >> shift) >= thr) into s_keys in any
 // order, then writes their positions best first to out_pos[0..c).  s_count: one int.
 template <class KeyFn>
-__device__ inline void collect_sorted(KeyFn key_of, int ncand, int c, uint64_t thr, int shift,
+__device__ __forceinline__ void collect_sorted(KeyFn key_of, int ncand, int c, uint64_t thr, int shift,
                                       uint64_t *s_keys, int *s_count, int32_t *out_pos) {
   if (threadIdx.x == 0) *s_count = 0;
   __syncthreads();
@@ -139,7 +139,7 @@ __device__ inline void collect_sorted(KeyFn key_of, int ncand, int c, uint64_t t
 // KPL ballots each, took 9 us of a 21 us chain next to the attention.)
 // This lane's share of row `row` as it stands in memory: raw[j] = slot j*64 + lane (anything beyond K).
 template <int KPL>
-__device__ inline void release_fetch(int row, const int32_t *__restrict__ slot_src, int K, int (&raw)[KPL]) {
+__device__ __forceinline__ void release_fetch(int row, const int32_t *__restrict__ slot_src, int K, int (&raw)[KPL]) {
   const int lane = threadIdx.x & 63;
   const int32_t *sp = slot_src + size_t(row) * K;
 #pragma unroll
@@ -150,7 +150,7 @@ __device__ inline void release_fetch(int row, const int32_t *__restrict__ slot_s
 }
 
 template <int KPL>
-__device__ inline void release_row(int row, int s_ins, const int32_t *__restrict__ slot_src,
+__device__ __forceinline__ void release_row(int row, int s_ins, const int32_t *__restrict__ slot_src,
                                    int32_t *__restrict__ slot_dst, const float *sc,
                                    int32_t *__restrict__ free_list, int32_t *__restrict__ released_pos,
                                    int32_t *__restrict__ map_out, int32_t *__restrict__ rel_out, int K,
@@ -296,7 +296,7 @@ __host__ __device__ inline bool choice_scores_cached(int n, int words) {
 // after the release (uniform policy: every head of a sequence holds the same positions).  assign_heads: also
 // enter the chosen positions into the slot maps of all heads and reserve the next free slot (otherwise whoever
 // writes the rebuilt rows does that).  smem64: dynamic LDS of rebuild_choice_lds_bytes().
-__device__ inline void rebuild_choice_block(const RebuildSelectArgs &a, int b, const int32_t *res_row,
+__device__ __forceinline__ void rebuild_choice_block(const RebuildSelectArgs &a, int b, const int32_t *res_row,
                                             bool assign_heads, uint64_t *smem64) {
   const bool cached = choice_keys_cached(a.n, a.words);
   const bool sc_cached = choice_scores_cached(a.n, a.words);
@@ -373,11 +373,11 @@ __device__ inline void rebuild_choice_block(const RebuildSelectArgs &a, int b, c
 // already at work: choice_fill_keys needs only the scores (any subset of the workgroup's threads may run it, with
 // their own tid / nthreads), choice_from_keys then drops the residents (res_row) and picks.  Requires
 // choice_keys_cached(n, 0); LDS of ridden_choice_lds_bytes() at smem64.
-__device__ inline void choice_fill_keys(const float *sc, int n, uint64_t *s_cache, int tid, int nthreads) {
+__device__ __forceinline__ void choice_fill_keys(const float *sc, int n, uint64_t *s_cache, int tid, int nthreads) {
   for (int i = tid; i <= n; i += nthreads) s_cache[i] = rank_key(sc[i], i);
 }
 
-__device__ inline void choice_from_keys(const RebuildSelectArgs &a, int b, const int32_t *res_row, uint64_t *smem64) {
+__device__ __forceinline__ void choice_from_keys(const RebuildSelectArgs &a, int b, const int32_t *res_row, uint64_t *smem64) {
   uint64_t *s_cache = smem64;                                   // [n + 1]
   uint64_t *s_keys = smem64 + a.n + 1;                          // [max(r,1)]
   uint64_t *s_ctl = s_keys + max(a.r, 1);                       // [4]
@@ -405,6 +405,123 @@ __device__ inline void choice_from_keys(const RebuildSelectArgs &a, int b, const
   for (int t = r + tid; t < a.Rdim; t += blockDim.x) {
     a.rebuilt_pos[size_t(b) * a.Rdim + t] = -1;
     if (a.rb_out) a.rb_out[size_t(b) * a.Rdim + t] = -1;
+  }
+}
+
+// The choice in parts, for sequences too long for one workgroup.  After the release the candidates are the tokens that held no row before
+// it and the released ones, so nothing of it but the last step has to wait for the release: workgroups of 256 threads take kPartTokens
+// tokens each and leave the best r of those without a row, the workgroup that releases head 0 leaves what it released, and the one
+// of them that comes last picks the best r of all.  None waits for another: the last is told by a counter, which it clears for the
+// next launch.  Keys and counter pass between the workgroups (and XCDs) as agent-scope atomics.
+constexpr int kPartTokens = 1024, kMostParts = 64, kMostPartKeys = 4096;
+struct ChoiceParts {
+  uint64_t *keys;              // [B][n_parts * max(R, 1) + R1], 0 = none
+  int32_t *arrived;            // [B], 0 between launches
+  int n_parts;                 // 0: the choice is not made in parts
+};
+__host__ __device__ inline int choice_part_keys(int n_parts, int Rdim) { return n_parts * Rdim + Rdim + 1; }
+inline size_t choice_parts_lds_bytes(int n_parts, int Rdim) {
+  const int total = choice_part_keys(n_parts, Rdim), most = total > kPartTokens ? total : kPartTokens;
+  return size_t(most) * 8 + size_t(Rdim) * 8 + 4 * 8 + 256 * 4 + kPartTokens / 32 * 4 + size_t(Rdim) * 4 + 16;
+}
+
+__device__ __forceinline__ void put_part_key(uint64_t *p, uint64_t key) {
+  __hip_atomic_store(p, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One part: tokens part * kPartTokens .. below a.n.  row: head 0's positions before the release (the current token is not among them).
+__device__ __forceinline__ void choice_part(const RebuildSelectArgs &a, const ChoiceParts &c, int b, int part, const int32_t *row, uint64_t *smem64) {
+  uint64_t *s_key = smem64;                                     // [kPartTokens]
+  uint64_t *s_ctl = s_key + kPartTokens;                        // [4]
+  uint32_t *s_hist = reinterpret_cast<uint32_t *>(s_ctl + 4);   // [256]
+  uint32_t *s_bits = s_hist + 256;                              // [kPartTokens / 32] tokens that hold a row
+  int *s_count = reinterpret_cast<int *>(s_bits + kPartTokens / 32);   // [2] candidates, keys left behind
+  constexpr int TPT = kPartTokens / 256, SPT = kMaxSlots / 256;
+  const int tid = threadIdx.x, t0 = part * kPartTokens, count = min(kPartTokens, a.n - t0);
+  const float *sc = a.score + size_t(b) * a.N_max + t0;
+  float v[TPT];
+  int pos[SPT];
+#pragma unroll
+  for (int u = 0; u < TPT; ++u) v[u] = sc[min(tid + 256 * u, count - 1)];
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) pos[u] = tid + 256 * u < a.K ? row[tid + 256 * u] : -1;
+  if (tid < kPartTokens / 32) s_bits[tid] = 0;
+  if (tid < 2) s_count[tid] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) {
+    const int p = pos[u] - t0;
+    if (pos[u] >= 0 && p >= 0 && p < count) atomicOr(&s_bits[p >> 5], 1u << (p & 31));
+  }
+  __syncthreads();
+  int mine = 0;
+#pragma unroll
+  for (int u = 0; u < TPT; ++u) {
+    const int i = tid + 256 * u;
+    const bool free = i < count && !((s_bits[i >> 5] >> (i & 31)) & 1u);
+    s_key[i] = free ? rank_key(v[u], t0 + i) : uint64_t(0);
+    mine += free;
+  }
+  if (mine) atomicAdd(&s_count[0], mine);
+  __syncthreads();
+  auto key_of = [&](int i) -> uint64_t { return s_key[i]; };
+  uint64_t thr = 0;
+  int shift = 0;
+  if (s_count[0] > a.r) radix_select(key_of, count, a.r, s_hist, s_ctl, &thr, &shift);   // uniform over the workgroup
+  uint64_t *out = c.keys + size_t(b) * choice_part_keys(c.n_parts, a.Rdim) + size_t(part) * a.Rdim;
+#pragma unroll
+  for (int u = 0; u < TPT; ++u) {
+    const uint64_t key = s_key[tid + 256 * u];
+    if (key != 0 && (key >> shift) >= thr) {
+      const int idx = atomicAdd(&s_count[1], 1);
+      if (idx < a.Rdim) put_part_key(out + idx, key);
+    }
+  }
+  __syncthreads();
+  for (int i = s_count[1] + tid; i < a.Rdim; i += 256) put_part_key(out + i, 0);
+}
+
+// The keys of the n_rel released tokens of head 0 (LDS or global memory written by this workgroup behind a barrier).
+__device__ __forceinline__ void choice_released(const RebuildSelectArgs &a, const ChoiceParts &c, int b, const int32_t *released) {
+  uint64_t *out = c.keys + size_t(b) * choice_part_keys(c.n_parts, a.Rdim) + size_t(c.n_parts) * a.Rdim;
+  const float *sc = a.score + size_t(b) * a.N_max;
+  for (int i = threadIdx.x; i < a.Rdim + 1; i += blockDim.x) {
+    const int p = i < a.R1 ? released[i] : -1;
+    put_part_key(out + i, p >= 0 ? rank_key(sc[p], p) : uint64_t(0));
+  }
+}
+
+// Behind either of the two: the last workgroup of the sequence to get here chooses.
+__device__ __forceinline__ void choice_arrive(const RebuildSelectArgs &a, const ChoiceParts &c, int b, uint64_t *smem64) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this wave's keys are where the others will look for them
+  __syncthreads();
+  const int total = choice_part_keys(c.n_parts, a.Rdim);
+  uint64_t *s_key = smem64;                                     // [total]
+  uint64_t *s_keys = s_key + total;                             // [Rdim]
+  uint64_t *s_ctl = s_keys + a.Rdim;                            // [4]
+  uint32_t *s_hist = reinterpret_cast<uint32_t *>(s_ctl + 4);   // [256]
+  int *s_sel = reinterpret_cast<int *>(s_hist + 256);           // [Rdim]
+  int *s_count = s_sel + a.Rdim;                                // [2]
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    const int before = __hip_atomic_fetch_add(c.arrived + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_count[1] = before == c.n_parts;                           // n_parts parts and the release
+    if (before == c.n_parts) __hip_atomic_store(c.arrived + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (s_count[1] == 0) return;                                  // uniform over the workgroup
+  const uint64_t *in = c.keys + size_t(b) * total;
+  for (int i = tid; i < total; i += blockDim.x) s_key[i] = __hip_atomic_load(in + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  auto key_of = [&](int i) -> uint64_t { return s_key[i]; };
+  uint64_t thr;
+  int shift;
+  radix_select(key_of, total, a.r, s_hist, s_ctl, &thr, &shift);
+  collect_sorted(key_of, total, a.r, thr, shift, s_keys, s_count, s_sel);
+  for (int t = tid; t < a.Rdim; t += blockDim.x) {
+    const int p = t < a.r ? s_sel[t] : -1;
+    a.rebuilt_pos[size_t(b) * a.Rdim + t] = p;
+    if (a.rb_out) a.rb_out[size_t(b) * a.Rdim + t] = p;
   }
 }
 

@@ -1,5 +1,5 @@
-"""Steps that carry their controller inside the attention's and the projection's launches, against the same steps with the controller in
-launches of its own on the side streams (which the oracle follows elsewhere): the same arithmetic in the same order, bit for bit."""
+"""Steps that carry their selections and their controller inside the attention's and the projection's launches, against the same steps with
+both in launches of their own on the side streams (which the oracle follows elsewhere): the same arithmetic in the same order, bit for bit."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -15,14 +15,28 @@ CASES = [
     (16, 8, 128, 1024, 96, 32, 300, "bf16", False, 10000.0),  # 256 narrow tiles: the tail behind them, or wider tiles
     (4, 32, 128, 4096, 128, 32, 200, "bf16", False, 0.0),  # the tail behind 256 narrow tiles, splits merged there
     (2, 8, 128, 392, 150, 5, 180, "bf16", True, 0.0),      # a width the projection's tiles do not take: launches of its own
+    # sequences whose choice is made in parts of 1024 tokens: five heads, one, parts that begin within the run, the most slots and
+    # tokens to rebuild, scores that are made anew, fp32, fewer candidates than ranks in a part
+    (2, 5, 64, 128, 64, 8, 7164, "bf16", False, 0.0), (1, 1, 64, 128, 20, 4, 40955, "bf16", False, 0.0),
+    (2, 2, 128, 256, 1024, 300, 6000, "bf16", False, 0.0), (1, 4, 64, 128, 130, 48, 5117, "bf16", True, 0.0),
+    (3, 4, 64, 128, 200, 17, 6140, "f32", False, 0.0), (1, 3, 64, 128, 1000, 40, 5116, "bf16", False, 0.0),
+    (2, 4, 64, 128, 300, 8, 1996, "bf16", False, 0.0),     # from one workgroup to parts within the run
 ]
 
 
-def _run(case, streams, ordered, monkeypatch, steps=9):
+def _of_state(state, n):
+    """What a snapshot at position n defines: rows of free slots hold whatever was there."""
+    free = (state["slot_pos"] < 0)[None, ..., None]
+    return [state["slot_pos"], state["z"], state["cache_k"].masked_fill(free, 0), state["cache_v"].masked_fill(free, 0),
+            state["scores"][:, :n].clone()]
+
+
+def _run(case, carried, ordered, monkeypatch, steps=9):
     import torch
     from paper_2407_02328_amd import Adore, make_config
     B, H, d, D, K, R, S, dtype, rescore, rope = case
-    monkeypatch.setenv("ADORE_STEP_STREAMS", streams)
+    monkeypatch.setenv("ADORE_STEP_STREAMS", "0" if carried else "1")
+    monkeypatch.setenv("ADORE_NO_RIDE", "0" if carried else "1")
     st = torch.bfloat16 if dtype == "bf16" else torch.float32
     g = torch.Generator(device="cuda")
     g.manual_seed(B * 1009 + H * 31 + K)
@@ -51,15 +65,15 @@ def _run(case, streams, ordered, monkeypatch, steps=9):
     a.get_state(**state)
     torch.cuda.synchronize()
     a.close()
-    return seen + [state[k] for k in ("slot_pos", "z", "cache_k", "cache_v")] + [state["scores"][:, :S + steps]]
+    return seen + _of_state(state, S + steps)
 
 
 @pytest.mark.parametrize("ordered", [True, False])
 @pytest.mark.parametrize("case", CASES)
-def test_carried_controller_is_the_controller(case, ordered, monkeypatch):
+def test_carried_steps_are_the_steps(case, ordered, monkeypatch):
     import torch
-    carried = _run(case, "0", ordered, monkeypatch)
-    apart = _run(case, "1", ordered, monkeypatch)
+    carried = _run(case, True, ordered, monkeypatch)
+    apart = _run(case, False, ordered, monkeypatch)
     for i, (x, y) in enumerate(zip(carried, apart)):
         same = torch.equal(x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32), y.view(torch.int16 if y.dtype == torch.bfloat16 else torch.int32))
         assert same, f"{case}: tensor {i} of {len(carried)}"
