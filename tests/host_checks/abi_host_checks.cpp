@@ -178,7 +178,9 @@ int main() {
           groups += launched_grid[i].x;
         }
         EXPECT(!launched_grid.empty());
-        const int32_t queries = launched_grid.empty() ? 1 : int32_t(launched_block[0].x) / 8;
+        // blocks of 64 queries where they fill the compute units, else of 32; four waves either way
+        const int32_t queries = int64_t(rows) * ((seq + 63) / 64) < (d == 128 ? 256 : 512) ? 32 : 64;
+        EXPECT(!launched_block.empty() && launched_block[0].x == 256);
         EXPECT(groups == uint64_t(rows) * ((seq + queries - 1) / queries));
       }
   if (failures) {
