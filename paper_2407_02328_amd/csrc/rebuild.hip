@@ -272,7 +272,11 @@ __device__ inline void cur_rows_role(const GemmArgs &a, int e, u32x4 *smem) {
 //                        k-step.  With LS >= 3 the tile of ks+1 is complete during ks, so the first
 //                        fragments of the next step are fetched before the barrier.
 //   LDS -> fragments:    one 16-wide k-slice ahead of the MFMAs that use them
-// sched_barrier keeps the compiler from sinking the fragment loads below the MFMAs they overlap with.
+// sched_barrier keeps the compiler from sinking the fragment loads below the MFMAs they overlap with.  Where a wave has several
+// MFMAs a slice, its LDS reads and writes and its reads from memory go out one behind each of them instead of in front of and
+// behind them all (a wave issues in order, and an MFMA waits for the one before it): M = 512 43.0 -> 42.0 us, 1024 73.5 -> 71.8, 2048
+// 133.5 -> 130.5, 256 35.0 -> 34.0 at N = 8192, D = 4096; two LDS operations behind each, whatever they are, 131.3 at M = 2048, the
+// reads from memory in the last slice 135; with one MFMA a slice (128x32) 24.5 -> 25.5, left as it was.
 template <int MODE_, int BM, int BN, int BK, int KG, int WM, int WN, int LS, int NS>
 __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   constexpr int MODE = MODE_ == MODE_TAIL ? MODE_REBUILD : MODE_;
@@ -286,6 +290,7 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   constexpr int KSUB = BK / 16 / KG;     // 16-wide k-slices per wave and k-step
   static_assert(KSUB == 2 || KSUB == 4, "fragment double buffering needs an even number of k-slices");
   constexpr int LEAD = LS - 1;
+  constexpr bool kMixed = TM * TN > 1;
   constexpr int STAGE = (BM + BN) * CH;  // 16-byte units per LDS stage
   constexpr int LOOP_BYTES = LS * STAGE * 16;
   constexpr int RED_BYTES = KG == 2 ? 4 * TM * TN * 16 * 64 * 4 : 0;
@@ -477,12 +482,24 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
       } else if (LS > 2) {                                                               \
         IF((KS) + 1 < nk) { FRAGS(0, st1, kbase) }                                       \
       }                                                                                  \
-      __builtin_amdgcn_sched_barrier(0);                                                 \
-      MFMAS(kk & 1)                                                                      \
-      __builtin_amdgcn_sched_barrier(0);                                                 \
+      if (!kMixed) {                                                                     \
+        __builtin_amdgcn_sched_barrier(0);                                               \
+        MFMAS(kk & 1)                                                                    \
+        __builtin_amdgcn_sched_barrier(0);                                               \
+      }                                                                                  \
       if (kk == 0) {                                                                     \
         IF((KS) + LEAD < nk) { LSTORE(((U) + LEAD) % NS, stw) }                          \
         IF((KS) + LEAD + NS < nk) { GLOAD(((U) + LEAD) % NS, (KS) + LEAD + NS) }         \
+      }                                                                                  \
+      if (kMixed) {                                                                      \
+        MFMAS(kk & 1)                                                                    \
+        _Pragma("unroll") for (int q = 0; q < TM * TN; ++q) {                            \
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   /* a matrix instruction */ \
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   /* an LDS read */          \
+          __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);   /* an LDS write */         \
+          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   /* a read from memory */   \
+        }                                                                                \
+        __builtin_amdgcn_sched_barrier(0);                                               \
       }                                                                                  \
     }                                                                                    \
     __syncthreads();                                                                     \
