@@ -645,8 +645,9 @@ int do_attend(adore_ctx *ctx, int32_t layer, const void *q, const void *k_new, c
   return ADORE_OK;
 }
 
+// released: the H2O mode's release is done already (with the attention)
 int do_schedule(adore_ctx *ctx, const void *x_n, const float *score_override, int32_t *slot_map,
-                int32_t *released_pos, int32_t *rebuilt_pos) {
+                int32_t *released_pos, int32_t *rebuilt_pos, bool released = false) {
   const adore_config &c = ctx->cfg;
   if (h2o_mode(ctx)) {
     // The step's attention is added to the scores, every head releases on its own (how many rows, it counts
@@ -654,7 +655,7 @@ int do_schedule(adore_ctx *ctx, const void *x_n, const float *score_override, in
     // which cannot happen before there are more tokens than persistent rows; how many are chosen is decided on
     // the device, and the GEMM skips the ranks that stay empty.
     const int dst = (ctx->cur + 1) % kRing;
-    ADORE_TRY(launch_h2o_release(ctx, ctx->cur, dst, slot_map, released_pos));
+    if (!released) ADORE_TRY(launch_h2o_release(ctx, ctx->cur, dst, slot_map, released_pos));
     ADORE_TRY(launch_h2o_choice(ctx, dst, dst, ctx->n, slot_map, rebuilt_pos));
     ctx->scheduled = true;
     ctx->r_step = ctx->n + 1 > c.cache_slots - c.rebuild_budget - 1 ? c.rebuild_budget : 0;
@@ -797,9 +798,12 @@ int adore_decode_step(adore_ctx *ctx, const void *q, const void *k_new, const vo
     return do_ridden_step(ctx, q, k_new, v_new, hidden_store, x_n, score_override, out, slot_map);
   }
   if (h2o_mode(ctx)) {   // the selections need this step's attention
-    int rc = do_attend(ctx, 0, q, k_new, v_new, out);
+    const bool releases = h2o_attend_releases(ctx);
+    int rc = ADORE_OK;
+    if (releases) ADORE_TRY(launch_h2o_attend_release(ctx, q, k_new, v_new, out, (ctx->cur + 1) % kRing, slot_map));
+    else rc = do_attend(ctx, 0, q, k_new, v_new, out);
     if (rc != ADORE_OK) return rc;
-    rc = do_schedule(ctx, x_n, score_override, slot_map, nullptr, nullptr);
+    rc = do_schedule(ctx, x_n, score_override, slot_map, nullptr, nullptr, releases);
     if (rc != ADORE_OK) return rc;
     return do_rebuild(ctx, 0, hidden_store);
   }

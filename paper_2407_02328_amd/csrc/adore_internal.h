@@ -205,6 +205,10 @@ inline bool h2o_mode(const adore_ctx *ctx) { return ctx->cfg.score_mode == ADORE
 hipError_t launch_h2o_init_scores(adore_ctx *ctx, const float *score_init, int S);
 hipError_t launch_h2o_init_select(adore_ctx *ctx, int dst, int lists, int S, int keep);
 hipError_t launch_h2o_release(adore_ctx *ctx, int src, int dst, int32_t *map_out, int32_t *rel_out);
+// a step's attention with the release behind it (adore_decode_step, where h2o_attend_releases())
+bool h2o_attend_releases(const adore_ctx *ctx);
+hipError_t launch_h2o_attend_release(adore_ctx *ctx, const void *q, const void *k_new, const void *v_new, float *out, int dst,
+                                     int32_t *map_out);
 // n: the last position that exists (the current token of a step, S - 1 at init)
 hipError_t launch_h2o_choice(adore_ctx *ctx, int maps, int lists, int n, int32_t *map_out, int32_t *rb_out);
 size_t h2o_choice_lds_bytes(const adore_config &c, int n);

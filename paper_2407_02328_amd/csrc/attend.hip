@@ -152,7 +152,35 @@ __device__ __forceinline__ void selections_in_parts_role(const AttendArgs &a, in
   }
 }
 
-template <typename T, int DH, int U, int WAVES>
+// The H2O mode's release of row bh by the first wave of the workgroup that attended over it: what h2o_release_kernel does, from the
+// logits in LDS and the row's (M, L) at hand.  s.x: the rows to keep.
+template <int KPL>
+__device__ __forceinline__ void h2o_release_role(const AttendArgs &a, int bh, int s_ins, float M, float L, const float *logit, uint32_t *hist) {
+  const SchedArgs &s = a.s;
+  const int lane = threadIdx.x & 63;
+  float *sc = const_cast<float *>(s.score) + size_t(bh) * s.N_max;
+  int raw[KPL];
+  float held[KPL];
+  release_fetch<KPL>(bh, s.slot_src, s.K, raw);
+#pragma unroll
+  for (int j = 0; j < KPL; ++j) {
+    const int k = j * 64 + lane, pos = k == s_ins ? s.n : raw[j];
+    held[j] = k < s.K && pos >= 0 && pos != s.n ? sc[pos] : 0.f;
+  }
+#pragma unroll
+  for (int j = 0; j < KPL; ++j) {
+    const int k = j * 64 + lane, pos = k == s_ins ? s.n : raw[j];
+    if (k >= s.K || pos < 0) continue;
+    const float p = exp2f(logit[k] - M) / L;
+    held[j] = pos == s.n ? p : held[j] + p;      // the current token starts its score here
+    sc[pos] = held[j];
+  }
+  release_row<KPL>(bh, s_ins, s.slot_src, s.slot_dst, sc, s.free_list, s.released_pos, s.map_out, s.rel_out, s.K, s.n, -1, s.R1, nullptr,
+                   hist, raw, s.x, held);
+}
+
+// KPL > 0: the H2O mode's whole step, each row's release behind its attention (rows that one workgroup takes whole).
+template <typename T, int DH, int U, int WAVES, int KPL = 0>
 __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs a) {
   constexpr int EPL = Vec16<T>::EPL;    // elements per lane
   constexpr int LPR = DH / EPL;         // lanes per cache row
@@ -165,8 +193,8 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
   __shared__ float s_acc[G][DH];
   static_assert(G * DH >= WAVES * 256 && G * DH >= (sizeof(T) == 2 ? kInputTileLds : 4 * JT * NB), "room for one 256-bin histogram per wave, for an input tile's sums");
 
-  if (int(blockIdx.x) < a.n_sel) {   // uniform over the workgroup
-    extern __shared__ uint64_t dyn_smem[];
+  extern __shared__ uint64_t dyn_smem[];
+  if (KPL == 0 && int(blockIdx.x) < a.n_sel) {   // uniform over the workgroup
     const int e = blockIdx.x;
     uint32_t *hist = reinterpret_cast<uint32_t *>(&s_acc[0][0]);
     if constexpr (WAVES == 4) {
@@ -188,7 +216,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
     }
     return;
   }
-  if (int(blockIdx.x) < a.n_sel + a.c.n) {
+  if (KPL == 0 && int(blockIdx.x) < a.n_sel + a.c.n) {
     step_ctrl_role<T>(a.c, blockIdx.x - a.n_sel, &s_acc[0][0]);
     return;
   }
@@ -265,7 +293,11 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
       for (int off = LPR / 2; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
       logit[u] = valid[u] ? dot : -INFINITY;
       mb = fmaxf(mb, logit[u]);
-      if (a.logit_out && lig == 0 && base + u * G + grp < end) a.logit_out[size_t(bh) * a.K + base + u * G + grp] = logit[u];
+      if (KPL > 0) {
+        if (lig == 0 && base + u * G + grp < end) reinterpret_cast<float *>(dyn_smem)[base + u * G + grp] = logit[u];
+      } else if (a.logit_out && lig == 0 && base + u * G + grp < end) {
+        a.logit_out[size_t(bh) * a.K + base + u * G + grp] = logit[u];
+      }
     }
     if (mb == -INFINITY) continue;  // nothing occupied so far in this lane group
     const float corr = exp2f(m - mb);
@@ -308,7 +340,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
     }
     if (a.nsplit == 1) {
       a.out[size_t(bh) * DH + tid] = sum / L;   // the current token is always present: L > 0
-      if (a.ml_out && tid == 0) {
+      if (KPL == 0 && a.ml_out && tid == 0) {
         a.ml_out[size_t(bh) * 2] = M;
         a.ml_out[size_t(bh) * 2 + 1] = L;
       }
@@ -321,11 +353,29 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
       }
     }
   }
+  if constexpr (KPL > 0) {
+    if (tid >= 64) return;                // (the sums below in the order of the ones above)
+    float L = 0.f;
+#pragma unroll 8
+    for (int g = 0; g < G; ++g) L += s_l[g];
+    __shared__ uint32_t s_hist[256];
+    h2o_release_role<KPL>(a, bh, s_ins, M, L, reinterpret_cast<const float *>(dyn_smem), s_hist);
+  }
 }
 
 template <int DH>
 __global__ __launch_bounds__(DH) void attend_combine_kernel(const float *part, float *out, int nsplit, float *ml_out) {
   merge_splits(part, out, ml_out, blockIdx.x, threadIdx.x, nsplit, DH);
+}
+
+template <typename T, int DH>
+hipError_t launch_h2o_typed(adore_ctx *ctx, const AttendArgs &a, int rows) {
+  ScopedTimer t(ctx, ADORE_KERNEL_ATTEND, ctx->stream);
+  const size_t lds = size_t(a.K) * 4;
+  if (a.K <= 256) ADORE_LAUNCH(t, (attend_kernel<T, DH, 4, 4, 4>), dim3(rows), dim3(256), lds, ctx->stream, a);
+  else if (a.K <= 512) ADORE_LAUNCH(t, (attend_kernel<T, DH, 4, 4, 8>), dim3(rows), dim3(256), lds, ctx->stream, a);
+  else ADORE_LAUNCH(t, (attend_kernel<T, DH, 4, 4, 16>), dim3(rows), dim3(256), lds, ctx->stream, a);
+  return hipGetLastError();
 }
 
 template <typename T, int DH>
@@ -459,6 +509,34 @@ hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k
   }
   return c.head_dim == 128 ? launch_typed<float, 128>(ctx, a, rows, waves, extra, dyn, !ctrl)
                            : launch_typed<float, 64>(ctx, a, rows, waves, extra, dyn, !ctrl);
+}
+
+// H2O mode: attention, the step's probabilities added to the scores and the release in one launch, where a workgroup takes a whole
+// row.  16 sequences of 32 heads, K = 512: 22.5 + 15.5 us (and the logits' way through memory) -> 29 us, the
+// step 101 -> 90 us.
+bool h2o_attend_releases(const adore_ctx *ctx) { return h2o_mode(ctx) && ctx->nsplit == 1; }
+
+hipError_t launch_h2o_attend_release(adore_ctx *ctx, const void *q, const void *k_new, const void *v_new, float *out, int dst,
+                                     int32_t *map_out) {
+  const adore_config &c = ctx->cfg;
+  AttendArgs a = {};
+  a.q = q; a.k_new = k_new; a.v_new = v_new;
+  a.Kc = ctx->cache_k; a.Vc = ctx->cache_v;
+  a.slot_pos = ctx->slot_pos[ctx->cur];
+  a.insert_slot = reserved_slots(ctx, ctx->cur);
+  a.ins_stride = ctx->ins_stride; a.ins_off = ctx->ins_off;
+  a.out = out;
+  a.K = c.cache_slots; a.chunk = c.cache_slots; a.nsplit = 1;
+  a.scale_log2 = 1.4426950408889634f / sqrtf(float(c.head_dim));
+  SchedArgs &s = a.s;
+  s.slot_src = ctx->slot_pos[ctx->cur]; s.slot_dst = ctx->slot_pos[dst];
+  s.score = ctx->score; s.free_list = ctx->free_list[dst];
+  s.released_pos = ctx->released_pos; s.map_out = map_out; s.rel_out = nullptr;
+  s.K = c.cache_slots; s.N_max = c.max_positions; s.n = ctx->n;
+  s.x = c.cache_slots - c.rebuild_budget - 1; s.R1 = c.rebuild_budget + 1;
+  const int rows = c.batch * c.heads;
+  if (c.dtype == ADORE_BF16) return c.head_dim == 128 ? launch_h2o_typed<bf16_t, 128>(ctx, a, rows) : launch_h2o_typed<bf16_t, 64>(ctx, a, rows);
+  return c.head_dim == 128 ? launch_h2o_typed<float, 128>(ctx, a, rows) : launch_h2o_typed<float, 64>(ctx, a, rows);
 }
 
 }  // namespace adore

@@ -155,7 +155,7 @@ __device__ __forceinline__ void release_row(int row, int s_ins, const int32_t *_
                                    int32_t *__restrict__ free_list, int32_t *__restrict__ released_pos,
                                    int32_t *__restrict__ map_out, int32_t *__restrict__ rel_out, int K,
                                    int n, int x, int R1, int32_t *row_copy, uint32_t *hist, const int *raw = nullptr,
-                                   int m_keep = 0) {
+                                   int m_keep = 0, const float *held = nullptr) {
   const int lane = threadIdx.x & 63;
   const int32_t *sp = slot_src + size_t(row) * K;
 
@@ -172,7 +172,7 @@ __device__ __forceinline__ void release_row(int row, int s_ins, const int32_t *_
   for (int j = 0; j < KPL; ++j) {
     khi[j] = klo[j] = 0;
     if (pos[j] >= 0 && pos[j] != n) {
-      const uint64_t key = rank_key(sc[pos[j]], pos[j]);
+      const uint64_t key = rank_key(held ? held[j] : sc[pos[j]], pos[j]);
       khi[j] = uint32_t(key >> 32);
       klo[j] = uint32_t(key);
       cand |= 1u << j;
