@@ -424,8 +424,8 @@ def prefill_line(w, args):
                      peak=MFMA_PEAK_TFLOPS["f32"], unit="TFLOP/s",
                      frac=round(cell_flops / (us["ctrl_cell"] * 1e-6) / 1e12 / MFMA_PEAK_TFLOPS["f32"], 5),
                      traffic=None, us_per_launch=round(us["ctrl_cell"], 1),
-                     note="a recurrence: one workgroup per sequence, so at most B of the 256 compute units work on it (with bf16 weights "
-                          "on the matrix cores, the state as three bf16 terms; priced as the fp32 product that is)")
+                     note="a recurrence: with bf16 weights on the matrix cores (the state as three bf16 terms; priced as the fp32 product that "
+                          "is), a chunk in up to 14 pieces per sequence whose joints a second launch checks; the scoring is counted here too")
     roof_in = dict(kernel="ctrl_input", bound="mfma", achieved=round(in_flops / (us["ctrl_input"] * 1e-6) / 1e12, 1),
                    peak=MFMA_PEAK_TFLOPS.get(w.dtype, 157.3), unit="TFLOP/s",
                    frac=round(in_flops / (us["ctrl_input"] * 1e-6) / 1e12 / MFMA_PEAK_TFLOPS.get(w.dtype, 157.3), 4),
