@@ -149,18 +149,20 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
   int *s_flag = reinterpret_cast<int *>(s_part + 2 * KB * NQ);      // [0] count images again, [1] a crowded bin of equal weights, [2] count ranges again, [3] some queries need images counted, [4] huge weights
 
   // Workgroup -> (row, query block): all blocks of a row on one XCD (consecutive workgroups go to the 8 XCDs in turn), so
-  // that its K and V come from memory once; within a row the blocks with the most keys first.
+  // that its K and V come from memory once; within a row the blocks with the most keys first.  Rows that do not make up a
+  // group of eight go to all XCDs and come first, the longest blocks of all of them before the next: a launch ends with
+  // short blocks (behind the others before: 10 rows of 6152 tokens, d = 64, 294 -> 215 us; 12 of 2048, d = 128, 105 -> 83; 61 of
+  // 2048, 290 -> 264).
   const int nq = (a.S + NQ - 1) / NQ;
-  const int L = blockIdx.x, full = a.rows / 8 * 8;
+  const int odd = a.rows & 7, L = int(blockIdx.x) - odd * nq;
   int row_, qi;
-  if (L < full * nq) {
+  if (L < 0) {
+    qi = int(blockIdx.x) / odd;
+    row_ = (a.rows & ~7) + int(blockIdx.x) - qi * odd;
+  } else {
     const int slot = L >> 3;
     row_ = slot / nq * 8 + (L & 7);
     qi = slot - slot / nq * nq;
-  } else {
-    const int rest = L - full * nq;
-    row_ = full + rest / nq;
-    qi = rest - rest / nq * nq;
   }
   const int q0 = (nq - 1 - qi) * NQ;
   const int nkeys = min(a.S, q0 + NQ);
