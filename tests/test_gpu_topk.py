@@ -208,6 +208,7 @@ def test_topk_attention_at_the_long_context_shape_sampled_rows():
     (1, 257, 64, 256, 0), (1, 320, 128, 400, 0),                                      # top_k at and beyond the sequence
     (512, 40, 64, 12, 0), (260, 65, 128, 20, 0),                                      # query blocks of 64, key steps of 64
     (512, 64, 128, 63, 0), (176, 129, 128, 40, 0), (128, 193, 64, 50, 0), (56, 577, 128, 96, 0), (104, 300, 64, 30, 250),
+    (7, 193, 64, 20, 0), (15, 290, 128, 30, 0), (61, 330, 128, 40, 0),                # rows that make up no group of eight, which go first
     (1, 300, 128, 50, 300), (2, 200, 64, 30, 60),   # (runs of) identical keys: more equal weights than are ranked directly
 ])
 def test_topk_attention_at_the_edges_of_its_blocks(rows, S, d, top_k, same):
