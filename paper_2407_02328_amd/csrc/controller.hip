@@ -15,6 +15,8 @@
 // recurrent part token by token: W_hh z, the gates, the MLP and the score.
 // All sums are fp32 in a fixed order, so results are reproducible run to run.
 #include <algorithm>
+#include <cstdlib>
+#include <type_traits>
 
 #include "ctrl_device.h"
 
@@ -332,23 +334,30 @@ __device__ inline float quad_add(float v) {   // v + the value of the lane that 
 // through LDS, 16 tokens at a time.  Otherwise a lane reads its own three values, kAhead tokens before their use: a wait for a
 // block of staged loads cost 2 to 3 us per 16 tokens, as much as the arithmetic.
 //
-// PIECES, MEET: the recurrence forgets where it started, so a chunk need not be one chain.  PIECES takes it in m.pieces pieces, one
-// workgroup each: the first starts from the state before the chunk, every other one from zero kWarmUp tokens before its own (grid
-// [sequences][pieces]).  MEET, one workgroup per sequence, then compares the state with which each piece began with the one in which
-// the piece before it ended.  Where they agree to kMeet in every unit, the piece stands: from there on the two are one chain, but for
-// rounding (two runs that differ in the last place of one state stay 2e-7 apart, they do not become equal).  Where they do not, the
-// tokens are worked through again from the true state until it meets the one that is there, which costs what the chain costs.  So
-// the result never hangs on how fast the recurrence forgets, only the time does; a sequence that had to do half a chunk again takes
-// its later chunks (m.first = 0) as one chain at once.  Error of z against 64 bits as above, 1.0e-7 to 2.1e-7.
-// 16 sequences, a chunk of 512 tokens: 187 -> 55 us (50 the pieces, next to the projection of the chunk after, 4 the meeting); where no
+// PIECES, MEET: most recurrences forget where they started, and then a chunk need not be one chain.  PIECES takes it in m.pieces
+// pieces, one workgroup each: the first starts from the state before the chunk, every other one from zero kWarmUp tokens before its
+// own (grid [sequences][pieces]).  What that costs is what is left, behind the kWarmUp tokens, of the state they should have started
+// from.  It is not looked for in the states themselves, where it would have to stand out from their rounding (two runs of one chain
+// that differ in the last place of one state stay 2e-7 apart, and units that hardly forget can lose less than that at every joint):
+// the derivative of the state carries a vector of +-1 from the first token of the warm-up to the last, in the fourth column of the
+// matrix operand.  A piece stands if no unit keeps more than kForget = 2^-24 of it, half a unit in the last place; any other one
+// ends there.
+// MEET, one workgroup per sequence, also compares the state with which each piece began with the one in which the piece before it
+// ended: with no more than kMeet between them in any unit they are one chain, but for rounding.  Where a piece ended early or began
+// elsewhere the tokens are worked through again from the true state until it meets the one that is there, which costs what the
+// chain costs.  So the result never hangs on how fast the recurrence forgets, only the time does; a sequence that had to do half a
+// chunk again takes its later chunks (m.first = 0) as one chain at once.  Error against 64 bits (2-norm, prompts of 200 to 1024
+// tokens, update gates as drawn and opened by 0.3, 0.5, 0.65): z 1.06e-7 to 1.54e-7 as one chain, 1.08e-7 to 1.48e-7 in pieces;
+// from gates opened by 0.8 on, or with a few units that hardly forget, no piece stands and both are the same bits.
+// 16 sequences, a chunk of 512 tokens: 187 -> 60 us (55 the pieces, next to the projection of the chunk after, 4 the meeting); where no
 // piece stands 215 for the first chunk and 205 for the ones after it.
 enum { WHOLE = 0, PIECES = 1, MEET = 2 };
 constexpr int kWarmUp = 64, kMinPiece = 32, kMaxPieces = 14;
-constexpr float kMeet = 0x1p-21f;
+constexpr float kMeet = 0x1p-21f, kForget = 0x1p-24f;
 struct ScanPieces {
-  int pieces, len;             // tokens of every piece but the first, which has what is left
+  int pieces, len;             // tokens of every piece but the first, which has what is left, and the last, which has nsteps % 8 more
   int first;                   // the prompt's first chunk
-  float *guess;                // [B][pieces][128] the state a piece began with
+  float *guess;                // [B][pieces][128] the state a piece began with; NaN: it ended before its first token
   int *alone;                  // [B] this sequence does not forget
 };
 
@@ -365,17 +374,17 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
   const int c = lane & 15, g = lane >> 4;
   // this lane's unit: register c / 4 of the rows 4g .. 4g+3 of the half c % 2 (lanes with c & 2 repeat it)
   const int unit = wave * 32 + (c & 1) * 16 + 4 * g + (c >> 2);
-  const int len0 = PART == WHOLE ? a.nsteps : a.nsteps - (m.pieces - 1) * m.len;   // tokens of the first piece
+  const int len0 = PART == WHOLE ? a.nsteps : (a.nsteps & ~7) - (m.pieces - 1) * m.len;   // tokens of the first piece
   float *zrow = zseq + size_t(b) * a.nsteps * 128 + unit;
   int begin = 0, end = a.nsteps, keep = 0;                 // tokens to go through; those from `keep` on are its own
-  uint32_t apart = 0;                                      // MEET: pieces (bits) that did not begin where the one before ended
+  uint32_t apart = 0, slow = 0;                            // MEET: pieces (bits) that did not begin where the one before ended; that ended early
   if constexpr (PART == PIECES) {
     const int j = blockIdx.y;
     const bool alone = !m.first && m.alone[b];
     if (j > 0 && alone) return;
     keep = j == 0 ? 0 : len0 + (j - 1) * m.len;
-    begin = j == 0 ? 0 : max(keep - kWarmUp, 0);
-    end = alone ? a.nsteps : len0 + j * m.len;
+    begin = j == 0 ? 0 : keep - kWarmUp;
+    end = alone || j == m.pieces - 1 ? a.nsteps : len0 + j * m.len;
   }
   if constexpr (PART == MEET) {
     const bool alone = !m.first && m.alone[b];   // its first piece was the whole chunk
@@ -387,8 +396,12 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
         was[j] = m.guess[(size_t(b) * m.pieces + jj) * 128 + unit];
         is[j] = zrow[size_t(len0 + (jj - 1) * m.len - 1) * 128];
       }
+      static_assert(kMaxPieces <= 16, "two masks in a word");
 #pragma unroll
-      for (int j = 1; j < kMaxPieces; ++j) apart |= j < m.pieces && !(fabsf(was[j] - is[j]) <= kMeet) ? 1u << j : 0u;
+      for (int j = 1; j < kMaxPieces; ++j) {
+        apart |= j < m.pieces && !(fabsf(was[j] - is[j]) <= kMeet) ? 1u << j : 0u;
+        apart |= j < m.pieces && was[j] != was[j] ? 0x10000u << j : 0u;
+      }
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) apart |= __shfl_xor(apart, off, 64);
       if (lane == 0) s_meet[wave] = int(apart);
@@ -397,6 +410,8 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
       __syncthreads();
     }
     apart = __builtin_amdgcn_readfirstlane(apart);
+    slow = apart >> 16;
+    apart &= 0xffffu;
     if (apart == 0) {            // as a rule: all of them stand
       if ((c & 2) == 0) a.z[size_t(b) * 128 + unit] = zrow[size_t(a.nsteps - 1) * 128];
       if (tid == 0 && !alone) m.alone[b] = 0;
@@ -425,8 +440,14 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     if (!twin) dst[2 * SPS + unit] = uint16_t(__float_as_uint(lo) >> 16);
   };
   int cur = 0;
-  // one token, from the state in sp[cur] to the state in sp[cur ^ 1]; the caller's barrier follows
-  auto token = [&](int i, float g_r, float g_u, float g_n) {
+  float along = PART == PIECES ? (uint32_t(unit) * 0x9e3779b1u >> 31 ? -1.f : 1.f) : 0.f;   // the vector that the derivative carries
+  auto put_along = [&](uint16_t *dst) {
+    if (twin) dst[3 * SPS + unit] = f32_to_bf16_rne(along);
+  };
+  // one token, from the state in sp[cur] to the state in sp[cur ^ 1]; the caller's barrier follows.  warm: of a warm-up, with the
+  // vector and without the state's way out
+  auto token = [&](auto warm_, int i, float g_r, float g_u, float g_n) {
+    constexpr bool WARM = decltype(warm_)::value;
     bf16x8 hv[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) hv[s] = *reinterpret_cast<const bf16x8 *>(&sp[cur][(c & 3) * SPS + s * 32 + g * 8]);
@@ -444,35 +465,61 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int t = 4; t < 6; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t][s], hv[s], acc[t], 0, 0, 0);
-    float sum[3];
+    float sum[3], dsum[3] = {0.f, 0.f, 0.f};
 #pragma unroll
     for (int gate = 0; gate < 3; ++gate) {
-      float x[2];
+      float x[2], dx[2] = {0.f, 0.f};
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         const f32x4 v = acc[gate * 2 + hf];
         const float lo2 = odd ? v[1] : v[0], hi2 = odd ? v[3] : v[2];
-        x[hf] = quad_add<0x4E>(quad_add<0xB1>(upper ? hi2 : lo2));   // lanes 0+1, 2+3 of a quad, then both
+        float term = upper ? hi2 : lo2;
+        if (WARM) {              // lane 3 of a quad holds the vector's product
+          dx[hf] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(term), 0xFF, 0xf, 0xf, true));
+          if ((c & 3) == 3) term = 0.f;
+        }
+        x[hf] = quad_add<0x4E>(quad_add<0xB1>(term));   // lanes 0+1, 2+3 of a quad, then both
       }
       sum[gate] = half1 ? x[1] : x[0];
+      dsum[gate] = half1 ? dx[1] : dx[0];
     }
     const float r = scan_sigmoid(g_r + b_r + sum[0]);
     const float u = scan_sigmoid(g_u + b_u + sum[1]);
     const float cand = scan_tanh(g_n + b_in + r * (sum[2] + b_hn));
+    if (WARM) {
+      const float dr = r * (1.f - r) * dsum[0], du = u * (1.f - u) * dsum[1];
+      const float dcand = (1.f - cand * cand) * (dr * (sum[2] + b_hn) + r * dsum[2]);
+      along = u * along + (du * (hcur - cand) + (1.f - u) * dcand);
+    }
     hcur = (1.0f - u) * cand + u * hcur;
     cur ^= 1;
     put_state(sp[cur]);
-    if (!twin && (PART != PIECES || i >= keep)) zrow[size_t(i) * DP] = hcur;
-    if (PART == PIECES && i == keep - 1 && !twin) m.guess[(size_t(b) * m.pieces + blockIdx.y) * DP + unit] = hcur;
+    if (WARM) put_along(sp[cur]);
+    else if (!twin) zrow[size_t(i) * DP] = hcur;
   };
-  for (int i = tid; i < SPS; i += 256) sp[0][3 * SPS + i] = sp[1][3 * SPS + i] = 0;
+  constexpr std::false_type own = {};
+  constexpr std::true_type warm_up = {};
+  // Behind the warm-up: whether the piece goes on.
+  auto forgot = [&]() {
+    const uint64_t kept = __ballot(!(fabsf(along) <= kForget));
+    if (lane == 0) s_meet[wave] = kept != 0;
+    for (int i = tid; i < SPS; i += 256) sp[0][3 * SPS + i] = sp[1][3 * SPS + i] = 0;
+    __syncthreads();
+    const bool ok = (s_meet[0] | s_meet[1] | s_meet[2] | s_meet[3]) == 0;
+    if (!twin) m.guess[(size_t(b) * m.pieces + blockIdx.y) * DP + unit] = ok ? hcur : __builtin_nanf("");
+    return ok;
+  };
+  const bool warms = PART == PIECES && keep > 0;           // uniform over the workgroup
+  if (warms) put_along(sp[0]);
+  else
+    for (int i = tid; i < SPS; i += 256) sp[0][3 * SPS + i] = sp[1][3 * SPS + i] = 0;
   const float *gsrc = a.gi + size_t(b) * a.nsteps * (3 * DP) + unit;
   if constexpr (PART == MEET) {
-    // from the first piece apart on, the tokens again, eight at a time, until the state met the one that is there; then the next
-    // piece apart
+    // from the first piece apart on, the tokens again, eight at a time, until the state met the one that is there or the one with which
+    // the next piece began (never inside a piece that ended early, where there is none); then the next piece apart
     int again = 0;
     bool on = false;             // hcur is the true state behind token i - 1 (otherwise the one that is there stands)
-    float pre[kAhead][3], there = 0.f;
+    float pre[kAhead][3];
     auto ahead = [&](float (&v)[3], int i) {
       const float *p = gsrc + size_t(min(i, a.nsteps - 1)) * (3 * DP);
       v[0] = p[0]; v[1] = p[DP]; v[2] = p[2 * DP];
@@ -485,7 +532,7 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     };
     for (int i = 0; i < a.nsteps;) {             // uniform over the workgroup
       if (!on) {
-        const int next = i < len0 ? 1 : (i - len0 + m.len - 1) / m.len + 1;   // the first piece that begins at i or later
+        const int next = i < len0 ? 1 : (i - len0) / m.len + 2;   // the first piece that begins behind i
         const uint32_t rest = next < m.pieces ? apart >> next << next : 0u;
         if (rest == 0) break;
         i = len0 + (__builtin_ctz(rest) - 1) * m.len;
@@ -496,12 +543,15 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
         __syncthreads();
         on = true;
       }
-      const int count = min(kAhead, a.nsteps - i);
-      there = zrow[size_t(i + count - 1) * DP];
+      const int count = min(kAhead, a.nsteps - i), to = i + count;
+      // (pieces begin at multiples of eight)
+      const int piece = to < len0 ? 0 : min((to - len0) / m.len + 1, m.pieces - 1);
+      const bool joint = piece > 0 && to == len0 + (piece - 1) * m.len, may = to < a.nsteps && ((slow >> piece) & 1u) == 0;
+      const float there = joint ? m.guess[(size_t(b) * m.pieces + piece) * DP + unit] : zrow[size_t(to - 1) * DP];
       if (count == kAhead) {
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
-          token(i + u, pre[u][0], pre[u][1], pre[u][2]);
+          token(own, i + u, pre[u][0], pre[u][1], pre[u][2]);
           ahead(pre[u], i + u + kAhead);
           __syncthreads();
         }
@@ -509,7 +559,7 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
           if (u < count) {
-            token(i + u, pre[u][0], pre[u][1], pre[u][2]);
+            token(own, i + u, pre[u][0], pre[u][1], pre[u][2]);
             __syncthreads();
           }
         }
@@ -518,10 +568,10 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
       const uint64_t off = __ballot(!(fabsf(hcur - there) <= kMeet));
       if (lane == 0) s_meet[wave] = off != 0;
       __syncthreads();
-      if ((s_meet[0] | s_meet[1] | s_meet[2] | s_meet[3]) == 0) on = false;
+      if (may && (s_meet[0] | s_meet[1] | s_meet[2] | s_meet[3]) == 0) on = false;
       __syncthreads();
       again += count;
-      i += count;
+      i = to;
     }
     if (!on) hcur = zrow[size_t(a.nsteps - 1) * DP];
     if (tid == 0) m.alone[b] = again * 2 > a.nsteps;
@@ -556,17 +606,26 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     fetch(0);
     park(0);
     __syncthreads();
-    for (int blk = 0; blk < nblk; ++blk) {
+    auto block = [&](auto warm_, int blk) {
       if (blk + 1 < nblk) fetch(blk + 1);
       const float *gt = reinterpret_cast<const float *>(gbuf[blk & 1]) + unit;
       const int rows = min(ntok - blk * TB, TB);
       for (int ii = 0; ii < rows; ++ii, gt += 3 * DP) {
-        token(begin + blk * TB + ii, gt[0], gt[DP], gt[2 * DP]);
+        token(warm_, begin + blk * TB + ii, gt[0], gt[DP], gt[2 * DP]);
         // the next block's rows: their buffer was last read a block ago, and they are read behind the barrier
         if (ii == rows - 1 && blk + 1 < nblk) park((blk + 1) & 1);
         __syncthreads();
       }
+    };
+    static_assert(kWarmUp % TB == 0 && kWarmUp % kAhead == 0, "a warm-up of whole blocks");
+    int blk = 0;
+    if constexpr (PART == PIECES) {
+      if (warms) {
+        for (; blk < kWarmUp / TB; ++blk) block(warm_up, blk);
+        if (!forgot()) return;
+      }
     }
+    for (; blk < nblk; ++blk) block(own, blk);
   } else {
     float pre[kAhead][3];
     auto ahead = [&](float (&v)[3], int i) {
@@ -577,18 +636,26 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     for (int j = 0; j < kAhead; ++j) ahead(pre[j], begin + j);
     __syncthreads();
     int i0 = begin;
-    for (; i0 + kAhead <= end; i0 += kAhead) {
+    auto eight = [&](auto warm_) {
 #pragma unroll
       for (int j = 0; j < kAhead; ++j) {
-        token(i0 + j, pre[j][0], pre[j][1], pre[j][2]);
+        token(warm_, i0 + j, pre[j][0], pre[j][1], pre[j][2]);
         ahead(pre[j], i0 + j + kAhead);
         __syncthreads();
       }
+      i0 += kAhead;
+    };
+    if constexpr (PART == PIECES) {
+      if (warms) {
+        for (int n = 0; n < kWarmUp / kAhead; ++n) eight(warm_up);
+        if (!forgot()) return;
+      }
     }
+    while (i0 + kAhead <= end) eight(own);
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) {
       if (i0 + j < end) {                 // uniform over the workgroup
-        token(i0 + j, pre[j][0], pre[j][1], pre[j][2]);
+        token(own, i0 + j, pre[j][0], pre[j][1], pre[j][2]);
         __syncthreads();
       }
     }
@@ -842,6 +909,8 @@ bool ctrl_chunk_in_two(const adore_config &c, int nsteps) { return c.ctrl_hidden
 // kMinPiece tokens; 1: as one chain (two launches cost 5 us more than one, 14 tokens).
 int scan_pieces(const adore_config &c, int nsteps) {
   const int most = std::min(kMaxPieces, (c.heads * kMaxSplits * (c.head_dim + 2) - 1) / 128);   // (what the attention's partials have room for)
+  const char *whole = getenv("ADORE_NO_PIECES");       // comparison runs
+  if (whole && atoi(whole) != 0) return 1;
   const int n = std::min({most, 512 / c.batch, (nsteps - kWarmUp) / kMinPiece});
   return n >= 2 && nsteps - kWarmUp - (nsteps - kWarmUp) / n > 32 ? n : 1;
 }
@@ -864,7 +933,7 @@ hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf,
       ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<false, WHOLE>), dim3(c.batch), dim3(256), 0, st, a, zseq, m);
     return hipGetLastError();
   }
-  m.len = (nsteps - kWarmUp) / m.pieces;
+  m.len = (nsteps - kWarmUp) / m.pieces & ~7;
   m.first = first;
   m.guess = ctx->att_part;     // no attention runs before the init is through
   m.alone = reinterpret_cast<int *>(ctx->att_part + size_t(c.batch) * m.pieces * 128);

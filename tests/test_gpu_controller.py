@@ -37,7 +37,8 @@ def test_scores_and_state_after_a_prompt_other_controller_widths(batch, S, D, DP
     _check_prompt(batch, S, D, DP)
 
 
-def _check_prompt(batch, S, D, DP, H=2, K=24, slow=0.0):
+def _prompt(batch, S, D, DP, H=2, K=24, change=None):
+    """An init behind random prompts; change(w) may alter the weights.  -> weights, prompts, scores, z, position scale"""
     from paper_2407_02328_amd import Adore, make_config
     g = torch.Generator().manual_seed(1000 * S + D)
 
@@ -50,7 +51,8 @@ def _check_prompt(batch, S, D, DP, H=2, K=24, slow=0.0):
          "gru_b_hh": normal((3 * DP,), 0.1, f32), "pos_w": normal((DP,), 1.0, f32), "pos_b": normal((DP,), 0.1, f32),
          "mlp_w1": normal((DP, DP), DP ** -0.5, f32), "mlp_b1": normal((DP,), 0.1, f32), "out_w": normal((DP,), 0.3, f32),
          "out_b": normal((1,), 0.1, f32)}
-    w["gru_b_ih"][DP:2 * DP] += slow
+    if change:
+        change(w)
     pos_scale = 2.0 ** -12
     job = Adore(make_config(layers=1, batch=batch, heads=H, head_dim=d, hidden=D, cache_slots=K, rebuild_budget=R,
                             max_positions=n_max, ctrl_hidden=DP, dtype="bf16", pos_scale=pos_scale), w, "cuda")
@@ -63,12 +65,40 @@ def _check_prompt(batch, S, D, DP, H=2, K=24, slow=0.0):
     job.init_cache(kv, kv, hidden, x.contiguous(), None, S)
     job.get_state(scores=scores, z=z)
     torch.cuda.synchronize()
+    job.close()
+    return w, x, scores[:, :S].cpu(), z.cpu(), pos_scale
+
+
+def _check_prompt(batch, S, D, DP, H=2, K=24, change=None):
+    w, x, scores, z, pos_scale = _prompt(batch, S, D, DP, H, K, change)
     want_scores, want_z = _reference(w, x, pos_scale)
     # |z| <= 1; a pre-activation is a sum of D + 128 fp32 products of order one (error about 2^-24 sqrt(D) < 2e-6), the gates
     # damp what earlier tokens bring along, and the scores are as smooth: 4e-6 leaves a factor of two
-    assert (z.cpu().double() - want_z).abs().max() <= 4e-6
-    assert (scores[:, :S].cpu().double() - want_scores).abs().max() <= 4e-6
-    job.close()
+    assert (z.double() - want_z).abs().max() <= 4e-6
+    assert (scores.double() - want_scores).abs().max() <= 4e-6
+
+
+def _opened(by):
+    """Update gates opened by so much: a state keeps more of itself from one token to the next."""
+    def change(w):
+        w["gru_b_ih"][128:256] += by
+    return change
+
+
+def _slow_units(w):
+    """A few units that hardly forget and take in next to nothing."""
+    w["gru_b_ih"][128:136] += 11.5
+    w["gru_w_ih"][256:264] *= 1e-4
+    w["gru_w_hh"][256:264] *= 1e-4
+    for name in ("gru_b_ih", "gru_b_hh"):
+        w[name][256:264] *= 1e-4
+
+
+def _small_states(w):
+    w["gru_w_ih"][256:] *= 2e-5
+    for name in ("gru_b_ih", "gru_b_hh"):
+        w[name][256:] *= 2e-5
+    w["gru_b_ih"][128:256] += 1.0
 
 
 # The recurrence in pieces: chunks just long enough for two of them and just too short, the most there are, sliced projections, a last chunk
@@ -77,7 +107,41 @@ def _check_prompt(batch, S, D, DP, H=2, K=24, slow=0.0):
                                          (40, 600, 128, 4), (2, 200, 200, 4)])
 @pytest.mark.parametrize("slow", [0.0, 2.0, 6.0])
 def test_prompts_in_pieces(batch, S, D, H, slow):
-    _check_prompt(batch, S, D, 128, H=H, slow=slow)
+    _check_prompt(batch, S, D, 128, H=H, change=_opened(slow))
+
+
+# Whatever keeps more of itself over a warm-up than fp32 would show takes the steps of one chain, bit for bit: gates opened to where the
+# pieces' ends come close, units that lose a part of the state at every joint that is too small to see there, states as small.
+@pytest.mark.parametrize("batch,S,D", [(2, 512, 256), (1, 163, 512), (3, 200, 128), (2, 1100, 256)])
+@pytest.mark.parametrize("change", [_opened(0.9), _opened(1.0), _opened(1.1), _slow_units, _small_states],
+                         ids=["opened 0.9", "opened 1.0", "opened 1.1", "slow units", "small states"])
+def test_prompts_that_are_remembered(batch, S, D, change, monkeypatch):
+    _, _, scores, z, _ = _prompt(batch, S, D, 128, H=4, change=change)
+    monkeypatch.setenv("ADORE_NO_PIECES", "1")
+    _, _, one_scores, one_z, _ = _prompt(batch, S, D, 128, H=4, change=change)
+    assert torch.equal(scores.view(torch.int32), one_scores.view(torch.int32)) and torch.equal(z.view(torch.int32), one_z.view(torch.int32))
+
+
+# What slow units take in adds up over chunks: a state of 512 tokens behind one of 4096 is not lost.  |z| is the sum of 4608 candidates of at
+# most 3e-4 x 1e-5; an fp32 sum of so many is off by 4608 x 2^-24 of it at most, 4e-9, the other units' states by 5e-7.
+def test_prompts_with_slow_units_against_64_bits():
+    w, x, _, z, pos_scale = _prompt(1, 4608, 128, 128, H=4, change=_slow_units)
+    _, want = _reference(w, x, pos_scale)
+    assert (z.double() - want).abs().max() <= 1e-6
+    assert (z.double() - want)[:, :8].abs().max() <= 1e-8, (z[:, :8], want[:, :8])
+
+
+# Pieces that stand differ from one chain by its own rounding: errors against 64 bits of the same size (2-norm over all scores)
+@pytest.mark.parametrize("batch,S,D", [(4, 512, 256), (2, 1100, 256)])
+@pytest.mark.parametrize("slow", [0.0, 0.3, 0.5])
+def test_prompts_in_pieces_are_as_exact_as_one_chain(batch, S, D, slow, monkeypatch):
+    w, x, scores, z, pos_scale = _prompt(batch, S, D, 128, H=4, change=_opened(slow))
+    monkeypatch.setenv("ADORE_NO_PIECES", "1")
+    _, _, one_scores, one_z, _ = _prompt(batch, S, D, 128, H=4, change=_opened(slow))
+    want_scores, want_z = _reference(w, x, pos_scale)
+    off, one_off = (scores.double() - want_scores).norm(), (one_scores.double() - want_scores).norm()
+    assert off <= 1.05 * one_off, (off, one_off)
+    assert (scores - one_scores).abs().max() <= 1e-6 and (z - one_z).abs().max() <= 1e-6
 
 
 # The chunks' second copy in the cache (with sliced tails, and at the smallest cache that holds it), behind everything else, and
