@@ -380,7 +380,7 @@ hipError_t prompt_controller(adore_ctx *ctx, const void *ctrl_input, const float
     const hipError_t e_ = (EXPR);                \
     if (e_ != hipSuccess) return e_;             \
   } while (0)
-  CHUNK_TRY(launch_fill_i32(ctx, reinterpret_cast<int32_t *>(ctx->z), 0, size_t(c.batch) * c.ctrl_hidden));
+  CHUNK_TRY(launch_ctrl_start(ctx));
   if (apart) {   // the side streams start behind what the caller's stream holds
     CHUNK_TRY(hipEventRecord(ev_scan, st));
     CHUNK_TRY(hipStreamWaitEvent(st_proj, ev_scan, 0));
@@ -392,7 +392,7 @@ hipError_t prompt_controller(adore_ctx *ctx, const void *ctrl_input, const float
     const float *given = score_override ? score_override + pos0 : nullptr;
     const bool two = ctrl_chunk_in_two(c, len);
     if (apart && i > 0) CHUNK_TRY(hipStreamWaitEvent(st, ev_proj, 0));
-    if (two) CHUNK_TRY(launch_ctrl_scan(ctx, st, len, buf, ksplit[buf], i == 0));
+    if (two) CHUNK_TRY(launch_ctrl_scan(ctx, st, len, buf, ksplit[buf]));
     else CHUNK_TRY(launch_ctrl_cell(ctx, st, len, pos0, given, S, buf, ksplit[buf]));
     if (i + 1 < nchunks) {
       if (apart && i > 0) CHUNK_TRY(hipStreamWaitEvent(st_proj, ev_scan, 0));   // of chunk i - 1

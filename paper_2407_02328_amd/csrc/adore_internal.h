@@ -179,7 +179,8 @@ hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0
                             const float *score_override, int override_stride, int buf, int ksplit);
 // A prompt chunk of more than one token where ctrl_chunk_in_two(): the recurrence, then the layers above it.
 bool ctrl_chunk_in_two(const adore_config &c, int nsteps);
-hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf, int ksplit, bool first);   // first: chunk of its prompt
+hipError_t launch_ctrl_start(adore_ctx *ctx);   // ahead of a prompt's first chunk
+hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf, int ksplit);
 hipError_t launch_ctrl_score(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0, const float *score_override,
                              int override_stride, int buf);
 // The two selections also write the caller's copies of their results (slot map, released and rebuilt

@@ -343,23 +343,27 @@ __device__ inline float quad_add(float v) {   // v + the value of the lane that 
 // matrix operand.  A piece stands if no unit keeps more than kForget = 2^-24 of it, half a unit in the last place; any other one
 // ends there.
 // MEET, one workgroup per sequence, also compares the state with which each piece began with the one in which the piece before it
-// ended: with no more than kMeet between them in any unit they are one chain, but for rounding.  Where a piece ended early or began
-// elsewhere the tokens are worked through again from the true state until it meets the one that is there, which costs what the
-// chain costs.  So the result never hangs on how fast the recurrence forgets, only the time does; a sequence that had to do half a
-// chunk again takes its later chunks (m.first = 0) as one chain at once.  Error against 64 bits (2-norm, prompts of 200 to 1024
+// ended: with no more than kMeet between them in any unit they are one chain, but for rounding.  Where a piece began elsewhere the
+// tokens are worked through again from the true state until it meets the one that is there, which costs what the chain costs.  A
+// piece that ended early says so, and so does one that is through where the next has said nothing yet: the later of the two goes on,
+// through the tokens of the piece that ended early, from the state the one before it left (none waits for another).  So the result
+// never hangs on how fast the recurrence forgets, only the time does; a sequence half of whose chunk was not done in pieces takes its
+// later chunks as one chain at once.  Error against 64 bits (2-norm, prompts of 200 to 1024
 // tokens, update gates as drawn and opened by 0.3, 0.5, 0.65): z 1.06e-7 to 1.54e-7 as one chain, 1.08e-7 to 1.48e-7 in pieces;
 // from gates opened by 0.8 on, or with a few units that hardly forget, no piece stands and both are the same bits.
 // 16 sequences, a chunk of 512 tokens: 187 -> 60 us (55 the pieces, next to the projection of the chunk after, 4 the meeting); where no
-// piece stands 215 for the first chunk and 205 for the ones after it.
+// piece stands 196.  Inits of remembered prompts, one chain / pieces whose tokens are left to MEET / as it is: 16 of 1024 610 / 681 / 637
+// us, 1 of 512 241 / 276 / 247, 64 of 2048 1110 / 1220 / 1180.
 enum { WHOLE = 0, PIECES = 1, MEET = 2 };
 constexpr int kWarmUp = 64, kMinPiece = 32, kMaxPieces = 14;
 constexpr float kMeet = 0x1p-21f, kForget = 0x1p-24f;
 struct ScanPieces {
   int pieces, len;             // tokens of every piece but the first, which has what is left, and the last, which has nsteps % 8 more
-  int first;                   // the prompt's first chunk
-  float *guess;                // [B][pieces][128] the state a piece began with; NaN: it ended before its first token
-  int *alone;                  // [B] this sequence does not forget
+  float *guess;                // [B][pieces][128] the state a piece began with, unless it ended early
+  int *alone;                  // [B] this sequence does not forget; 0 before the prompt's first chunk
+  int *said;                   // [B][kMaxPieces] what is known at the joint in front of a piece (bits below); 0 before every chunk
 };
+enum { LEFT = 1, EARLY = 2, STANDS = 4 };   // the one before it is through, its state in memory; it ended before its first token; it goes on itself
 
 template <bool SPLIT, int PART>
 __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArgs a, float *__restrict__ zseq, const ScanPieces m) {
@@ -380,27 +384,28 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
   uint32_t apart = 0, slow = 0;                            // MEET: pieces (bits) that did not begin where the one before ended; that ended early
   if constexpr (PART == PIECES) {
     const int j = blockIdx.y;
-    const bool alone = !m.first && m.alone[b];
+    const bool alone = m.alone[b] != 0;
     if (j > 0 && alone) return;
     keep = j == 0 ? 0 : len0 + (j - 1) * m.len;
     begin = j == 0 ? 0 : keep - kWarmUp;
     end = alone || j == m.pieces - 1 ? a.nsteps : len0 + j * m.len;
   }
   if constexpr (PART == MEET) {
-    const bool alone = !m.first && m.alone[b];   // its first piece was the whole chunk
+    const bool alone = m.alone[b] != 0;   // its first piece was the whole chunk
     if (!alone) {
       float was[kMaxPieces], is[kMaxPieces];
+      int said[kMaxPieces];
 #pragma unroll
       for (int j = 1; j < kMaxPieces; ++j) {
         const int jj = min(j, m.pieces - 1);
+        said[j] = m.said[b * kMaxPieces + jj];
         was[j] = m.guess[(size_t(b) * m.pieces + jj) * 128 + unit];
         is[j] = zrow[size_t(len0 + (jj - 1) * m.len - 1) * 128];
       }
       static_assert(kMaxPieces <= 16, "two masks in a word");
 #pragma unroll
       for (int j = 1; j < kMaxPieces; ++j) {
-        apart |= j < m.pieces && !(fabsf(was[j] - is[j]) <= kMeet) ? 1u << j : 0u;
-        apart |= j < m.pieces && was[j] != was[j] ? 0x10000u << j : 0u;
+        if (j < m.pieces) apart |= said[j] & EARLY ? 0x10000u << j : !(fabsf(was[j] - is[j]) <= kMeet) ? 1u << j : 0u;
       }
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) apart |= __shfl_xor(apart, off, 64);
@@ -408,13 +413,14 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
       __syncthreads();
       apart = uint32_t(s_meet[0] | s_meet[1] | s_meet[2] | s_meet[3]);
       __syncthreads();
+      if (tid < kMaxPieces) m.said[b * kMaxPieces + tid] = 0;
     }
     apart = __builtin_amdgcn_readfirstlane(apart);
     slow = apart >> 16;
     apart &= 0xffffu;
     if (apart == 0) {            // as a rule: all of them stand
       if ((c & 2) == 0) a.z[size_t(b) * 128 + unit] = zrow[size_t(a.nsteps - 1) * 128];
-      if (tid == 0 && !alone) m.alone[b] = 0;
+      if (tid == 0 && !alone) m.alone[b] = 2 * __builtin_popcount(slow) * m.len > a.nsteps;
       return;
     }
   }
@@ -506,8 +512,44 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     for (int i = tid; i < SPS; i += 256) sp[0][3 * SPS + i] = sp[1][3 * SPS + i] = 0;
     __syncthreads();
     const bool ok = (s_meet[0] | s_meet[1] | s_meet[2] | s_meet[3]) == 0;
-    if (!twin) m.guess[(size_t(b) * m.pieces + blockIdx.y) * DP + unit] = ok ? hcur : __builtin_nanf("");
-    return ok;
+    if (ok && !twin) m.guess[(size_t(b) * m.pieces + blockIdx.y) * DP + unit] = hcur;
+    if (tid == 0) {
+      const int known = __hip_atomic_fetch_or(m.said + b * kMaxPieces + blockIdx.y, ok ? STANDS : EARLY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_meet[0] = !ok && (known & LEFT);
+    }
+    if (ok) return true;
+    __syncthreads();
+    if (s_meet[0] == 0) return false;
+    hcur = __hip_atomic_load(zrow + size_t(keep - 1) * DP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    put_state(sp[cur]);
+    __syncthreads();
+    return true;
+  };
+  // At the end of a piece: whether to go on through those behind it; then `end` has moved.
+  int done = PART == PIECES ? int(blockIdx.y) + 1 : 0;      // the first piece behind `end`
+  auto goes_on = [&]() {
+    if (PART != PIECES || end == a.nsteps) return false;
+    int *said = m.said + b * kMaxPieces;
+    if (wave == 0) {
+      const int known = lane < m.pieces ? __hip_atomic_load(said + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+      const int more = __builtin_ctzll(~(__ballot(known & EARLY) >> done));
+      if (lane == done) s_meet[0] = more > 0 ? more : known & STANDS ? 0 : -1;
+    }
+    __syncthreads();
+    int more = s_meet[0];
+    if (more < 0) {              // nothing is known of the next one
+      if (!twin) __hip_atomic_store(zrow + size_t(end - 1) * DP, hcur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (tid == 0) s_meet[0] = __hip_atomic_fetch_or(said + done, LEFT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & EARLY ? 1 : 0;
+      __syncthreads();
+      more = s_meet[0];
+    }
+    __syncthreads();
+    more = __builtin_amdgcn_readfirstlane(more);
+    done += more;
+    end = done == m.pieces ? a.nsteps : end + more * m.len;
+    return more > 0;
   };
   const bool warms = PART == PIECES && keep > 0;           // uniform over the workgroup
   if (warms) put_along(sp[0]);
@@ -517,7 +559,7 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
   if constexpr (PART == MEET) {
     // from the first piece apart on, the tokens again, eight at a time, until the state met the one that is there or the one with which
     // the next piece began (never inside a piece that ended early, where there is none); then the next piece apart
-    int again = 0;
+    int again = __builtin_popcount(slow) * m.len;
     bool on = false;             // hcur is the true state behind token i - 1 (otherwise the one that is there stands)
     float pre[kAhead][3];
     auto ahead = [&](float (&v)[3], int i) {
@@ -570,7 +612,7 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
       __syncthreads();
       if (may && (s_meet[0] | s_meet[1] | s_meet[2] | s_meet[3]) == 0) on = false;
       __syncthreads();
-      again += count;
+      if (((slow >> (i < len0 ? 0 : min((i - len0) / m.len + 1, m.pieces - 1))) & 1u) == 0) again += count;
       i = to;
     }
     if (!on) hcur = zrow[size_t(a.nsteps - 1) * DP];
@@ -578,18 +620,17 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
   } else {
   put_state(sp[0]);
   if constexpr (SPLIT) {
-    const int ntok = end - begin, nblk = (ntok + TB - 1) / TB;
-    const float4 *gsrc4 = reinterpret_cast<const float4 *>(a.gi) + (size_t(b) * a.nsteps + begin) * (3 * DP / 4);
+    const float4 *gsrc4 = reinterpret_cast<const float4 *>(a.gi) + size_t(b) * a.nsteps * (3 * DP / 4);
     const size_t slice4 = size_t(a.ntok) * (3 * DP / 4);   // distance between two D-slices
     float4 stage[GPT];
     auto fetch = [&](int blk) {
-      const int rows = min(ntok - blk * TB, TB);
+      const int rows = min(end - begin - blk * TB, TB);
 #pragma unroll
       for (int q = 0; q < GPT; ++q) {
         const int idx = tid + 256 * q;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (idx < rows * (3 * DP / 4)) {
-          const float4 *p = gsrc4 + size_t(blk) * TB * (3 * DP / 4) + idx;
+          const float4 *p = gsrc4 + size_t(begin + blk * TB) * (3 * DP / 4) + idx;
           v = p[0];
           for (int k = 1; k < a.ksplit; ++k) {
             const float4 t = p[size_t(k) * slice4];
@@ -603,13 +644,10 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
 #pragma unroll
       for (int q = 0; q < GPT; ++q) gbuf[buf][tid + 256 * q] = stage[q];
     };
-    fetch(0);
-    park(0);
-    __syncthreads();
-    auto block = [&](auto warm_, int blk) {
+    auto block = [&](auto warm_, int blk, int nblk) {
       if (blk + 1 < nblk) fetch(blk + 1);
       const float *gt = reinterpret_cast<const float *>(gbuf[blk & 1]) + unit;
-      const int rows = min(ntok - blk * TB, TB);
+      const int rows = min(end - begin - blk * TB, TB);
       for (int ii = 0; ii < rows; ++ii, gt += 3 * DP) {
         token(warm_, begin + blk * TB + ii, gt[0], gt[DP], gt[2 * DP]);
         // the next block's rows: their buffer was last read a block ago, and they are read behind the barrier
@@ -618,18 +656,25 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
       }
     };
     static_assert(kWarmUp % TB == 0 && kWarmUp % kAhead == 0, "a warm-up of whole blocks");
-    int blk = 0;
-    if constexpr (PART == PIECES) {
-      if (warms) {
-        for (; blk < kWarmUp / TB; ++blk) block(warm_up, blk);
-        if (!forgot()) return;
+    do {
+      const int nblk = (end - begin + TB - 1) / TB;
+      int blk = 0;
+      fetch(0);
+      park(0);
+      __syncthreads();
+      if constexpr (PART == PIECES) {
+        if (warms && begin < keep) {
+          for (; blk < kWarmUp / TB; ++blk) block(warm_up, blk, nblk);
+          if (!forgot()) return;
+        }
       }
-    }
-    for (; blk < nblk; ++blk) block(own, blk);
+      for (; blk < nblk; ++blk) block(own, blk, nblk);
+      begin = end;
+    } while (goes_on());
   } else {
     float pre[kAhead][3];
     auto ahead = [&](float (&v)[3], int i) {
-      const float *p = gsrc + size_t(min(i, end - 1)) * (3 * DP);
+      const float *p = gsrc + size_t(min(i, a.nsteps - 1)) * (3 * DP);
       v[0] = p[0]; v[1] = p[DP]; v[2] = p[2 * DP];
     };
 #pragma unroll
@@ -651,7 +696,9 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
         if (!forgot()) return;
       }
     }
-    while (i0 + kAhead <= end) eight(own);
+    do {
+      while (i0 + kAhead <= end) eight(own);
+    } while (goes_on());                    // (pieces end at multiples of eight, but for the last)
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) {
       if (i0 + j < end) {                 // uniform over the workgroup
@@ -905,17 +952,31 @@ CellArgs cell_args(adore_ctx *ctx, int nsteps, int pos0, const float *score_over
 // A chunk of several tokens at d' = 128 is two launches, of which only the first has to wait for the chunk before it.
 bool ctrl_chunk_in_two(const adore_config &c, int nsteps) { return c.ctrl_hidden == 128 && nsteps > 1; }
 
+// What a prompt starts from: states of zero, and nothing known of any sequence or piece (see ScanPieces).
+__global__ void ctrl_start_kernel(float *z, int n_z, int *words, int n_words) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n_z) z[i] = 0.f;
+  if (i < n_words) words[i] = 0;
+}
+
 // In how many pieces a chunk's recurrence is worked through (bf16): as many as keep two workgroups a compute unit, of at least
 // kMinPiece tokens; 1: as one chain (two launches cost 5 us more than one, 14 tokens).
 int scan_pieces(const adore_config &c, int nsteps) {
-  const int most = std::min(kMaxPieces, (c.heads * kMaxSplits * (c.head_dim + 2) - 1) / 128);   // (what the attention's partials have room for)
+  const int most = std::min(kMaxPieces, (c.heads * kMaxSplits * (c.head_dim + 2) - kMaxPieces - 1) / 128);   // (what the attention's partials have room for)
   const char *whole = getenv("ADORE_NO_PIECES");       // comparison runs
   if (whole && atoi(whole) != 0) return 1;
   const int n = std::min({most, 512 / c.batch, (nsteps - kWarmUp) / kMinPiece});
   return n >= 2 && nsteps - kWarmUp - (nsteps - kWarmUp) / n > 32 ? n : 1;
 }
 
-hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf, int ksplit, bool first) {
+hipError_t launch_ctrl_start(adore_ctx *ctx) {
+  const int B = ctx->cfg.batch, n_z = B * ctx->cfg.ctrl_hidden, n_words = B * (kMaxPieces + 1);
+  hipLaunchKernelGGL(ctrl_start_kernel, dim3((std::max(n_z, n_words) + 255) / 256), dim3(256), 0, ctx->stream, ctx->z, n_z,
+                     reinterpret_cast<int *>(ctx->att_part), n_words);
+  return hipGetLastError();
+}
+
+hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf, int ksplit) {
   const adore_config &c = ctx->cfg;
   const CellArgs a = cell_args(ctx, nsteps, 0, nullptr, 0, buf, ksplit);
   ScopedTimer t(ctx, ADORE_KERNEL_CTRL_CELL, st);
@@ -934,10 +995,9 @@ hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf,
     return hipGetLastError();
   }
   m.len = (nsteps - kWarmUp) / m.pieces & ~7;
-  m.first = first;
-  m.guess = ctx->att_part;     // no attention runs before the init is through
-  m.alone = reinterpret_cast<int *>(ctx->att_part + size_t(c.batch) * m.pieces * 128);
-  if (!first) m.alone = reinterpret_cast<int *>(ctx->att_part + size_t(c.batch) * scan_pieces(c, kPromptChunk) * 128);   // where the chunk before left it
+  m.alone = reinterpret_cast<int *>(ctx->att_part);   // no attention runs before the init is through
+  m.said = m.alone + c.batch;
+  m.guess = ctx->att_part + size_t(c.batch) * (kMaxPieces + 1);
   if (ksplit > 1)
     ADORE_LAUNCH(t, (ctrl_scan128_mfma_kernel<true, PIECES>), dim3(c.batch, m.pieces), dim3(256), 0, st, a, zseq, m);
   else
