@@ -800,8 +800,13 @@ int adore_decode_step(adore_ctx *ctx, const void *q, const void *k_new, const vo
   if (h2o_mode(ctx)) {   // the selections need this step's attention
     const bool releases = h2o_attend_releases(ctx);
     int rc = ADORE_OK;
-    if (releases) ADORE_TRY(launch_h2o_attend_release(ctx, q, k_new, v_new, out, (ctx->cur + 1) % kRing, slot_map));
-    else rc = do_attend(ctx, 0, q, k_new, v_new, out);
+    if (releases) {
+      ADORE_TRY(launch_h2o_attend_release(ctx, q, k_new, v_new, out, (ctx->cur + 1) % kRing, slot_map));
+      ctx->attended[0] = 1;      // the scores have this step's attention: should the rest fail, it is not added a second time
+      ctx->n_attended = 1;
+    } else {
+      rc = do_attend(ctx, 0, q, k_new, v_new, out);
+    }
     if (rc != ADORE_OK) return rc;
     rc = do_schedule(ctx, x_n, score_override, slot_map, nullptr, nullptr, releases);
     if (rc != ADORE_OK) return rc;

@@ -22,9 +22,13 @@ extern "C" hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, 
   return hipSuccess;
 }
 extern "C" hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { return hipSuccess; }
-extern "C" hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { return hipSuccess; }
+static int launches = 0, failing_launch = -1;   // the one that is refused, counted from 1
+extern "C" hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) {
+  ++launches;
+  return hipSuccess;
+}
 extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
-extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+extern "C" hipError_t hipGetLastError() { return launches == failing_launch ? hipErrorLaunchFailure : hipSuccess; }
 
 static int failures = 0;
 #define EXPECT(cond)                                                          \
@@ -136,6 +140,24 @@ int main() {
     EXPECT(adore_create(&x, &wt, fake, adore_workspace_bytes(&x), nullptr, &hx) == ADORE_OK);
     EXPECT(hx->one_stream && hx->one_when[0] && hx->one_when[1]);
     EXPECT(adore_set_input_order(hx, 0) == ADORE_OK && !hx->one_stream && hx->one_when[0]);
+    EXPECT(adore_destroy(hx) == ADORE_OK);
+  }
+  // H2O mode: a step that fails behind its attention, which adds to the scores, is not taken a second time
+  for (const int heads : {4, 256}) {   // rows cut into splits, with a release of its own; whole rows, released with the attention
+    adore_config x = tiny();
+    x.score_mode = ADORE_SCORE_H2O; x.batch = heads / 4; x.cache_slots = 128;
+    adore_ctx *hx = nullptr;
+    EXPECT(adore_create(&x, &wt, fake, adore_workspace_bytes(&x), nullptr, &hx) == ADORE_OK);
+    EXPECT((hx->nsplit == 1) == (heads == 256));
+    EXPECT(adore_init_cache(hx, fake, fake, fake, fake, nullptr, 300) == ADORE_OK);
+    EXPECT(adore_decode_step(hx, fake, fake, fake, fake, nullptr, nullptr, ffake, nullptr) == ADORE_OK);
+    launches = 0;
+    failing_launch = heads == 256 ? 2 : 4;   // the choice
+    EXPECT(adore_decode_step(hx, fake, fake, fake, fake, nullptr, nullptr, ffake, nullptr) == ADORE_E_HIP);
+    failing_launch = -1;
+    EXPECT(adore_decode_step(hx, fake, fake, fake, fake, nullptr, nullptr, ffake, nullptr) == ADORE_E_STATE);
+    EXPECT(adore_init_cache(hx, fake, fake, fake, fake, nullptr, 300) == ADORE_OK);
+    EXPECT(adore_decode_step(hx, fake, fake, fake, fake, nullptr, nullptr, ffake, nullptr) == ADORE_OK);
     EXPECT(adore_destroy(hx) == ADORE_OK);
   }
   // the debug layout
