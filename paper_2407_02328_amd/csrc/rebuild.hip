@@ -67,7 +67,7 @@ struct GemmArgs {
   const float2 *rope;          // tile kernel: [N_max][d/2] (cos, sin), the key (and query) tiles turn their rows by
                                // position as they leave; null: no rotary embedding, or a pass of its own does it
   int tail_at;                 // TAIL: its first workgroup
-  StepTail tail;               // TAIL, and where the fp32 kernel carries one (tail.n > 0)
+  StepTail tail;               // TAIL
 };
 
 // A rank that stays empty (position -1: fewer tokens were chosen than the launch has rows for) reads row 0 of its
@@ -664,18 +664,23 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
 // end (chains through the whole row were further from 64 bits than the kernel before: 1.5e-7 against 1.0e-7 at k = 1024).
 // One wave per output element, which read both rows from the L1 for every output, reached 4 to 6 TFLOP/s.  Before / on these
 // tiles: 32 rows x 1024 columns x 512 13.7 / 5.7 us, 160 x 2048 x 1024 119 / 25 us (27 TFLOP/s), 128 x 4096 x 1024 189 / 26 us, 256 x 8192 x
-// 4096 4440 / 288 us (60 TFLOP/s).
-template <int MODE, int MT, int NT, int U>
+// 4096 4440 / 288 us (60 TFLOP/s).  TAIL is an instance of its own here too: the tail's role inside REBUILD took the 16x16 tile from 52
+// registers and 7 waves a SIMD to 115 and 3, the 32x32 one from 97 and 4 to 115 and 3 (256 x 4096 x 2048 71 -> 75 us, 32 x 1024 x 512 5.9 -> 6.3).
+template <int MODE_, int MT, int NT, int U>
 __global__ __launch_bounds__(256) void f32_tile_kernel(const GemmArgs a) {
+  constexpr int MODE = MODE_ == MODE_TAIL ? MODE_REBUILD : MODE_;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
   __shared__ double red[4][MT * NT][16][17];
-  if (MODE == MODE_REBUILD && int(blockIdx.x) < a.n_cur) {
+  int bx = blockIdx.x;
+  if constexpr (MODE_ == MODE_TAIL) {
     static_assert(sizeof(red) >= kStepTailLds * sizeof(float), "room for the tail");
-    step_tail_role<256>(a.tail, blockIdx.x, reinterpret_cast<float *>(red));
-    return;
+    if (bx < a.n_cur) {
+      step_tail_role<256>(a.tail, bx, reinterpret_cast<float *>(red));
+      return;
+    }
+    bx -= a.n_cur;
   }
-  const int bx = blockIdx.x - a.n_cur;
   const int tm = bx / a.tiles_n, tn = bx - tm * a.tiles_n;
   const int m0 = tm * (16 * MT), n0 = tn * (16 * NT);
   const float *pa[MT], *pb[NT];
@@ -980,7 +985,7 @@ void launch_f32_tile(ScopedTimer &t, hipStream_t stream, GemmArgs &a) {
   const int side = big >= 256 ? 32 : 16;
   a.tiles_m = (a.M + side - 1) / side;
   a.tiles_n = (a.N + side - 1) / side;
-  const dim3 grid(unsigned(a.tiles_m) * unsigned(a.tiles_n) + unsigned(a.n_cur)), block(256);
+  const dim3 grid(unsigned(a.tiles_m) * unsigned(a.tiles_n) + (MODE == MODE_TAIL ? unsigned(a.n_cur) : 0u)), block(256);
   if (side == 32) ADORE_LAUNCH(t, (f32_tile_kernel<MODE, 2, 2, 2>), grid, block, 0, stream, a);
   else ADORE_LAUNCH(t, (f32_tile_kernel<MODE, 1, 1, 4>), grid, block, 0, stream, a);
 }
@@ -1104,6 +1109,8 @@ hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_lay
     launch_tile<MODE_TAIL>(t, ctx->stream, pick, a);
   } else if (pick >= 0) {
     launch_tile<MODE_REBUILD>(t, ctx->stream, pick, a);
+  } else if (c.dtype == ADORE_F32 && tail) {
+    launch_f32_tile<MODE_TAIL>(t, ctx->stream, a);
   } else if (c.dtype == ADORE_F32) {
     launch_f32_tile<MODE_REBUILD>(t, ctx->stream, a);
   } else {
