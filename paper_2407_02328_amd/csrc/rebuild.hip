@@ -1277,7 +1277,9 @@ hipError_t launch_fwd_oproj(adore_ctx *ctx, const void *w_o_layer, const void *x
 bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, const void *x, const void *W, float *out,
                              int ntok, int per_seq, int seq_rows, int N, int D) {
   // 256 x 128 x 64 where its rounds over the compute units come out shorter than those of 128 x 128 x 64 (65536 tokens x 384 rows of 4096: 401 ->
-  // 242 us, with the order of the tiles below; 8192 tokens, one round of either: 54 us for 66)
+  // 242 us, with the order of the tiles below; 8192 tokens, one round of either: 54 us for 66).  Its two groups of four waves cut D as the
+  // narrow tile's do, so that a sum is the same either way (all of D in one chain per wave, twice as long: no faster);
+  // one set of tiles on its way in registers is what that leaves room for (two: 26 registers spilled, 330 us).
   const long long wide = ((ntok + 255) / 256) * (N / 128), narrow = ((ntok + 127) / 128) * (N / 128);
   const int kTile = float((wide + 255) / 256) * kTileMicros[1] < float((narrow + 255) / 256) * kTileMicros[2] ? 1 : 2;
   const bool bf16 = ctx->cfg.dtype == ADORE_BF16;
@@ -1296,7 +1298,7 @@ bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, con
   a.tiles_n = a.N / kTiles[kTile].bn;
   const dim3 grid((a.tiles_m * a.tiles_n + 7) / 8 * 8), block(512);
   if (kTile == 1)
-    ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE_PLAIN, 256, 128, 64, 1, 4, 2, 3, 2>), grid, block, 0, st, a);
+    ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE_PLAIN, 256, 128, 64, 2, 2, 2, 3, 1>), grid, block, 0, st, a);
   else
     ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE_PLAIN, 128, 128, 64, 2, 2, 2, 3, 4>), grid, block, 0, st, a);
   return true;

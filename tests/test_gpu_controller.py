@@ -147,6 +147,20 @@ def test_prompts_in_pieces_are_as_exact_as_one_chain(batch, S, D, slow, monkeypa
     assert (scores - one_scores).abs().max() <= 1e-6 and (z - one_z).abs().max() <= 1e-6
 
 
+# 24 sequences go over the wide tiles of the input projection, 12 over the narrow ones: the same sums
+def test_prompts_over_wide_and_narrow_tiles_are_the_same(monkeypatch):
+    randn = torch.randn
+    _, x, scores, z, _ = _prompt(24, 512, 2048, 128, H=2)
+
+    def again(*shape, generator=None):
+        out = randn(*shape, generator=generator)
+        return x[:12].float().cpu() if shape[0] == tuple(x[:12].shape) else out
+    monkeypatch.setattr(torch, "randn", again)
+    _, x12, few_scores, few_z, _ = _prompt(12, 512, 2048, 128, H=2)
+    assert torch.equal(x12, x[:12])
+    assert torch.equal(few_scores, scores[:12]) and torch.equal(few_z, z[:12])
+
+
 # The chunks' second copy in the cache (with sliced tails, and at the smallest cache that holds it), behind everything else, and
 # missing; with the guard words of the debug layout, which tests/conftest.py counts when the job closes.
 @pytest.mark.parametrize("guards", [False, True])
