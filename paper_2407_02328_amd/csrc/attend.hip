@@ -372,6 +372,15 @@ template <typename T, int DH>
 hipError_t launch_h2o_typed(adore_ctx *ctx, const AttendArgs &a, int rows) {
   ScopedTimer t(ctx, ADORE_KERNEL_ATTEND, ctx->stream);
   const size_t lds = size_t(a.K) * 4;
+  if constexpr (sizeof(T) == 4) {
+    // fp32 rows of 256 to 511 slots keep to the eight waves that the attention alone takes (choose_split): with four a lane group adds
+    // up twice as many of them (1.71e-7 -> 1.79e-7 off 64 bits at 256 slots, 1.85e-7 -> 2.05e-7 at 500; in bf16 1.91e-7 -> 1.74e-7).
+    if (ctx->attend_waves == 8 && a.K <= 512) {
+      if (a.K <= 256) ADORE_LAUNCH(t, (attend_kernel<T, DH, 4, 8, 4>), dim3(rows), dim3(512), lds, ctx->stream, a);
+      else ADORE_LAUNCH(t, (attend_kernel<T, DH, 4, 8, 8>), dim3(rows), dim3(512), lds, ctx->stream, a);
+      return hipGetLastError();
+    }
+  }
   if (a.K <= 256) ADORE_LAUNCH(t, (attend_kernel<T, DH, 4, 4, 4>), dim3(rows), dim3(256), lds, ctx->stream, a);
   else if (a.K <= 512) ADORE_LAUNCH(t, (attend_kernel<T, DH, 4, 4, 8>), dim3(rows), dim3(256), lds, ctx->stream, a);
   else ADORE_LAUNCH(t, (attend_kernel<T, DH, 4, 4, 16>), dim3(rows), dim3(256), lds, ctx->stream, a);
@@ -513,7 +522,8 @@ hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k
 
 // H2O mode: attention, the step's probabilities added to the scores and the release in one launch, where a workgroup takes a whole
 // row.  16 sequences of 32 heads, K = 512: 22.5 + 15.5 us (and the logits' way through memory) -> 29 us, the
-// step 101 -> 90 us.
+// step 101 -> 90 us.  With four waves also at 256 to 511 slots in bf16, where the attention alone takes eight: 40 steps 2075 -> 1806 us at 256,
+// 2315 -> 1975 at 300, 2839 -> 2362 at 500, 1935 -> 1625 with 40 sequences of 12 heads of 64 and 300.
 bool h2o_attend_releases(const adore_ctx *ctx) { return h2o_mode(ctx) && ctx->nsplit == 1; }
 
 hipError_t launch_h2o_attend_release(adore_ctx *ctx, const void *q, const void *k_new, const void *v_new, float *out, int dst,

@@ -79,6 +79,57 @@ def test_h2o_at_the_benchmark_shape():
     job.adore.close()
 
 
+# Whole rows: adore_decode_step releases each row with its attention (4, 8 or 16 keys a lane), the calls one by one in a launch of its
+# own (which the oracle follows above).  The same arithmetic in the same order: bit for bit.  Edges of the 64-slot groups, a cache
+# that fills up within the run, no rebuild budget.
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("K,R,S", [(65, 5, 90), (256, 9, 300), (257, 12, 254), (500, 0, 700), (512, 32, 509), (513, 40, 700), (1000, 17, 1100),
+                                   (1024, 31, 1021)])
+def test_h2o_release_with_the_attention_is_the_release(K, R, S, dtype, d, monkeypatch):
+    import torch
+    from paper_2407_02328_amd import Adore, make_config
+    monkeypatch.setenv("ADORE_ATTEND_SPLIT", "1")
+    if dtype == "bf16" or not 256 <= K < 512:                   # (fp32 rows of 256 to 511 slots: eight waves either way)
+        monkeypatch.setenv("ADORE_ATTEND_WAVES", "4")
+    B, H, D, T, dp = 2, 3, 128, 7, 64
+    st, f = torch.bfloat16 if dtype == "bf16" else torch.float32, torch.float32
+
+    def run(whole):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(K + d)
+        n = lambda shape, std, dt=st: torch.empty(shape, dtype=dt, device="cuda").normal_(0.0, std, generator=g)
+        w = {"w_kv": n((1, 2 * H * d, D), 0.05), "gru_w_ih": n((3 * dp, D), 0.1), "gru_w_hh": n((3 * dp, dp), 0.1), "gru_b_ih": n((3 * dp,), 0.1, f),
+             "gru_b_hh": n((3 * dp,), 0.1, f), "pos_w": n((dp,), 1.0, f), "pos_b": n((dp,), 0.1, f), "mlp_w1": n((dp, dp), 0.1, f),
+             "mlp_b1": n((dp,), 0.1, f), "out_w": n((dp,), 0.1, f), "out_b": n((1,), 0.1, f)}
+        a = Adore(make_config(layers=1, batch=B, heads=H, head_dim=d, hidden=D, cache_slots=K, rebuild_budget=R, max_positions=S + T,
+                              ctrl_hidden=dp, dtype=dtype, pos_scale=2.0 ** -12, score_mode=2), w)
+        pk, pv, hid, qkv = n((1, B, H, S, d), 1.0), n((1, B, H, S, d), 1.0), n((1, B, S + T, D), 1.0), n((T, 3, B, H, d), 1.0)
+        seen = []
+        a.init_cache(pk, pv, hid, hid[0][:, :S].contiguous(), torch.rand((B, H, S), device="cuda", generator=g), S)
+        a.set_timing(True)
+        for t in range(T):
+            out = torch.empty((B, H, d), dtype=f, device="cuda")
+            maps = torch.empty((B, H, K), dtype=torch.int32, device="cuda")
+            if whole:
+                a.decode_step(qkv[t, 0], qkv[t, 1], qkv[t, 2], hid[0], None, None, out, maps)
+            else:
+                a.attend(0, qkv[t, 0], qkv[t, 1], qkv[t, 2], out)
+                a.schedule(None, None, maps)
+                a.rebuild(0, hid[0])
+            seen += [out, maps]
+        assert a.read_timing()["h2o_release"][1] == (0 if whole else T)
+        state = a.empty_state()
+        a.get_state(**state)
+        torch.cuda.synchronize()
+        a.close()
+        free = (state["slot_pos"] < 0)[None, ..., None]        # rows of free slots hold whatever was there
+        return seen + [state["slot_pos"], state["scores"], state["cache_k"].masked_fill(free, 0), state["cache_v"].masked_fill(free, 0)]
+
+    for i, (x, y) in enumerate(zip(run(True), run(False))):
+        as_bits = torch.int16 if x.dtype == torch.bfloat16 else torch.int32
+        assert torch.equal(x.view(as_bits), y.view(as_bits)), f"tensor {i}"
+
+
 def _random_h2o_workloads(count, seed):
     rng = np.random.default_rng(seed)
     out = []
