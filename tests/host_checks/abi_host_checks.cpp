@@ -142,6 +142,17 @@ int main() {
     EXPECT(adore_set_input_order(hx, 0) == ADORE_OK && !hx->one_stream && hx->one_when[0]);
     EXPECT(adore_destroy(hx) == ADORE_OK);
   }
+  // the choice in parts of 1024 tokens: at most 64 of them, and (parts + 1) R + 1 <= 4096 keys
+  for (const int (&v)[3] :
+       (const int[][3]){{63, 65537, 1}, {63, 65538, 0}, {64, 63489, 1}, {64, 63490, 0}, {128, 30721, 1}, {128, 30722, 0}, {300, 12289, 1}, {300, 12290, 0}}) {
+    adore_config x = tiny();
+    x.dtype = ADORE_BF16; x.ctrl_hidden = 128; x.cache_slots = 1024;
+    x.rebuild_budget = v[0]; x.max_positions = v[1];
+    adore_ctx *hx = nullptr;
+    EXPECT(adore_create(&x, &wt, fake, adore_workspace_bytes(&x), nullptr, &hx) == ADORE_OK);
+    EXPECT(hx->ride_parts == (v[2] != 0));
+    EXPECT(adore_destroy(hx) == ADORE_OK);
+  }
   // H2O mode: a step that fails behind its attention, which adds to the scores, is not taken a second time
   for (const int heads : {4, 256}) {   // rows cut into splits, with a release of its own; whole rows, released with the attention
     adore_config x = tiny();

@@ -31,7 +31,7 @@ def _of_state(state, n):
             state["scores"][:, :n].clone()]
 
 
-def _run(case, carried, ordered, monkeypatch, steps=9):
+def _run(case, carried, ordered, monkeypatch, steps):
     import torch
     from paper_2407_02328_amd import Adore, make_config
     B, H, d, D, K, R, S, dtype, rescore, rope = case
@@ -54,6 +54,7 @@ def _run(case, carried, ordered, monkeypatch, steps=9):
     xs = hid[0][:, S:].transpose(0, 1).contiguous()
     a.init_cache(pk, pv, hid, hid[0][:, :S].contiguous(), None, S)
     torch.cuda.synchronize()
+    a.set_timing(True)
     seen = []
     for t in range(steps):
         out = torch.empty((B, H, d), dtype=f, device="cuda")
@@ -64,16 +65,27 @@ def _run(case, carried, ordered, monkeypatch, steps=9):
     state = a.empty_state()
     a.get_state(**state)
     torch.cuda.synchronize()
+    launches = {name: count for name, (_, count) in a.read_timing().items()}
     a.close()
-    return seen + _of_state(state, S + steps)
+    return seen + _of_state(state, S + steps), launches
 
 
 @pytest.mark.parametrize("ordered", [True, False])
 @pytest.mark.parametrize("case", CASES)
 def test_carried_steps_are_the_steps(case, ordered, monkeypatch):
     import torch
-    carried = _run(case, True, ordered, monkeypatch)
-    apart = _run(case, False, ordered, monkeypatch)
+    steps = 9
+    carried, launches = _run(case, True, ordered, monkeypatch, steps)
+    # what is carried is no launch of its own: the selections in every step, the controller and the merge of the splits in every step
+    # with a projection (all of them but where a cache fills up first) that can carry them
+    assert launches["attend"] == steps and launches["release"] == launches["rebuild_select"] == 0
+    own = steps if case[3] == 392 else 0
+    if case[6] >= case[4]:
+        assert launches["ctrl_input"] == launches["ctrl_cell"] == own and (own or launches["attend_combine"] == 0)
+    else:
+        assert launches["ctrl_input"] == launches["ctrl_cell"] < steps
+    apart, launches = _run(case, False, ordered, monkeypatch, steps)
+    assert launches["ctrl_input"] == launches["ctrl_cell"] == launches["release"] == steps
     for i, (x, y) in enumerate(zip(carried, apart)):
         same = torch.equal(x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32), y.view(torch.int16 if y.dtype == torch.bfloat16 else torch.int32))
         assert same, f"{case}: tensor {i} of {len(carried)}"
