@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
   int cur = 0;
   float along = PART == PIECES ? (uint32_t(unit) * 0x9e3779b1u >> 31 ? -1.f : 1.f) : 0.f;   // the vector that the derivative carries
   auto put_along = [&](uint16_t *dst) {
-    if (twin) dst[3 * SPS + unit] = f32_to_bf16_rne(along);
+    if (twin) dst[3 * SPS + unit] = uint16_t(__float_as_uint(along) >> 16);   // (rounded down: 64 tokens take off an eighth of it)
   };
   // one token, from the state in sp[cur] to the state in sp[cur ^ 1]; the caller's barrier follows.  warm: of a warm-up, with the
   // vector and without the state's way out
@@ -479,15 +479,15 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
       for (int hf = 0; hf < 2; ++hf) {
         const f32x4 v = acc[gate * 2 + hf];
         const float lo2 = odd ? v[1] : v[0], hi2 = odd ? v[3] : v[2];
-        float term = upper ? hi2 : lo2;
-        if (WARM) {              // lane 3 of a quad holds the vector's product
-          dx[hf] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(term), 0xFF, 0xf, 0xf, true));
-          if ((c & 3) == 3) term = 0.f;
-        }
+        const float term = upper ? hi2 : lo2;
+        if (WARM) dx[hf] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(term), 0xFF, 0xf, 0xf, true));   // lane 3 of a quad
         x[hf] = quad_add<0x4E>(quad_add<0xB1>(term));   // lanes 0+1, 2+3 of a quad, then both
       }
       sum[gate] = half1 ? x[1] : x[0];
-      dsum[gate] = half1 ? dx[1] : dx[0];
+      if (WARM) {                // (where a piece stands, the vector is below the state's last place long before its own tokens)
+        dsum[gate] = half1 ? dx[1] : dx[0];
+        sum[gate] -= dsum[gate];
+      }
     }
     const float r = scan_sigmoid(g_r + b_r + sum[0]);
     const float u = scan_sigmoid(g_u + b_u + sum[1]);
