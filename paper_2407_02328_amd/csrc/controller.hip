@@ -351,9 +351,9 @@ __device__ inline float quad_add(float v) {   // v + the value of the lane that 
 // later chunks as one chain at once.  Error against 64 bits (2-norm, prompts of 200 to 1024
 // tokens, update gates as drawn and opened by 0.3, 0.5, 0.65): z 1.06e-7 to 1.54e-7 as one chain, 1.08e-7 to 1.48e-7 in pieces;
 // from gates opened by 0.8 on, or with a few units that hardly forget, no piece stands and both are the same bits.
-// 16 sequences, a chunk of 512 tokens: 187 -> 60 us (55 the pieces, next to the projection of the chunk after, 4 the meeting); where no
-// piece stands 196.  Inits of remembered prompts, one chain / pieces whose tokens are left to MEET / as it is: 16 of 1024 610 / 681 / 637
-// us, 1 of 512 241 / 276 / 247, 64 of 2048 1110 / 1220 / 1180.
+// 16 sequences, a chunk of 512 tokens: 187 -> 57 us (52 the pieces, 50 without the vector, 5 the meeting); where no piece stands 196.
+// Inits, one chain / pieces: 16 prompts of 1024 610 / 375 us, 1 of 512 241 / 105, 64 of 2048 1110 / 840; of remembered prompts, one
+// chain / pieces whose tokens are left to MEET / as it is: 610 / 681 / 633, 241 / 276 / 247, 1110 / 1220 / 1190.
 enum { WHOLE = 0, PIECES = 1, MEET = 2 };
 constexpr int kWarmUp = 64, kMinPiece = 32, kMaxPieces = 14;
 constexpr float kMeet = 0x1p-21f, kForget = 0x1p-24f;
