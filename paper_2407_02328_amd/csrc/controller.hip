@@ -373,7 +373,8 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
   constexpr int SPS = DP + 32;                             // distance between two terms: 16 lanes' reads hit 64 different banks
   __shared__ __attribute__((aligned(16))) uint16_t sp[2][4 * SPS];   // z as bf16 terms, of two tokens in turn
   __shared__ float4 gbuf[SPLIT ? 2 : 1][SPLIT ? TB * (3 * DP / 4) : 1];   // input pre-activations of two blocks of tokens
-  __shared__ int s_meet[4];                             // MEET: what the waves found
+  __shared__ int s_meet[4];                             // what the waves found
+  __shared__ int s_joint;                               // PIECES: what is known at a joint
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
   // this lane's unit: register c / 4 of the rows 4g .. 4g+3 of the half c % 2 (lanes with c & 2 repeat it)
@@ -515,11 +516,11 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     if (ok && !twin) m.guess[(size_t(b) * m.pieces + blockIdx.y) * DP + unit] = hcur;
     if (tid == 0) {
       const int known = __hip_atomic_fetch_or(m.said + b * kMaxPieces + blockIdx.y, ok ? STANDS : EARLY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_meet[0] = !ok && (known & LEFT);
+      if (!ok) s_joint = known & LEFT;   // (a word of its own: other waves may still be reading s_meet)
     }
     if (ok) return true;
     __syncthreads();
-    if (s_meet[0] == 0) return false;
+    if (s_joint == 0) return false;
     hcur = __hip_atomic_load(zrow + size_t(keep - 1) * DP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     put_state(sp[cur]);
     __syncthreads();
@@ -533,17 +534,17 @@ __global__ __launch_bounds__(256, 2) void ctrl_scan128_mfma_kernel(const CellArg
     if (wave == 0) {
       const int known = lane < m.pieces ? __hip_atomic_load(said + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
       const int more = __builtin_ctzll(~(__ballot(known & EARLY) >> done));
-      if (lane == done) s_meet[0] = more > 0 ? more : known & STANDS ? 0 : -1;
+      if (lane == done) s_joint = more > 0 ? more : known & STANDS ? 0 : -1;
     }
     __syncthreads();
-    int more = s_meet[0];
+    int more = s_joint;
     if (more < 0) {              // nothing is known of the next one
       if (!twin) __hip_atomic_store(zrow + size_t(end - 1) * DP, hcur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      if (tid == 0) s_meet[0] = __hip_atomic_fetch_or(said + done, LEFT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & EARLY ? 1 : 0;
+      if (tid == 0) s_joint = __hip_atomic_fetch_or(said + done, LEFT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & EARLY ? 1 : 0;
       __syncthreads();
-      more = s_meet[0];
+      more = s_joint;
     }
     __syncthreads();
     more = __builtin_amdgcn_readfirstlane(more);
