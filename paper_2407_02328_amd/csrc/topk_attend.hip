@@ -11,19 +11,22 @@
 //
 //   1 range     mean and deviation of the weights over an evenly spaced sample of the keys give a range in which the K-th
 //               largest is expected.
-//   2 count     a histogram per query in LDS over that range (128 bins, [bin][query]: every query has a bank of its own);
-//               the bin that holds the K-th largest weight and its rank in it.  Counted again for the queries whose K-th largest is
-//               outside the range, or in a bin with more than 16 weights: up to twice over another range, then over bins that
-//               are equal in the order-preserving integer images of the weights, between the two weights it is known to lie
-//               between (7 of at most 32 bits a count; at once where the bin stands alone, as one of equal weights does).  So a
-//               workgroup counts at most 3 + 5 times whatever the weights' sizes and distribution, and the result never
-//               depends on the sample, only the time does.
+//   2 count     a histogram per query in LDS over that range (256 bins, two to a word, [word][query]: every query has a bank of its
+//               own); the bin that holds the K-th largest weight and its rank in it.  Counted again for the queries whose K-th largest
+//               is outside the range, or in a bin with more than 16 weights that do not all stay: up to twice over another range,
+//               then over bins that are equal in the order-preserving integer images of the weights, between the two weights it is
+//               known to lie between (8 of at most 32 bits a count; at once where the bin stands alone, as one of equal weights
+//               does).  So a workgroup counts at most 3 + 4 times whatever the weights' sizes and distribution, and the result
+//               never depends on the sample, only the time does.
 //   3 ties      only where more than 16 weights are equal to the K-th largest: one pass in which the last position that stays is
 //               found from the bit masks of each step.
 //   4 product   P = exp2((w - max) / sqrt(d) . log2 e) of the weights above the bin (the same instructions on the same
 //               operands give the weights the very bits they had in 2), as two bf16 terms (16 significant bits), and
 //               O^T += V^T . P^T.  A lane's weights sit where the second product wants its operand; V comes out of LDS
-//               transposed (ds_read_b64_tr_b16).  The few weights inside the bin are set aside with their positions.
+//               transposed (ds_read_b64_tr_b16).  The few weights inside the bin are set aside with their positions, unless the whole
+//               bin stays: then they are above it like the others.  Setting one aside is a detour of the wave's other 63 lanes: with
+//               128 bins, and bins that stay whole set aside as well, 3.2 weights a query made that a fifth of 512 rows of 1024 tokens;
+//               now it is one (660 -> 610 us; 8192 tokens 5690 -> 5520, 40 rows of 1000 tokens at d = 64 55.1 -> 48.8).
 //   5 the rest  the weights set aside are ranked directly (equal ones by position), those that stay add their rows of V in fp32;
 //               the waves' partial sums are added through LDS in a fixed order, rounded once.
 //
@@ -34,21 +37,23 @@
 // rows of V of the weights set aside (a third of the time at 1024 tokens).  One workgroup of eight waves and KB = 4 per unit took 850
 // us for 512 rows of 1024 tokens and 6670 us for 128 rows of 8192.
 //
-// Measured (us per call, K = 96): 512 rows of 1024 tokens, d = 128: 1900 -> 662; 128 rows of 8192 tokens, d = 128:
-// 80900 -> 5640; 4 rows of 128 tokens, d = 64: 21.3 -> 10.6.  At first, 16 queries per workgroup kept their fp32 weights in LDS (in
+// Measured (us per call, K = 96): 512 rows of 1024 tokens, d = 128: 1900 -> 610; 128 rows of 8192 tokens, d = 128:
+// 80900 -> 5520; 4 rows of 128 tokens, d = 64: 21.3 -> 10.5.  At first, 16 queries per workgroup kept their fp32 weights in LDS (in
 // memory beyond 2048 tokens, read again by every pass of a radix select), with K and a transposed copy of V loaded straight
 // into the operand layout: 16 look-ups in the L1 per 256 bytes, K and V read from the L2 once per 16 queries.
-// Those are Gaussian weights, which mostly need one count.  512 rows of 1024 tokens with 60 % of the keys zeroed take 866 us, with
-// whole-numbered q and k 674 us (ranges alone would take 17 counts to close in on a zero).
-// What bounds it now, at 8192 tokens: a wave issues an instruction in 42 % of its cycles, waits for LDS or a barrier in 26 %, and for
-// the matrix unit or the other wave of its SIMD in 32 % (counters); a SIMD issues vector instructions in 50 % of the cycles and has
-// matrix work in 31 %; two waves a SIMD are what 253 registers leave room for.  The counts take 1.6 ms of the 5.6 (0.5 of them the K
-// tiles' way through LDS, 0.3 the histograms' additions), the products 3.3, the weights set aside 0.5.
+// Those are Gaussian weights, which mostly need one count.  256 rows of 1024 tokens (before / now): Gaussian 339 / 312, 60 % of the keys
+// zeroed 455 / 453, whole-numbered q and k 592 / 606 (ranges alone would take 17 counts to close in on a zero), all keys equal 559 / 593.
+// What bounds it now, at 8192 tokens (counters): a SIMD issues vector instructions in 46 % of its cycles and has matrix work in 32 %, which
+// two waves a SIMD (what 253 registers leave room for) hardly overlap; a wave waits for LDS or a barrier in 24 %.  LDS is busy in 34 %.  A
+// quarter fewer vector instructions a step gave 1 %.  The wave in a step's products goes first (s_setprio): 609 -> 598 us at 1024 tokens, 451 ->
+// 429 for 64 rows of 3000; not at d = 64 nor with 32 queries, where it makes no difference or costs 1 %.
 // Tried and not kept: thresholds from a sample and candidate lists in LDS instead of histograms (6.5 vector instructions per
 // weight and a selection of 20000 cycles per workgroup; 1080 us / 8800 us); a pass of its own for the weights of the bin (965 us /
 // 7700 us); the K operand of the next step fetched a step ahead (132 registers too many); the bins' ends searched for in every
 // workgroup, so that the product compares instead of multiplying (the same, 10.6 -> 11.0 us for the smallest); the product's loop
-// unrolled by two like the counts' (78 registers spilled).
+// unrolled by two like the counts' (78 registers spilled); 128 queries and eight waves a workgroup, one per unit, which reads K and V half
+// as often (759 us / 5730 us); all sixteen weights of a step looked at ahead of its products, for one detour a step (661 us / 5900 us); a
+// narrower range, 0.75 of the deviation (598 us / 5500 us, but where 60 % of the keys are zero its counts miss: 491 for 455).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -68,12 +73,13 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kBins = 128;           // bin 0: below the range, the last one: above it
+constexpr int kRows = 128;           // a histogram's words: two bins each, the even one's and the odd one's weights together in the lower
+constexpr int kBins = 2 * kRows;     // half, the odd one's in the upper (at most 32768 keys).  Bin 0: below the range, the last one: above it
 constexpr int kFew = 16;             // weights of a bin that are ranked directly
 constexpr int kSample = 128;         // keys of the sample: mean and deviation to a tenth of the deviation, for a range of two
-// A weight's bin is read off the bits of y = a w + b: with bin 0 at kBin0 = 2^23, where floats are the integers, and kBinWidth =
-// 2^8 units a bin, bits 8 .. 14 of y hold it (one multiply-add and a clamp, no conversion).
-constexpr float kBin0 = 8388608.f, kBinWidth = 256.f;
+// A weight's bin is read off the bits of y = a w + b: with bin 0 at kBin0 = 2^23, where floats are the integers, and as many units a
+// bin as half a row of the histogram has bytes, the bits of y hold the row's place (one multiply-add, a clamp and an and-or, no conversion).
+constexpr float kBin0 = 8388608.f;
 constexpr int kRangeCounts = 3;      // most counts over ranges of weights; then at most ceil(32 / 7) over images
 
 // Order-preserving image of a weight (larger float <=> larger integer, never 0 for a number) and back.
@@ -91,9 +97,16 @@ __device__ inline float normal_quantile(float p) {
   return p <= 0.5f ? z : -z;
 }
 
+// Bits of the lanes whose x is at least y (none where one is NaN).
+// ... in [0, y) for a y whose bits are `end`.
+__device__ __forceinline__ uint64_t lanes_below(float x, uint32_t end) {
+  return __builtin_amdgcn_uicmp(__float_as_uint(x), end, 36);   // 36: unsigned, <
+}
+__device__ __forceinline__ uint64_t lanes_ge(float x, float y) { return __builtin_amdgcn_fcmpf(x, y, 3); }   // 3: ordered, >=
+
 constexpr uint32_t kLowest = 0x007fffffu, kHighest = 0xff800000u;   // images of the infinities
 // Right shift after which the distances 0 .. span fit the bins.
-__device__ inline int image_shift(uint32_t span) { return max(0, 25 - __clz(int(span))); }
+__device__ inline int image_shift(uint32_t span) { return max(0, 24 - __clz(int(span))); }
 
 struct TopkArgs {
   const bf16_t *Q, *K, *V;   // [rows][S][d]
@@ -108,7 +121,7 @@ template <int DH, int NQB, int KB>
 struct TopkLds {
   static constexpr int NQ = 32 * NQB;
   static constexpr int kTile = 32 * KB * DH * 2;
-  static constexpr int kHist = NQ * kBins * 4;
+  static constexpr int kHist = NQ * kRows * 4;
   static constexpr int kBig = 2 * kTile + (kHist > 2 * kTile ? kHist : 2 * kTile);
   static constexpr int kMerge = KB * NQB * (DH / 32) * 16 * 64 * 4;
   static constexpr int kFewAt = kBig > kMerge ? kBig : kMerge;
@@ -121,12 +134,15 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
   using Lds = TopkLds<DH, NQB, KB>;
   constexpr int NT = 64 * NQB * KB, NQ = 32 * NQB;
   constexpr int kStep = 32 * KB;               // keys per step
-  constexpr int TPQ = NT / NQ, BPT = kBins / TPQ;   // threads per query and bins per thread where the histograms are read
+  constexpr int TPQ = NT / NQ, RPT = kRows / TPQ;   // threads per query and rows per thread where the histograms are read
   constexpr int CPR = DH / 8;                  // 16-byte chunks per row
   constexpr int NLD = kStep * CPR / NT;        // chunks of a tile per thread
   constexpr int KT = DH / 16, DB = DH / 32;
+  constexpr bool kFirst = DH == 128 && NQB == 2;   // a wave in its products issues before the other one of its SIMD
+  constexpr uint32_t kRow = NQ * 4;            // bytes of a histogram's row
+  constexpr float kBinWidth = float(kRow / 2);
   extern __shared__ __align__(16) unsigned char smem[];
-  uint32_t *s_hist = reinterpret_cast<uint32_t *>(smem + 2 * Lds::kTile);   // [kBins][NQ]
+  uint32_t *s_hist = reinterpret_cast<uint32_t *>(smem + 2 * Lds::kTile);   // [kRows][NQ]
   float2 *s_few = reinterpret_cast<float2 *>(smem + Lds::kFewAt);       // [NQ][kFew] weight, bits of its position, of the weights set aside
   float *s_a = reinterpret_cast<float *>(smem + Lds::kMisc);   // [NQ] bin of w = a w + b, while its range is counted (else 0)
   float *s_b = s_a + NQ;
@@ -183,11 +199,19 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
   };
   const int ld_row = tid / CPR;
   const uint32_t ld_col = uint32_t(tid % CPR) * 16u;
-  auto load_tile = [&](const bf16_t *src, int step, u32x4 (&r)[NLD], int row) {   // row: ld_row
+  // Keys beyond the last one read the last one; only a step that has some works out an address per row.
+  const uint32_t ld_at = uint32_t(ld_row) * (DH * 2) + ld_col;
+  auto load_tile = [&](const bf16_t *src, int step, u32x4 (&r)[NLD]) {
+    auto at = (const __attribute__((address_space(1))) char *)src + size_t(step) * (kStep * DH * 2);
+    asm("" : "+s"(at));   // a scalar base and one offset per thread, not an address per thread and row kept from step to step
+    if ((step + 1) * kStep <= a.S) {
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int key = min(step * kStep + row + i * (NT / CPR), a.S - 1);
-      r[i] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(src) + (uint32_t(key) * (DH * 2) + ld_col));
+      for (int i = 0; i < NLD; ++i) r[i] = *(const __attribute__((address_space(1))) u32x4 *)(at + i * (NT / CPR * DH * 2) + ld_at);
+    } else {
+      const int last = a.S - 1 - step * kStep;
+#pragma unroll
+      for (int i = 0; i < NLD; ++i)
+        r[i] = *(const __attribute__((address_space(1))) u32x4 *)(at + (uint32_t(min(ld_row + i * (NT / CPR), last)) * (DH * 2) + ld_col));
     }
   };
   auto load_sample = [&](int step, uint32_t stride_fp, u32x4 (&r)[NLD]) {   // key = (index * stride_fp) >> 12
@@ -244,9 +268,13 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
   auto nothing = [](int) {};
   // keys from kb on that the query cannot see become NaN, which no comparison lets through
   auto hide = [&](f32x16 &s, int kb) {
+    const int seen = qpos - 4 * h - kb;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (kb + 8 * (i >> 2) + 4 * h + (i & 3) > qpos) s[i] = __builtin_nanf("");
+    for (int i = 0; i < 16; ++i) {
+      constexpr int kGreater = 38;               // signed
+      const uint64_t hidden = __builtin_amdgcn_sicmp(8 * (i >> 2) + (i & 3), seen, kGreater);
+      s[i] = __builtin_amdgcn_inverse_ballot_w64(hidden) ? __builtin_nanf("") : s[i];
+    }
   };
 
   // ---- one pass over the keys (SAMPLE: over a sample of those before q0, which all queries see): consume(w0, .. w3, g, first
@@ -258,7 +286,7 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
       if constexpr (SAMPLE)
         load_sample(st, stride_fp, kr);
       else
-        load_tile(Kb, st, kr, ld_row);
+        load_tile(Kb, st, kr);
     };
     load(0);
     __syncthreads();                   // the tiles of the pass before are done with
@@ -277,7 +305,9 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
       __syncthreads();                 // tile st is there, and nobody reads tile st - 1 any more
       if (st + 1 < steps) store_tile(kOther, kr);
       if (st + 2 < steps) load(st + 2);
+      if constexpr (kFirst) __builtin_amdgcn_s_setprio(1);
       next = weights(kThis, [&](int g) { consume(w[4 * g], w[4 * g + 1], w[4 * g + 2], w[4 * g + 3], g, kb); });
+      if constexpr (kFirst) __builtin_amdgcn_s_setprio(0);
       kb += kStep;
       if (!SAMPLE && kb + 31 > qfirst) hide(next, kb);
     };
@@ -387,7 +417,7 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
   for (int tries = 0, ranges = 1; tries < kRangeCounts + 5; ++tries) {
     if (tid == 0) s_flag[0] = 0;
     if (tid == 1) s_flag[2] = 0;
-    for (int i = tid; i < NQ * kBins / 4; i += NT) reinterpret_cast<u32x4 *>(s_hist)[i] = u32x4{0u, 0u, 0u, 0u};
+    for (int i = tid; i < NQ * kRows / 4; i += NT) reinterpret_cast<u32x4 *>(s_hist)[i] = u32x4{0u, 0u, 0u, 0u};
     if (tid < NQ) {
       s_min[tid] = ~0u;
       s_most[tid] = 0u;
@@ -396,15 +426,20 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
     if (ranges) {
       const float sa = s_a[ql], sb = s_b[ql];
       float top = -INFINITY;
+      using LdsCount = __attribute__((address_space(3))) uint32_t;
+      const uint32_t column = uint32_t(uintptr_t((LdsCount *)smem)) + uint32_t(ql) * 4u;   // (shared memory starts at 0: nothing in it is static)
       sweep(std::false_type(), steps, 0u, [&](float w0, float w1, float w2, float w3, int, int) {
         const float w[4] = {w0, w1, w2, w3};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float y = __builtin_amdgcn_fmed3f(fmaf(w[i], sa, sb), kBin0, kBin0 + float(kBins - 1) * kBinWidth);
-          const uint32_t at = (__float_as_uint(y) & uint32_t(kBins - 1) << 8) / (256 / NQ) | uint32_t(ql);   // row y's bin of [kBins][NQ]
-          __hip_atomic_fetch_add(&s_hist[at], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          top = __builtin_amdgcn_fmed3f(top, w[i], INFINITY);   // the larger one, or the one that is a number
+          uint32_t at = (__float_as_uint(y) & (uint32_t(kRows - 1) * kRow)) | column;   // row y's bin is in, of [kRows][NQ]
+          asm("" : "+v"(at));                    // (one operation; left to itself the or joins the address's sum)
+          const uint32_t one = (__float_as_uint(y) & (kRow / 2)) * (65536u / (kRow / 2)) | 1u;   // in both halves where the bin is odd
+          __hip_atomic_fetch_add((LdsCount *)uintptr_t(at + 2 * Lds::kTile), one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
+        top = fmaxf(fmaxf(fmaxf(fmaxf(top, w0), w1), w2), w3);   // (numbers go before NaN)
+        asm volatile("" : "+v"(top));
       });
       __hip_atomic_fetch_max(&s_max[ql], weight_image(top), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       if (fabsf(top) * a.scale_log2 > 0x1p27f && top != -INFINITY) s_flag[4] = 1;   // (-infinity: no key of these was visible)
@@ -418,7 +453,8 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
         for (int i = 0; i < 4; ++i) {
           const uint32_t u = weight_image(w[i] + 0.f), down = last - u;   // (-0 counts as 0)
           if (down <= span) {                    // not for the NaN of a hidden key, whose image is beyond both infinities'
-            __hip_atomic_fetch_add(&s_hist[(kBins - 1 - (down >> shift)) * NQ + ql], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const uint32_t bin = uint32_t(kBins - 1) - (down >> shift);
+            __hip_atomic_fetch_add(&s_hist[bin / 2 * NQ + ql], bin & 1u ? 65537u : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             least = min(least, u);
             most = max(most, u);
           }
@@ -428,14 +464,14 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
       __hip_atomic_fetch_max(&s_most[ql], most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __syncthreads();
-    // TPQ threads per query, BPT bins each
+    // TPQ threads per query, RPT rows each
     const int q = tid % NQ, grp = tid / NQ;
     const float sa = s_a[q];
-    uint32_t cnt[BPT], mine = 0u;
+    uint32_t word[RPT], mine = 0u;
 #pragma unroll
-    for (int j = 0; j < BPT; ++j) {
-      cnt[j] = s_hist[(grp * BPT + j) * NQ + q];
-      mine += cnt[j];
+    for (int j = 0; j < RPT; ++j) {
+      word[j] = s_hist[(grp * RPT + j) * NQ + q];
+      mine += word[j] & 0xffffu;
     }
     s_part[grp * NQ + q] = mine;
     const bool open = ranges ? sa != 0.f : s_last[q] != 0u;
@@ -446,29 +482,38 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
     const uint32_t want = uint32_t(a.topk);
     if (open && above < want && above + mine >= want) {   // this thread's bins hold it
       int bin = 0;
-      uint32_t in = 0u, need = 0u, beside = 0u;
+      uint32_t here = 0u, up = 0u, down = 0u, over = 0u;   // the row's word, the next one's, the one's before, the weights above the row
       bool found = false;
 #pragma unroll
-      for (int j = BPT - 1; j >= 0; --j) {
-        if (!found && above + cnt[j] >= want) {
+      for (int j = RPT - 1; j >= 0; --j) {
+        const uint32_t both = word[j] & 0xffffu;
+        if (!found && above + both >= want) {
           found = true;
-          bin = grp * BPT + j;
-          need = want - above;
-          in = cnt[j];
-          beside = (j > 0 ? cnt[j - 1] : 0u) + (j + 1 < BPT ? cnt[j + 1] : 0u);
+          bin = 2 * (grp * RPT + j);
+          here = word[j];
+          up = j + 1 < RPT ? word[j + 1] : 0u;
+          down = j > 0 ? word[j - 1] : 0u;
+          over = above;
         }
-        above += cnt[j];
+        above += both;
       }
+      const uint32_t odd = here >> 16, even = (here & 0xffffu) - odd;
+      const bool upper = over + odd >= want;     // in the odd bin
+      if (upper) ++bin;
+      else over += odd;
+      const uint32_t in = upper ? odd : even, need = want - over;
+      const uint32_t beside = upper ? even + (up & 0xffffu) - (up >> 16) : odd + (down >> 16);
+      const bool all = need == in;               // the whole bin stays: nothing of it has to be ranked, however many they are
       const bool few = in <= uint32_t(kFew);
       if (ranges) {
         const float sb = s_b[q];
         s_a[q] = 0.f;
         s_b[q] = 0.f;
-        if (few && bin > 0 && bin < kBins - 1) {
+        if ((few || all) && bin > 0 && bin < kBins - 1) {
           s_ga[q] = sa;
           s_gb[q] = sb;
           s_bin[q] = kBin0 + kBinWidth * float(bin);
-          s_need[q] = int(need);
+          s_need[q] = all ? 0 : int(need);
           s_first[q] = s_last[q] = 0u;
         } else {
           uint32_t end[2];
@@ -496,13 +541,13 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
         const uint32_t size = (1u << shift) - 1u;
         last -= uint32_t(kBins - 1 - bin) << shift;
         if (last - first > size) first = last - size;
-        if (few || shift == 0 || s_min[q] == s_most[q]) {   // few weights, or all of them equal
+        if (few || all || shift == 0 || s_min[q] == s_most[q]) {   // few weights, or all of them stay, or are equal
           s_ga[q] = image_weight(first);
-          s_gb[q] = image_weight(last + 1u);     // (NaN behind infinity: nothing is above)
+          s_gb[q] = image_weight(all ? first : last + 1u);   // (NaN behind infinity: nothing is above)
           s_bin[q] = -1.f;
-          s_need[q] = int(need);
+          s_need[q] = all ? 0 : int(need);
           first = last = 0u;
-          if (!few) {
+          if (!few && !all) {
             s_tie[q] = -2;
             s_flag[1] = 1;
           }
@@ -531,19 +576,20 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
       uint32_t end[2] = {kHighest, kLowest};     // no bin was looked for: all weights are above it
       if (bin > 0.f) ends_of(s_ga[tid], s_gb[tid], bin, end);
       s_ga[tid] = image_weight(end[0]);
-      s_gb[tid] = image_weight(end[1]);
+      s_gb[tid] = image_weight(bin > 0.f && s_need[tid] == 0 ? end[0] : end[1]);
     }
     __syncthreads();
   }
 
   // ---- 3: the position up to which the weights of a bin stay that holds many equal ones ----
   const float from = s_ga[ql], above = s_gb[ql], bin = s_bin[ql];   // the ends of the bin, or a, b and the bin
+  const float staying = s_need[ql] == 0 ? 0.f : kBinWidth;           // (all of the bin stays, none of it has to be ranked)
   auto inside = [&](float w) { return bool((w >= from) & !(w >= above)); };   // (false for the NaN of a hidden key)
   const bool crowded = s_flag[1] != 0;
   if (crowded) {
     for (int st = 0; st < steps; ++st) {
       u32x4 kr[NLD];
-      load_tile(Kb, st, kr, ld_row);
+      load_tile(Kb, st, kr);
       __syncthreads();
       store_tile(0, kr);
       __syncthreads();
@@ -585,8 +631,6 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
   float lsum = 0.f;
   auto product = [&](auto by_images_) {
     constexpr bool IMAGES = decltype(by_images_)::value;
-    int row = ld_row;
-    asm volatile("" : "+v"(row));   // its addresses are not kept from the sweeps on: 22 registers
     const float top = image_weight(s_max[ql]), negmax = -top * a.scale_log2;
     auto exponent = [&](float x) { return IMAGES ? (x - top) * a.scale_log2 : fmaf(x, a.scale_log2, negmax); };
     const int tie = s_tie[ql];
@@ -600,16 +644,16 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
     // K is one step ahead of V: a step's products Q K^T run next to the exponentials of the step before
     constexpr int kV = 2 * Lds::kTile;
     u32x4 kr[NLD], vr[NLD];
-    load_tile(Kb, 0, kr, row);
+    load_tile(Kb, 0, kr);
     __syncthreads();
     store_tile(0, kr);
-    if (steps > 1) load_tile(Kb, 1, kr, row);
-    load_tile(Vb, 0, vr, row);
+    if (steps > 1) load_tile(Kb, 1, kr);
+    load_tile(Vb, 0, vr);
     __syncthreads();
     if (steps > 1) store_tile(Lds::kTile, kr);
     store_tile(kV, vr);
-    if (steps > 2) load_tile(Kb, 2, kr, row);
-    if (steps > 1) load_tile(Vb, 1, vr, row);
+    if (steps > 2) load_tile(Kb, 2, kr);
+    if (steps > 1) load_tile(Vb, 1, vr);
     f32x16 s = weights(0, nothing);
     int kb = kg * 32;
     if (kb + 31 > qfirst) hide(s, kb);
@@ -621,14 +665,15 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
       if constexpr (!LAST) {
         if (st + 1 < steps) store_tile(other, kr);
         store_tile(kV + tile, vr);
-        if (st + 2 < steps) load_tile(Kb, st + 2, kr, row);
-        if (st + 1 < steps) load_tile(Vb, st + 1, vr, row);
+        if (st + 2 < steps) load_tile(Kb, st + 2, kr);
+        if (st + 1 < steps) load_tile(Vb, st + 1, vr);
       }
       // P of two of the lane's weights, as two bf16 terms: the upper 16 bits, and the upper 16 bits of what is left (exact, >= 0)
-      auto exponentials = [&](float x0, float x1, bool stays0, bool stays1, uint32_t &ph, uint32_t &pl) {
-        const float p0 = stays0 ? __builtin_amdgcn_exp2f(exponent(x0)) : 0.f;
-        const float p1 = stays1 ? __builtin_amdgcn_exp2f(exponent(x1)) : 0.f;
+      auto exponentials = [&](float x0, float x1, uint64_t stays0, uint64_t stays1, uint32_t &ph, uint32_t &pl) {
+        const float p0 = __builtin_amdgcn_inverse_ballot_w64(stays0) ? __builtin_amdgcn_exp2f(exponent(x0)) : 0.f;
+        const float p1 = __builtin_amdgcn_inverse_ballot_w64(stays1) ? __builtin_amdgcn_exp2f(exponent(x1)) : 0.f;
         lsum += p0 + p1;
+        asm volatile("" : "+v"(lsum));        // added here: sixteen of them are not kept for the end of the step
         const uint32_t h0 = __float_as_uint(p0), h1 = __float_as_uint(p1);
         ph = __builtin_amdgcn_perm(h1, h0, 0x07060302u);   // (h0 >> 16) | (h1 & 0xffff0000)
         pl = __builtin_amdgcn_perm(__float_as_uint(p1 - __uint_as_float(h1 & 0xffff0000u)),
@@ -656,38 +701,36 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
       };
       uint32_t ph[8], pl[8];
       auto share = [&](int g) {
-        bool stays[4], in[4], any;
-        if constexpr (IMAGES) {
+        // the lanes whose weight stays, and those whose weight is inside the bin (neither for the NaN of a hidden key)
+        uint64_t stays[4], in[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            stays[i] = w[4 * g + i] >= above;
-            in[i] = inside(w[4 * g + i]);
-          }
-          any = in[0] | in[1] | in[2] | in[3];
-        } else {
-          // >= kBinWidth above the bin, in [0, kBinWidth) inside it, else below (exact: rounding is monotone, and the difference is
-          // exact inside the bin), and so for the NaN of a hidden key
-          constexpr uint32_t kOutside = 0x43800000u;   // bits of kBinWidth
-          uint32_t z[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float d = fmaf(w[4 * g + i], from, above) - bin;
-            stays[i] = d >= kBinWidth;
-            z[i] = __float_as_uint(d);
-            in[i] = z[i] < kOutside;
-          }
-          any = min(min(z[0], z[1]), min(z[2], z[3])) < kOutside;
-        }
-        if (any) {
-          if (IMAGES && crowded && tie >= 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) stays[i] |= in[i] & (kb + 8 * g + 4 * h + i <= tie);
+        for (int i = 0; i < 4; ++i) {
+          const float x = w[4 * g + i];
+          if constexpr (IMAGES) {
+            stays[i] = lanes_ge(x, above);
+            in[i] = lanes_ge(x, from) & ~stays[i];
           } else {
-            int at = __hip_atomic_fetch_add(&s_n[ql], int(in[0]) + int(in[1]) + int(in[2]) + int(in[3]), __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_WORKGROUP);
+            // >= kBinWidth above the bin, in [0, kBinWidth) inside it, else below (exact: rounding is monotone, and the difference is
+            // exact inside the bin)
+            const float d = fmaf(x, from, above) - bin;
+            stays[i] = lanes_ge(d, staying);
+            in[i] = lanes_below(d, __float_as_uint(staying));
+          }
+        }
+        if ((in[0] | in[1] | in[2] | in[3]) != 0) {
+          if (IMAGES && crowded) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (in[i] && at < kFew) s_few[ql * kFew + at++] = float2{w[4 * g + i], __int_as_float(kb + 8 * g + 4 * h + i)};
+            for (int i = 0; i < 4; ++i) {
+              stays[i] |= in[i] & __builtin_amdgcn_ballot_w64(kb + 8 * g + 4 * h + i <= tie);
+              in[i] &= __builtin_amdgcn_ballot_w64(tie < 0);
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (__builtin_amdgcn_inverse_ballot_w64(in[i])) {
+              const int at = __hip_atomic_fetch_add(&s_n[ql], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+              if (at < kFew) s_few[ql * kFew + at] = float2{w[4 * g + i], __int_as_float(kb + 8 * g + 4 * h + i)};
+            }
           }
         }
         exponentials(w[4 * g], w[4 * g + 1], stays[0], stays[1], ph[2 * g], pl[2 * g]);
@@ -698,7 +741,9 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
 #pragma unroll
         for (int g = 0; g < 4; ++g) share(g);
       } else {
+        if constexpr (kFirst) __builtin_amdgcn_s_setprio(1);
         next = weights(tile, share);
+        if constexpr (kFirst) __builtin_amdgcn_s_setprio(0);
       }
 #pragma unroll
       for (int g = 0; g < DB; ++g) {
@@ -737,23 +782,23 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
       s_mrg[((wave * DB + db) * 4 + j) * 64 + (lane ^ ((db * 4 + j) & 7))] = f32x4{o[db][4 * j], o[db][4 * j + 1], o[db][4 * j + 2], o[db][4 * j + 3]};
   // TPQ threads per query: each ranks its share of the weights and notes the ones that stay; then each adds its share of their rows
   // of V, 16-byte chunks sub, sub + TPQ, .., in fp32.
-  constexpr int RPT = kFew / TPQ, CPT = CPR / TPQ;   // weights and chunks per thread
+  constexpr int WPT = kFew / TPQ, CPT = CPR / TPQ;   // weights and chunks per thread
   const int q = tid / TPQ, sub = tid % TPQ, held = min(s_n[q], kFew), need = s_need[q];
   float extra[8 * CPT] = {0.f}, extra_l = 0.f;
   if (held > 0) {
-    float2 mine[RPT];
-    int before[RPT] = {0};
+    float2 mine[WPT];
+    int before[WPT] = {0};
 #pragma unroll
-    for (int e = 0; e < RPT; ++e) mine[e] = s_few[q * kFew + sub + TPQ * e];
+    for (int e = 0; e < WPT; ++e) mine[e] = s_few[q * kFew + sub + TPQ * e];
     for (int j = 0; j < held; ++j) {
       const float2 v = s_few[q * kFew + j];
 #pragma unroll
-      for (int e = 0; e < RPT; ++e) before[e] += v.x > mine[e].x || (v.x == mine[e].x && __float_as_int(v.y) < __float_as_int(mine[e].y)) ? 1 : 0;
+      for (int e = 0; e < WPT; ++e) before[e] += v.x > mine[e].x || (v.x == mine[e].x && __float_as_int(v.y) < __float_as_int(mine[e].y)) ? 1 : 0;
     }
     // in the order of their rank, so that the sum does not hang on the order they were set aside in
     wave_lds_fence();
 #pragma unroll
-    for (int e = 0; e < RPT; ++e)
+    for (int e = 0; e < WPT; ++e)
       if (sub + TPQ * e < held) s_few[q * kFew + before[e]] = mine[e];
     wave_lds_fence();
     const float top = image_weight(s_max[q]), less = by_images ? top : 0.f, negmax = by_images ? 0.f : -top * a.scale_log2;

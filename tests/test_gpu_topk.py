@@ -270,3 +270,37 @@ def test_topk_attention_with_crowded_or_misleading_keys(rows, S, d, top_k, keys)
     rng = np.random.default_rng(rows * 31 + S + len(keys))
     q, k = (rng.integers(-8, 9, size=(rows, S, d)) / 4.0 for _ in range(2))
     _checked_rows(O, torch, topk_attention, q, KEYS[keys](k, rng), top_k, rng, f"rows={rows} {keys}")
+
+
+@pytest.mark.parametrize("S,d,levels,top_k,offset", [
+    (32768, 64, 1, 33, 0),        # 32735 equal keys in one bin: the fullest a histogram's 16 bits get
+    (32768, 64, 1, 33, 1),        # ... and one of them stays
+    (32768, 64, 1, 33, -1),       # one of the crowded upper bin goes
+    (700, 128, 40, 350, 0),       # a cut between two crowded bins, odd and even ones: the bin above it stays whole
+    (700, 128, 41, 350, 0),
+    (700, 64, 40, 350, 7),        # ... and inside one
+    (200, 128, 200, 50, 0),       # bins of a single weight
+])
+def test_bins_that_stay_whole_and_bins_that_are_full(S, d, levels, top_k, offset):
+    """Keys whose weights are whole numbers 0 .. levels, the same for every query (q is the first unit vector): how many of them a
+    bin holds is known.  Every query's kept set is the top_k highest, equal ones by position; the last queries are checked in 64
+    bits (the bound of the other tests)."""
+    torch, O, topk_attention = _mods()
+    rng = np.random.default_rng(S + levels + top_k)
+    level = np.zeros(S)
+    if levels == 1:
+        level[rng.permutation(S - 64)[:top_k]] = 1.0             # top_k keys above all others
+    else:
+        level = rng.integers(0, levels + 1, size=S).astype(np.float64)
+        above = np.sort(level)[::-1]
+        top_k = int(np.searchsorted(-above, -above[top_k - 1], side="right"))   # every key down to one level: the cut between two
+    keep = top_k + offset
+    q, k = np.zeros((1, S, d)), np.zeros((1, S, d))
+    q[..., 0], k[0, :, 0] = 1.0, level
+    v = _bf16_values(torch, rng.standard_normal((1, S, d)))
+    got = topk_attention(_to_gpu(torch, q), _to_gpu(torch, k), _to_gpu(torch, v), keep).float().cpu().numpy().astype(np.float64)
+    for i in range(S - 40, S):
+        sel = np.sort(np.argsort(-level[:i + 1], kind="stable")[:keep])
+        want = O.softmax_row(level[sel] / np.sqrt(np.float64(d))) @ v[0, sel]
+        e = np.abs(got[0, i] - want).max() / np.abs(want).max()
+        assert e < TOL, f"S={S} K={keep}: query {i}: {e}"
