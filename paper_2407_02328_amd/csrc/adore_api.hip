@@ -359,20 +359,33 @@ hipError_t launch_controller(adore_ctx *ctx, const void *x_n, int seq_rows, cons
 // compute units: they become ready with the recurrence that runs beside them, which is ahead of them by a queue's latency.
 // Two copies of what passes between the three (one, and one stream, where the workspace has no room): a chunk's projection waits for the recurrence, a chunk's recurrence for the
 // scoring, of the chunk two before it.  Everything is complete on the caller's stream when this returns its last wait.
-// 16 prompts of 1024 tokens (two chunks) to the first token 770 -> 684 us; 32 prompts of 2048 tokens: 4 x 370 us of controller
-// -> 1.14 ms in all.
+// A recurrence that is made in pieces takes a longer chunk in hardly more time (its pieces go side by side, and each has a warm-up of
+// its own), so where the cache holds the second copy the chunks are as long as it has room for: the whole prompt at once, else two halves in
+// turn.  Init of 16 prompts of 1024 tokens 384 -> 347 us, 1 of 1000 231 -> 173, 4 of 8192 1173 -> 722, 128 of 1024 1330 -> 1246; of
+// remembered ones (one chain whatever the chunks) 649 -> 637, 513 -> 469, 3474 -> 3244, 1430 -> 1434.
 hipError_t prompt_controller(adore_ctx *ctx, const void *ctrl_input, const float *score_override, int S) {
   const adore_config &c = ctx->cfg;
   const size_t token_bytes = size_t(c.hidden) * elem_size(c);
-  const int nchunks = (S + kPromptChunk - 1) / kPromptChunk;
-  const bool two_copies = ctx->gi_rows[1] > 0, apart = ctx->overlap && nchunks > 1 && two_copies;
+  int chunk = kPromptChunk, first_copy = 0, copies = ctx->gi_rows[1] > 0 ? 2 : 1;
+  if (S > kPromptChunk && ctx->gi_rows[2] > 0 && c.dtype == ADORE_BF16 && ctrl_chunk_in_two(c, S) && scan_pieces(c, S) > 1) {
+    const int whole = int(std::min<size_t>(ctx->gi_rows[1] / c.batch, S)), half = int(std::min<size_t>(ctx->gi_rows[2] / c.batch, S));
+    const int most = whole >= S ? S : half & ~7;
+    if (most > kPromptChunk) {
+      const int n = (S + most - 1) / most;
+      chunk = n == 1 ? S : ((S + n - 1) / n + 7) & ~7;      // even lengths, of whole groups of eight tokens: no more than `most`
+      first_copy = 1;
+      copies = n == 1 ? 1 : 2;
+    }
+  }
+  const int nchunks = (S + chunk - 1) / chunk;
+  const bool apart = ctx->overlap && nchunks > 1 && copies == 2;
   hipStream_t st = ctx->stream, st_proj = apart ? ctx->side : st, st_score = apart ? ctx->side2 : st;
   hipEvent_t ev_proj = ctx->ev_in, ev_scan = ctx->ev_att, ev_score = ctx->ev_join;
-  int ksplit[2] = {1, 1};
-  auto length = [&](int i) { return std::min(kPromptChunk, S - i * kPromptChunk); };
-  auto copy_of = [&](int i) { return two_copies ? i & 1 : 0; };
+  int ksplit[3] = {1, 1, 1};
+  auto length = [&](int i) { return std::min(chunk, S - i * chunk); };
+  auto copy_of = [&](int i) { return first_copy + (copies == 2 ? i & 1 : 0); };
   auto project = [&](int i, hipStream_t on) {
-    const char *x = static_cast<const char *>(ctrl_input) + size_t(i) * kPromptChunk * token_bytes;
+    const char *x = static_cast<const char *>(ctrl_input) + size_t(i) * chunk * token_bytes;
     return launch_ctrl_input(ctx, on, x, c.batch * length(i), length(i), S, copy_of(i), &ksplit[copy_of(i)]);
   };
 #define CHUNK_TRY(EXPR)                          \
@@ -388,7 +401,7 @@ hipError_t prompt_controller(adore_ctx *ctx, const void *ctrl_input, const float
   }
   CHUNK_TRY(project(0, st));
   for (int i = 0; i < nchunks; ++i) {
-    const int len = length(i), buf = copy_of(i), pos0 = i * kPromptChunk;
+    const int len = length(i), buf = copy_of(i), pos0 = i * chunk;
     const float *given = score_override ? score_override + pos0 : nullptr;
     const bool two = ctrl_chunk_in_two(c, len);
     if (apart && i > 0) CHUNK_TRY(hipStreamWaitEvent(st, ev_proj, 0));
@@ -469,6 +482,10 @@ int adore_create(const adore_config *cfg, const adore_weights *weights, void *wo
     ctx->gi[i] = ctx->gi_rows[i] ? reinterpret_cast<float *>(base + l.gi[i]) : nullptr;
     ctx->zseq[i] = ctx->gi_rows[i] ? reinterpret_cast<float *>(base + l.zseq[i]) : nullptr;
   }
+  // a copy in the cache can be taken in halves: the second one's rows
+  ctx->gi_rows[2] = l.gi[1] == l.cache_k && ctx->gi_rows[1] > 0 ? ctx->gi_rows[1] / 2 : 0;
+  ctx->gi[2] = ctx->gi_rows[2] ? ctx->gi[1] + ctx->gi_rows[2] * 3 * cfg->ctrl_hidden : nullptr;
+  ctx->zseq[2] = ctx->gi_rows[2] ? ctx->zseq[1] + ctx->gi_rows[2] * cfg->ctrl_hidden : nullptr;
   ctx->cvec = reinterpret_cast<float *>(base + l.cvec);
   ctx->avec = reinterpret_cast<float *>(base + l.avec);
   ctx->fwd_q = base + l.fwd_q;

@@ -74,12 +74,13 @@ struct adore_ctx {
   float *att_part;           // [B*H][kMaxSplits][d+2]
   float *att_logit;          // H2O mode: [B*H][K] the step's logits in base 2, as the attention kernel scaled them
   float *att_ml;             // H2O mode: [B*H][2] their maximum and the sum of exp2(logit - maximum) over the row
-  // two copies, which the chunks of a prompt take in turn (the second may lie in the cache, or be missing)
-  float *gi[2];              // [ksplit][tokens][3d'] GRU input pre-activations, per D-slice (steps: copy 0)
-  float *zseq[2];            // [B][kPromptChunk][d'] GRU states of a prompt chunk, between its scan and its scoring
+  // copies that the chunks of a prompt take in turn: 0 and 1, of which 1 may lie in the cache or be missing; where it lies in the cache
+  // also 1 alone, for longer chunks, or 1 and 2, its halves
+  float *gi[3];              // [ksplit][tokens][3d'] GRU input pre-activations, per D-slice (steps: copy 0)
+  float *zseq[3];            // [B][tokens of a chunk][d'] GRU states of a prompt chunk, between its scan and its scoring
   uint64_t *part_keys;       // the choice in parts: in zseq[0], which is free between inits ([B][keys], then part_arrived [B])
   int32_t *part_arrived;
-  size_t gi_rows[2];         // rows of 3d' floats in each; 0: no such copy
+  size_t gi_rows[3];         // rows of 3d' floats in each; 0: no such copy
   float *cvec;               // rescore mode: [B][N_max][d']  W_1 (z_i + pos_b) + b_1 of every token
   float *avec;               // rescore mode: [d']  W_1 pos_w  (what one unit of distance adds)
   void *fwd_q, *fwd_o;       // rebuild forward: [B*(R+1)][H*d] query rows / attention outputs of the layer in flight
@@ -179,6 +180,7 @@ hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0
                             const float *score_override, int override_stride, int buf, int ksplit);
 // A prompt chunk of more than one token where ctrl_chunk_in_two(): the recurrence, then the layers above it.
 bool ctrl_chunk_in_two(const adore_config &c, int nsteps);
+int scan_pieces(const adore_config &c, int nsteps);   // of how many pieces its recurrence is made (bf16)
 hipError_t launch_ctrl_start(adore_ctx *ctx);   // ahead of a prompt's first chunk
 hipError_t launch_ctrl_scan(adore_ctx *ctx, hipStream_t st, int nsteps, int buf, int ksplit);
 hipError_t launch_ctrl_score(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0, const float *score_override,

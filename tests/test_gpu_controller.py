@@ -202,7 +202,12 @@ def test_prompts_over_wide_and_narrow_tiles_are_the_same(monkeypatch):
 @pytest.mark.parametrize("guards", [False, True])
 @pytest.mark.parametrize("batch,S,D,H,K,without", [(1, 1100, 512, 16, 512, False), (1, 770, 1024, 12, 512, False),
                                                    (3, 1537, 256, 12, 512, False), (2, 1100, 256, 2, 24, False),
-                                                   (2, 1100, 256, 2, 24, True), (1, 700, 512, 2, 24, True)])
+                                                   (2, 1100, 256, 2, 24, True), (1, 700, 512, 2, 24, True),
+                                                   # a cache with room for exactly the whole prompt in one chunk (682, 1365 tokens a
+                                                   # sequence), for one token less, and for chunks of half the room (680)
+                                                   (1, 682, 256, 16, 512, False), (1, 683, 256, 16, 512, False),
+                                                   (2, 1365, 256, 16, 1024, False), (2, 1366, 256, 16, 1024, False),
+                                                   (1, 2040, 128, 16, 1024, False), (3, 2041, 128, 16, 1024, False)])
 def test_places_of_the_chunks_second_copy(batch, S, D, H, K, without, guards, monkeypatch):
     import os
     from paper_2407_02328_amd import binding
