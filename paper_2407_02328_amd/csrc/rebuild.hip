@@ -16,12 +16,14 @@
 // 16-byte vectors with no transposes.  One kernel template covers a family of
 // output tiles; the launcher takes the largest tile that still gives every compute
 // unit a workgroup (M = 512 at the 7B shape: 128x128, one tile per unit;
-// M >= 2048: 256x256; M <= 128: 128x32).  Larger tiles move fewer bytes per flop, from the
+// M >= 2048: 256x256; M = 128: 64x64; M <= 32: 32x32).  Larger tiles move fewer bytes per flop, from the
 // L2 to the compute unit and through LDS, and that path is what the 128x128 tile runs into first.  LDS stages
 // are XOR-swizzled (conflict-free for 16-byte reads and writes).  The output tile
 // is rounded to bf16 into LDS and leaves as 16-byte vectors: a row of the tile is
 // a run of contiguous head slices of cache rows.
 // fp32 path: tiles of 16x16x4 fp32 matrix instructions (f32_tile_kernel).  bf16 shapes that no tile takes: one wave per output.
+#include <algorithm>
+
 #include "ctrl_device.h"
 
 namespace adore {
@@ -89,6 +91,7 @@ __device__ inline size_t row_by_position(const GemmArgs &a, int b, int j) {
 // into operands through 4 KB of LDS of its own (XOR-swizzled; only the wave itself reads and writes it, so no
 // barrier).  Epilogue as in the tile kernel, one rounding.
 constexpr int kCurCols = 256;   // output columns per workgroup in this role when the contraction is not cut
+constexpr int kCurLds = 8 * 32 * 8 * 16 + 8 * 2 * 4 * 64 * 4 + 16 * kCurCols * 2;   // the waves' tiles, their sums, the rounded rows
 
 template <int MODE>
 __device__ inline void cur_rows_role(const GemmArgs &a, int e, u32x4 *smem) {
@@ -264,9 +267,14 @@ __device__ inline void cur_rows_role(const GemmArgs &a, int e, u32x4 *smem) {
 
 // Workgroup = 8 waves on a BM x BN output tile, k-steps of BK.
 //   KG = 1: the waves form a WM x WN grid, each holding (BM/WM) x (BN/WN) of the tile.
-//   KG = 2: two such grids of four waves (k-groups); each multiplies one half of every k-step, so the
-//           LDS read traffic is that of four waves while every SIMD still has two waves to switch
-//           between.  The halves are added through LDS at the end.
+//   KG = 2, 4, 8: that many such grids of fewer waves (k-groups); each multiplies its share of every k-step, so the
+//           LDS read traffic is that of one grid while every SIMD still has two waves to switch
+//           between, and a tile may be small.  The shares are added through LDS at the end, in order.
+// A k-step costs a barrier and the trips through LDS behind it, some 500 cycles whatever its length: where a tile has little to multiply
+// a step, or much, longer ones pay (N = 8192, D = 4096): M = 2048 133 -> 117 us (256x256, steps of 64 in two stages; 32 in four before).  Behind
+// a decode step's attention (us a step): M = 128 44.7 -> 39.2 (64x64, steps of 128, two workgroups a unit; 128x32 of 64 before), 64 36.8 ->
+// 30.0 (64x32, 128), 32 36.1 -> 27.5 (32x32, 256; the 128-row tile multiplied padding), 16 x 4096 x 4096 34.0 -> 23.1.  No faster there: 128x128
+// and 128x64 in steps of 128 (two stages and three; with cold operands they are, 58.5 -> 54 and 47.5 -> 43.5), 256x128 in two stages or k-groups.
 //   global -> registers: NS k-steps ahead (NS register sets, refilled right after they are spilled to LDS)
 //   registers -> LDS:    LS stages; the tile of step ks+LS-1 is written while ks is read, one barrier per
 //                        k-step.  With LS >= 3 the tile of ks+1 is complete during ks, so the first
@@ -283,7 +291,7 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   constexpr int CH = BK / 8;             // 16-byte chunks per tile row
   constexpr int RPP = 512 / CH;          // tile rows the workgroup loads per pass
   constexpr int TM = BM / (WM * 32), TN = BN / (WN * 32);   // 32x32 blocks per wave
-  static_assert(KG * WM * WN == 8 && (KG == 1 || KG == 2), "eight waves");
+  static_assert(KG * WM * WN == 8, "eight waves");
   static_assert(TM * WM * 32 == BM && TN * WN * 32 == BN, "tile shape");
   constexpr int NA = BM / RPP, NB = (BN + RPP - 1) / RPP;   // 16-byte loads per thread and k-step
   static_assert(NA * RPP == BM && (NB * RPP == BN || BN < RPP), "tile rows");
@@ -291,20 +299,25 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   static_assert(KSUB == 2 || KSUB == 4, "fragment double buffering needs an even number of k-slices");
   constexpr int LEAD = LS - 1;
   constexpr bool kMixed = TM * TN > 1;
+  // reads and stores of a k-step's tile all in the first k-slice, or spread over them (256x256: 120 -> 117 us; the others have too few
+  // matrix instructions a slice: 64x64 33 -> 34.5)
+  constexpr bool kSpread = TM * TN >= 8;
   constexpr int STAGE = (BM + BN) * CH;  // 16-byte units per LDS stage
   constexpr int LOOP_BYTES = LS * STAGE * 16;
-  constexpr int RED_BYTES = KG == 2 ? 4 * TM * TN * 16 * 64 * 4 : 0;
+  constexpr int RED_BYTES = (KG - 1) * WM * WN * TM * TN * 16 * 64 * 4;
   constexpr int OUT_BYTES = BM * BN * 2;
-  constexpr int SMEM_BYTES = LOOP_BYTES > RED_BYTES ? (LOOP_BYTES > OUT_BYTES ? LOOP_BYTES : OUT_BYTES)
-                                                    : (RED_BYTES > OUT_BYTES ? RED_BYTES : OUT_BYTES);
+  constexpr int ROLE_BYTES = MODE_ == MODE_QKV || MODE_ == MODE_OPROJ ? kCurLds : MODE_ == MODE_TAIL ? kStepTailLds * 4 : 0;
+  constexpr int SMEM_BYTES = std::max({LOOP_BYTES, RED_BYTES, OUT_BYTES, ROLE_BYTES});
   constexpr int NH_MAX = BN / 64 > 0 ? BN / 64 : 1;
   // one LDS block: the stages during the k-loop, then the upper k-group's accumulators, then the bf16 output tile
   __shared__ u32x4 smem[SMEM_BYTES / 16];
   __shared__ long long s_dst[BM * NH_MAX];   // element offset of each output row slice in its destination, -1 = none
   __shared__ long long s_res[MODE == MODE_OPROJ ? BM : 1];   // element offset of each row's residual, -1 = none
   __shared__ int s_rpos[MODE == MODE_REBUILD || MODE == MODE_QKV ? BM : 1];   // position of each row's token
-  // rows are 128 B (BK = 64) or 64 B (BK = 32): 16 consecutive rows at one chunk index hit 16 different bank groups
-  auto swz = [](int row, int chunk) { return row * CH + (chunk ^ (CH == 8 ? (row >> 1) & 7 : (row >> 2) & 3)); };
+  // rows are 256 or 512 B (BK = 128, 256), 128 B (64) or 64 B (32): 16 consecutive rows at one chunk index hit 16 different bank groups
+  auto swz = [](int row, int chunk) {
+    return row * CH + (chunk ^ (CH >= 16 ? row & 15 : CH == 8 ? (row >> 1) & 7 : (row >> 2) & 3));
+  };
 
   int bx = blockIdx.x;
   if constexpr (MODE == MODE_QKV || MODE == MODE_OPROJ) {
@@ -351,16 +364,20 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   u32x4 ra[NS][NA], rb[NS][NB];
 #define SA(ST) (smem + (ST) * STAGE)
 #define SB(ST) (smem + (ST) * STAGE + BM * CH)
-#define GLOAD_A(SET, KS) { _Pragma("unroll") for (int i = 0; i < NA; ++i) ra[SET][i] = gA[i][(KS) * CH]; }
-#define GLOAD_B(SET, KS) { _Pragma("unroll") for (int i = 0; i < NB; ++i) rb[SET][i] = gB[i][(KS) * CH]; }
-#define GLOAD(SET, KS) { GLOAD_A(SET, KS) GLOAD_B(SET, KS) }
-#define LSTORE(SET, ST)                                                                  \
+// PART: all of a tile's rows (-1), or the share of k-slice PART of a step
+#define IN_PART(I, PART) ((PART) < 0 || (I) * KSUB / (NA + NB) == (PART))
+#define GLOAD_A(SET, KS, PART)                                                           \
+  { _Pragma("unroll") for (int i = 0; i < NA; ++i) if (IN_PART(i, PART)) ra[SET][i] = gA[i][(KS) * CH]; }
+#define GLOAD_B(SET, KS, PART)                                                           \
+  { _Pragma("unroll") for (int i = 0; i < NB; ++i) if (IN_PART(NA + i, PART)) rb[SET][i] = gB[i][(KS) * CH]; }
+#define GLOAD(SET, KS, PART) { GLOAD_A(SET, KS, PART) GLOAD_B(SET, KS, PART) }
+#define LSTORE(SET, ST, PART)                                                            \
   {                                                                                      \
     _Pragma("unroll") for (int i = 0; i < NA; ++i)                                       \
-      SA(ST)[swz(lrow + RPP * i, lchunk)] = ra[SET][i];                                  \
+      if (IN_PART(i, PART)) SA(ST)[swz(lrow + RPP * i, lchunk)] = ra[SET][i];            \
     if (b_on) {                                                                          \
       _Pragma("unroll") for (int i = 0; i < NB; ++i)                                     \
-        SB(ST)[swz(lrow + RPP * i, lchunk)] = rb[SET][i];                                \
+        if (IN_PART(NA + i, PART)) SB(ST)[swz(lrow + RPP * i, lchunk)] = rb[SET][i];     \
     }                                                                                    \
   }
 #define FRAGS(BUF, ST, KK)                                                               \
@@ -386,7 +403,7 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   // what the previous kernel wrote takes a microsecond or two; one after the other they cost a tenth of the launch.)
 #pragma unroll
   for (int t = 0; t < NS; ++t) {
-    if (t < nk) { GLOAD_B(t, t) }
+    if (t < nk) { GLOAD_B(t, t, -1) }
   }
 #pragma unroll
   for (int i = 0; i < NA; ++i) {
@@ -400,7 +417,7 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   }
 #pragma unroll
   for (int t = 0; t < NS; ++t) {
-    if (t < nk) { GLOAD_A(t, t) }
+    if (t < nk) { GLOAD_A(t, t, -1) }
   }
   // where every row of the output tile goes: looked up now, used after the k-loop
   const int sw = MODE == MODE_OPROJ ? BN : a.d;   // width of a contiguous piece of an output row
@@ -453,8 +470,8 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   }
 #pragma unroll
   for (int t = 0; t < LEAD; ++t) {
-    if (t < nk) { LSTORE(t % NS, t) }
-    if (t + NS < nk) { GLOAD(t % NS, t + NS) }   // the set just stored takes the tile NS further on
+    if (t < nk) { LSTORE(t % NS, t, -1) }
+    if (t + NS < nk) { GLOAD(t % NS, t + NS, -1) }   // the set just stored takes the tile NS further on
   }
   __syncthreads();
 
@@ -466,9 +483,10 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const int kbase = KSUB * kgrp;   // first k-slice of this wave's k-group
+  // k-slice kk of this wave's k-group.  Of two groups each takes 32 of every 64 k, whatever the step: tiles of two groups all add up alike.
+  auto slice = [&](int kk) { return KG == 2 ? (kk / 2) * 4 + kgrp * 2 + kk % 2 : KSUB * kgrp + kk; };
   bf16x8 fa[2][TM], fb[2][TN];     // double-buffered fragments
-  FRAGS(0, 0, kbase)
+  FRAGS(0, 0, slice(0))
   int st = 0;                      // LDS stage of tile ks
   // One k-step.  IF(c) guards the parts that run out near the end; it is empty in the steady loop so
   // that the loop body is a single basic block (the wait counters are then tracked exactly).
@@ -478,18 +496,18 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
     const int stw = st + LEAD >= LS ? st + LEAD - LS : st + LEAD;                        \
     _Pragma("unroll") for (int kk = 0; kk < KSUB; ++kk) {                                \
       if (kk + 1 < KSUB) {                                                               \
-        FRAGS((kk + 1) & 1, st, kbase + kk + 1)                                          \
+        FRAGS((kk + 1) & 1, st, slice(kk + 1))                                          \
       } else if (LS > 2) {                                                               \
-        IF((KS) + 1 < nk) { FRAGS(0, st1, kbase) }                                       \
+        IF((KS) + 1 < nk) { FRAGS(0, st1, slice(0)) }                                       \
       }                                                                                  \
       if (!kMixed) {                                                                     \
         __builtin_amdgcn_sched_barrier(0);                                               \
         MFMAS(kk & 1)                                                                    \
         __builtin_amdgcn_sched_barrier(0);                                               \
       }                                                                                  \
-      if (kk == 0) {                                                                     \
-        IF((KS) + LEAD < nk) { LSTORE(((U) + LEAD) % NS, stw) }                          \
-        IF((KS) + LEAD + NS < nk) { GLOAD(((U) + LEAD) % NS, (KS) + LEAD + NS) }         \
+      if (kSpread || kk == 0) {                                                          \
+        IF((KS) + LEAD < nk) { LSTORE(((U) + LEAD) % NS, stw, kSpread ? kk : -1) }       \
+        IF((KS) + LEAD + NS < nk) { GLOAD(((U) + LEAD) % NS, (KS) + LEAD + NS, kSpread ? kk : -1) } \
       }                                                                                  \
       if (kMixed) {                                                                      \
         MFMAS(kk & 1)                                                                    \
@@ -503,7 +521,7 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
       }                                                                                  \
     }                                                                                    \
     __syncthreads();                                                                     \
-    if (LS == 2) { IF((KS) + 1 < nk) { FRAGS(0, st1, kbase) } }                          \
+    if (LS == 2) { IF((KS) + 1 < nk) { FRAGS(0, st1, slice(0)) } }                          \
     st = st1;                                                                            \
   }
 #define ALWAYS(c)
@@ -524,6 +542,7 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
 #undef ALWAYS
 #undef GUARDED
 #undef GLOAD
+#undef IN_PART
 #undef GLOAD_A
 #undef GLOAD_B
 #undef LSTORE
@@ -532,25 +551,28 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
 #undef SA
 #undef SB
 
-  // ---- add the two k-groups: the upper four waves hand their accumulators over through LDS ----
-  if (KG == 2) {
+  // ---- add the k-groups: all but the first hand their accumulators over through LDS ----
+  if (KG > 1) {
+    constexpr int kGroup = WM * WN * TM * TN * 16 * 64;
     float *red = reinterpret_cast<float *>(smem) + (wave % (WM * WN)) * (TM * TN * 16 * 64) + lane;
-    if (kgrp == 1) {
+    if (kgrp > 0) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) red[((i * TN + j) * 16 + v) * 64] = acc[i][j][v];
+          for (int v = 0; v < 16; ++v) red[(kgrp - 1) * kGroup + ((i * TN + j) * 16 + v) * 64] = acc[i][j][v];
     }
     __syncthreads();
     if (kgrp == 0) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int g = 0; g < KG - 1; ++g)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) acc[i][j][v] += red[((i * TN + j) * 16 + v) * 64];
+          for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] += red[g * kGroup + ((i * TN + j) * 16 + v) * 64];
     }
     __syncthreads();   // the output tile below overwrites what was just read
   }
@@ -938,13 +960,16 @@ __global__ __launch_bounds__(256) void cur_rows_kernel(const GemmArgs a) {
   }
 }
 
-// The tile shapes the launcher chooses from, largest first.
+// The tile shapes the launcher chooses from.  The first five multiply any contraction that is a multiple of 64 (or 32) and are the ones the
+// rebuild forward counts with (pick_with_riders).
 struct TileShape {
   int bm, bn, bk;
+  int per_unit;                // workgroups that share a compute unit
 };
-constexpr TileShape kTiles[] = {{256, 256, 32}, {256, 128, 64}, {128, 128, 64}, {128, 64, 64}, {128, 32, 64}};
-constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
-constexpr int kFirstTailTile = 2;   // short steps take none of the 256-wide ones
+constexpr TileShape kTiles[] = {{256, 256, 32, 1}, {256, 128, 64, 1}, {128, 128, 64, 1}, {128, 64, 64, 1}, {128, 32, 64, 2},
+                                {256, 256, 64, 1}, {64, 64, 128, 2}, {64, 32, 128, 2}, {32, 32, 256, 2}};
+constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]), kForwardTiles = 5;
+bool takes_tail(int tile) { return tile >= 0 && kTiles[tile].bm <= 128; }   // short steps take none of the 256-wide ones
 
 // kdim = length of the contraction; scatter modes write head slices (section = H*d columns of one kind)
 bool tile_fits(const TileShape &t, int kdim, int section, int head_dim, bool dense) {
@@ -953,16 +978,18 @@ bool tile_fits(const TileShape &t, int kdim, int section, int head_dim, bool den
 }
 
 // Time of one workgroup on its tile in microseconds at a contraction length of 4096, measured with one tile per
-// compute unit (largest tile first); the launch takes ceil(tiles / 256) rounds of that.  The tile with the lowest
+// compute unit; the launch takes ceil(tiles / 256) rounds of that.  The tile with the lowest
 // estimate is used: a launch that fills three quarters of the units once (256x128 at M = 512, N = 12288: 192 tiles,
 // 64 us) beats one that fills all of them one and a half times (128x128: 384 tiles, 88 us).
-constexpr float kTileMicros[kNumTiles] = {125.f, 66.f, 41.f, 40.f, 25.f};
+// Small products (us): 128 rows x 2048 columns x 1024 on 64 tiles of 128x32 12.5, on 256 of 32x32 8.4; 39 x 1536 x 768 11.0 / 7.8;
+// 16 x 4096 x 4096 35 / 19.
+constexpr float kTileMicros[kNumTiles] = {125.f, 66.f, 41.f, 40.f, 25.f, 112.f, 21.f, 17.f, 12.f};
 
-// extra: workgroups that ride in the launch and need a compute unit each (the current tokens' rows)
-int pick_tile(int M, int N, int kdim, int section, int head_dim, bool dense, int extra = 0) {
+// extra: workgroups that ride in the launch and need a compute unit each (the current tokens' rows); of the first `among` shapes
+int pick_tile(int M, int N, int kdim, int section, int head_dim, bool dense, int extra = 0, int among = kNumTiles) {
   int pick = -1;
   float best = 0.f;
-  for (int i = 0; i < kNumTiles; ++i) {
+  for (int i = 0; i < among; ++i) {
     if (!tile_fits(kTiles[i], kdim, section, head_dim, dense)) continue;
     const long long tiles = (long long)((M + kTiles[i].bm - 1) / kTiles[i].bm) * (N / kTiles[i].bn);
     const float est = float((tiles + extra + 255) / 256) * kTileMicros[i];
@@ -973,7 +1000,7 @@ int pick_tile(int M, int N, int kdim, int section, int head_dim, bool dense, int
   }
   if (const char *e = getenv("ADORE_GEMM_TILE")) {   // tuning runs: force a tile shape by index
     const int v = atoi(e);
-    if (v >= 0 && v < kNumTiles && tile_fits(kTiles[v], kdim, section, head_dim, dense)) pick = v;
+    if (v >= 0 && v < among && tile_fits(kTiles[v], kdim, section, head_dim, dense)) pick = v;
   }
   return pick;
 }
@@ -999,18 +1026,26 @@ void launch_tile(ScopedTimer &t, hipStream_t stream, int pick, GemmArgs &a) {
   const bool behind = MODE == MODE_TAIL && a.n_cur == 0;
   if (behind) a.tail_at = (total + 7) / 8 * 8;
   const dim3 grid((total + 7) / 8 * 8 + (behind ? a.tail.n : a.n_cur)), block(512);
-  //                                              BM   BN  BK KG WM WN LS NS
-  if constexpr (MODE == MODE_TAIL) {
-    if (pick == 2) ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 128, 64, 2, 2, 2, 3, 4>), grid, block, 0, stream, a);
-    else if (pick == 3) ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 64, 64, 2, 2, 2, 3, 4>), grid, block, 0, stream, a);
-    else ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 32, 64, 2, 4, 1, 3, 4>), grid, block, 0, stream, a);
-  } else switch (pick) {
-    case 0: ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 256, 256, 32, 1, 2, 4, 4, 2>), grid, block, 0, stream, a); break;
-    case 1: ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 256, 128, 64, 1, 4, 2, 3, 2>), grid, block, 0, stream, a); break;
-    case 2: ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 128, 64, 2, 2, 2, 3, 4>), grid, block, 0, stream, a); break;
-    case 3: ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 64, 64, 2, 2, 2, 3, 4>), grid, block, 0, stream, a); break;
-    default: ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, 128, 32, 64, 2, 4, 1, 3, 4>), grid, block, 0, stream, a); break;
+#define TILE(...) ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, __VA_ARGS__>), grid, block, 0, stream, a)
+  if constexpr (MODE != MODE_TAIL) {
+    switch (pick) {
+      //             BM   BN   BK KG WM WN LS NS
+      case 0: TILE(256, 256,  32, 1, 2, 4, 4, 2); return;
+      case 1: TILE(256, 128,  64, 1, 4, 2, 3, 2); return;
+      case 5: TILE(256, 256,  64, 1, 2, 4, 2, 1); return;
+    }
   }
+  switch (pick) {
+    case 2: TILE(128, 128,  64, 2, 2, 2, 3, 4); return;
+    case 3: TILE(128,  64,  64, 2, 2, 2, 3, 4); return;
+    case 4: TILE(128,  32,  64, 2, 4, 1, 3, 4); return;
+    case 6: TILE(64,   64, 128, 2, 2, 2, 2, 3); return;
+  }
+  if constexpr (MODE == MODE_REBUILD || MODE == MODE_TAIL) {
+    if (pick == 7) TILE(64, 32, 128, 4, 2, 1, 2, 3);
+    else TILE(32, 32, 256, 8, 1, 1, 2, 2);
+  }
+#undef TILE
 }
 
 void fill_common(adore_ctx *ctx, GemmArgs &a, int lists, int r) {
@@ -1053,20 +1088,16 @@ float rebuild_gemm_micros(const adore_config &c) {
 }
 
 namespace {
-// Tile of a launch that carries a tail of `wgs` workgroups, which take compute units of their own next to the tiles (whose LDS leaves
-// room for nothing else): the tile that is best with them in front, unless that costs more than they take behind the tiles of the
-// one that is best without (about 4 us), where they start as the first tiles end.
+// Tile of a launch that carries a tail of `wgs` workgroups: the same as without, so that the step's rows have the same bits either
+// way.  The tail goes in front of the tiles where the chip holds all of them at once (14: both parts of the grid are padded to multiples of
+// 8), otherwise behind them, where it starts as the first tiles end.
 int pick_tile_with_tail(const adore_config &c, int M, int wgs, bool *front) {
-  const int Hd = c.heads * c.head_dim;
-  const int alone = pick_tile(M, 2 * Hd, c.hidden, Hd, c.head_dim, false), with = pick_tile(M, 2 * Hd, c.hidden, Hd, c.head_dim, false, wgs + 14);
+  const int Hd = c.heads * c.head_dim, pick = pick_tile(M, 2 * Hd, c.hidden, Hd, c.head_dim, false);
   *front = false;
-  if (alone < 0) return alone;
-  auto micros = [&](int pick, int extra) {
-    const long long tiles = (long long)((M + kTiles[pick].bm - 1) / kTiles[pick].bm) * (2 * Hd / kTiles[pick].bn);
-    return float((tiles + extra + 255) / 256) * kTileMicros[pick] * c.hidden / 4096.f;
-  };
-  *front = micros(with, wgs + 14) <= micros(alone, 0) + 4.f;   // (14: both parts of the grid are padded to multiples of 8)
-  return *front ? with : alone;
+  if (pick < 0) return pick;
+  const long long tiles = (long long)((M + kTiles[pick].bm - 1) / kTiles[pick].bm) * (2 * Hd / kTiles[pick].bn);
+  *front = tiles + wgs + 14 <= 256 * kTiles[pick].per_unit;
+  return pick;
 }
 }  // namespace
 
@@ -1074,7 +1105,7 @@ bool rebuild_gemm_takes_tail(const adore_ctx *ctx, int r) {
   const adore_config &c = ctx->cfg;
   if (r <= 0) return false;
   bool front;
-  return c.dtype == ADORE_F32 || pick_tile_with_tail(c, c.batch * r, step_tail_wgs(ctx, 512), &front) >= kFirstTailTile;
+  return c.dtype == ADORE_F32 || takes_tail(pick_tile_with_tail(c, c.batch * r, step_tail_wgs(ctx, 512), &front));
 }
 
 hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_layer, int lists, int r,
@@ -1153,15 +1184,20 @@ int pick_with_riders(GemmArgs &a, int kdim, int section, int head_dim, bool dens
   a.n_cur = 0;
   a.cur_ks = 1;
   const int base = cur_row_riders(a, 1);
-  const int pick = pick_tile(a.M, a.N, kdim, section, head_dim, dense, base);
-  if (pick < 0 || base == 0) return pick;
+  const int pick = pick_tile(a.M, a.N, kdim, section, head_dim, dense, base, kForwardTiles);
+  // The rows of a layer are the next one's input, without a norm between them here, and a last bit that falls the other way in an
+  // early layer can be another key's softmax in a late one: so the choice is made among the shapes that were always there, and a
+  // newer one stands in where its sums are the same (one k-group for one, two for two).
+  const int stand_in = pick == 0 ? 5 : pick == 4 ? 6 : pick;
+  const int tile = pick >= 0 && tile_fits(kTiles[stand_in], kdim, section, head_dim, dense) ? stand_in : pick;
+  if (pick < 0 || base == 0) return tile;
   const int tiles = ((a.M + kTiles[pick].bm - 1) / kTiles[pick].bm) * (a.N / kTiles[pick].bn);
   const int rounds = (tiles + base + 255) / 256;
   int ks = 1;
   while (ks < 8 && cur_row_riders(a, ks * 2) > 0 && (tiles + cur_row_riders(a, ks * 2) + 255) / 256 <= rounds) ks *= 2;
   a.cur_ks = ks;
   a.n_cur = cur_row_riders(a, ks);
-  return pick;
+  return tile;
 }
 
 template <int MODE>
@@ -1280,6 +1316,7 @@ bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, con
   // 242 us, with the order of the tiles below; 8192 tokens, one round of either: 54 us for 66).  Its two groups of four waves cut D as the
   // narrow tile's do, so that a sum is the same either way (all of D in one chain per wave, twice as long: no faster);
   // one set of tiles on its way in registers is what that leaves room for (two: 26 registers spilled, 330 us).
+  // (128-wide steps for both, which the wide one has no room for, or for one of them, would be other sums.)
   const long long wide = ((ntok + 255) / 256) * (N / 128), narrow = ((ntok + 127) / 128) * (N / 128);
   const int kTile = float((wide + 255) / 256) * kTileMicros[1] < float((narrow + 255) / 256) * kTileMicros[2] ? 1 : 2;
   const bool bf16 = ctx->cfg.dtype == ADORE_BF16;

@@ -340,14 +340,19 @@ def test_full_attention_cache_holds_every_token():
     job.adore.close()
 
 
-@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
-def test_rebuild_gemm_tile_shapes(tile, monkeypatch):
-    """Every output-tile shape of the re-projection kernel (256x256 ... 128x32) gives the oracle's cache rows
+# the tiles, and how long their contraction is: a few k-steps more than the pipeline is deep, and as few as there can be
+TILES = [(0, 448), (1, 448), (2, 448), (3, 448), (4, 448), (5, 448), (6, 896), (7, 896), (8, 1280), (5, 64), (6, 128), (6, 256), (7, 128), (7, 384),
+         (8, 256), (8, 512)]
+
+
+@pytest.mark.parametrize("tile,D", TILES)
+def test_rebuild_gemm_tile_shapes(tile, D, monkeypatch):
+    """Every output-tile shape of the re-projection kernel (256x256 ... 32x32) gives the oracle's cache rows
     and outputs: M = B*R = 3*45 = 135 rows is a ragged tile in each of them, d = 64 puts up to four head
-    slices into one tile row, and D = 448 leaves a guarded tail in every pipeline depth."""
+    slices into one tile row, and the contraction leaves a guarded tail in every pipeline depth."""
     h = _harness()
     monkeypatch.setenv("ADORE_GEMM_TILE", str(tile))
-    w = Workload("tiles", L=1, B=3, H=8, d=64, D=448, K=128, R=45, S=200, T=5, dtype="bf16", dprime=32)
+    w = Workload("tiles", L=1, B=3, H=8, d=64, D=D, K=128, R=45, S=200, T=5, dtype="bf16", dprime=32)
     worst, job, _ = h.lockstep(w, steps=w.T, check_cache_every=1)
     job.adore.close()
 
@@ -1051,14 +1056,14 @@ def test_rotary_embedding_on_rebuilt_keys(name, kw, calls):
     job.adore.close()
 
 
-@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("tile,D", TILES[:9])
 @pytest.mark.parametrize("d", [64, 128])
-def test_rotary_embedding_with_every_tile_shape(tile, d, monkeypatch):
+def test_rotary_embedding_with_every_tile_shape(tile, D, d, monkeypatch):
     """The key tiles turn their rows themselves when a tile holds whole heads (256- to 64-wide tiles at d = 64,
     256- and 128-wide ones at d = 128); narrower tiles leave it to the pass that follows.  Both give the same rows."""
     h = _harness()
     monkeypatch.setenv("ADORE_GEMM_TILE", str(tile))
-    w = Workload("rope_tiles", L=1, B=3, H=512 // d, d=d, D=448, K=128, R=45, S=200, T=4, dtype="bf16", dprime=32,
+    w = Workload("rope_tiles", L=1, B=3, H=512 // d, d=d, D=D, K=128, R=45, S=200, T=4, dtype="bf16", dprime=32,
                  rope_base=10000.0)
     worst, job, _ = h.lockstep(w, steps=w.T, check_cache_every=1)
     job.adore.close()
