@@ -29,7 +29,8 @@ namespace {
 struct SchedArgs {
   int kpl, rel_wgs;                 // keys per lane of a row (K / 64 rounded up to 2, 4, 8, 16); 0 workgroups = off
   int prio;                         // wave priority of the role (0 .. 3)
-  int hpw;                          // heads a wave releases one after the other (1, or 4 for short rows of many sequences)
+  int hpw;                          // heads a wave releases one after the other (1, or 4 for short rows of many sequences); 0: a
+                                    // workgroup per head (few rows)
   const int32_t *slot_src;          // [B*H][K]
   int32_t *slot_dst;                // [B*H][K]
   const float *score;               // [B][N_max]
@@ -82,6 +83,27 @@ __device__ __forceinline__ void selections_role(const AttendArgs &a, int e, uint
   }
   float *s_score = reinterpret_cast<float *>(dyn);
   const float *sc = s.score + size_t(b) * s.N_max;
+  if constexpr (WAVES == 4) {
+    if (s.hpw == 0) {              // head 1 + part, the last one head 0 and the choice
+      constexpr int WIDE = KPL >= 4 ? KPL / 4 : 1;
+      const bool first = part == s.rel_wgs;
+      const int row = b * s.H + (first ? 0 : 1 + part);
+      const int s_ins = a.insert_slot[size_t(row) * a.ins_stride + a.ins_off];
+      int raw[WIDE];
+      release_fetch_wide<WIDE>(row, s.slot_src, s.K, raw);
+      for (int i = tid; i <= s.n; i += 256) s_score[i] = sc[i];
+      __syncthreads();
+      int32_t *row_copy = first ? reinterpret_cast<int32_t *>(dyn + (s.n + 2) / 2) : nullptr;
+      uint64_t *choice = dyn + (s.n + 2) / 2 + (s.K + 1) / 2;
+      if (first) choice_fill_keys(s_score, s.n, choice, tid, 256);
+      release_row_wide<WIDE>(row, s_ins, s.slot_dst, s_score, s.free_list, s.released_pos, s.map_out, s.rel_out, s.K, s.n, s.x, s.R1,
+                             row_copy, hist, raw);
+      if (!first) return;
+      __syncthreads();
+      choice_from_keys(s.sel, b, row_copy, choice, hist, dyn, (s.n + 2) / 2);   // (the scores are done with)
+      return;
+    }
+  }
   if (part < s.rel_wgs) {          // heads 1 .. H-1
     const int hpw = HPW > 1 ? s.hpw : 1;
     const int h0 = 1 + (part * WAVES + wave) * hpw;
@@ -120,7 +142,7 @@ __device__ __forceinline__ void selections_role(const AttendArgs &a, int e, uint
     choice_fill_keys(s_score, s.n, choice, tid - 64, 64 * (WAVES - 1));   // the other waves meanwhile
   }
   __syncthreads();
-  choice_from_keys(s.sel, b, row_copy, choice);
+  choice_from_keys(s.sel, b, row_copy, choice, hist, dyn, (s.n + 2) / 2);   // (the scores are done with)
 }
 
 // The same for sequences whose scores do not fit a workgroup's LDS (one launch, parts.n_parts > 0): per sequence rel_wgs workgroups
@@ -135,11 +157,20 @@ __device__ __forceinline__ void selections_in_parts_role(const AttendArgs &a, in
   __builtin_amdgcn_s_setprio(3);
   if (part > s.rel_wgs) {
     choice_part(s.sel, s.parts, b, part - s.rel_wgs - 1, s.slot_src + size_t(b) * s.H * s.K, dyn);
-    choice_arrive(s.sel, s.parts, b, dyn);
+    choice_arrive(s.sel, s.parts, b, dyn, hist);
     return;
   }
+  if (s.hpw == 0) {                // a workgroup per head
+    constexpr int WIDE = KPL >= 4 ? KPL / 4 : 1;
+    const int row = b * s.H + (part < s.rel_wgs ? 1 + part : 0);
+    const int s_ins = a.insert_slot[size_t(row) * a.ins_stride + a.ins_off];
+    int raw[WIDE];
+    release_fetch_wide<WIDE>(row, s.slot_src, s.K, raw);
+    release_row_wide<WIDE>(row, s_ins, s.slot_dst, s.score + size_t(b) * s.N_max, s.free_list, s.released_pos, s.map_out, s.rel_out, s.K,
+                           s.n, s.x, s.R1, nullptr, hist, raw);
+  }
   // heads 1 .. H-1, a wave each; the last of these workgroups head 0
-  const int h = part < s.rel_wgs ? 1 + part * WAVES + wave : wave == 0 ? 0 : s.H;
+  const int h = s.hpw == 0 ? s.H : part < s.rel_wgs ? 1 + part * WAVES + wave : wave == 0 ? 0 : s.H;
   if (h < s.H) {                 // whole waves
     const int row = b * s.H + h;
     release_row<KPL>(row, a.insert_slot[size_t(row) * a.ins_stride + a.ins_off], s.slot_src, s.slot_dst, s.score + size_t(b) * s.N_max,
@@ -148,7 +179,7 @@ __device__ __forceinline__ void selections_in_parts_role(const AttendArgs &a, in
   if (part == s.rel_wgs) {
     __syncthreads();             // head 0's released positions, written by this workgroup
     choice_released(s.sel, s.parts, b, s.released_pos + size_t(b) * s.H * s.R1);
-    choice_arrive(s.sel, s.parts, b, dyn);
+    choice_arrive(s.sel, s.parts, b, dyn, hist);
   }
 }
 
@@ -190,10 +221,10 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
   // merge of the lane groups at the end of a row; a workgroup that carries selections instead keeps its waves'
   // radix histograms there
   __shared__ float s_m[G], s_l[G];
-  __shared__ float s_acc[G][DH];
-  static_assert(G * DH >= WAVES * 256 && G * DH >= (sizeof(T) == 2 ? kInputTileLds : 4 * JT * NB), "room for one 256-bin histogram per wave, for an input tile's sums");
+  __shared__ __align__(16) float s_acc[G][DH];
+  static_assert(G * DH >= kWideWords && G * DH >= WAVES * 256 && G * DH >= (sizeof(T) == 2 ? kInputTileLds : 4 * JT * NB), "room for one 256-bin histogram per wave, for an input tile's sums");
 
-  extern __shared__ uint64_t dyn_smem[];
+  extern __shared__ __align__(16) uint64_t dyn_smem[];
   if (KPL == 0 && int(blockIdx.x) < a.n_sel) {   // uniform over the workgroup
     const int e = blockIdx.x;
     uint32_t *hist = reinterpret_cast<uint32_t *>(&s_acc[0][0]);
@@ -429,6 +460,11 @@ size_t parts_bytes(const adore_config &c) {
 // 50 in parts (attention and all of it 25 us, projection 26).
 bool ride_in_parts(const adore_ctx *ctx, int r) { return ctx->ride_parts && r > 0 && (!ctx->ride_whole || ctx->n >= kPartsFrom); }
 
+// Rows up to which a workgroup releases one head rather than one a wave.  Attention and all it carries (us, a wave / a workgroup): 4
+// sequences of 32 heads, K = 1024, behind 8192 tokens 24.1 / 17.8, behind 1500 19.7 / 16.4; 2 of 32, K = 512 13.8 / 12.6; 16 of 16, K = 256
+// 12.2 / 12.2; 32 of 8, K = 512 17.9 / 18.5 to 18.9; 16 of 32 the same (the attention is what takes the time).
+constexpr int kWideRows = 128;
+
 size_t riding_lds_bytes(int n, int K, int r) {
   return size_t((n + 2) / 2) * 8 + size_t((K + 1) / 2) * 8 + ridden_choice_lds_bytes(r, n);
 }
@@ -476,7 +512,9 @@ hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k
     if (const char *e = getenv("ADORE_RIDE_HPW")) {   // tests: the four-heads path on a small shape
       if (atoi(e) == 4 && s.kpl <= 4) s.hpw = 4;
     }
-    s.rel_wgs = (c.heads - 1 + waves * s.hpw - 1) / (waves * s.hpw);
+    const bool per_head = waves == 4 && s.hpw == 1 && rows <= kWideRows;
+    s.rel_wgs = per_head ? c.heads - 1 : (c.heads - 1 + waves * s.hpw - 1) / (waves * s.hpw);
+    if (per_head) s.hpw = 0;
     s.slot_src = ctx->slot_pos[ctx->cur]; s.slot_dst = ctx->slot_pos[sel->dst];
     s.score = ctx->score; s.free_list = ctx->free_list[sel->dst];
     s.released_pos = ctx->released_pos; s.map_out = sel->map_out; s.rel_out = sel->rel_out;
@@ -493,8 +531,8 @@ hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k
     dyn = riding_lds_bytes(ctx->n, c.cache_slots, sel->r);
     if (ride_in_parts(ctx, sel->r)) {
       waves = 4;
-      s.hpw = 1;
-      s.rel_wgs = (c.heads - 1 + waves - 1) / waves;
+      s.hpw = rows <= kWideRows ? 0 : 1;
+      s.rel_wgs = s.hpw == 0 ? c.heads - 1 : (c.heads - 1 + waves - 1) / waves;
       s.parts.n_parts = choice_parts(ctx->n);
       s.parts.keys = ctx->part_keys;
       s.parts.arrived = ctx->part_arrived;

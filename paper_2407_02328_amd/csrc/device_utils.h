@@ -99,9 +99,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 // Scan of a 256-bin histogram from the top bin down: the bin in which the rank `need` (1 = the largest) falls, the
 // rank left inside it, and how many entries it holds.  Lane l owns bins 255 - 4l .. 252 - 4l.  Wave-uniform results.
-__device__ __forceinline__ void pick_bin(const uint32_t *hist, int lane, int need, int &bin, int &rest, int &inbin) {
-  const uint4 hq = *reinterpret_cast<const uint4 *>(hist + 252 - 4 * lane);
-  const int c0 = int(hq.w), c1 = int(hq.z), c2 = int(hq.y), c3 = int(hq.x);
+__device__ __forceinline__ void pick_bin(int c0, int c1, int c2, int c3, int lane, int need, int &bin, int &rest, int &inbin) {
   const int own = c0 + c1 + c2 + c3;
   int incl = own;
 #pragma unroll
@@ -123,6 +121,11 @@ __device__ __forceinline__ void pick_bin(const uint32_t *hist, int lane, int nee
   bin = __shfl(b, src, 64);
   rest = __shfl(r, src, 64);
   inbin = __shfl(n, src, 64);
+}
+// hist: 256 words, 16-byte aligned
+__device__ __forceinline__ void pick_bin(const uint32_t *hist, int lane, int need, int &bin, int &rest, int &inbin) {
+  const uint4 hq = *reinterpret_cast<const uint4 *>(hist + 252 - 4 * lane);
+  pick_bin(int(hq.w), int(hq.z), int(hq.y), int(hq.x), lane, need, bin, rest, inbin);
 }
 
 // One wave's LDS operations run in order; this keeps the compiler from moving them across the point.

@@ -15,7 +15,7 @@ namespace adore {
 // Radix select.  key_of(i) for i in [0, ncand) returns the key of candidate i or 0
 // if i is not a candidate.  Finds (*thr, *shift) such that exactly c candidates
 // have (key >> shift) >= thr.  Needs 1 <= c <= number of candidates.
-// s_hist: 256 uints; s_ctl: 4 uint64.  All threads of the block must call it.
+// s_hist: 256 uints; s_ctl: 4 uint64.  All threads of the block (whole waves) must call it.
 // The first digit starts at the highest bit in which two candidates differ: scores of one sequence share most of their
 // exponent, so that a digit from the top of the key would put nearly all of them into one or two bins (atomics on one
 // address, 64 in turn per wave) and tell nothing.  4 sequences of 8200 tokens: release 22.4 -> 19.0 us, choice 19.2 -> 17.1 us.
@@ -64,37 +64,29 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int ncand, int c, uin
       }
     }
     __syncthreads();
-    if (threadIdx.x < 64) {
-      // lane L owns digits 4L..4L+3; suffix sums from the top digit down
-      const int L = threadIdx.x;
-      const uint32_t h0 = s_hist[4 * L], h1 = s_hist[4 * L + 1], h2 = s_hist[4 * L + 2], h3 = s_hist[4 * L + 3];
-      const uint32_t own = h0 + h1 + h2 + h3;
-      uint32_t incl = own;  // sum over lanes >= L
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = __shfl_down(incl, off, 64);
-        if (L + off < 64) incl += v;
-      }
-      const uint32_t above_lane = incl - own;  // keys in digits of higher lanes
-      // the lane where the running count first reaches `remaining`
-      if (above_lane < uint32_t(remaining) && incl >= uint32_t(remaining)) {
-        uint32_t above = above_lane;
-        int digit;
-        uint32_t cnt;
-        if (above + h3 >= uint32_t(remaining)) { digit = 4 * L + 3; cnt = h3; }
-        else if ((above += h3) + h2 >= uint32_t(remaining)) { digit = 4 * L + 2; cnt = h2; }
-        else if ((above += h2) + h1 >= uint32_t(remaining)) { digit = 4 * L + 1; cnt = h1; }
-        else { above += h1; digit = 4 * L; cnt = h0; }
-        s_ctl[0] = uint64_t(digit);
-        s_ctl[1] = uint64_t(uint32_t(remaining) - above);  // still to take inside this bucket
-        s_ctl[2] = uint64_t(cnt);
+    // four waves find the bin each by itself, without an exchange and its barrier; of sixteen one does (13.0 us a choice for 13.5)
+    const int lane = threadIdx.x & 63;
+    const bool all = blockDim.x <= 256;
+    int digit = 0, rest = 0, inbin = 0;
+    if (all || threadIdx.x < 64) {
+      const uint32_t *top = s_hist + 252 - 4 * lane;
+      pick_bin(int(top[3]), int(top[2]), int(top[1]), int(top[0]), lane, remaining, digit, rest, inbin);
+      if (!all && lane == 0) {
+        s_ctl[0] = uint64_t(uint32_t(digit));
+        s_ctl[1] = uint64_t(uint32_t(rest));
+        s_ctl[2] = uint64_t(uint32_t(inbin));
       }
     }
-    __syncthreads();
-    prefix = (prefix << (prev - shift)) | s_ctl[0];
-    remaining = int(s_ctl[1]);
-    const bool whole_bucket = s_ctl[2] == s_ctl[1];
-    __syncthreads();
+    if (!all) {
+      __syncthreads();
+      digit = int(s_ctl[0]);
+      rest = int(s_ctl[1]);
+      inbin = int(s_ctl[2]);
+    }
+    prefix = (prefix << (prev - shift)) | uint32_t(digit);
+    remaining = rest;
+    const bool whole_bucket = inbin == rest;
+    __syncthreads();                              // the bins are read before the next pass clears them
     prev = shift;
     if (whole_bucket || shift == 0) break;   // the last digit used: keys are distinct, the bucket held one key
   }
@@ -120,8 +112,90 @@ __device__ __forceinline__ void collect_sorted(KeyFn key_of, int ncand, int c, u
   for (int t = threadIdx.x; t < c; t += blockDim.x) {
     const uint64_t mine = s_keys[t];
     int rank = 0;
+#pragma unroll 8
     for (int j = 0; j < c; ++j) rank += s_keys[j] > mine;
     out_pos[rank] = key_pos(mine);
+  }
+  __syncthreads();
+}
+
+// The best r of few: radix_select and collect_sorted meet at a barrier four times a digit and three more, which is what a short
+// choice costs (5 us for 32 of 1024).  Here each of the workgroup's four waves finds the best r of its quarter alone, and the at most
+// 4 r that are left are ranked against each other (3 us).
+constexpr int kFewRanks = 64;        // r up to here: 4 r threads rank 4 r keys
+
+// One wave: leaves the best r of the keys [first, end) (0: none) in out[0 .. r), in any order, and zeros behind them where there are
+// fewer.  hist: 256 words of the wave's own, 16-byte aligned.
+__device__ __forceinline__ void wave_best(const uint64_t *s_key, int first, int end, int r, uint32_t *hist, uint64_t *out) {
+  const int lane = threadIdx.x & 63;
+  uint32_t or_hi = 0u, and_hi = ~0u;
+  int count = 0;
+  for (int i0 = first; i0 < end; i0 += 64) {                    // (the whole wave, for the ballots)
+    const uint64_t key = i0 + lane < end ? s_key[i0 + lane] : 0;
+    if (key != 0) {
+      or_hi |= uint32_t(key >> 32);
+      and_hi &= uint32_t(key >> 32);
+    }
+    count += __popcll(__ballot(key != 0));
+  }
+  uint64_t thr = 0;
+  int shift = 0;
+  if (count > r) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      or_hi |= __shfl_xor(or_hi, off, 64);
+      and_hi &= __shfl_xor(and_hi, off, 64);
+    }
+    const uint32_t diff = or_hi & ~and_hi;                      // as in radix_select from here on
+    int prev = diff ? 64 - __clz(int(diff)) : 24, remaining = r;
+    uint64_t prefix = prev == 64 ? 0 : ((uint64_t(and_hi) << 32) | 0xff000000u) >> prev;
+    for (;;) {
+      shift = max(prev - 8, 0);
+      const uint32_t digits = (1u << (prev - shift)) - 1u;
+      *reinterpret_cast<uint4 *>(hist + 4 * lane) = uint4{0u, 0u, 0u, 0u};
+      wave_lds_fence();
+      for (int i = first + lane; i < end; i += 64) {
+        const uint64_t key = s_key[i];
+        if (key != 0 && (prev == 64 || (key >> prev) == prefix)) atomicAdd(&hist[uint32_t(key >> shift) & digits], 1u);
+      }
+      wave_lds_fence();
+      int digit, rest, inbin;
+      pick_bin(hist, lane, remaining, digit, rest, inbin);
+      wave_lds_fence();                                         // the bins are read before the next pass clears them
+      prefix = (prefix << (prev - shift)) | uint32_t(digit);
+      remaining = rest;
+      prev = shift;
+      if (inbin == rest || shift == 0) break;
+    }
+    thr = prefix;
+  }
+  int taken = 0;
+  for (int i0 = first; i0 < end; i0 += 64) {
+    const uint64_t key = i0 + lane < end ? s_key[i0 + lane] : 0;
+    const bool in = key != 0 && (key >> shift) >= thr;
+    const uint64_t mask = __ballot(in);
+    if (in) out[taken + __popcll(mask & ((uint64_t(1) << lane) - 1))] = key;
+    taken += __popcll(mask);
+  }
+  for (int t = taken + lane; t < r; t += 64) out[t] = 0;
+}
+
+// 256 threads: positions of the best r of the keys [0, n) to out_pos[0 .. r), best first.  list: 4 r keys, 16-byte aligned.  hist: 4 x 256
+// words, 16-byte aligned.  Needs at least r keys and r <= kFewRanks; the keys are complete (barrier).
+__device__ __forceinline__ void best_of_few(const uint64_t *s_key, int n, int r, uint32_t *hist, uint64_t *list, int32_t *out_pos) {
+  const int tid = threadIdx.x, wave = tid >> 6, per = (n + 3) / 4;
+  wave_best(s_key, wave * per, min(n, (wave + 1) * per), r, hist + wave * 256, list + wave * r);
+  __syncthreads();
+  if (tid < 4 * r) {
+    const uint64_t mine = list[tid];
+    int rank = 0;
+    const ulonglong2 *two = reinterpret_cast<const ulonglong2 *>(list);
+#pragma unroll 8
+    for (int j = 0; j < 2 * r; ++j) {
+      const ulonglong2 v = two[j];
+      rank += (v.x > mine) + (v.y > mine);
+    }
+    if (mine != 0 && rank < r) out_pos[rank] = key_pos(mine);
   }
   __syncthreads();
 }
@@ -267,6 +341,160 @@ __device__ __forceinline__ void release_row(int row, int s_ins, const int32_t *_
   }
 }
 
+// The same by a workgroup of 256 threads, for rows that are few: thread t holds the keys of slots t, t + 256, ... (KPL of them).  A wave
+// alone works 16 keys a lane through every pass and through the compaction, 15 us of a chain of 17 at K = 1024; this takes 5.
+// red: kWideWords words of LDS, 16-byte aligned.  x >= 0.  All threads; row_copy is complete behind a barrier.
+constexpr int kWideWords = 2 * 256 + 4 * 5 + 4 * 4 * 2;
+template <int KPL>
+__device__ __forceinline__ void release_fetch_wide(int row, const int32_t *__restrict__ slot_src, int K, int (&raw)[KPL]) {
+  const int32_t *sp = slot_src + size_t(row) * K;
+#pragma unroll
+  for (int j = 0; j < KPL; ++j) {
+    const int k = j * 256 + int(threadIdx.x);
+    raw[j] = k < K ? sp[k] : -1;
+  }
+}
+template <int KPL>
+__device__ __forceinline__ void release_row_wide(int row, int s_ins, int32_t *__restrict__ slot_dst, const float *sc,
+                                                 int32_t *__restrict__ free_list, int32_t *__restrict__ released_pos,
+                                                 int32_t *__restrict__ map_out, int32_t *__restrict__ rel_out, int K, int n, int x, int R1,
+                                                 int32_t *row_copy, uint32_t *red, const int (&raw)[KPL]) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t *hist = red, *s_bits = red + 512, *s_count = s_bits + 20;   // [2][256]; [4 waves][5]; [KPL][4 waves][2]
+  int pos[KPL];
+  uint32_t khi[KPL], klo[KPL], cand = 0;
+  uint32_t or_hi = 0, or_lo = 0, and_hi = ~0u, and_lo = ~0u;
+#pragma unroll
+  for (int j = 0; j < KPL; ++j) {
+    const int k = j * 256 + tid;
+    pos[j] = k < K ? (k == s_ins ? n : raw[j]) : -1;
+    khi[j] = klo[j] = 0;
+  }
+  int nactive = 0;
+#pragma unroll
+  for (int j = 0; j < KPL; ++j) {
+    const bool in = pos[j] >= 0 && pos[j] != n;
+    if (in) {
+      const uint64_t key = rank_key(sc[pos[j]], pos[j]);
+      khi[j] = uint32_t(key >> 32);
+      klo[j] = uint32_t(key);
+      cand |= 1u << j;
+      or_hi |= khi[j]; or_lo |= klo[j];
+      and_hi &= khi[j]; and_lo &= klo[j];
+    }
+    nactive += __popcll(__ballot(in));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    or_hi |= __shfl_xor(or_hi, off, 64); or_lo |= __shfl_xor(or_lo, off, 64);
+    and_hi &= __shfl_xor(and_hi, off, 64); and_lo &= __shfl_xor(and_lo, off, 64);
+  }
+  if (lane == 0) {
+    s_bits[wave * 5] = or_hi; s_bits[wave * 5 + 1] = or_lo;
+    s_bits[wave * 5 + 2] = and_hi; s_bits[wave * 5 + 3] = and_lo;
+    s_bits[wave * 5 + 4] = uint32_t(nactive);
+  }
+  hist[tid] = 0u;
+  __syncthreads();
+  or_hi = or_lo = 0u;
+  and_hi = and_lo = ~0u;
+  nactive = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    or_hi |= s_bits[w * 5]; or_lo |= s_bits[w * 5 + 1];
+    and_hi &= s_bits[w * 5 + 2]; and_lo &= s_bits[w * 5 + 3];
+    nactive += int(s_bits[w * 5 + 4]);
+  }
+  const uint32_t diff_hi = or_hi & ~and_hi, diff_lo = or_lo & ~and_lo;
+  uint32_t active = cand, sel = 0;
+  int need = x, cur = 0;
+  if (need > 0 && nactive > need) {              // as in release_row; everything but the lanes' own keys is the same in all threads
+    bool done = false;
+#pragma unroll 1
+    for (int word = 1; word >= 0 && !done; --word) {
+      uint32_t diff = word ? diff_hi : diff_lo;
+#pragma unroll 1
+      while (diff != 0u && !done) {
+        const int shift = max(24 - __clz(int(diff)), 0);
+        diff &= (1u << shift) - 1u;
+        uint32_t *bins = hist + cur * 256;
+#pragma unroll
+        for (int j = 0; j < KPL; ++j) {
+          const uint32_t kw = ~(word ? khi[j] : klo[j]);
+          if ((active >> j) & 1u) atomicAdd(&bins[(kw >> shift) & 0xffu], 1u);
+        }
+        cur ^= 1;
+        hist[cur * 256 + tid] = 0u;              // the other one's, last read before the barrier of the pass before
+        __syncthreads();
+        int bin, rest, inbin;
+        pick_bin(bins, lane, need, bin, rest, inbin);
+#pragma unroll
+        for (int j = 0; j < KPL; ++j) {
+          if (!((active >> j) & 1u)) continue;
+          const int dgt = int(((~(word ? khi[j] : klo[j])) >> shift) & 0xffu);
+          if (dgt > bin) sel |= 1u << j;
+          if (dgt != bin) active &= ~(1u << j);
+        }
+        need = rest;
+        done = inbin == rest;
+        __syncthreads();
+      }
+    }
+  }
+  if (need > 0) sel |= active;
+
+  // ascending slot order: j, then the wave, then the lane
+  uint64_t bf[KPL], br[KPL];
+#pragma unroll
+  for (int j = 0; j < KPL; ++j) {
+    const bool rel = (sel >> j) & 1u;
+    bf[j] = __ballot(j * 256 + tid < K && (pos[j] < 0 || rel));
+    br[j] = __ballot(rel);
+    if (lane == 0) {
+      s_count[(j * 4 + wave) * 2] = uint32_t(__popcll(bf[j]));
+      s_count[(j * 4 + wave) * 2 + 1] = uint32_t(__popcll(br[j]));
+    }
+  }
+  __syncthreads();
+  int nfree = 0, nrel = 0;
+  int32_t *dp = slot_dst + size_t(row) * K;
+  const uint64_t below = (uint64_t(1) << lane) - 1;
+#pragma unroll
+  for (int j = 0; j < KPL; ++j) {
+    int free_at = nfree, rel_at = nrel;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int f = int(s_count[(j * 4 + w) * 2]), r = int(s_count[(j * 4 + w) * 2 + 1]);
+      if (w < wave) {
+        free_at += f;
+        rel_at += r;
+      }
+      nfree += f;
+      nrel += r;
+    }
+    const int k = j * 256 + tid;
+    const bool rel = (sel >> j) & 1u;
+    if ((bf[j] >> lane) & 1u) {
+      const int idx = free_at + __popcll(bf[j] & below);
+      if (idx < R1) free_list[size_t(row) * R1 + idx] = k;
+    }
+    if (rel) {
+      const size_t at = size_t(row) * R1 + rel_at + __popcll(br[j] & below);
+      released_pos[at] = pos[j];
+      if (rel_out) rel_out[at] = pos[j];
+    }
+    if (k < K) {
+      if (row_copy) row_copy[k] = rel ? -1 : pos[j];
+      dp[k] = rel ? -1 : pos[j];
+      if (map_out) map_out[size_t(row) * K + k] = rel ? -1 : pos[j];
+    }
+  }
+  for (int t = nrel + tid; t < R1; t += 256) {
+    released_pos[size_t(row) * R1 + t] = -1;
+    if (rel_out) rel_out[size_t(row) * R1 + t] = -1;
+  }
+}
+
 // ---- per-sequence choice of the tokens to rebuild -------------------------------
 struct RebuildSelectArgs {
   int32_t *slot_pos;           // [B][H][K]
@@ -377,7 +605,10 @@ __device__ __forceinline__ void choice_fill_keys(const float *sc, int n, uint64_
   for (int i = tid; i <= n; i += nthreads) s_cache[i] = rank_key(sc[i], i);
 }
 
-__device__ __forceinline__ void choice_from_keys(const RebuildSelectArgs &a, int b, const int32_t *res_row, uint64_t *smem64) {
+// hist: 4 x 256 words, 16-byte aligned; list: room for n_list keys, 16-byte aligned, or null (then, and where the workgroup has not 256
+// threads, the keys are ranked by all of them together)
+__device__ __forceinline__ void choice_from_keys(const RebuildSelectArgs &a, int b, const int32_t *res_row, uint64_t *smem64, uint32_t *hist,
+                                                 uint64_t *list, int n_list) {
   uint64_t *s_cache = smem64;                                   // [n + 1]
   uint64_t *s_keys = smem64 + a.n + 1;                          // [max(r,1)]
   uint64_t *s_ctl = s_keys + max(a.r, 1);                       // [4]
@@ -392,11 +623,15 @@ __device__ __forceinline__ void choice_from_keys(const RebuildSelectArgs &a, int
       if (p >= 0) s_cache[p] = 0;                               // a resident is no candidate
     }
     __syncthreads();
-    auto key_c = [&](int i) -> uint64_t { return s_cache[i]; };
-    uint64_t thr;
-    int shift;
-    radix_select(key_c, a.n + 1, r, s_hist, s_ctl, &thr, &shift);
-    collect_sorted(key_c, a.n + 1, r, thr, shift, s_keys, s_count, s_sel);
+    if (blockDim.x == 256 && r <= kFewRanks && 4 * r <= n_list) {   // uniform over the launch
+      best_of_few(s_cache, a.n + 1, r, hist, list, s_sel);
+    } else {
+      auto key_c = [&](int i) -> uint64_t { return s_cache[i]; };
+      uint64_t thr;
+      int shift;
+      radix_select(key_c, a.n + 1, r, s_hist, s_ctl, &thr, &shift);
+      collect_sorted(key_c, a.n + 1, r, thr, shift, s_keys, s_count, s_sel);
+    }
     for (int t = tid; t < r; t += blockDim.x) {
       a.rebuilt_pos[size_t(b) * a.Rdim + t] = s_sel[t];
       if (a.rb_out) a.rb_out[size_t(b) * a.Rdim + t] = s_sel[t];
@@ -492,7 +727,8 @@ __device__ __forceinline__ void choice_released(const RebuildSelectArgs &a, cons
 }
 
 // Behind either of the two: the last workgroup of the sequence to get here chooses.
-__device__ __forceinline__ void choice_arrive(const RebuildSelectArgs &a, const ChoiceParts &c, int b, uint64_t *smem64) {
+// hist: 4 x 256 words, 16-byte aligned.
+__device__ __forceinline__ void choice_arrive(const RebuildSelectArgs &a, const ChoiceParts &c, int b, uint64_t *smem64, uint32_t *hist) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this wave's keys are where the others will look for them
   __syncthreads();
   const int total = choice_part_keys(c.n_parts, a.Rdim);
@@ -513,13 +749,20 @@ __device__ __forceinline__ void choice_arrive(const RebuildSelectArgs &a, const 
   const uint64_t *in = c.keys + size_t(b) * total;
   for (int i = tid; i < total; i += blockDim.x) s_key[i] = __hip_atomic_load(in + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  auto key_of = [&](int i) -> uint64_t { return s_key[i]; };
-  uint64_t thr;
-  int shift;
-  radix_select(key_of, total, a.r, s_hist, s_ctl, &thr, &shift);
-  collect_sorted(key_of, total, a.r, thr, shift, s_keys, s_count, s_sel);
+  const int list = (total + 1) / 2 * 2;                         // (behind the keys, within what a part takes: choice_parts_lds_bytes)
+  int *sel = s_sel;
+  if (a.r <= kFewRanks && list + 4 * a.r + kFewRanks / 2 <= kPartTokens) {
+    sel = reinterpret_cast<int *>(s_key + list + 4 * a.r);      // (s_sel lies where the list does)
+    best_of_few(s_key, total, a.r, hist, s_key + list, sel);
+  } else {
+    auto key_of = [&](int i) -> uint64_t { return s_key[i]; };
+    uint64_t thr;
+    int shift;
+    radix_select(key_of, total, a.r, s_hist, s_ctl, &thr, &shift);
+    collect_sorted(key_of, total, a.r, thr, shift, s_keys, s_count, s_sel);
+  }
   for (int t = tid; t < a.Rdim; t += blockDim.x) {
-    const int p = t < a.r ? s_sel[t] : -1;
+    const int p = t < a.r ? sel[t] : -1;
     a.rebuilt_pos[size_t(b) * a.Rdim + t] = p;
     if (a.rb_out) a.rb_out[size_t(b) * a.Rdim + t] = p;
   }

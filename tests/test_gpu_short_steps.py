@@ -31,7 +31,7 @@ def _of_state(state, n):
             state["scores"][:, :n].clone()]
 
 
-def _run(case, carried, ordered, monkeypatch, steps):
+def _run(case, carried, ordered, monkeypatch, steps, coarse=False):
     import torch
     from paper_2407_02328_amd import Adore, make_config
     B, H, d, D, K, R, S, dtype, rescore, rope = case
@@ -52,14 +52,18 @@ def _run(case, carried, ordered, monkeypatch, steps):
     qkv = n((steps, 3, B, H, d), 1.0, st)
     given = torch.rand((steps, (B + 3) // 4 * 4), device="cuda", generator=g)
     xs = hid[0][:, S:].transpose(0, 1).contiguous()
-    a.init_cache(pk, pv, hid, hid[0][:, :S].contiguous(), None, S)
+    prompt_scores = None
+    if coarse:                                                         # eight values in all, the caller's own at every step
+        given = (given * 8).floor() / 8
+        prompt_scores = (torch.rand((B, S), device="cuda", generator=g) * 8).floor() / 8
+    a.init_cache(pk, pv, hid, hid[0][:, :S].contiguous(), prompt_scores, S)
     torch.cuda.synchronize()
     a.set_timing(True)
     seen = []
     for t in range(steps):
         out = torch.empty((B, H, d), dtype=f, device="cuda")
         maps = torch.empty((B, H, K), dtype=torch.int32, device="cuda")
-        ov = given[t, :B] if not rescore and t % 3 == 2 else None     # now and then the caller's own scores
+        ov = given[t, :B] if coarse or (not rescore and t % 3 == 2) else None     # now and then the caller's own scores
         a.decode_step(qkv[t, 0], qkv[t, 1], qkv[t, 2], hid[0], xs[t], ov, out, maps)
         seen += [out, maps]
     state = a.empty_state()
@@ -86,6 +90,22 @@ def test_carried_steps_are_the_steps(case, ordered, monkeypatch):
         assert launches["ctrl_input"] == launches["ctrl_cell"] < steps
     apart, launches = _run(case, False, ordered, monkeypatch, steps)
     assert launches["ctrl_input"] == launches["ctrl_cell"] == launches["release"] == steps
+    for i, (x, y) in enumerate(zip(carried, apart)):
+        same = torch.equal(x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32), y.view(torch.int16 if y.dtype == torch.bfloat16 else torch.int32))
+        assert same, f"{case}: tensor {i} of {len(carried)}"
+
+
+# Equal scores: positions decide, in the low word of the keys.  A workgroup per head with one, two and four keys a thread, a wave per head; the
+# choice by all of a workgroup, by its waves, in parts, and with more ranks than four waves rank.
+@pytest.mark.parametrize("case", [(2, 3, 64, 128, 150, 9, 400, "bf16", False, 0.0), (4, 32, 64, 128, 400, 32, 700, "bf16", False, 0.0),
+                                  (1, 4, 128, 256, 1024, 64, 1500, "bf16", False, 0.0), (9, 16, 64, 128, 500, 17, 700, "bf16", False, 0.0),
+                                  (2, 4, 64, 128, 700, 65, 1000, "bf16", False, 0.0), (2, 3, 64, 128, 1000, 40, 5000, "bf16", False, 0.0),
+                                  (1, 2, 64, 128, 40, 12, 37, "f32", False, 0.0)])
+def test_carried_steps_with_equal_scores(case, monkeypatch):
+    import torch
+    carried, launches = _run(case, True, True, monkeypatch, 7, coarse=True)
+    assert launches["release"] == launches["rebuild_select"] == 0
+    apart, _ = _run(case, False, True, monkeypatch, 7, coarse=True)
     for i, (x, y) in enumerate(zip(carried, apart)):
         same = torch.equal(x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32), y.view(torch.int16 if y.dtype == torch.bfloat16 else torch.int32))
         assert same, f"{case}: tensor {i} of {len(carried)}"
