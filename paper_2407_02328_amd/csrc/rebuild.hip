@@ -286,7 +286,8 @@ __device__ inline void cur_rows_role(const GemmArgs &a, int e, u32x4 *smem) {
 // 133.5 -> 130.5, 256 35.0 -> 34.0 at N = 8192, D = 4096; two LDS operations behind each, whatever they are, 131.3 at M = 2048, the
 // reads from memory in the last slice 135; with one MFMA a slice (128x32) 24.5 -> 25.5, left as it was.
 template <int MODE_, int BM, int BN, int BK, int KG, int WM, int WN, int LS, int NS>
-__global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(512, BM * BN <= 64 * 64 && (MODE_ == MODE_REBUILD || MODE_ == MODE_TAIL) ? 4 : 2)   // two workgroups a unit, or one
+void rebuild_mfma_kernel(const GemmArgs a) {
   constexpr int MODE = MODE_ == MODE_TAIL ? MODE_REBUILD : MODE_;
   constexpr int CH = BK / 8;             // 16-byte chunks per tile row
   constexpr int RPP = 512 / CH;          // tile rows the workgroup loads per pass
@@ -355,10 +356,18 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   const bf16_t *W = MODE == MODE_QKV ? (n0 < Hd ? static_cast<const bf16_t *>(a.Wq) + size_t(n0) * a.D
                                                   : static_cast<const bf16_t *>(a.W) + size_t(n0 - Hd) * a.D)
                                      : static_cast<const bf16_t *>(a.W) + size_t(n0) * a.D;
+  // Rotary embedding: the tiles of the sections that are turned hold whole planes.  One that is narrower than a head takes half of its
+  // columns from the head's lower half and half of them, d / 2 further on, from its upper one (a pass of its own behind the launch: 18.3 ->
+  // 15.8 us a step at 3 sequences of 12 heads of 64, 28.5 -> 26.0 at 16 of 16 heads of 128, 42.3 -> 39.2 at 4 of 32).
+  const int section = MODE == MODE_OPROJ || MODE == MODE_PLAIN ? 0 : n0 / Hd;   // REBUILD: K, V; QKV: Q, K, V (a tile lies in one)
+  const bool turn = (MODE == MODE_REBUILD ? section == 0 : MODE == MODE_QKV ? section <= 1 : false) && a.rope != nullptr;
+  const bool paired = turn && BN < a.d;
+  const int piece = paired ? n0 % a.d / BN : 0;   // which part of the head's planes
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    const int nrow = b_on ? lrow + RPP * i : 0;
-    gB[i] = reinterpret_cast<const u32x4 *>(W + size_t(nrow) * a.D) + lchunk;
+    int nrow = b_on ? lrow + RPP * i : 0;
+    if (paired) nrow += nrow < BN / 2 ? -piece * (BN / 2) : a.d / 2 - (piece + 1) * (BN / 2);   // (counted from the head's column piece * BN)
+    gB[i] = reinterpret_cast<const u32x4 *>(W + ptrdiff_t(nrow) * a.D) + lchunk;
   }
   const int nk = a.D / BK;
   u32x4 ra[NS][NA], rb[NS][NB];
@@ -422,7 +431,6 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   // where every row of the output tile goes: looked up now, used after the k-loop
   const int sw = MODE == MODE_OPROJ ? BN : a.d;   // width of a contiguous piece of an output row
   const int nh = BN / sw > 0 ? BN / sw : 1;       // pieces in one tile row
-  const int section = MODE == MODE_OPROJ ? 0 : n0 / Hd;   // REBUILD: K, V; QKV: Q, K, V (a tile lies in one)
   for (int t = tid; MODE != MODE_PLAIN && t < BM * nh; t += 512) {
     const int row = t / nh, hh = t - row * nh;
     const int mi = m0 + row;
@@ -435,10 +443,10 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
         const int rem = (n0 + hh * a.d) % Hd;
         const int h = rem / a.d;
         if (MODE == MODE_QKV && section == 0) {
-          off = (long long)(size_t(b) * a.xrps + j) * Hd + rem;
+          off = (long long)(size_t(b) * a.xrps + j) * Hd + rem - piece * (BN / 2);
         } else {
           const int slot = a.free_list[(size_t(b) * a.H + h) * a.R1 + j];
-          off = ((long long)(size_t(b) * a.H + h) * a.K + slot) * a.d + (rem - h * a.d);
+          off = ((long long)(size_t(b) * a.H + h) * a.K + slot) * a.d + (rem - h * a.d) - piece * (BN / 2);
           // no slot: the head still holds this token's row (heads with maps of their own), or the rank is empty
           if (MODE == MODE_REBUILD && (slot < 0 || a.rebuilt_pos[size_t(b) * a.Rdim + j] < 0)) off = -1;
           if (MODE == MODE_REBUILD && a.map_dst && section == 0) {   // the K half's tiles visit every (token, head)
@@ -616,14 +624,14 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
   bf16_t *dst_half = static_cast<bf16_t *>(MODE == MODE_OPROJ ? a.Out
                                            : MODE == MODE_QKV ? (section == 0 ? a.Out : section == 1 ? a.Kc : a.Vc)
                                                               : (section == 0 ? a.Kc : a.Vc));
-  // Rotary embedding (query and key tiles, when the tile holds whole heads): the rounded row is turned by its
+  // Rotary embedding (query and key tiles): the rounded row is turned by its
   // token's position on the way out, in fp32, and rounded again.  A thread takes 8 planes at a time: the 8-element
   // vectors of elements j and j + d/2 of a head, which share their angles; the angles of two such pairs are fetched
   // before either is used (a fetch costs a trip to the L2).
-  const bool turn = (MODE == MODE_REBUILD ? section == 0 : MODE == MODE_QKV ? section <= 1 : false) && a.rope != nullptr;
   if (turn) {
     constexpr int PV = BM * BN / 16;           // pairs of vectors in the tile
-    const int half = a.d / 2, hv = half / 8;   // vectors per half head
+    const int half = a.d / 2;
+    const int width = paired ? BN : a.d, hv = width / 16;   // columns of a head in the tile, pairs of vectors among them
     const int per_row = BN / 16;
     for (int i0 = 0; i0 < (PV + 511) / 512; i0 += 2) {
       float2 cs[2][8];
@@ -639,11 +647,11 @@ __global__ __launch_bounds__(512) void rebuild_mfma_kernel(const GemmArgs a) {
           const long long off = s_dst[row * nh + hh];
           if (off >= 0) {
             offv[u] = off + v * 8;
-            const float2 *src = a.rope + size_t(s_rpos[row]) * half + v * 8;
+            const float2 *src = a.rope + size_t(s_rpos[row]) * half + piece * (BN / 2) + v * 8;
 #pragma unroll
             for (int e = 0; e < 8; ++e) cs[u][e] = src[e];
-            lo[u] = *reinterpret_cast<const u32x4 *>(sOut + row * BN + hh * a.d + v * 8);
-            hi[u] = *reinterpret_cast<const u32x4 *>(sOut + row * BN + hh * a.d + half + v * 8);
+            lo[u] = *reinterpret_cast<const u32x4 *>(sOut + row * BN + hh * width + v * 8);
+            hi[u] = *reinterpret_cast<const u32x4 *>(sOut + row * BN + hh * width + width / 2 + v * 8);
           }
         }
       }
@@ -1127,9 +1135,9 @@ hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_lay
   const int pick = c.dtype != ADORE_BF16 ? -1
                    : tail ? pick_tile_with_tail(c, a.M, step_tail_wgs(ctx, 512), &front)
                           : pick_tile(a.M, a.N, c.hidden, c.heads * c.head_dim, c.head_dim, false);
-  // the key tiles turn their rows themselves when a tile holds whole heads; otherwise a pass of its own follows
+  // the key tiles turn their rows themselves; behind the other kernels a pass of its own follows
   const bool rope = c.rope_base > 0.f;
-  const bool turned = rope && pick >= 0 && kTiles[pick].bn >= c.head_dim;
+  const bool turned = rope && pick >= 0;
   if (turned) a.rope = ctx->rope_f;
   if (tail) {
     a.tail = *tail;
@@ -1256,7 +1264,7 @@ hipError_t launch_fwd_qkv(adore_ctx *ctx, int layer, const void *w_q_layer, cons
     ScopedTimer t(ctx, ADORE_KERNEL_FWD_QKV, ctx->stream);
     const int pick = pick_with_riders(a, c.hidden, Hd, c.head_dim, false);
     if (pick < 0) return hipErrorInvalidValue;
-    turned = c.rope_base > 0.f && kTiles[pick].bn >= c.head_dim;
+    turned = c.rope_base > 0.f;
     if (turned) a.rope = ctx->rope_f;
     // the current tokens' rows riding in this launch turn themselves when a workgroup's columns are whole heads
     cur_turned = c.rope_base > 0.f && a.n_cur > 0 && (kCurCols / a.cur_ks) % c.head_dim == 0;

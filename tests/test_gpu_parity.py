@@ -1059,8 +1059,8 @@ def test_rotary_embedding_on_rebuilt_keys(name, kw, calls):
 @pytest.mark.parametrize("tile,D", TILES[:9])
 @pytest.mark.parametrize("d", [64, 128])
 def test_rotary_embedding_with_every_tile_shape(tile, D, d, monkeypatch):
-    """The key tiles turn their rows themselves when a tile holds whole heads (256- to 64-wide tiles at d = 64,
-    256- and 128-wide ones at d = 128); narrower tiles leave it to the pass that follows.  Both give the same rows."""
+    """The key tiles turn their rows themselves: those that hold whole heads (256- to 64-wide tiles at d = 64, 256- and 128-wide
+    ones at d = 128), and narrower ones, which take both elements of a plane (half of a head to an eighth of it)."""
     h = _harness()
     monkeypatch.setenv("ADORE_GEMM_TILE", str(tile))
     w = Workload("rope_tiles", L=1, B=3, H=512 // d, d=d, D=D, K=128, R=45, S=200, T=4, dtype="bf16", dprime=32,
