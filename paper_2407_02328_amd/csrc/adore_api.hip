@@ -260,6 +260,9 @@ int ensure_side_stream(adore_ctx *ctx) {
 //   in fp32, either order: 1 of 4 heads 20 / 39 and 34, 4 of 8 heads of 128 (17 us) 30 / 46 and 41, 4 of 16 (33 us) 39 / 55 and 47;
 //   selections as launches of their own, ordered inputs or not: 8 of 16 heads (16 us) 48 / 78 and 48 / 66, 4 of 32 (28 us) 56 / 78 and
 //     56 / 63; 1 of 4 heads behind 5000, 16000 and 40000 tokens 31 / 76, 42 / 76, 67 / 80 and 31 / 59, 42 / 58, 66 / 57.
+//   riding, ordered inputs, the projection's tiles leaving compute units free for the tail: whatever the size.  12 sequences of 24 heads
+//     (46 us) 46 / 55, 16 of 24 (51) 52 / 60, 12 of 32 (61) 59 / 68, 11 of 32 behind 1024 slots (78) 77 / 84, 30 of 32 behind
+//     700 (110) 125 / 138; known ahead 46 / 47, 52 / 53, 58 / 60, 75 / 76, but 32 of 16 (42) 49 / 48, 48 of 12 (46) 55 / 54, 20 of 24 (55) 59 / 57.
 //   A riding step whose controller is in launches of its own (no hidden size of 128, no room next to the projection): ordered 8 of 16 39 /
 //     45, 4 of 32 48 / 47, known ahead 1 of 4 heads 24 / 25 to 25 / 28, 8 of 12 32 / 27; fp32 a half of that, known ahead an eighth.
 // A stack of layers called one by one with ordered inputs starts its selections behind the last layer's attention, so
@@ -278,7 +281,10 @@ bool steps_on_one_stream(const adore_ctx *ctx, bool forward, bool riding) {
   const double attention = 2.0 * c.batch * c.heads * double(c.cache_slots) * c.head_dim * elem_size(c) / 5e6;
   const bool f32 = c.dtype == ADORE_F32, rescore = c.score_mode == ADORE_SCORE_RESCORE;
   float limit;
-  if (riding && step_ctrl_supported(c) && rebuild_gemm_takes_tail(ctx, c.rebuild_budget))
+  bool beside;
+  const bool tail = rebuild_gemm_takes_tail(ctx, c.rebuild_budget, &beside);
+  if (riding && step_ctrl_supported(c) && tail && beside && ctx->ordered) return true;
+  if (riding && step_ctrl_supported(c) && tail)
     limit = rescore ? kCarriedRescoreMicros : (ctx->ordered || f32 ? kCarriedMicros : kCarriedReadyMicros)[attention >= kShortAttention];
   else if (riding && !ctx->ordered && !rescore)
     limit = kOneStreamReadyMicros * (f32 ? 0.125f : 1.f);

@@ -196,7 +196,7 @@ hipError_t launch_rebuild_select(adore_ctx *ctx, hipStream_t st, int dst, int r,
 float rebuild_gemm_micros(const adore_config &c);
 hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_layer, int lists, int r,
                                int32_t *map_dst = nullptr, int32_t *map_out = nullptr, const StepTail *tail = nullptr);
-bool rebuild_gemm_takes_tail(const adore_ctx *ctx, int r);   // whether a launch of r tokens per sequence can carry a StepTail
+bool rebuild_gemm_takes_tail(const adore_ctx *ctx, int r, bool *beside = nullptr);   // beside: on compute units the tiles leave free (bf16)   // whether a launch of r tokens per sequence can carry a StepTail
 bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, const void *x, const void *W, float *out,
                              int ntok, int per_seq, int seq_rows, int N, int D);
 hipError_t launch_init_select(adore_ctx *ctx, int dst, int lists, int S, int keep, int r0);

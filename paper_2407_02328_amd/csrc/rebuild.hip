@@ -1109,11 +1109,12 @@ int pick_tile_with_tail(const adore_config &c, int M, int wgs, bool *front) {
 }
 }  // namespace
 
-bool rebuild_gemm_takes_tail(const adore_ctx *ctx, int r) {
+bool rebuild_gemm_takes_tail(const adore_ctx *ctx, int r, bool *beside) {
   const adore_config &c = ctx->cfg;
-  if (r <= 0) return false;
-  bool front;
-  return c.dtype == ADORE_F32 || takes_tail(pick_tile_with_tail(c, c.batch * r, step_tail_wgs(ctx, 512), &front));
+  bool front = false;
+  const bool takes = r > 0 && (c.dtype == ADORE_F32 || takes_tail(pick_tile_with_tail(c, c.batch * r, step_tail_wgs(ctx, 512), &front)));
+  if (beside) *beside = takes && front;
+  return takes;
 }
 
 hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_layer, int lists, int r,
