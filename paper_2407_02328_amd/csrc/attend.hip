@@ -320,8 +320,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void attend_kernel(const AttendArgs 
 #pragma unroll
         for (int e = 0; e < EPL; ++e) dot = fmaf(qf[e], kf[e], dot);
       }
-#pragma unroll
-      for (int off = LPR / 2; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
+      dot = group_sum<LPR>(dot);
       logit[u] = valid[u] ? dot : -INFINITY;
       mb = fmaxf(mb, logit[u]);
       if (KPL > 0) {

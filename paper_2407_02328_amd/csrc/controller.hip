@@ -862,8 +862,7 @@ __global__ __launch_bounds__(256) void rescore_kernel(const float *__restrict__ 
     s = fmaf(wv.z, tanhf(fmaf(delta, av.z, cv.z)), s);
     s = fmaf(wv.w, tanhf(fmaf(delta, av.w, cv.w)), s);
   }
-#pragma unroll
-  for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  s = group_sum<16>(s);
   if (lig == 0 && i <= upto) score[size_t(b) * N_max + i] = sigmoidf_(s + out_b[0]);
 }
 

@@ -54,19 +54,27 @@ __device__ __forceinline__ void ctrl_input_mfma_tile(const bf16_t *__restrict__ 
 }
 
 // Sums over a wave of a batch of rows at once: at every halving step a lane keeps one half of its partial sums and hands the
-// other half to its partner, so N rows cost N-1 shuffles instead of 6N.
+// other half to its partner, so N rows cost N-1 exchanges instead of 6N.
 // v[i] is this lane's partial sum of row i.  Returns, in every lane, the complete sum of row
 // lane / (64 / N).
 template <int N, int OFF>
 struct ReduceRows {
   __device__ static __forceinline__ float run(float (&v)[N], int lane) {
-    const bool upper = (lane & OFF) != 0;
     float w[N / 2];
 #pragma unroll
     for (int i = 0; i < N / 2; ++i) {
-      const float keep = upper ? v[i + N / 2] : v[i];
-      const float send = upper ? v[i] : v[i + N / 2];
-      w[i] = keep + __shfl_xor(send, OFF, 64);
+      const uint32_t lo = __float_as_uint(v[i]), hi = __float_as_uint(v[i + N / 2]);
+      if constexpr (OFF == 32) {
+        const auto s = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+        w[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+      } else if constexpr (OFF == 16) {
+        const auto s = __builtin_amdgcn_permlane16_swap(lo, hi, false, false);
+        w[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+      } else {
+        const bool upper = (lane & OFF) != 0;
+        const float a = add_lane_xor<OFF>(v[i]), b = add_lane_xor<OFF>(v[i + N / 2]);
+        w[i] = upper ? b : a;
+      }
     }
     return ReduceRows<N / 2, OFF / 2>::run(w, lane);
   }
@@ -74,10 +82,7 @@ struct ReduceRows {
 template <int OFF>
 struct ReduceRows<1, OFF> {
   __device__ static __forceinline__ float run(float (&v)[1], int) {
-    float s = v[0];
-#pragma unroll
-    for (int off = OFF; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    return s;
+    return group_sum<2 * OFF>(v[0]);
   }
 };
 template <int N>
@@ -187,7 +192,7 @@ __device__ __forceinline__ float gi_sum(const CellArgs &a, size_t tok, int j) {
 // A weight row of 128 elements is one coalesced wave load
 // (two elements per lane); a wave multiplies a batch of rows by the state it holds in registers and
 // reduces the whole batch at once: at every halving step a lane keeps one half of its partial sums
-// and hands the other half to its partner, so N rows cost N-1 shuffles instead of 6N.
+// and hands the other half to its partner, so N rows cost N-1 exchanges instead of 6N.
 
 // two consecutive elements of a weight row, raw, and their conversion
 __device__ __forceinline__ uint32_t load_raw2(const bf16_t *p) { return *reinterpret_cast<const uint32_t *>(p); }

@@ -91,23 +91,83 @@ __device__ __forceinline__ uint64_t rank_key(float sigma, int pos) {
 __device__ __forceinline__ int key_pos(uint64_t key) { return int(0xffffffffu - uint32_t(key & 0xffffffffu)); }
 
 // ---- wave helpers (64 lanes) ------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+// A shuffle is a trip through LDS; a lane's neighbours within its row of 16 come with the instruction that uses them (DPP), and rows
+// and halves change places in registers (permlane swaps): the same sums in the same order.  All of these need their partners active.
+// Shuffles before: attention launches with both selections 28.1 -> 26.5 us (16 sequences of 32 heads, H2O), 25.5 -> 24.8 (scores), 8.7 ->
+// 7.5 (1 of 4 heads), the H2O choice 13.2 -> 12.3, the controller's cell on its side stream 14 -> 12.
+template <int CTRL>
+__device__ __forceinline__ float lane_dpp(uint32_t v) {
+  return __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xf, 0xf, true)));
+}
+// v + the value of lane ^ OFF
+template <int OFF>
+__device__ __forceinline__ float add_lane_xor(float v) {
+  static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8 || OFF == 16 || OFF == 32, "one bit of the lane");
+  const uint32_t u = __float_as_uint(v);
+  if constexpr (OFF == 32) {
+    const auto s = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  } else if constexpr (OFF == 16) {
+    const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  } else if constexpr (OFF == 8) {
+    return v + lane_dpp<0x128>(u);                               // row_ror:8
+  } else if constexpr (OFF == 4) {
+    const int up = __builtin_amdgcn_update_dpp(0, int(u), 0x104, 0xf, 0x5, false);                       // row_shl:4 into quads 0 and 2
+    return v + __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(up, int(u), 0x114, 0xf, 0xa, false)));   // row_shr:4 into 1 and 3
+  } else {
+    return v + lane_dpp<OFF == 2 ? 0x4e : 0xb1>(u);              // quad_perm
+  }
+}
+// the larger of v and the value of lane ^ OFF
+template <int OFF>
+__device__ __forceinline__ float max_lane_xor(float v) {
+  static_assert(OFF == 16 || OFF == 32, "rows or halves");
+  const uint32_t u = __float_as_uint(v);
+  if constexpr (OFF == 32) {
+    const auto s = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+  } else {
+    const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+  }
+}
+// Sum over groups of N lanes, in all of them: pairs N/2 apart first.
+template <int N>
+__device__ __forceinline__ float group_sum(float v) {
+  if constexpr (N > 1) return group_sum<N / 2>(add_lane_xor<N / 2>(v));
   return v;
 }
+__device__ __forceinline__ float wave_sum(float v) { return group_sum<64>(v); }
+
+// Inclusive sum of lanes 0 .. own; all 64 lanes active.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+// All lanes' bits together; all 64 lanes active.  Wave-uniform.
+__device__ __forceinline__ uint32_t wave_or(uint32_t u) {
+  int v = int(u);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return uint32_t(__builtin_amdgcn_readlane(v, 63));
+}
+__device__ __forceinline__ uint32_t wave_and(uint32_t u) { return ~wave_or(~u); }
 
 // Scan of a 256-bin histogram from the top bin down: the bin in which the rank `need` (1 = the largest) falls, the
 // rank left inside it, and how many entries it holds.  Lane l owns bins 255 - 4l .. 252 - 4l.  Wave-uniform results.
 __device__ __forceinline__ void pick_bin(int c0, int c1, int c2, int c3, int lane, int need, int &bin, int &rest, int &inbin) {
   const int own = c0 + c1 + c2 + c3;
-  int incl = own;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int other = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += other;
-  }
-  const int excl = incl - own;
+  const int incl = wave_scan(own), excl = incl - own;
   const bool mine = excl < need && need <= incl;   // exactly one lane: need <= the number of candidates
   int b = 252 - 4 * lane, r = need - excl - c0 - c1 - c2, n = c3;
   if (need <= excl + c0) {
@@ -117,10 +177,10 @@ __device__ __forceinline__ void pick_bin(int c0, int c1, int c2, int c3, int lan
   } else if (need <= excl + c0 + c1 + c2) {
     b = 253 - 4 * lane; r = need - excl - c0 - c1; n = c2;
   }
-  const int src = __builtin_ctzll(__builtin_amdgcn_ballot_w64(mine));
-  bin = __shfl(b, src, 64);
-  rest = __shfl(r, src, 64);
-  inbin = __shfl(n, src, 64);
+  const int src = __builtin_ctzll(__builtin_amdgcn_ballot_w64(mine) | (uint64_t(1) << 63));
+  bin = __builtin_amdgcn_readlane(b, src);
+  rest = __builtin_amdgcn_readlane(r, src);
+  inbin = __builtin_amdgcn_readlane(n, src);
 }
 // hist: 256 words, 16-byte aligned
 __device__ __forceinline__ void pick_bin(const uint32_t *hist, int lane, int need, int &bin, int &rest, int &inbin) {

@@ -216,8 +216,7 @@ __global__ __launch_bounds__(256, (DH == 128 && NQB == 4) ? 1 : 2) void fwd_atte
           x[sb * 4 + i] = uint32_t(sp4[sb][i]) <= qpos[qb] ? s[sb][qb][i] : -INFINITY;
           bm = fmaxf(bm, x[sb * 4 + i]);
         }
-      bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
-      bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
+      bm = max_lane_xor<32>(max_lane_xor<16>(bm));
       const bool move = bm > m[qb] + lazy_raw;          // the same in the four lanes of a query
       if (__builtin_amdgcn_ballot_w64(move) != 0) {
         const float alpha = move ? __builtin_amdgcn_exp2f((m[qb] - bm) * a.scale_log2) : 1.f;
@@ -289,9 +288,7 @@ __global__ __launch_bounds__(256, (DH == 128 && NQB == 4) ? 1 : 2) void fwd_atte
   // ---- merge the four waves: common maximum per query, then sums in wave order ----
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
-    float l = lsum[qb];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
+    const float l = add_lane_xor<32>(add_lane_xor<16>(lsum[qb]));
     lsum[qb] = l;
     if (g == 0) {
       s_m[wave * NQ16 + qb * 16 + c] = m[qb];

@@ -134,12 +134,7 @@ __global__ __launch_bounds__(1024) void init_select_kernel(const InitSelectArgs 
     // exclusive prefix of popcounts over the block
     const int cnt = __popc(bits);
     const int lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
-    int incl = cnt;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += v;
-    }
+    const int incl = wave_scan(cnt);
     if (lane == 63) s_cnt[wave] = incl;
     __syncthreads();
     int before = s_carry;

@@ -36,11 +36,8 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int ncand, int c, uin
       and_hi &= uint32_t(key >> 32);
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    or_hi |= __shfl_xor(or_hi, off, 64);
-    and_hi &= __shfl_xor(and_hi, off, 64);
-  }
+  or_hi = wave_or(or_hi);
+  and_hi = wave_and(and_hi);
   if ((threadIdx.x & 63) == 0) {
     atomicOr(s_or, or_hi);
     atomicAnd(s_and, and_hi);
@@ -64,7 +61,7 @@ __device__ __forceinline__ void radix_select(KeyFn key_of, int ncand, int c, uin
       }
     }
     __syncthreads();
-    // four waves find the bin each by itself, without an exchange and its barrier; of sixteen one does (13.0 us a choice for 13.5)
+    // four waves find the bin each by itself, without an exchange and its barrier; of sixteen one does
     const int lane = threadIdx.x & 63;
     const bool all = blockDim.x <= 256;
     int digit = 0, rest = 0, inbin = 0;
@@ -141,11 +138,8 @@ __device__ __forceinline__ void wave_best(const uint64_t *s_key, int first, int 
   uint64_t thr = 0;
   int shift = 0;
   if (count > r) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      or_hi |= __shfl_xor(or_hi, off, 64);
-      and_hi &= __shfl_xor(and_hi, off, 64);
-    }
+    or_hi = wave_or(or_hi);
+    and_hi = wave_and(and_hi);
     const uint32_t diff = or_hi & ~and_hi;                      // as in radix_select from here on
     int prev = diff ? 64 - __clz(int(diff)) : 24, remaining = r;
     uint64_t prefix = prev == 64 ? 0 : ((uint64_t(and_hi) << 32) | 0xff000000u) >> prev;
@@ -254,11 +248,10 @@ __device__ __forceinline__ void release_row(int row, int s_ins, const int32_t *_
       and_hi &= khi[j]; and_lo &= klo[j];
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    or_hi |= __shfl_xor(or_hi, off, 64); or_lo |= __shfl_xor(or_lo, off, 64);
-    and_hi &= __shfl_xor(and_hi, off, 64); and_lo &= __shfl_xor(and_lo, off, 64);
-  }
+  or_hi = wave_or(or_hi);
+  or_lo = wave_or(or_lo);
+  and_hi = wave_and(and_hi);
+  and_lo = wave_and(and_lo);
   const uint32_t diff_hi = or_hi & ~and_hi, diff_lo = or_lo & ~and_lo;   // bits that tell candidates apart
 
   uint32_t active = cand, sel = 0;
@@ -384,11 +377,10 @@ __device__ __forceinline__ void release_row_wide(int row, int s_ins, int32_t *__
     }
     nactive += __popcll(__ballot(in));
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    or_hi |= __shfl_xor(or_hi, off, 64); or_lo |= __shfl_xor(or_lo, off, 64);
-    and_hi &= __shfl_xor(and_hi, off, 64); and_lo &= __shfl_xor(and_lo, off, 64);
-  }
+  or_hi = wave_or(or_hi);
+  or_lo = wave_or(or_lo);
+  and_hi = wave_and(and_hi);
+  and_lo = wave_and(and_lo);
   if (lane == 0) {
     s_bits[wave * 5] = or_hi; s_bits[wave * 5 + 1] = or_lo;
     s_bits[wave * 5 + 2] = and_hi; s_bits[wave * 5 + 3] = and_lo;
