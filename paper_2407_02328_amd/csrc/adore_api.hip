@@ -353,7 +353,7 @@ hipError_t launch_controller(adore_ctx *ctx, const void *x_n, int seq_rows, cons
   const adore_config &c = ctx->cfg;
   hipStream_t st = controller_stream(ctx);
   int ksplit = 1;
-  hipError_t e = launch_ctrl_input(ctx, st, x_n, c.batch, 1, seq_rows, 0, &ksplit);
+  hipError_t e = launch_ctrl_input(ctx, st, x_n, c.batch, 1, seq_rows, 0, ctx->gi_rows[0], &ksplit);
   if (e == hipSuccess) e = launch_ctrl_cell(ctx, st, 1, ctx->n, score_override, 1, 0, ksplit);
   if (e == hipSuccess && side_steps(ctx)) e = hipEventRecord(ctx->ev_ctrl, st);
   return e;
@@ -390,9 +390,12 @@ hipError_t prompt_controller(adore_ctx *ctx, const void *ctrl_input, const float
   int ksplit[3] = {1, 1, 1};
   auto length = [&](int i) { return std::min(chunk, S - i * chunk); };
   auto copy_of = [&](int i) { return first_copy + (copies == 2 ? i & 1 : 0); };
+  // copy 1 in its halves is copy 1 and copy 2 of half its rows: a chunk's slices must not reach what the chunk before it is read from
+  auto rows_of = [&](int copy) { return first_copy == 1 && copies == 2 ? ctx->gi_rows[2] : ctx->gi_rows[copy]; };
   auto project = [&](int i, hipStream_t on) {
     const char *x = static_cast<const char *>(ctrl_input) + size_t(i) * chunk * token_bytes;
-    return launch_ctrl_input(ctx, on, x, c.batch * length(i), length(i), S, copy_of(i), &ksplit[copy_of(i)]);
+    const int copy = copy_of(i);
+    return launch_ctrl_input(ctx, on, x, c.batch * length(i), length(i), S, copy, rows_of(copy), &ksplit[copy]);
   };
 #define CHUNK_TRY(EXPR)                          \
   do {                                           \

@@ -20,7 +20,7 @@ struct bf16_t {
 constexpr int kMaxSplits = 16;        // attention partials per (b,h) row
 constexpr int kMaxSlots = 1024;       // largest K of a cache that releases (a row's keys live in one wave's registers)
 constexpr int kMaxPositions = 1 << 18; // residency bitmap of a sequence lives in LDS
-constexpr int kPromptChunk = 512;     // tokens per GRU input-projection launch at init
+constexpr int kPromptChunk = 512;     // tokens a sequence in a chunk of a prompt (prompt_controller makes longer ones in the cache)
 constexpr int kMaxCtrlSplit = 16;     // D-slices of the GRU input projection
 constexpr int kCtrlSplitTokens = 256; // the projection is only sliced for launches of at most this many tokens
 constexpr int kRing = 8;              // copies of the per-step lists (slot map, reserved slot, free slots, rebuilt tokens)
@@ -175,7 +175,7 @@ hipError_t launch_attend(adore_ctx *ctx, int layer, const void *q, const void *k
 bool step_ctrl_supported(const adore_config &c);
 void fill_step_ctrl(adore_ctx *ctx, const void *x, int pos, const float *score_override, StepCtrl &s, StepTail &t);
 hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int ntok, int per_seq,
-                             int seq_rows, int buf, int *ksplit_out);
+                             int seq_rows, int buf, size_t rows, int *ksplit_out);   // rows: what the copy has room for
 hipError_t launch_ctrl_cell(adore_ctx *ctx, hipStream_t st, int nsteps, int pos0,
                             const float *score_override, int override_stride, int buf, int ksplit);
 // A prompt chunk of more than one token where ctrl_chunk_in_two(): the recurrence, then the layers above it.
@@ -196,7 +196,8 @@ hipError_t launch_rebuild_select(adore_ctx *ctx, hipStream_t st, int dst, int r,
 float rebuild_gemm_micros(const adore_config &c);
 hipError_t launch_rebuild_gemm(adore_ctx *ctx, int layer, const void *hidden_layer, int lists, int r,
                                int32_t *map_dst = nullptr, int32_t *map_out = nullptr, const StepTail *tail = nullptr);
-bool rebuild_gemm_takes_tail(const adore_ctx *ctx, int r, bool *beside = nullptr);   // beside: on compute units the tiles leave free (bf16)   // whether a launch of r tokens per sequence can carry a StepTail
+// Whether a launch of r tokens per sequence can carry a StepTail; beside: on compute units that the tiles leave free (bf16).
+bool rebuild_gemm_takes_tail(const adore_ctx *ctx, int r, bool *beside = nullptr);
 bool launch_plain_projection(adore_ctx *ctx, ScopedTimer &t, hipStream_t st, const void *x, const void *W, float *out,
                              int ntok, int per_seq, int seq_rows, int N, int D);
 hipError_t launch_init_select(adore_ctx *ctx, int dst, int lists, int S, int keep, int r0);

@@ -890,9 +890,9 @@ bool input_on_tiles(const adore_config &c, int ntok) { return ntok >= 16 && (lon
 
 }  // namespace
 
-// buf: which of the two copies of the pre-activations is written (a prompt's chunks take them in turn).
+// buf: which copy of the pre-activations is written (a prompt's chunks take them in turn), rows: how many it has room for.
 hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int ntok, int per_seq,
-                             int seq_rows, int buf, int *ksplit_out) {
+                             int seq_rows, int buf, size_t rows, int *ksplit_out) {
   const adore_config &c = ctx->cfg;
   const int G3 = 3 * c.ctrl_hidden;
   float *gi = ctx->gi[buf];
@@ -908,7 +908,8 @@ hipError_t launch_ctrl_input(adore_ctx *ctx, hipStream_t st, const void *x, int 
                        static_cast<const bf16_t *>(ctx->w.gru_w_ih), static_cast<const bf16_t *>(x), gi,
                        c.hidden, G3, ntok, per_seq, seq_rows);
   } else if (c.dtype == ADORE_BF16 && c.hidden % 128 == 0) {
-    const int ks = ctrl_input_ksplit(c, ntok, ctx->gi_rows[buf]);
+    const int ks = ctrl_input_ksplit(c, ntok, rows);
+    if (size_t(ks) * ntok > rows) return hipErrorInvalidValue;
     *ksplit_out = ks;
     dim3 grid((G3 + 15) / 16, (ntok + 15) / 16, ks);
     ADORE_LAUNCH(t, ctrl_input_mfma_kernel, grid, dim3(256), 0, st,

@@ -21,10 +21,23 @@ extern "C" hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, 
   launched_block.push_back(block);
   return hipSuccess;
 }
-extern "C" hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { return hipSuccess; }
+extern "C" hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *, hipStream_t *) {
+  *grid = launched_grid.back();
+  *block = launched_block.back();
+  return hipSuccess;
+}
 static int launches = 0, failing_launch = -1;   // the one that is refused, counted from 1
-extern "C" hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) {
+// A controller's input projection whose contraction is cut into slices is the one kernel with a grid in three dimensions:
+// (W, x, gi, D, 3d', tokens, ...), a slice behind the other in gi.
+struct SlicedProjection {
+  const float *gi;
+  int width, tokens, slices;
+};
+static std::vector<SlicedProjection> sliced;
+extern "C" hipError_t hipLaunchKernel(const void *, dim3 grid, dim3, void **args, size_t, hipStream_t) {
   ++launches;
+  if (grid.z > 1)
+    sliced.push_back({*static_cast<float **>(args[2]), *static_cast<int *>(args[4]), *static_cast<int *>(args[5]), int(grid.z)});
   return hipSuccess;
 }
 extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
@@ -171,6 +184,27 @@ int main() {
     EXPECT(adore_decode_step(hx, fake, fake, fake, fake, nullptr, nullptr, ffake, nullptr) == ADORE_OK);
     EXPECT(adore_destroy(hx) == ADORE_OK);
   }
+  // A prompt's chunks in the halves of a copy that lies in the cache: a short last one, whose projection is cut into slices, stays in
+  // its half (the other one is being read meanwhile).  34 chunks of 520 tokens and one of 241; 33 and one of 250 in the upper half; 49 and
+  // one of 122 of two sequences.
+  setenv("ADORE_NO_OVERLAP", "1", 1);   // (no streams to be made; the chunks and their copies are the same)
+  for (const int (&v)[4] : (const int[][4]){{1, 780, 17921, 4096}, {1, 780, 17921, 2048}, {1, 780, 17410, 4096}, {2, 780, 25602, 2048}}) {
+    adore_config x = tiny();
+    x.dtype = ADORE_BF16; x.ctrl_hidden = 128; x.heads = 8; x.head_dim = 128; x.rebuild_budget = 8;
+    x.batch = v[0]; x.cache_slots = v[1]; x.max_positions = v[2] + 8; x.hidden = v[3];
+    adore_ctx *hx = nullptr;
+    EXPECT(adore_create(&x, &wt, fake, adore_workspace_bytes(&x), nullptr, &hx) == ADORE_OK);
+    EXPECT(hx->gi_rows[2] * 2 == hx->gi_rows[1] && hx->gi_rows[1] < size_t(v[0]) * v[2]);
+    sliced.clear();
+    EXPECT(adore_init_cache(hx, fake, fake, fake, fake, nullptr, v[2]) == ADORE_OK);
+    EXPECT(!sliced.empty());
+    for (const SlicedProjection &p : sliced) {
+      EXPECT(p.gi == hx->gi[1] || p.gi == hx->gi[2]);
+      EXPECT(p.width == 384 && size_t(p.slices) * p.tokens <= hx->gi_rows[2]);
+    }
+    EXPECT(adore_destroy(hx) == ADORE_OK);
+  }
+  unsetenv("ADORE_NO_OVERLAP");
   // the debug layout
   setenv("ADORE_GUARD_WORDS", "1", 1);
   const size_t guarded = adore_workspace_bytes(&c);

@@ -197,7 +197,7 @@ def test_prompts_over_wide_and_narrow_tiles_are_the_same(monkeypatch):
     assert torch.equal(few_scores, scores[:12]) and torch.equal(few_z, z[:12])
 
 
-# The chunks' second copy in the cache (with sliced tails, and at the smallest cache that holds it), behind everything else, and
+# The chunks' second copy in the cache (undivided with sliced tails, and at the smallest cache that holds it), behind everything else, and
 # missing; with the guard words of the debug layout, which tests/conftest.py counts when the job closes.
 @pytest.mark.parametrize("guards", [False, True])
 @pytest.mark.parametrize("batch,S,D,H,K,without", [(1, 1100, 512, 16, 512, False), (1, 770, 1024, 12, 512, False),
@@ -207,7 +207,9 @@ def test_prompts_over_wide_and_narrow_tiles_are_the_same(monkeypatch):
                                                    # sequence), for one token less, and for chunks of half the room (680)
                                                    (1, 682, 256, 16, 512, False), (1, 683, 256, 16, 512, False),
                                                    (2, 1365, 256, 16, 1024, False), (2, 1366, 256, 16, 1024, False),
-                                                   (1, 2040, 128, 16, 1024, False), (3, 2041, 128, 16, 1024, False)])
+                                                   (1, 2040, 128, 16, 1024, False), (3, 2041, 128, 16, 1024, False),
+                                                   # halves of 520 rows with a sliced last chunk in the lower one (35 chunks), in the upper (34)
+                                                   (1, 17921, 2048, 16, 780, False), (1, 17410, 1024, 16, 780, False)])
 def test_places_of_the_chunks_second_copy(batch, S, D, H, K, without, guards, monkeypatch):
     import os
     from paper_2407_02328_amd import binding
