@@ -21,8 +21,11 @@
 //   3 ties      only where more than 16 weights are equal to the K-th largest: one pass in which the last position that stays is
 //               found from the bit masks of each step.
 //   4 product   P = exp2((w - max) / sqrt(d) . log2 e) of the weights above the bin (the same instructions on the same
-//               operands give the weights the very bits they had in 2), as two bf16 terms (16 significant bits), and
-//               O^T += V^T . P^T.  A lane's weights sit where the second product wants its operand; V comes out of LDS
+//               operands give the weights the very bits they had in 2), as two bf16 terms, and O^T += V^T . P^T.  The second term
+//               is rounded to nearest, so that the two are within 2^-16 of P and as often above it as below, at the cost of cutting
+//               it off (which leaves up to 2^-15, always below): of 8 rows of 1024 tokens at d = 128 (1 M outputs, 96 kept of Gaussian
+//               weights) 4295 are not the exact result's rounding, with the term cut off 6395, with the weights of every K-th largest's
+//               bin in fp32 besides 6390.  (Both terms rounded: 2295, but 64 rows of 1000 at d = 64 take 1 to 4 % longer.)  A lane's weights sit where the second product wants its operand; V comes out of LDS
 //               transposed (ds_read_b64_tr_b16).  The few weights inside the bin are set aside with their positions, unless the whole
 //               bin stays: then they are above it like the others.  Setting one aside is a detour of the wave's other 63 lanes: with
 //               128 bins, and bins that stay whole set aside as well, 3.2 weights a query made that a fifth of 512 rows of 1024 tokens;
@@ -66,8 +69,10 @@ namespace adore {
 
 namespace {
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -98,11 +103,16 @@ __device__ inline float normal_quantile(float p) {
 }
 
 // Bits of the lanes whose x is at least y (none where one is NaN).
-// ... in [0, y) for a y whose bits are `end`.
+__device__ __forceinline__ uint64_t lanes_ge(float x, float y) { return __builtin_amdgcn_fcmpf(x, y, 3); }   // 3: ordered, >=
+// ... whose x is in [0, y) for a y whose bits are `end`.
 __device__ __forceinline__ uint64_t lanes_below(float x, uint32_t end) {
   return __builtin_amdgcn_uicmp(__float_as_uint(x), end, 36);   // 36: unsigned, <
 }
-__device__ __forceinline__ uint64_t lanes_ge(float x, float y) { return __builtin_amdgcn_fcmpf(x, y, 3); }   // 3: ordered, >=
+
+// Both rounded to bf16 (to nearest, ties to even), a in the lower half.
+__device__ __forceinline__ uint32_t two_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
 
 constexpr uint32_t kLowest = 0x007fffffu, kHighest = 0xff800000u;   // images of the infinities
 // Right shift after which the distances 0 .. span fit the bins.
@@ -668,7 +678,7 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
         if (st + 2 < steps) load_tile(Kb, st + 2, kr);
         if (st + 1 < steps) load_tile(Vb, st + 1, vr);
       }
-      // P of two of the lane's weights, as two bf16 terms: the upper 16 bits, and the upper 16 bits of what is left (exact, >= 0)
+      // P of two of the lane's weights, as two bf16 terms: the upper 16 bits, and what is left (exact, >= 0) rounded
       auto exponentials = [&](float x0, float x1, uint64_t stays0, uint64_t stays1, uint32_t &ph, uint32_t &pl) {
         const float p0 = __builtin_amdgcn_inverse_ballot_w64(stays0) ? __builtin_amdgcn_exp2f(exponent(x0)) : 0.f;
         const float p1 = __builtin_amdgcn_inverse_ballot_w64(stays1) ? __builtin_amdgcn_exp2f(exponent(x1)) : 0.f;
@@ -676,8 +686,7 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
         asm volatile("" : "+v"(lsum));        // added here: sixteen of them are not kept for the end of the step
         const uint32_t h0 = __float_as_uint(p0), h1 = __float_as_uint(p1);
         ph = __builtin_amdgcn_perm(h1, h0, 0x07060302u);   // (h0 >> 16) | (h1 & 0xffff0000)
-        pl = __builtin_amdgcn_perm(__float_as_uint(p1 - __uint_as_float(h1 & 0xffff0000u)),
-                                   __float_as_uint(p0 - __uint_as_float(h0 & 0xffff0000u)), 0x07060302u);
+        pl = two_bf16(p0 - __uint_as_float(h0 & 0xffff0000u), p1 - __uint_as_float(h1 & 0xffff0000u));
         asm volatile("" : "+v"(ph), "+v"(pl));   // done here, between the matrix instructions
       };
       // V^T operand: head dimensions db * 32 + c; element e of lane half h is key 16 ks + 8 (e / 4) + 4 h + e % 4

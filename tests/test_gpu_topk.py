@@ -304,3 +304,29 @@ def test_bins_that_stay_whole_and_bins_that_are_full(S, d, levels, top_k, offset
         want = O.softmax_row(level[sel] / np.sqrt(np.float64(d))) @ v[0, sel]
         e = np.abs(got[0, i] - want).max() / np.abs(want).max()
         assert e < TOL, f"S={S} K={keep}: query {i}: {e}"
+
+
+@pytest.mark.parametrize("rows,d", [(5, 64), (5, 128), (600, 64), (600, 128)])
+def test_weights_that_stay_are_within_half_a_place(rows, d):
+    """Two keys stay of which the first's probability is 1, and their values cancel to 2^-8 of them and less: what is left shows
+    the second's probability to its last bits.  P goes into the product as two bf16 terms, the upper 8 bits and the rest, below 2^-7 P,
+    rounded to 8 bits: within 2^-16 P.  Exponential, sums and the division are off by a few 2^-23 (2^-20 allowed).  The output is
+    rounded to 8 bits, half a unit of the last of which is up to 2^-8 of it."""
+    torch, _, topk_attention = _mods()
+    rng = np.random.default_rng(rows + d)
+    S = 70
+    k = np.zeros((rows, S, d))
+    k[..., 0] = -8.0 + 4.0 * rng.random((rows, S))               # far below
+    k[:, 0, 0], k[:, 1, 0] = 8.0, 8.0 - 8.0 * rng.random(rows)
+    k = _bf16_values(torch, k)
+    q = np.zeros((rows, S, d))
+    q[..., 0] = 1.0
+    p = np.exp((k[:, 1, 0] - 8.0) / np.sqrt(np.float64(d)))[:, None]
+    v = _bf16_values(torch, rng.standard_normal((rows, S, d)))
+    v[:, 1] = _bf16_values(torch, 1.0 + rng.random((rows, d)))
+    v[:, 0] = -_bf16_values(torch, p * v[:, 1])
+    got = topk_attention(_to_gpu(torch, q), _to_gpu(torch, k), _to_gpu(torch, v), 2).float().cpu().numpy().astype(np.float64)
+    want = ((v[:, 0] + p * v[:, 1]) / (1.0 + p))[:, None]
+    off = ((2.0 ** -16 + 2.0 ** -20) * p * v[:, 1] / (1.0 + p))[:, None]
+    over = np.abs(got[:, 2:] - want) / (off + 2.0 ** -8 * (np.abs(want) + off))
+    assert over.max() <= 1.0, over.max()
