@@ -25,8 +25,8 @@
 //               is rounded to nearest, so that the two are within 2^-16 of P and as often above it as below, at the cost of cutting
 //               it off (which leaves up to 2^-15, always below): of 8 rows of 1024 tokens at d = 128 (1 M outputs, 96 kept of Gaussian
 //               weights) 4295 are not the exact result's rounding, with the term cut off 6395, with the weights of every K-th largest's
-//               bin in fp32 besides 6390.  (Both terms rounded: 2295, but 64 rows of 1000 at d = 64 take 1 to 4 % longer.)  A lane's weights sit where the second product wants its operand; V comes out of LDS
-//               transposed (ds_read_b64_tr_b16).  The few weights inside the bin are set aside with their positions, unless the whole
+//               bin in fp32 besides 6390.  (Both terms rounded: 2295, but 64 rows of 1000 at d = 64 take 1 to 4 % longer.)
+//               A lane's weights sit where the second product wants its operand; V comes out of LDS transposed (ds_read_b64_tr_b16).  The few weights inside the bin are set aside with their positions, unless the whole
 //               bin stays: then they are above it like the others.  Setting one aside is a detour of the wave's other 63 lanes: with
 //               128 bins, and bins that stay whole set aside as well, 3.2 weights a query made that a fifth of 512 rows of 1024 tokens;
 //               now it is one (660 -> 610 us; 8192 tokens 5690 -> 5520, 40 rows of 1000 tokens at d = 64 55.1 -> 48.8).
@@ -44,8 +44,13 @@
 // 80900 -> 5520; 4 rows of 128 tokens, d = 64: 21.3 -> 10.5.  At first, 16 queries per workgroup kept their fp32 weights in LDS (in
 // memory beyond 2048 tokens, read again by every pass of a radix select), with K and a transposed copy of V loaded straight
 // into the operand layout: 16 look-ups in the L1 per 256 bytes, K and V read from the L2 once per 16 queries.
-// Those are Gaussian weights, which mostly need one count.  256 rows of 1024 tokens (before / now): Gaussian 339 / 312, 60 % of the keys
-// zeroed 455 / 453, whole-numbered q and k 592 / 606 (ranges alone would take 17 counts to close in on a zero), all keys equal 559 / 593.
+// Those are Gaussian weights, which mostly need one count.  256 rows of 1024 tokens (128 bins a word each / now): Gaussian 339 / 312, 60 %
+// of the keys zeroed 456 / 433, whole-numbered q and k 592 / 598 (ranges alone would take 17 counts to close in on a zero), all keys equal 560 /
+// 541.  Two bins a word cost a count over a range one operation a weight (21.4 -> 22.4 thousand cycles a workgroup, the one per cent of the
+// whole numbers).  What gave the equal keys their time back (593 before): counts over images number their bins from below (30.6 -> 28.8
+// thousand cycles), the pass of the ties has its next tile on the way (21.6 -> 20.7), and in the product one end of the bin tells which of
+// the equal weights stay wherever a block of keys is all before the last of them or all behind it (40.8 -> 31.1; each weight's position was
+// compared at every step).
 // What bounds it now, at 8192 tokens (counters): a SIMD issues vector instructions in 46 % of its cycles and has matrix work in 32 %, which
 // two waves a SIMD (what 253 registers leave room for) hardly overlap; a wave waits for LDS or a barrier in 24 %.  LDS is busy in 34 %.  A
 // quarter fewer vector instructions a step gave 1 %.  The wave in a step's products goes first (s_setprio): 609 -> 598 us at 1024 tokens, 451 ->
@@ -85,7 +90,7 @@ constexpr int kSample = 128;         // keys of the sample: mean and deviation t
 // A weight's bin is read off the bits of y = a w + b: with bin 0 at kBin0 = 2^23, where floats are the integers, and as many units a
 // bin as half a row of the histogram has bytes, the bits of y hold the row's place (one multiply-add, a clamp and an and-or, no conversion).
 constexpr float kBin0 = 8388608.f;
-constexpr int kRangeCounts = 3;      // most counts over ranges of weights; then at most ceil(32 / 7) over images
+constexpr int kRangeCounts = 3;      // most counts over ranges of weights; then at most ceil(32 / 8) over images
 
 // Order-preserving image of a weight (larger float <=> larger integer, never 0 for a number) and back.
 __device__ inline uint32_t weight_image(float x) {
@@ -424,7 +429,7 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
     }
   };
 #pragma unroll 1
-  for (int tries = 0, ranges = 1; tries < kRangeCounts + 5; ++tries) {
+  for (int tries = 0, ranges = 1; tries < kRangeCounts + 4; ++tries) {
     if (tid == 0) s_flag[0] = 0;
     if (tid == 1) s_flag[2] = 0;
     for (int i = tid; i < NQ * kRows / 4; i += NT) reinterpret_cast<u32x4 *>(s_hist)[i] = u32x4{0u, 0u, 0u, 0u};
@@ -454,17 +459,17 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
       __hip_atomic_fetch_max(&s_max[ql], weight_image(top), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       if (fabsf(top) * a.scale_log2 > 0x1p27f && top != -INFINITY) s_flag[4] = 1;   // (-infinity: no key of these was visible)
     } else {
-      const uint32_t last = s_last[ql], span = last - s_first[ql];
+      const uint32_t first = s_first[ql], span = s_last[ql] - first;
       const int shift = image_shift(span);
       uint32_t least = ~0u, most = 0u;
       sweep(std::false_type(), steps, 0u, [&](float w0, float w1, float w2, float w3, int, int) {
         const float w[4] = {w0, w1, w2, w3};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const uint32_t u = weight_image(w[i] + 0.f), down = last - u;   // (-0 counts as 0)
-          if (down <= span) {                    // not for the NaN of a hidden key, whose image is beyond both infinities'
-            const uint32_t bin = uint32_t(kBins - 1) - (down >> shift);
-            __hip_atomic_fetch_add(&s_hist[bin / 2 * NQ + ql], bin & 1u ? 65537u : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          const uint32_t u = weight_image(w[i] + 0.f), up = u - first;   // (-0 counts as 0)
+          if (up <= span) {                      // not for the NaN of a hidden key, whose image is beyond both infinities'
+            __hip_atomic_fetch_add(&s_hist[(up >> (shift + 1)) * NQ + ql], ((up >> shift) & 1u) << 16 | 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
             least = min(least, u);
             most = max(most, u);
           }
@@ -549,8 +554,8 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
         uint32_t first = s_first[q], last = s_last[q];
         const int shift = image_shift(last - first);
         const uint32_t size = (1u << shift) - 1u;
-        last -= uint32_t(kBins - 1 - bin) << shift;
-        if (last - first > size) first = last - size;
+        first += uint32_t(bin) << shift;
+        if (last - first > size) last = first + size;
         if (few || all || shift == 0 || s_min[q] == s_most[q]) {   // few weights, or all of them stay, or are equal
           s_ga[q] = image_weight(first);
           s_gb[q] = image_weight(all ? first : last + 1u);   // (NaN behind infinity: nothing is above)
@@ -597,11 +602,12 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
   auto inside = [&](float w) { return bool((w >= from) & !(w >= above)); };   // (false for the NaN of a hidden key)
   const bool crowded = s_flag[1] != 0;
   if (crowded) {
+    u32x4 kr[NLD];
+    load_tile(Kb, 0, kr);
     for (int st = 0; st < steps; ++st) {
-      u32x4 kr[NLD];
-      load_tile(Kb, st, kr);
       __syncthreads();
       store_tile(0, kr);
+      if (st + 1 < steps) load_tile(Kb, st + 1, kr);
       __syncthreads();
       const int kb = st * kStep + kg * 32;
       uint32_t mask = 0u;
@@ -708,6 +714,13 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vo[db].v, *reinterpret_cast<const bf16x8 *>(&pl), o[db], 0, 0, 0);
         asm volatile("" : "+v"(o[db]));
       };
+      // Of equal weights those up to `tie` stay: in a block that is all before it or all behind it one end of the bin tells them.
+      float low = from, high = above;
+      if (IMAGES && crowded) {
+        const bool before = kb + 31 <= tie, behind = tie >= 0 && kb > tie;
+        high = before ? from : above;
+        low = before | behind ? high : from;
+      }
       uint32_t ph[8], pl[8];
       auto share = [&](int g) {
         // the lanes whose weight stays, and those whose weight is inside the bin (neither for the NaN of a hidden key)
@@ -716,8 +729,8 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
         for (int i = 0; i < 4; ++i) {
           const float x = w[4 * g + i];
           if constexpr (IMAGES) {
-            stays[i] = lanes_ge(x, above);
-            in[i] = lanes_ge(x, from) & ~stays[i];
+            stays[i] = lanes_ge(x, high);
+            in[i] = lanes_ge(x, low) & ~stays[i];
           } else {
             // >= kBinWidth above the bin, in [0, kBinWidth) inside it, else below (exact: rounding is monotone, and the difference is
             // exact inside the bin)

@@ -330,3 +330,19 @@ def test_weights_that_stay_are_within_half_a_place(rows, d):
     off = ((2.0 ** -16 + 2.0 ** -20) * p * v[:, 1] / (1.0 + p))[:, None]
     over = np.abs(got[:, 2:] - want) / (off + 2.0 ** -8 * (np.abs(want) + off))
     assert over.max() <= 1.0, over.max()
+
+
+@pytest.mark.parametrize("rows,d", [(2, 64), (150, 64), (2, 128), (90, 128)])
+@pytest.mark.parametrize("top_k", [17, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 191, 192, 193])
+def test_equal_weights_stay_up_to_the_last_position(rows, d, top_k):
+    """All keys equal: the first top_k positions stay, which end before, at and behind the edges of a wave's block of 32 keys, of a
+    step's and of a workgroup's queries; a query's result is the mean of their values."""
+    torch, O, topk_attention = _mods()
+    rng = np.random.default_rng(rows + d + top_k)
+    S = 230
+    q, k = (np.broadcast_to(rng.integers(-8, 9, size=(rows, 1, d)) / 4.0, (rows, S, d)) for _ in range(2))
+    v = _bf16_values(torch, rng.standard_normal((rows, S, d)))
+    got = topk_attention(_to_gpu(torch, q), _to_gpu(torch, k), _to_gpu(torch, v), top_k).float().cpu().numpy().astype(np.float64)
+    last = np.minimum(np.arange(S), top_k - 1)
+    want = np.cumsum(v, axis=1)[:, last] / (last + 1.0)[:, None]
+    assert _row_err(got, want).max() < TOL
