@@ -990,7 +990,9 @@ bool tile_fits(const TileShape &t, int kdim, int section, int head_dim, bool den
 // estimate is used: a launch that fills three quarters of the units once (256x128 at M = 512, N = 12288: 192 tiles,
 // 64 us) beats one that fills all of them one and a half times (128x128: 384 tiles, 88 us).
 // Small products (us): 128 rows x 2048 columns x 1024 on 64 tiles of 128x32 12.5, on 256 of 32x32 8.4; 39 x 1536 x 768 11.0 / 7.8;
-// 16 x 4096 x 4096 35 / 19.
+// 16 x 4096 x 4096 35 / 19.  The estimate counts shapes of which two share a unit like the others: 64x64 tiles between one and two a unit are
+// charged twice, and lose M = 160 and 192 at N = 8192 to 128x64 (42.4 and 43.2 us a step, 40.8 and 41.2 on 64x64); 256x256 against 128x128 at M
+// = 1280 127 / 157, 1536 141 / 181, and 98 / 119 with D = 2048.
 constexpr float kTileMicros[kNumTiles] = {125.f, 66.f, 41.f, 40.f, 25.f, 112.f, 21.f, 17.f, 12.f};
 
 // extra: workgroups that ride in the launch and need a compute unit each (the current tokens' rows); of the first `among` shapes
@@ -1035,10 +1037,11 @@ void launch_tile(ScopedTimer &t, hipStream_t stream, int pick, GemmArgs &a) {
   if (behind) a.tail_at = (total + 7) / 8 * 8;
   const dim3 grid((total + 7) / 8 * 8 + (behind ? a.tail.n : a.n_cur)), block(512);
 #define TILE(...) ADORE_LAUNCH(t, (rebuild_mfma_kernel<MODE, __VA_ARGS__>), grid, block, 0, stream, a)
+  constexpr bool kStep = MODE == MODE_REBUILD || MODE == MODE_TAIL;   // the forward takes none of the shapes guarded by it
   if constexpr (MODE != MODE_TAIL) {
     switch (pick) {
       //             BM   BN   BK KG WM WN LS NS
-      case 0: TILE(256, 256,  32, 1, 2, 4, 4, 2); return;
+      case 0: if constexpr (kStep) TILE(256, 256, 32, 1, 2, 4, 4, 2); return;
       case 1: TILE(256, 128,  64, 1, 4, 2, 3, 2); return;
       case 5: TILE(256, 256,  64, 1, 2, 4, 2, 1); return;
     }
@@ -1046,10 +1049,10 @@ void launch_tile(ScopedTimer &t, hipStream_t stream, int pick, GemmArgs &a) {
   switch (pick) {
     case 2: TILE(128, 128,  64, 2, 2, 2, 3, 4); return;
     case 3: TILE(128,  64,  64, 2, 2, 2, 3, 4); return;
-    case 4: TILE(128,  32,  64, 2, 4, 1, 3, 4); return;
+    case 4: if constexpr (kStep) TILE(128, 32, 64, 2, 4, 1, 3, 4); return;
     case 6: TILE(64,   64, 128, 2, 2, 2, 2, 3); return;
   }
-  if constexpr (MODE == MODE_REBUILD || MODE == MODE_TAIL) {
+  if constexpr (kStep) {
     if (pick == 7) TILE(64, 32, 128, 4, 2, 1, 2, 3);
     else TILE(32, 32, 256, 8, 1, 1, 2, 2);
   }
@@ -1196,9 +1199,11 @@ int pick_with_riders(GemmArgs &a, int kdim, int section, int head_dim, bool dens
   const int pick = pick_tile(a.M, a.N, kdim, section, head_dim, dense, base, kForwardTiles);
   // The rows of a layer are the next one's input, without a norm between them here, and a last bit that falls the other way in an
   // early layer can be another key's softmax in a late one: so the choice is made among the shapes that were always there, and a
-  // newer one stands in where its sums are the same (one k-group for one, two for two).
-  const int stand_in = pick == 0 ? 5 : pick == 4 ? 6 : pick;
-  const int tile = pick >= 0 && tile_fits(kTiles[stand_in], kdim, section, head_dim, dense) ? stand_in : pick;
+  // newer one stands in whose sums are the same (one k-group for one, two for two) and which fits wherever the old one does, widths and
+  // contractions being multiples of 128 here (fwd_gemm_supported).  How finely the current tokens' rows are cut decides their sums as
+  // well: it goes by the old shape's number of tiles.
+  static_assert(kTiles[5].bn == kTiles[0].bn && 128 % kTiles[5].bk == 0 && 128 % kTiles[6].bk == 0 && 64 % kTiles[6].bn == 0, "the stand-ins fit");
+  const int tile = pick == 0 ? 5 : pick == 4 ? 6 : pick;
   if (pick < 0 || base == 0) return tile;
   const int tiles = ((a.M + kTiles[pick].bm - 1) / kTiles[pick].bm) * (a.N / kTiles[pick].bn);
   const int rounds = (tiles + base + 255) / 256;

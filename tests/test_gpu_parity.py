@@ -357,6 +357,74 @@ def test_rebuild_gemm_tile_shapes(tile, D, monkeypatch):
     job.adore.close()
 
 
+def _same_bits(got, want):
+    import torch
+    for x, y in zip(got, want):
+        assert torch.equal(x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32), y.view(torch.int16 if y.dtype == torch.bfloat16 else torch.int32))
+
+
+def _tile_job(forward, rope=0.0):
+    """A job with 165 rows to rebuild a step (ragged in every tile) and contractions of 512: (job, what its steps take)."""
+    import torch
+    from paper_2407_02328_amd import Adore, make_config
+    L, B, H, d, D, K, R, S, T, dp = 2 if forward else 1, 3, 8, 64, 512, 128, 55, 200, 3, 32
+    bf, f32, g = torch.bfloat16, torch.float32, torch.Generator(device="cuda")
+    g.manual_seed(77)
+    n = lambda shape, std, dt=bf: torch.empty(shape, dtype=dt, device="cuda").normal_(0.0, std, generator=g)
+    w = {"w_kv": n((L, 2 * H * d, D), 0.04), "gru_w_ih": n((3 * dp, D), D ** -0.5), "gru_w_hh": n((3 * dp, dp), dp ** -0.5),
+         "gru_b_ih": n((3 * dp,), 0.1, f32), "gru_b_hh": n((3 * dp,), 0.1, f32), "pos_w": n((dp,), 1.0, f32), "pos_b": n((dp,), 0.1, f32),
+         "mlp_w1": n((dp, dp), dp ** -0.5, f32), "mlp_b1": n((dp,), 0.1, f32), "out_w": n((dp,), 0.5, f32), "out_b": n((1,), 0.1, f32)}
+    a = Adore(make_config(layers=L, batch=B, heads=H, head_dim=d, hidden=D, cache_slots=K, rebuild_budget=R, max_positions=S + T,
+                          ctrl_hidden=dp, dtype="bf16", pos_scale=2.0 ** -12, rope_base=rope), w, "cuda")
+    kv, hidden = n((L, B, H, S, d), 1.0), n((1 if forward else L, B, S + T, D), 1.0)
+    q, w_q, w_o = n((T, 3, B, H, d), 1.0), n((L, H * d, D), 0.04), n((L, D, H * d), 0.04)
+
+    def run():
+        maps = torch.empty((B, H, K), dtype=torch.int32, device="cuda")
+        out = torch.zeros((T, B, R + 1, D), dtype=bf, device="cuda") if forward else torch.zeros((T, B, H, d), dtype=f32, device="cuda")
+        a.init_cache(kv, kv, None if forward else hidden, hidden[0][:, :S].contiguous(), None, S)
+        for t in range(T):
+            if forward:
+                a.forward_step(w_q, w_o, hidden[0], None, out[t], maps, None, None)
+            else:
+                a.decode_step(q[t, 0], q[t, 1], q[t, 2], hidden[0], hidden[0][:, S + t].contiguous(), None, out[t], maps)
+        if forward:                                  # (the rows of what the last step chose are made by the next)
+            return [out, maps]
+        state = a.empty_state()
+        a.get_state(**state)
+        free = (maps < 0)[None, ..., None]
+        return [out, maps, state["cache_k"].masked_fill(free, 0), state["cache_v"].masked_fill(free, 0)]
+    return a, run
+
+
+@pytest.mark.parametrize("tiles", [(0, 1, 5), (4, 2, 3, 6)])
+@pytest.mark.parametrize("rope", [0.0, 10000.0])
+def test_tiles_with_as_many_groups_of_waves_add_up_alike(tiles, rope, monkeypatch):
+    """Tiles whose waves do not cut the contraction, and those that cut it in two, give a row the same bits whatever their shape and the
+    length of their k-steps."""
+    job, run = _tile_job(False, rope)
+    monkeypatch.setenv("ADORE_GEMM_TILE", str(tiles[0]))
+    want = run()
+    for tile in tiles[1:]:
+        monkeypatch.setenv("ADORE_GEMM_TILE", str(tile))
+        _same_bits(run(), want)
+    job.close()
+
+
+@pytest.mark.parametrize("tiles", [(1, 0), (2, 3, 4)])
+@pytest.mark.parametrize("rope", [0.0, 10000.0])
+def test_forward_keeps_its_bits_on_the_tiles_that_stand_in(tiles, rope, monkeypatch):
+    """The rebuild forward's rows are the next layer's input, so its sums are the same on whatever tile: 256x256 and 128x32 are asked for,
+    of which newer shapes take the place, and give the bits of the others with as many groups of waves."""
+    job, run = _tile_job(True, rope)
+    monkeypatch.setenv("ADORE_GEMM_TILE", str(tiles[0]))
+    want = run()
+    for tile in tiles[1:]:
+        monkeypatch.setenv("ADORE_GEMM_TILE", str(tile))
+        _same_bits(run(), want)
+    job.close()
+
+
 def test_llama7b_layer_full_size_steps():
     """The benchmark workload at its full size and in the launch configuration bench.py times
     (B16 H32 d128 D4096 K512 R32, prompt 1024): init plus six free-running steps, every slot map,
