@@ -263,6 +263,10 @@ int ensure_side_stream(adore_ctx *ctx) {
 //   riding, ordered inputs, the projection's tiles leaving compute units free for the tail: whatever the size.  12 sequences of 24 heads
 //     (46 us) 46 / 55, 16 of 24 (51) 52 / 60, 12 of 32 (61) 59 / 68, 11 of 32 behind 1024 slots (78) 77 / 84, 30 of 32 behind
 //     700 (110) 125 / 138; known ahead 46 / 47, 52 / 53, 58 / 60, 75 / 76, but 32 of 16 (42) 49 / 48, 48 of 12 (46) 55 / 54, 20 of 24 (55) 59 / 57.
+//     Short projections behind long attentions: 32 of 32 behind 1024 slots, hidden size 1024 (118) 118 / 135, 64 of 32, 256 (218) 210 / 218.
+//     With rescoring too, though the scores are made anew in front of the attention, over all tokens (the side streams' selections wait
+//     for them just so, and the projection for the selections): 12 of 32 behind 8000 tokens 78 / 108, 32 of 32, 16000 tokens 141 / 175,
+//     16 of 32, 30000 tokens 143 / 193, 64 of 16, 16000 tokens 174 / 199, 64 of 32, 8000 tokens 196 / 220, 128 of 16, 2000 tokens 110 / 109.
 //   A riding step whose controller is in launches of its own (no hidden size of 128, no room next to the projection): ordered 8 of 16 39 /
 //     45, 4 of 32 48 / 47, known ahead 1 of 4 heads 24 / 25 to 25 / 28, 8 of 12 32 / 27; fp32 a half of that, known ahead an eighth.
 // A stack of layers called one by one with ordered inputs starts its selections behind the last layer's attention, so
