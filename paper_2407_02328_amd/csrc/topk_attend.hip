@@ -719,7 +719,7 @@ __global__ __launch_bounds__(64 * NQB * KB, NQB) void topk_attend_kernel(const T
       if (IMAGES && crowded) {
         const bool before = kb + 31 <= tie, behind = tie >= 0 && kb > tie;
         high = before ? from : above;
-        low = before | behind ? high : from;
+        low = before || behind ? high : from;
       }
       uint32_t ph[8], pl[8];
       auto share = [&](int g) {
