@@ -19,7 +19,6 @@ namespace adore {
 namespace {
 
 constexpr int kChoiceThreads = 1024;     // 512: a trip to memory more for the maps and for the scores, 13.4 us for 12.6
-constexpr int kChoiceWaves = kChoiceThreads / 64;
 
 __global__ void h2o_init_scores_kernel(float *score, const float *init, int rows, int S, int N_max) {
   const size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -81,7 +80,7 @@ __global__ __launch_bounds__(kChoiceThreads) void h2o_choice_kernel(const H2OCho
   uint32_t *s_cnt = s_hist + 256;                               // [(n + 4) / 4] four counters per word
   int *s_sel = reinterpret_cast<int *>(s_cnt + (a.n + 4) / 4);  // [Rr] chosen positions, best first
   int *s_misc = s_sel + Rr;                                     // [0] collect's counter, [1] candidates
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.x, tid = threadIdx.x;
 
   for (int wd = tid; wd < (a.n + 4) / 4; wd += kChoiceThreads) s_cnt[wd] = 0;
   if (tid == 0) s_misc[1] = 0;
