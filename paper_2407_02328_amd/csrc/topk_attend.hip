@@ -50,9 +50,9 @@
 // whole numbers).  What gave the equal keys their time back (593 before): counts over images number their bins from below (30.6 -> 28.8
 // thousand cycles), the pass of the ties has its next tile on the way (21.6 -> 20.7), and in the product one end of the bin tells which of
 // the equal weights stay wherever a block of keys is all before the last of them or all behind it (40.8 -> 31.1; each weight's position was
-// compared at every step).
-// What bounds it now, at 8192 tokens (counters): a SIMD issues vector instructions in 46 % of its cycles and has matrix work in 32 %, which
-// two waves a SIMD (what 253 registers leave room for) hardly overlap; a wave waits for LDS or a barrier in 24 %.  LDS is busy in 34 %.  A
+// compared at every step).  Keys that wander from position to position (a random walk), 16 rows of 4096: 268 / 275, 256 of 1024: 362 / 332.
+// What bounds it now, at 8192 tokens (counters): a SIMD issues vector instructions in 51 % of its cycles and has matrix work in 33 %, which
+// two waves a SIMD (what 253 registers leave room for) hardly overlap; a wave waits for LDS or a barrier in 22 %.  LDS is busy in 34 %.  A
 // quarter fewer vector instructions a step gave 1 %.  The wave in a step's products goes first (s_setprio): 609 -> 598 us at 1024 tokens, 451 ->
 // 429 for 64 rows of 3000; not at d = 64 nor with 32 queries, where it makes no difference or costs 1 %.
 // Tried and not kept: thresholds from a sample and candidate lists in LDS instead of histograms (6.5 vector instructions per
