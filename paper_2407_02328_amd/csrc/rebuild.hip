@@ -275,6 +275,8 @@ __device__ inline void cur_rows_role(const GemmArgs &a, int e, u32x4 *smem) {
 // a decode step's attention (us a step): M = 128 44.7 -> 39.2 (64x64, steps of 128, two workgroups a unit; 128x32 of 64 before), 64 36.8 ->
 // 30.0 (64x32, 128), 32 36.1 -> 27.5 (32x32, 256; the 128-row tile multiplied padding), 16 x 4096 x 4096 34.0 -> 23.1.  No faster there: 128x128
 // and 128x64 in steps of 128 (two stages and three; with cold operands they are, 58.5 -> 54 and 47.5 -> 43.5), 256x128 in two stages or k-groups.
+// More groups are shorter chains of fp32 sums: of 524288 rebuilt elements (4 x 32 rows, 16 heads of 128, D = 4096) 142 are not the 64-bit
+// product's rounding with one group or two, 97 with four, 93 with eight; of 262144 at D = 2048 46, 25 and 15.
 //   global -> registers: NS k-steps ahead (NS register sets, refilled right after they are spilled to LDS)
 //   registers -> LDS:    LS stages; the tile of step ks+LS-1 is written while ks is read, one barrier per
 //                        k-step.  With LS >= 3 the tile of ks+1 is complete during ks, so the first
